@@ -92,8 +92,9 @@ lordba_status lordba_unpack_signs(const uint32_t* packedA, const uint32_t* packe
  * 1 <= r <= 64.
  * Arithmetic: fp16 inputs at their exact values, products s_in*x exact, fp32 accumulation, one
  * round-to-nearest-even to fp16 at the end; every token row is within 1e-3 relative L2 of the
- * exact result.  Shapes with d_in % 32 == 0, d_out % 8 == 0 and 16-byte aligned pointers take the
- * matrix-core kernel; anything else takes a slower general kernel with the same results.
+ * exact result.  Shapes with d_in % 32 == 0, d_out % 8 == 0 and 16-byte aligned pointers run
+ * fastest; other widths from 8 columns on and tensors aligned to their elements take variants of the same matrix-core
+ * kernel for them; fewer than 8 columns take a general kernel.  Same results up to the order of fp32 sums.
  * Non-finite inputs propagate by IEEE rules; nothing is clamped. */
 lordba_status lordba_forward(const void* x, const uint32_t* packedA, const uint32_t* packedB,
                              const void* s_in, const void* s_rank, const void* s_out,

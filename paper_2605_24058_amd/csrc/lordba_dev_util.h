@@ -16,6 +16,23 @@ __device__ __forceinline__ void store16(void* p, u4 v) { *reinterpret_cast<u4*>(
 // (carrier bits, scales) from the caches.
 __device__ __forceinline__ u4 load16_stream(const void* p) { return __builtin_nontemporal_load(reinterpret_cast<const u4*>(p)); }
 __device__ __forceinline__ void store16_stream(void* p, u4 v) { __builtin_nontemporal_store(v, reinterpret_cast<u4*>(p)); }
+// The same for tensors that are aligned to their fp16 elements only (rows of odd widths): the hardware takes any byte address,
+// and the type tells the compiler not to assume more.
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u1_any __attribute__((aligned(2)));
+typedef uint32_t u4_word __attribute__((ext_vector_type(4), aligned(4)));  // (packed words: aligned to a word)
+__device__ __forceinline__ u4 load16_any(const void* p) { return *static_cast<const u4_any*>(p); }
+__device__ __forceinline__ u4 load16_any_stream(const void* p) { return __builtin_nontemporal_load(static_cast<const u4_any*>(p)); }
+__device__ __forceinline__ void store16_any_stream(void* p, u4 v) { __builtin_nontemporal_store(static_cast<u4_any>(v), static_cast<u4_any*>(p)); }
+// Eight halves moved down by n (0 .. 8 or more) places, zeros from above: entry e becomes entry e + n.
+__device__ __forceinline__ u4 drop_halves(u4 v, int n) {
+    v = (n & 4) ? u4{v[2], v[3], 0u, 0u} : v;
+    v = (n & 2) ? u4{v[1], v[2], v[3], 0u} : v;
+    const u4 one = {__builtin_amdgcn_alignbit(v[1], v[0], 16), __builtin_amdgcn_alignbit(v[2], v[1], 16),
+                    __builtin_amdgcn_alignbit(v[3], v[2], 16), v[3] >> 16};
+    v = (n & 1) ? one : v;
+    return n < 8 ? v : u4{0u, 0u, 0u, 0u};
+}
 // Address = uniform base (kept in scalar registers) + unsigned 32-bit byte offset per lane: one add-free addressing
 // mode, no 64-bit vector arithmetic.
 __device__ __forceinline__ const void* at(const void* base, uint32_t byte_off) { return static_cast<const char*>(base) + byte_off; }

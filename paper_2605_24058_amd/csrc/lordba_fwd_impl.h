@@ -26,8 +26,11 @@
 //            operands come from a 256-entry LDS table (8 carrier bits -> 8 fp16); those of a wave's first
 //            block are built with the vector ALU while the wave waits for the others to finish stage 1.
 //
+// Tensors that are aligned to their elements only, or of widths that are no multiples of 32 / 8, take the variants of the same
+// kernel with element-aligned accesses (ANY; lordba_fwd_any.h).
+//
 // General kernel (lordba_fwd_general_kernel): plain vector-ALU code, one workgroup per token row, any
-// shape and alignment; also the fallback when the LDS need of the matrix-core kernel exceeds the CU.
+// shape and alignment: widths below 8 columns, and what the caller asks it for.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -38,12 +41,7 @@
 #include "lordba_dev_util.h"
 #include "lordba_host_util.h"
 
-namespace {
-
-constexpr unsigned kSplitBlocks = 4;  // output blocks per workgroup when a tile's blocks are split (one per SIMD)
-constexpr int kURow = 40;   // halves per row of the u tile: 32 slots + 8 pad
-constexpr int kLutBytes = 256 * 16;
-
+// (one type for every unit: the dispatch of one unit may launch kernels that another one holds)
 struct FwdArgs {
     const _Float16* x;
     const uint32_t* pA;
@@ -67,6 +65,18 @@ struct FwdArgs {
     int t_stride;
 };
 
+// Calls outside the conditions of the plain matrix-core variants (widths that are no multiples of 32 / 8, tensors aligned only
+// to their element): the variants with element-aligned accesses, which have units of their own.  LORDBA_ERR_ALGO where they
+// cannot run the call.
+lordba_status lordba_forward_any(const FwdArgs& a, hipStream_t stream);
+lordba_status lordba_forward_any_train(const FwdArgs& a, hipStream_t stream);
+
+namespace {
+
+constexpr unsigned kSplitBlocks = 4;  // output blocks per workgroup when a tile's blocks are split (one per SIMD)
+constexpr int kURow = 40;   // halves per row of the u tile: 32 slots + 8 pad
+constexpr int kLutBytes = 256 * 16;
+
 // The arguments of one adapter of a pool.
 __device__ __forceinline__ FwdArgs select_adapter(const FwdArgs& a, int id) {
     FwdArgs b = a;
@@ -76,17 +86,6 @@ __device__ __forceinline__ FwdArgs select_adapter(const FwdArgs& a, int id) {
     b.s_rank += static_cast<int64_t>(id) * a.ell * a.r;
     b.s_out += static_cast<int64_t>(id) * a.ell * a.d_out;
     return b;
-}
-
-// 8 carrier bits starting at bit `bit0` of a packed stream of `nwords` words.  Both words are always read from a
-// clamped, valid index (no branch, no access past the end); bits past the end of the stream are not meaningful and
-// the callers only use them for padded ranks, whose other operand is zero.
-__device__ __forceinline__ uint32_t fetch8(const uint32_t* __restrict__ words, int64_t bit0, int64_t nwords) {
-    int64_t w = bit0 >> 5;
-    w = w < nwords ? w : nwords - 1;
-    const int64_t w1 = (w + 1) < nwords ? w + 1 : nwords - 1;
-    const uint32_t lo = words[w], hi = words[w1];
-    return static_cast<uint32_t>(((static_cast<uint64_t>(hi) << 32) | lo) >> (bit0 & 31)) & 0xffu;
 }
 
 constexpr int kUBytes = 16 * kURow * 2;  // one rank block of the u tile
@@ -117,7 +116,9 @@ __host__ __device__ constexpr size_t mfma_lds_bytes(int RB, int TMV, int NW, int
 // fwd_tile: rows first..last (inclusive, relative to token row t0) of one tile through one adapter, by the whole
 // workgroup.  Rows of the tile outside that range are neither requested as such (loads are clamped into the range) nor
 // stored.  The function may be called several times in a row by a workgroup (its barriers order the reuse of LDS).
-template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool TR>
+// ANY  element-aligned tensors of any width from 8 columns on (see lordba_forward_any.hip): 16-byte accesses without an
+//      alignment, carrier rows that start at any bit, ragged last groups of 8 columns
+template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool TR, bool ANY>
 __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, const int64_t t0, const int first, const int last) {
     static_assert(NW >= 4, "stage 2 is spread over the first four waves");
     constexpr bool LP = GM == 1, SPLIT = GM == 2 || GM == 3, MASK = GM == 3 || GM == 4;
@@ -127,9 +128,16 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // waves with two.  The multi-adapter batch on 8 waves holds three (two of its workgroups share a compute unit, so a
     // lane has 128 registers).  Four envelopes on 16-row tiles (grids of at least 256 tiles, two workgroups per compute
     // unit) hold one.
-    constexpr int D2 = (TMV == 16 && L == 4) ? 1 : (GM == 4 && NW == 8 && RB == 1 && L == 1) ? 3 : (NW == 8 && TMV == 8 && GM != 4 && ((L >= 3 && RB == 1) || (L == 3 && RB == 2))) ? 4 : 2;
+    constexpr int D2 = (TMV == 16 && L == 4) ? 1 : (GM == 4 && NW == 8 && RB == 1 && L == 1 && BM != 0) ? 3 : (NW == 8 && TMV == 8 && GM != 4 && ((L >= 3 && RB == 1) || (L == 3 && RB == 2 && !ANY))) ? 4 : 2;
     constexpr bool R16 = BM == 1, R8 = BM == 2;
     static_assert(!R8 || RB == 1, "r = 8 is one rank block");
+    static_assert(!ANY || (BM == 0 && (GM == 2 || GM == 4)), "element-aligned tensors: one variant family");
+    // General r: the sign(B) bits of a lane's 8 columns are 8 r consecutive bits (at most 4 RB words, one more because they
+    // start inside a word).  They are requested with the block's y_base, 16 bytes at a time, and taken apart in registers; two
+    // dword loads per column and rank block when the block is consumed, as before, cost as many memory instructions as
+    // everything else together (4096 -> 4096 at T = 2048: r = 50 39.8 -> 18.0 us, r = 12 11.5 -> 9.9; 4096 -> 11008 at T = 4096,
+    // r = 24 58.8 -> 46.1; word-by-word loads of the same words 24.5, 10.2 and 48.2).
+    constexpr int NB = BM == 0 ? 4 * RB + 1 : 1;
     // Four envelopes on 16-row tiles: to stay inside the registers, no sign operands are built ahead and the row scalings
     // are read from LDS where they are used.
     constexpr bool LEAN = TMV == 16 && L == 4;
@@ -166,7 +174,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     _Float16* yot = a.y_out + t0 * d_out;
     // Multi-adapter batch: y_base and y_out of the tile as buffers of rows 0..last; rows of stage 3 that are not live get an
     // offset outside instead of a branch around the access (the runs of a tile make most accesses partial there).
-    constexpr bool BUFY = GM == 4 || (L == 1 && (GM == 0 || GM == 1) && TMV == 8 && NW == 8);
+    constexpr bool BUFY = !ANY && (GM == 4 || (L == 1 && (GM == 0 || GM == 1) && TMV == 8 && NW == 8));
     const uint32_t ytile_bytes = static_cast<uint32_t>(last + 1) * static_cast<uint32_t>(d_out) * 2u;
     const __amdgpu_buffer_rsrc_t yb_rs = buffer_over(ybt, BUFY ? ytile_bytes : 0u), yo_rs = buffer_over(yot, BUFY ? ytile_bytes : 0u);
 
@@ -181,18 +189,26 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // dword loads, each of which has the memory pipeline look up 16 cache lines for 256 bytes.  At decode sizes, where a
     // few workgroups run alone and the time to issue the loads is latency of the call, that is 2.4 us of 9.6 at r = 64;
     // grids that fill the chip gain 1 to 5 %.  (The multi-adapter batch keeps the round-robin deal: 128 registers.)
-    constexpr bool CA = OS && GM != 4;
+    constexpr bool CA = OS && GM != 4 && !ANY;
     const int words_per_row = d_in >> 5;  // d_in % 32 == 0 on this path
     // (the first nchunks mod NW waves own one chunk more than the others: at most ceil(nchunks / NW), <= D1 where OS)
     const int c_each = nchunks / NW, c_more = nchunks - c_each * NW;
     const int c_first = wave * c_each + (wave < c_more ? wave : c_more);   // first chunk of the wave's run
     const int my_n = CA ? c_each + (wave < c_more ? 1 : 0) : (wave < nchunks ? (nchunks - wave + NW - 1) / NW : 0);
+    // (the variants with element-aligned accesses keep the round-robin deal too: their rows of carrier bits start at any bit)
     // (16-byte loads need whole chunks and rows that start on 16-byte boundaries)
     const bool wide_a = CA && (d_in & 127) == 0 && (reinterpret_cast<uintptr_t>(a.pA) & 15) == 0;
     u4 xbuf[D1][NI];
     uint32_t sinbuf[D1][L];
     uint32_t abits[D1][RB];
+    uint32_t abits_hi[ANY ? D1 : 1][ANY ? RB : 1];  // ANY: a lane's 32 carrier bits lie in two words
+    const uint32_t words_a = static_cast<uint32_t>((static_cast<int64_t>(r) * d_in + 31) >> 5);
+    // ANY: position of the lane's 32 carrier bits of chunk c, rank rk, in the stream (columns past d_in meet x = s_in = 0), and
+    // the first of the two words that hold them
+    auto bits_of = [&](int c, int rk) { const int i = c * 128 + q_ * 32; return static_cast<uint32_t>(rk * d_in + (i < d_in ? i : d_in - 1)); };
+    auto word_of = [&](uint32_t bit) { const uint32_t w = bit >> 5; return w < words_a - 2 ? w : words_a - 2; };
 
+    auto load_x = [&](const void* p) { return ANY ? load16_any_stream(p) : load16_stream(p); };
     auto issue_x = [&](int slot, int n) {
         int c = CA ? c_first + n : wave + NW * n;
         c = c < nchunks ? c : nchunks - 1;  // past the end: re-read a valid chunk, the result is not used
@@ -207,6 +223,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
 #pragma unroll
         for (int en = 0; en < L; ++en) {
             const int pair = c * 64 + lane;  // fp16 pair index; d_in is even, so a pair is inside or outside as a whole
+            if constexpr (ANY) {
+                // (a pair that starts in the last column is read one column earlier)
+                const int i0 = 2 * pair, ic = i0 < d_in - 1 ? i0 : d_in - 2;
+                const uint32_t v = *static_cast<const u1_any*>(at(a.s_in, static_cast<uint32_t>(en * d_in + ic) * 2u));
+                sinbuf[slot][en] = i0 < d_in - 1 ? v : i0 == d_in - 1 ? v >> 16 : 0u;
+                continue;
+            }
             const uint32_t v = *static_cast<const uint32_t*>(
                 at(a.s_in, static_cast<uint32_t>(en * d_in) * 2u + static_cast<uint32_t>(pair * 2 < d_in ? pair : 0) * 4u));
             sinbuf[slot][en] = pair * 2 < d_in ? v : 0u;  // columns past d_in get scale 0
@@ -218,16 +241,27 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
             row = row < last ? row : last;
             row = row > first ? row : first;
             int col = c * 128 + li * 8;
-            col = col < d_in ? col : d_in - 8;
+            col = (ANY ? col <= d_in - 8 : col < d_in) ? col : d_in - 8;  // (ANY: consume_x moves a ragged group into place)
             if (MASK) {
                 // fewer than 8 token rows: rows past T are not requested at all (a tile with one live row moves an eighth)
                 xbuf[slot][m] = u4{0u, 0u, 0u, 0u};
-                if (live) xbuf[slot][m] = load16_stream(at(xt, static_cast<uint32_t>(row * d_in + col) * 2u));
+                if (live) xbuf[slot][m] = load_x(at(xt, static_cast<uint32_t>(row * d_in + col) * 2u));
+            } else if (ANY) {
+                xbuf[slot][m] = load_x(at(xt, static_cast<uint32_t>(row * d_in + col) * 2u));
             } else {
                 xbuf[slot][m] = load16_stream(at(xt, static_cast<uint32_t>(row * d_in + col) * 2u));
             }
         }
-        if (!wide_a) {
+        if constexpr (ANY) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                int rk = rb * 16 + li;
+                rk = rk < r ? rk : r - 1;
+                const uint32_t* pw = a.pA + word_of(bits_of(c, rk));
+                abits[slot][rb] = pw[0];
+                abits_hi[slot][rb] = pw[1];
+            }
+        } else if (!wide_a) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 int rk = rb * 16 + li;
@@ -256,7 +290,8 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
         }
     }
 #pragma unroll
-    for (int slot = 0; slot < D1; ++slot) issue_x(slot, slot);
+    for (int slot = 0; slot < D1; ++slot)
+        if (!ANY || slot < my_n) issue_x(slot, slot);
     __builtin_amdgcn_sched_barrier(0);  // keep the issue order: nothing below may be hoisted above these requests
     float sr[RB][L];
 #pragma unroll
@@ -293,7 +328,8 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     const int b_mine = even_runs ? (nblk - wave * b_run < b_run ? nblk - wave * b_run : b_run) : b_each + (wave < b_more ? 1 : 0);
     const int my_b = CB ? (b_mine > 0 ? b_mine : 0) : (wave < nblk ? (nblk - wave + NW - 1) / NW : 0);
     auto block_of = [&](int n) { return CB ? b_start + n : wave + NW * n; };  // the wave's n-th block (relative to b_first)
-    const int64_t nwordsB = (static_cast<int64_t>(d_out) * r + 31) >> 5;
+    const uint32_t words_b = static_cast<uint32_t>((static_cast<int64_t>(d_out) * r + 31) >> 5);
+    uint32_t braw[D2][NB];
     u4 ybuf[D2][NI];
     u4 sobuf[D2][L];
     u4 bbuf[D2][R16 ? RB : 1];
@@ -303,7 +339,22 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
         const bool mine = n < my_b;  // (past the wave's share: with buffer accesses the rows of y_base are not requested)
         b = b < nblk_all ? b : nblk_all - 1;  // past the end: re-read a valid block, the result is not used
         int j0 = b * 128 + li * 8;
-        j0 = j0 < d_out ? j0 : d_out - 8;
+        j0 = (ANY ? j0 <= d_out - 8 : j0 < d_out) ? j0 : d_out - 8;  // (ANY: a ragged last group takes the last 8 columns)
+        if constexpr (BM == 0) {
+            const uint32_t w = (static_cast<uint32_t>(j0) * static_cast<uint32_t>(r)) >> 5;
+            if ((static_cast<uint32_t>(b) * 128u + 127u) * static_cast<uint32_t>(r) / 32u + NB <= words_b) {  // scalar: whole block
+#pragma unroll
+                for (int v = 0; v < RB; ++v) {
+                    const u4_word g = *static_cast<const u4_word*>(static_cast<const void*>(a.pB + w + 4 * v));
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) braw[slot][4 * v + k] = g[k];
+                }
+                braw[slot][NB - 1] = a.pB[w + 4 * RB];
+            } else {  // near the end of the stream: word by word, none past the end (what lies there belongs to no rank)
+#pragma unroll
+                for (int k = 0; k < NB; ++k) braw[slot][k] = a.pB[w + k < words_b ? w + k : words_b - 1];
+            }
+        }
         if (R16) {  // 8 rows of r bits = RB * 16 contiguous, 16-byte aligned bytes
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) bbuf[slot][rb] = load16(at(a.pB, static_cast<uint32_t>(j0 * (r >> 3) + rb * 16)));
@@ -313,7 +364,10 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
             bbuf[slot][0] = u4{w.x, w.y, 0u, 0u};
         }
 #pragma unroll
-        for (int en = 0; en < L; ++en) sobuf[slot][en] = load16(at(a.s_out, static_cast<uint32_t>(en * d_out + j0) * 2u));
+        for (int en = 0; en < L; ++en) {
+            const void* so = at(a.s_out, static_cast<uint32_t>(en * d_out + j0) * 2u);
+            sobuf[slot][en] = ANY ? load16_any(so) : load16(so);
+        }
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             int row = TMV == 16 ? q * 4 + i : q * 2 + i;
@@ -324,9 +378,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
                 ybuf[slot][i] = buffer_load16_stream(yb_rs, (mine && (!MASK || live)) ? static_cast<uint32_t>(row * d_out + j0) * 2u : kBufferSkip);
             } else if (MASK) {
                 ybuf[slot][i] = u4{0u, 0u, 0u, 0u};
-                if (live) ybuf[slot][i] = load16_stream(at(ybt, static_cast<uint32_t>(row * d_out + j0) * 2u));
+                if (live) ybuf[slot][i] = load_x(at(ybt, static_cast<uint32_t>(row * d_out + j0) * 2u));
             } else {
-                ybuf[slot][i] = load16_stream(at(ybt, static_cast<uint32_t>(row * d_out + j0) * 2u));
+                ybuf[slot][i] = load_x(at(ybt, static_cast<uint32_t>(row * d_out + j0) * 2u));
             }
         }
     };
@@ -348,8 +402,24 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
         for (int en = 0; en < L; ++en) acc[rb][en] = f4{0.f, 0.f, 0.f, 0.f};
     }
 
-    auto consume_x = [&](int slot) {
+    auto consume_x = [&](int slot, int n) {
         _Float16* sw = sinw + slot * L * 128;
+        if constexpr (ANY) {
+            int c = wave + NW * n;
+            c = c < nchunks ? c : nchunks - 1;
+            if (c * 128 + 128 > d_in) {  // scalar: the last chunk, where a group of 8 columns may have been read from d_in - 8 on
+                const int back = c * 128 + li * 8 - (d_in - 8);
+#pragma unroll
+                for (int m = 0; m < NI; ++m) xbuf[slot][m] = drop_halves(xbuf[slot][m], back > 0 ? back : 0);
+            }
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const int rk = rb * 16 + li < r ? rb * 16 + li : r - 1;
+                const uint32_t bit = bits_of(c, rk);
+                const uint64_t both = static_cast<uint64_t>(abits_hi[slot][rb]) << 32 | abits[slot][rb];
+                abits[slot][rb] = static_cast<uint32_t>(both >> (bit - 32 * word_of(bit)));
+            }
+        }
 #pragma unroll
         for (int en = 0; en < L; ++en) reinterpret_cast<uint32_t*>(sw + en * 128)[lane] = sinbuf[slot][en];
 #pragma unroll
@@ -390,26 +460,27 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     if (OS) {
 #pragma unroll
         for (int slot = 0; slot < D1; ++slot)
-            if (slot < my_n) consume_x(slot);
+            if (slot < my_n) consume_x(slot, slot);
     } else {
         const int ngroups = (my_n + D1 - 1) / D1;
         for (int g = 0; g + 1 < ngroups; ++g) {
 #pragma unroll
             for (int slot = 0; slot < D1; ++slot) {
-                consume_x(slot);
-                issue_x(slot, (g + 1) * D1 + slot);
+                consume_x(slot, g * D1 + slot);
+                if (!ANY || (g + 1) * D1 + slot < my_n) issue_x(slot, (g + 1) * D1 + slot);
             }
         }
 #pragma unroll
         for (int slot = 0; slot < D1; ++slot)
-            if ((ngroups - 1) * D1 + slot < my_n) consume_x(slot);
+            if ((ngroups - 1) * D1 + slot < my_n && (!ANY || ngroups > 0)) consume_x(slot, (ngroups - 1) * D1 + slot);
     }
     // TR (training instantiation): t is also written, and with y_out == nullptr nothing else is computed.  The inference
     // instantiation carries none of this.
     const bool with_y = !TR || a.y_out != nullptr;  // uniform: a kernel argument
     if (with_y) {
 #pragma unroll
-        for (int slot = 0; slot < D2; ++slot) issue_y(slot, slot);
+        for (int slot = 0; slot < D2; ++slot)
+            if (!(ANY || (BM == 0 && SPLIT)) || slot < my_b) issue_y(slot, slot);
     }
 
     // ---------------------------------------------------------------- stage 2: reduce, scale, split -
@@ -537,10 +608,22 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // ---------------------------------------------------------------- stage 3: expand + epilogue ----
     // MFMA e of a block produces column 8 li + e of the block for lane group li, so after the 8 MFMAs a lane holds 8
     // consecutive columns of its token rows.
-    auto store_y = [&](int row, int j0, bool j_ok, u4 out) {
+    auto store_y = [&](int row, int j0, bool j_ok, u4 out, int jn = 0) {
         const bool wanted = j_ok && row >= first && row <= last;
         const uint32_t off = static_cast<uint32_t>(row * d_out + j0) * 2u;
         if (BUFY) buffer_store16_stream(yo_rs, wanted ? off : kBufferSkip, out);
+        else if constexpr (ANY) {
+            // (row, j0) is the first of the 8 columns that `out` holds; those before `from` belong to the group before this one,
+            // which may be another wave's, and y_out may be y_base: only the columns from there on are written.
+            const int from = jn - j0;
+            if (wanted && from == 0) store16_any_stream(at(yot, off), out);
+            else if (wanted) {
+                uint16_t* dst = static_cast<uint16_t*>(at(yot, off));
+#pragma unroll
+                for (int e = 1; e < 8; ++e)
+                    if (e >= from) dst[e] = static_cast<uint16_t>(out[e >> 1] >> (16 * (e & 1)));
+            }
+        }
         else if (wanted) store16_stream(at(yot, off), out);
     };
     // (`run` false, only with buffer accesses: nothing is computed or stored, but the same vector memory instructions are issued)
@@ -548,7 +631,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
         const int b = b_first + block_of(n);
         const int j0 = b * 128 + li * 8;
         const bool j_ok = j0 < d_out;
-        const int jc = j_ok ? j0 : d_out - 8;
+        const int jc = (ANY ? j0 <= d_out - 8 : j_ok) ? j0 : d_out - 8;
         if (!run) {
 #pragma unroll
             for (int i = 0; i < NI; ++i) store_y(0, 0, false, u4{0u, 0u, 0u, 0u});
@@ -556,7 +639,31 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
         }
         // Table offsets of all 8 * RB sign operands first (for a general r these are global loads: one wait for all).
         uint32_t off[8][RB];
-        if (!(PRE && use_pre)) {
+        if constexpr (BM == 0) {
+            // the 8 r bits brought to bit 0, then r bits taken off the bottom per column; lane group q supplies the ranks of byte q & 1
+            uint32_t w[NB];
+            const uint32_t s0 = static_cast<uint32_t>(jc) * static_cast<uint32_t>(r) & 31u, half = 8u * static_cast<uint32_t>(q & 1);
+#pragma unroll
+            for (int k = 0; k + 1 < NB; ++k) w[k] = __builtin_amdgcn_alignbit(braw[slot][k + 1], braw[slot][k], s0);
+            w[NB - 1] = 0u;
+            constexpr int SK = (RB - 1) / 2;            // whole words of r
+            const uint32_t rest = static_cast<uint32_t>(r) - 32u * SK;   // 1 .. 32
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) off[e][rb] = __builtin_amdgcn_ubfe(w[rb >> 1], half + 16u * (rb & 1), 8) << 4;
+#pragma unroll
+                for (int k = 0; k < (RB * (7 - e) + 1) / 2; ++k) {
+                    const uint32_t lo = w[k + SK], mid = k + SK + 1 < NB ? w[k + SK + 1] : 0u, hi = k + SK + 2 < NB ? w[k + SK + 2] : 0u;
+                    if constexpr (ANY && RB % 2 == 0) {  // rest may be 32, which the instruction takes for 0: in two steps
+                        const uint32_t lo1 = __builtin_amdgcn_alignbit(mid, lo, 16), mid1 = __builtin_amdgcn_alignbit(hi, mid, 16);
+                        w[k] = __builtin_amdgcn_alignbit(mid1, lo1, rest - 16u);
+                    } else {
+                        w[k] = __builtin_amdgcn_alignbit(mid, lo, rest);
+                    }
+                }
+            }
+        } else if (!(PRE && use_pre)) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
 #pragma unroll
@@ -567,8 +674,6 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
                         off[e][rb] = (hw & 1) ? (word >> 12) & 0xff0u : (word << 4) & 0xff0u;
                     } else if (R8) {
                         off[e][rb] = ((bbuf[slot][0][e >> 2] >> ((e & 3) * 8)) << 4) & 0xff0u;
-                    } else {
-                        off[e][rb] = fetch8(a.pB, static_cast<int64_t>(jc + e) * r + rb * 16 + (q & 1) * 8, nwordsB) << 4;
                     }
                 }
             }
@@ -606,7 +711,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
                     o[1] = static_cast<_Float16>(f1);
                     out[d] = __builtin_bit_cast(uint32_t, o);
                 }
-                store_y(row, j0, j_ok, out);
+                store_y(row, ANY ? jc : j0, j_ok, out, j0);
             }
         } else {
             // Several envelopes: the accumulator sets are run one after the other into the same registers, and each set is
@@ -673,7 +778,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
                     oh[1] = static_cast<_Float16>(o[i][2 * d + 1]);
                     out[d] = __builtin_bit_cast(uint32_t, oh);
                 }
-                store_y(row, j0, j_ok, out);
+                store_y(row, ANY ? jc : j0, j_ok, out, j0);
             }
         }
     };
@@ -729,14 +834,14 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
 // The second launch bound is the number of waves per SIMD the registers must leave room for: what the workgroup size
 // implies, except in the multi-adapter batch on 8 waves (one envelope; one rank block, or two with whole-word carrier rows),
 // where two workgroups have to share a compute unit.
-template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool TR>
-__global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && (RB == 1 || (RB == 2 && BM == 1))) ? 4 : NW / 4) void lordba_fwd_mfma_kernel(FwdArgs a) {
+template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool TR, bool ANY = false>
+__global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && !ANY && (RB == 1 || (RB == 2 && BM == 1))) ? 4 : NW / 4) void lordba_fwd_mfma_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     if constexpr (GM != 4) {
         const int64_t t0 = static_cast<int64_t>(blockIdx.x) * TMV;
         if ((GM == 2 || GM == 3) && t0 >= a.T) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
         const int last = static_cast<int>(a.T - 1 - t0 < TMV - 1 ? a.T - 1 - t0 : TMV - 1);  // last live row of the tile
-        fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR>(a, smem, t0, 0, last);
+        fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR, ANY>(a, smem, t0, 0, last);
     } else {
         // Multi-adapter batch: the rows of a tile are taken in runs of equal adapter index.  A tile of a sorted batch has
         // one run (two where requests meet), a decode batch has one per row.  The gridDim.y workgroups of a tile share its
@@ -772,6 +877,10 @@ __global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && (RB == 1 
             for (int row = first; row <= end; ++row) {
                 const _Float16* src = a.y_base + (t0 + row) * a.d_out;
                 _Float16* dst = a.y_out + (t0 + row) * a.d_out;
+                if constexpr (ANY) {
+                    for (int c = static_cast<int>(threadIdx.x); c < a.d_out; c += NW * 64) dst[c] = src[c];
+                    continue;
+                }
                 for (int c = static_cast<int>(threadIdx.x) * 8; c < a.d_out; c += NW * 64 * 8)
                     store16_stream(dst + c, load16_stream(src + c));
             }
@@ -785,14 +894,14 @@ __global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && (RB == 1 
         if (first > last) return;  // no run for this workgroup: it leaves, before any barrier
         {
             const int end = run_end(first), id = __builtin_amdgcn_readlane(my_id, first);
-            if (id >= 0) fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR>(select_adapter(a, id), smem, t0, first, end);
+            if (id >= 0) fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR, ANY>(select_adapter(a, id), smem, t0, first, end);
             else pass_through(first, end);
             first = skip_runs(end + 1, stride - 1);
         }
         while (first <= last) {
             const int end = run_end(first), id = __builtin_amdgcn_readlane(my_id, first);
             __syncthreads();  // the previous run's last LDS reads are over
-            if (id >= 0) fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR>(select_adapter(a, id), smem, t0, first, end);
+            if (id >= 0) fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR, ANY>(select_adapter(a, id), smem, t0, first, end);
             else pass_through(first, end);
             first = skip_runs(end + 1, stride - 1);
         }
@@ -904,18 +1013,18 @@ constexpr size_t kMaxLds = 160 * 1024;  // LDS per CU on gfx950
 #endif
 constexpr bool kTraining = LORDBA_FWD_TRAINING != 0;
 
-template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L>
+template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool ANY = false>
 lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
     constexpr bool TR = kTraining;
     if ((a.t_out != nullptr) != TR) return LORDBA_ERR_ALGO;  // (an entry point of the other kind of unit)
     // With several envelopes only the plain grid mode of the 8-row, 8-wave variants has a training instantiation (the
     // dispatch sends such calls there); the multi-adapter batch has none.
-    if constexpr (TR && !((L == 1 && GM != 4) || (L > 1 && GM == 0 && TMV == 8 && NW == 8))) {
+    if constexpr (TR && !((L == 1 && GM != 4) || (L > 1 && GM == 0 && TMV == 8 && NW == 8) || (ANY && GM == 2))) {
         return LORDBA_ERR_ALGO;
     } else {
     const size_t lds = mfma_lds_bytes(RB, TMV, NW, D1, L);
     if (lds > kMaxLds) return LORDBA_ERR_ALGO;
-    auto kern = lordba_fwd_mfma_kernel<RB, TMV, NW, D1, OS, BM, GM, L, TR>;
+    auto kern = lordba_fwd_mfma_kernel<RB, TMV, NW, D1, OS, BM, GM, L, TR, ANY>;
     if (lds > 64 * 1024) {
         // Opt in to more than 64 KiB of dynamic LDS once per device and kernel; raising the limit is idempotent.
         static std::mutex mu;
@@ -940,7 +1049,9 @@ lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
         // tile are split over several workgroups (each repeats the cheap stages 1 and 2; nothing is exchanged).
         const unsigned nblk = static_cast<unsigned>((a.d_out + 127) / 128);
         unsigned split = (nblk + kSplitBlocks - 1) / kSplitBlocks;
-        const unsigned cap = 256 / tiles;
+        // (ANY: two workgroups per compute unit where a workgroup is mostly stage 3: 1500 rows of 1000 -> 3001 8.5 against 9.9 us; where
+        // the repeated reads of x weigh as much they lose, 500 rows of 5001 -> 5001 11.6 against 9.1)
+        const unsigned cap = (ANY && a.d_out >= 2 * a.d_in ? 512 : 256) / tiles;
         split = split < cap ? split : cap;
         split = split < 1 ? 1 : split;
         b.blocks_per_wg = static_cast<int>((nblk + split - 1) / split);
@@ -1122,7 +1233,13 @@ lordba_status forward_impl(const void* x, const uint32_t* packedA, const uint32_
 
     if (algo == LORDBA_ALGO_GENERAL) return launch_general(a, st, vec_x);
     if (algo != LORDBA_ALGO_AUTO && !mfma_ok) return LORDBA_ERR_ALGO;
-    if (algo == LORDBA_ALGO_AUTO && !mfma_ok) return launch_general(a, st, vec_x);
+    // What the plain matrix-core variants do not take: the element-aligned ones, and what those do not take either (fewer than 8
+    // columns) the general kernel.
+    auto launch_rest = [&]() {
+        const lordba_status any = kTraining ? lordba_forward_any_train(a, st) : lordba_forward_any(a, st);
+        return any == LORDBA_ERR_ALGO ? launch_general(a, st, vec_x) : any;
+    };
+    if (algo == LORDBA_ALGO_AUTO && !mfma_ok) return launch_rest();
 
     // Tile and workgroup shape.  16-row tiles halve the per-row cost of building sign operands and are taken once
     // T / 16 tiles still fill the 256 CUs; below that, 8-row tiles keep every CU busy.  16 waves per workgroup hide
@@ -1186,7 +1303,7 @@ lordba_status forward_impl(const void* x, const uint32_t* packedA, const uint32_
             if (s == LORDBA_ERR_ALGO) s = launch_mfma_rb<8, 8, L>(a, st);
         }
     }
-    if (s == LORDBA_ERR_ALGO && algo == LORDBA_ALGO_AUTO) return launch_general(a, st, vec_x);
+    if (s == LORDBA_ERR_ALGO && algo == LORDBA_ALGO_AUTO) return launch_rest();
     return s;
 }
 
