@@ -53,7 +53,8 @@ struct FwdArgs {
     _Float16* y_out;
     int T, d_in, d_out, r;
     int ell;  // envelopes: s_in, s_rank, s_out are [ell, d_in], [ell, r], [ell, d_out]
-    int blocks_per_wg;  // matrix-core kernel: 128-column output blocks per workgroup (the grid's y extent covers d_out)
+    int blocks_per_wg;  // matrix-core kernel: 128-column output blocks per workgroup (the grid's y, or in the batch its z, extent covers d_out)
+    int by_xcd;         // multi-adapter batch: tiles are dealt to the XCDs in contiguous ranges
     // Multi-adapter batch (ids != nullptr): pA, pB, s_in, s_rank, s_out are pools of n_adapters adapters laid out one
     // after the other, and token row t uses adapter ids[t]; an id outside [0, n_adapters) means "no adapter".
     const int32_t* ids;
@@ -105,11 +106,12 @@ __host__ __device__ constexpr size_t mfma_lds_bytes(int RB, int TMV, int NW, int
 // BM   how a lane fetches the sign(B) bits of its 8 output columns: 1 = r is a multiple of 16 (RB aligned 16-byte
 //      loads), 2 = r is 8 (one aligned 8-byte load, one byte per column), 0 = any r (two dwords per operand)
 // GM   grid mode.  1 (grids that fill the chip): the waves that do not run stage 2 build their first block's sign
-//      operands during stage 2 instead of before it.  2 (a handful of tiles): gridDim.y workgroups share a token tile
-//      and split its output blocks; the x extent of the grid is padded to a multiple of 8 and padding workgroups exit.
-//      3 (fewer token rows than a tile): as 2, and rows past T are not requested at all.  4: multi-adapter batch,
-//      the gridDim.y workgroups of a tile share its runs of rows that use the same adapter (rows outside a run are not
-//      requested).  0: none of these.
+//      operands during stage 2 instead of before it.  0: the same without that; gridDim.y workgroups may share a token tile and
+//      split its output blocks; the x extent of such a grid is padded to a multiple of 8 and padding workgroups exit.  2 (tiles
+//      that do not fill the chip): as 0, with at most one output block per wave, so that no request is made for a second one.
+//      3 (fewer token rows than a tile): as 2, and rows past T are not requested at all.  4: multi-adapter batch, the
+//      gridDim.y workgroups of a tile share its runs of rows that use the same adapter (rows outside a run are not
+//      requested), gridDim.z workgroups share a run's output blocks.  5: as 4, with at most one output block per wave.
 // L    scale envelopes over the same carriers (Eq. (lordba)): s_in, s_rank, s_out hold L rows; everything that depends
 //      on a scale is done L times, everything that depends only on x or on the carrier bits once
 //
@@ -121,17 +123,18 @@ __host__ __device__ constexpr size_t mfma_lds_bytes(int RB, int TMV, int NW, int
 template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool TR, bool ANY>
 __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, const int64_t t0, const int first, const int last) {
     static_assert(NW >= 4, "stage 2 is spread over the first four waves");
-    constexpr bool LP = GM == 1, SPLIT = GM == 2 || GM == 3, MASK = GM == 3 || GM == 4;
+    constexpr bool LP = GM == 1, SPLIT = GM == 2 || GM == 3, POOL = GM == 4 || GM == 5, MASK = GM == 3 || POOL;
+    constexpr bool ONE = !ANY && (SPLIT || GM == 5);  // at most one output block per wave (the host sees to it)
     constexpr int NI = TMV / 4;           // 16-byte row accesses per lane per 128-column block of a tile
     // y_base column blocks in flight per wave.  Three and four envelopes run on 8 waves (their registers do not fit 16
     // waves): on 8-row tiles four blocks in flight per wave keep as many bytes of y_base under way per compute unit as 16
     // waves with two.  The multi-adapter batch on 8 waves holds three (two of its workgroups share a compute unit, so a
     // lane has 128 registers).  Four envelopes on 16-row tiles (grids of at least 256 tiles, two workgroups per compute
     // unit) hold one.
-    constexpr int D2 = (TMV == 16 && L == 4) ? 1 : (GM == 4 && NW == 8 && RB == 1 && L == 1 && BM != 0) ? 3 : (NW == 8 && TMV == 8 && GM != 4 && ((L >= 3 && RB == 1) || (L == 3 && RB == 2 && !ANY))) ? 4 : 2;
+    constexpr int D2 = ONE ? 1 : (TMV == 16 && L == 4) ? 1 : (GM == 4 && NW == 8 && RB == 1 && L == 1 && BM != 0) ? 3 : (NW == 8 && TMV == 8 && !POOL && ((L >= 3 && RB == 1) || (L == 3 && RB == 2 && !ANY))) ? 4 : 2;
     constexpr bool R16 = BM == 1, R8 = BM == 2;
     static_assert(!R8 || RB == 1, "r = 8 is one rank block");
-    static_assert(!ANY || (BM == 0 && (GM == 2 || GM == 4)), "element-aligned tensors: one variant family");
+    static_assert(!ANY || (BM == 0 && (GM == 2 || POOL)), "element-aligned tensors: one variant family");
     // General r: the sign(B) bits of a lane's 8 columns are 8 r consecutive bits (at most 4 RB words, one more because they
     // start inside a word).  They are requested with the block's y_base, 16 bytes at a time, and taken apart in registers; two
     // dword loads per column and rank block when the block is consumed, as before, cost as many memory instructions as
@@ -174,7 +177,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     _Float16* yot = a.y_out + t0 * d_out;
     // Multi-adapter batch: y_base and y_out of the tile as buffers of rows 0..last; rows of stage 3 that are not live get an
     // offset outside instead of a branch around the access (the runs of a tile make most accesses partial there).
-    constexpr bool BUFY = !ANY && (GM == 4 || (L == 1 && (GM == 0 || GM == 1) && TMV == 8 && NW == 8));
+    constexpr bool BUFY = !ANY && (POOL || (L == 1 && (GM == 0 || GM == 1) && TMV == 8 && NW == 8));
     const uint32_t ytile_bytes = static_cast<uint32_t>(last + 1) * static_cast<uint32_t>(d_out) * 2u;
     const __amdgpu_buffer_rsrc_t yb_rs = buffer_over(ybt, BUFY ? ytile_bytes : 0u), yo_rs = buffer_over(yot, BUFY ? ytile_bytes : 0u);
 
@@ -189,7 +192,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // dword loads, each of which has the memory pipeline look up 16 cache lines for 256 bytes.  At decode sizes, where a
     // few workgroups run alone and the time to issue the loads is latency of the call, that is 2.4 us of 9.6 at r = 64;
     // grids that fill the chip gain 1 to 5 %.  (The multi-adapter batch keeps the round-robin deal: 128 registers.)
-    constexpr bool CA = OS && GM != 4 && !ANY;
+    constexpr bool CA = OS && !POOL && !ANY;
     const int words_per_row = d_in >> 5;  // d_in % 32 == 0 on this path
     // (the first nchunks mod NW waves own one chunk more than the others: at most ceil(nchunks / NW), <= D1 where OS)
     const int c_each = nchunks / NW, c_more = nchunks - c_each * NW;
@@ -311,13 +314,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // gridDim.y workgroups may share a token tile (small T: most of the chip would idle otherwise): each repeats stages 1
     // and 2, which costs no extra HBM traffic worth naming at such T, and takes its own contiguous range of blocks.
     const int nblk_all = (d_out + 127) >> 7;
-    const int per_wg = SPLIT ? a.blocks_per_wg : nblk_all;
-    const int b_first = SPLIT ? static_cast<int>(blockIdx.y) * per_wg : 0;
+    const int per_wg = GM == 1 ? nblk_all : a.blocks_per_wg;
+    const int b_first = GM == 1 ? 0 : static_cast<int>(POOL ? blockIdx.z : blockIdx.y) * per_wg;
     const int nblk = nblk_all - b_first < per_wg ? (nblk_all - b_first > 0 ? nblk_all - b_first : 0) : per_wg;
     // A wave owns CONSECUTIVE blocks (its blocks in flight are then one contiguous piece of each row: 512 bytes per row at
     // the headline shape instead of two pieces 4 KiB apart: C2 9.99 -> 9.61 us, 4096 -> 11008 at T = 4096 42.1 -> 39.7),
     // The multi-adapter batch keeps the round-robin deal, which measured faster there.
-    constexpr bool CB = GM != 4;
+    constexpr bool CB = !POOL;
     // Runs of ceil(nblk / NW) blocks while that leaves the last wave at least half a run (108 blocks over 8 waves: 14 .. 14 10,
     // measured 1.5 % faster than 14 14 14 14 13 13 13 13); otherwise the first nblk mod NW waves own one block more than
     // the others (40 blocks over 16 waves: 3 .. 3 2 .. 2; runs of 3 would leave two waves without a block and cost 8 %).
@@ -480,7 +483,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     if (with_y) {
 #pragma unroll
         for (int slot = 0; slot < D2; ++slot)
-            if (!(ANY || (BM == 0 && SPLIT)) || slot < my_b) issue_y(slot, slot);
+            if (!(ANY || ONE) || slot < my_b) issue_y(slot, slot);
     }
 
     // ---------------------------------------------------------------- stage 2: reduce, scale, split -
@@ -512,7 +515,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // The waves that run stage 2 build theirs while they wait for the slower waves to finish stage 1.  The others idle
     // during stage 2 anyway: with LP they build theirs there, which takes the work off the slowest wave's way to the
     // first barrier; without LP (a few workgroups, latency-bound) everything is built as early as possible.
-    if (PRE && (!LP || wave < 4) && with_y) build_pre();
+    if (PRE && (!LP || wave < 4) && with_y && (!ONE || my_b > 0)) build_pre();
     __syncthreads();
 
     // Training: the rank-r intermediate t (before the rank scaling) is kept for the backward pass.  The stores are issued
@@ -787,7 +790,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // memory instructions whatever the wave's number of blocks is (what is not wanted is skipped by its offset), so that
     // the wait for a slot's y_base leaves the later requests and the stores in flight; with requests under branches the
     // compiler has to wait for all of them.
-    constexpr bool kSteadyLoop = BUFY && GM != 4;
+    constexpr bool kSteadyLoop = BUFY && !POOL;
     if constexpr (kSteadyLoop) {
         if (my_b > 0) consume_y(0, 0, true, true);
         if (nblk > NW * D2) {
@@ -837,9 +840,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
 template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool TR, bool ANY = false>
 __global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && !ANY && (RB == 1 || (RB == 2 && BM == 1))) ? 4 : NW / 4) void lordba_fwd_mfma_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    if constexpr (GM != 4) {
+    if constexpr (GM < 4) {
         const int64_t t0 = static_cast<int64_t>(blockIdx.x) * TMV;
-        if ((GM == 2 || GM == 3) && t0 >= a.T) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
+        if (GM != 1 && t0 >= a.T) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
         const int last = static_cast<int>(a.T - 1 - t0 < TMV - 1 ? a.T - 1 - t0 : TMV - 1);  // last live row of the tile
         fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR, ANY>(a, smem, t0, 0, last);
     } else {
@@ -857,7 +860,7 @@ __global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && !ANY && (
         // of one request then read their adapter through one L2 instead of pulling it into several.
         static_assert(TMV == 8, "runs are found among 8 rows");
         const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV, per_xcd = (tiles + 7) >> 3;
-        const bool by_xcd = a.blocks_per_wg != 0;  // (set by the host on grids that fill the chip; the x extent is then padded)
+        const bool by_xcd = a.by_xcd != 0;  // (set by the host on grids that fill the chip; the x extent is then padded)
         const int64_t tile = by_xcd ? static_cast<int64_t>(blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3) : static_cast<int64_t>(blockIdx.x);
         if (tile >= tiles) return;  // padding workgroup
         const int64_t t0 = tile * TMV;
@@ -873,7 +876,7 @@ __global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && !ANY && (
             return end;
         };
         auto pass_through = [&](int first, int end) {  // no adapter: the rows pass through
-            if (a.y_out == a.y_base) return;
+            if (a.y_out == a.y_base || blockIdx.z != 0) return;
             for (int row = first; row <= end; ++row) {
                 const _Float16* src = a.y_base + (t0 + row) * a.d_out;
                 _Float16* dst = a.y_out + (t0 + row) * a.d_out;
@@ -1013,13 +1016,49 @@ constexpr size_t kMaxLds = 160 * 1024;  // LDS per CU on gfx950
 #endif
 constexpr bool kTraining = LORDBA_FWD_TRAINING != 0;
 
+// Output blocks per workgroup of a call whose tiles do not fill the chip: its tiles' blocks are split over several workgroups
+// (each repeats stages 1 and 2; nothing is exchanged), at least kSplitBlocks for each, up to one workgroup per compute unit.
+// Up to 128 tiles, where that is two workgroups per tile (us, whole tiles in brackets): T = 512, 4096 -> 4096 6.1 (7.1), 4096 ->
+// 11008 7.6 (13.7), 11008 -> 4096 11.7 (13.2), r = 64 9.9 (15.0); T = 1000, 4096 -> 11008 13.1 (16.0), 4096 -> 4096 7.2 (7.6).
+// Where that leaves a wave at most one block, the variants for it (grid modes 2 and 3) make no request for a second: T = 8,
+// 4096 -> 4096 4.86 against 5.16, 64 x 512 -> 512 at r = 4 3.85 against 4.43.
+constexpr unsigned kFewTiles = 128;
+template <int TMV, int NW, bool ANY>
+int split_blocks(const FwdArgs& a) {
+    const unsigned nblk = static_cast<unsigned>((a.d_out + 127) / 128);
+    const unsigned tiles = static_cast<unsigned>((static_cast<int64_t>(a.T) + TMV - 1) / TMV);
+    if (TMV != 8 || NW < 8 || (!ANY && tiles > kFewTiles)) return static_cast<int>(nblk);
+    // (ANY: two workgroups per compute unit where a workgroup is mostly stage 3: 1500 rows of 1000 -> 3001 8.5 against 9.9 us; where
+    // the repeated reads of x weigh as much they lose, 500 rows of 5001 -> 5001 11.6 against 9.1)
+    const unsigned cap = (ANY && a.d_out >= 2 * a.d_in ? 512 : 256) / tiles;
+    unsigned split = (nblk + kSplitBlocks - 1) / kSplitBlocks;
+    split = split < cap ? split : cap;
+    split = split < 1 ? 1 : split;
+    return static_cast<int>((nblk + split - 1) / split);
+}
+// The same for the multi-adapter batch, whose every row may be a run with a workgroup of its own (us, one workgroup per run in
+// brackets; 64 rows, each with its adapter): 4096 -> 4096 6.5 (7.4), 4096 -> 11008 7.4 (10.5), 11008 -> 4096 10.1 (11.4), r = 32
+// 8.5 (10.7); 8 rows 5.8 (7.0).  Two workgroups per compute unit lose what they gain (the adapter's bits are read once more
+// each): 12.5 us at 4096 -> 4096.
+constexpr unsigned kFewPoolTiles = 32;
+int pool_split_blocks(const FwdArgs& a) {
+    const unsigned nblk = static_cast<unsigned>((a.d_out + 127) / 128);
+    const unsigned tiles = static_cast<unsigned>((static_cast<int64_t>(a.T) + 7) / 8);
+    if (tiles > kFewPoolTiles) return static_cast<int>(nblk);
+    const unsigned cap = 256 / (8 * tiles);
+    unsigned split = (nblk + kSplitBlocks - 1) / kSplitBlocks;
+    split = split < cap ? split : cap;
+    split = split < 1 ? 1 : split;
+    return static_cast<int>((nblk + split - 1) / split);
+}
+
 template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool ANY = false>
 lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
     constexpr bool TR = kTraining;
     if ((a.t_out != nullptr) != TR) return LORDBA_ERR_ALGO;  // (an entry point of the other kind of unit)
     // With several envelopes only the plain grid mode of the 8-row, 8-wave variants has a training instantiation (the
     // dispatch sends such calls there); the multi-adapter batch has none.
-    if constexpr (TR && !((L == 1 && GM != 4) || (L > 1 && GM == 0 && TMV == 8 && NW == 8) || (ANY && GM == 2))) {
+    if constexpr (TR && !((L == 1 && GM < 4) || (L > 1 && GM == 0 && TMV == 8 && NW == 8) || (ANY && GM == 2))) {
         return LORDBA_ERR_ALGO;
     } else {
     const size_t lds = mfma_lds_bytes(RB, TMV, NW, D1, L);
@@ -1043,28 +1082,22 @@ lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
     }
     const unsigned tiles = static_cast<unsigned>((static_cast<int64_t>(a.T) + TMV - 1) / TMV);
     FwdArgs b = a;
+    const unsigned nblk = static_cast<unsigned>((a.d_out + 127) / 128);
+    b.blocks_per_wg = static_cast<int>(nblk);
     dim3 grid(tiles);
-    if constexpr (GM == 2 || GM == 3) {
-        // A handful of tiles leaves most CUs idle and each workgroup with a long serial stage 3: the output blocks of a
-        // tile are split over several workgroups (each repeats the cheap stages 1 and 2; nothing is exchanged).
-        const unsigned nblk = static_cast<unsigned>((a.d_out + 127) / 128);
-        unsigned split = (nblk + kSplitBlocks - 1) / kSplitBlocks;
-        // (ANY: two workgroups per compute unit where a workgroup is mostly stage 3: 1500 rows of 1000 -> 3001 8.5 against 9.9 us; where
-        // the repeated reads of x weigh as much they lose, 500 rows of 5001 -> 5001 11.6 against 9.1)
-        const unsigned cap = (ANY && a.d_out >= 2 * a.d_in ? 512 : 256) / tiles;
-        split = split < cap ? split : cap;
-        split = split < 1 ? 1 : split;
-        b.blocks_per_wg = static_cast<int>((nblk + split - 1) / split);
-        split = (nblk + b.blocks_per_wg - 1) / b.blocks_per_wg;  // no workgroup without a block
+    if constexpr (GM < 4 && GM != 1) {
+        b.blocks_per_wg = split_blocks<TMV, NW, ANY>(a);
+        const unsigned split = (nblk + b.blocks_per_wg - 1) / b.blocks_per_wg;  // no workgroup without a block
         // Workgroups are dealt to the 8 XCDs round-robin in launch order (x fastest).  With an x extent that is a
         // multiple of 8, the workgroups that share a tile (same x) land on one XCD and read x, s_in and the carriers
         // through one L2 instead of fetching them into eight; the padding workgroups exit at once.
-        grid = dim3((tiles + 7u) & ~7u, split);
+        if (split > 1 || GM != 0) grid = dim3((tiles + 7u) & ~7u, split);
     }
-    if constexpr (GM == 4) {  // see the kernel
-        const bool big = tiles > 32;
-        b.blocks_per_wg = big ? 1 : 0;  // (read by the kernel as "tiles are dealt to the XCDs in contiguous ranges")
-        grid = big ? dim3((tiles + 7u) & ~7u, 2) : dim3(tiles, TMV);
+    if constexpr (GM == 4 || GM == 5) {  // see the kernel
+        const bool big = tiles > kFewPoolTiles;
+        b.by_xcd = big ? 1 : 0;
+        b.blocks_per_wg = pool_split_blocks(a);
+        grid = big ? dim3((tiles + 7u) & ~7u, 2) : dim3(tiles, TMV, (nblk + b.blocks_per_wg - 1) / b.blocks_per_wg);
     }
     hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, stream, b);
     return hipGetLastError() == hipSuccess ? LORDBA_OK : LORDBA_ERR_LAUNCH;
@@ -1072,8 +1105,8 @@ lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
 }
 
 // Grid mode 1 only exists where sign operands are built ahead (one rank block, byte-aligned carrier rows); it pays once
-// the grid covers the chip, where the slowest wave at the first barrier sets the pace of the workgroup.  Grid mode 2
-// is for 8-row tiles when there are at most 32 of them, grid mode 3 for a single partial tile (decode).
+// the grid covers the chip, where the slowest wave at the first barrier sets the pace of the workgroup.  Grid modes 2 and 3
+// are for few 8-row tiles (split_blocks), 3 for a single partial tile (decode).
 template <int RB, int TMV, int NW, int D1, bool OS, int BM, int L>
 lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
     const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
@@ -1082,6 +1115,7 @@ lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
         // Pools of adapters with several envelopes run the 8-wave variants (one workgroup per compute unit) up to r = 32 (r = 16 with four envelopes); beyond
         // that the registers do not hold the batch mode's two copies of the tile code, and the general kernel runs.
         if constexpr (TMV == 8 && D1 <= 4 && ((L == 1 && (NW == 8 || (NW == 16 && RB == 1))) || (L > 1 && NW == 8 && (RB == 1 || (RB == 2 && L <= 3))))) {
+            if (tiles <= kFewPoolTiles && pool_split_blocks(a) <= NW) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 5, L>(a, stream);
             return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 4, L>(a, stream);
         }
         return LORDBA_ERR_ALGO;
@@ -1093,8 +1127,10 @@ lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
         if (tiles >= 128) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 1, L>(a, stream);
     }
     if constexpr (TMV == 8 && NW >= 8) {
-        if (a.T < TMV) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 3, L>(a, stream);
-        if (tiles <= 32 && a.d_out > static_cast<int>(kSplitBlocks) * 128) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 2, L>(a, stream);
+        if (tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {  // at most one block per wave
+            if (a.T < TMV) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 3, L>(a, stream);
+            return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 2, L>(a, stream);
+        }
     }
     return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 0, L>(a, stream);
 }
@@ -1109,6 +1145,23 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
     if (per_wave <= 2) return launch_mfma<RB, TMV, NW, 2, true, BM, L>(a, stream);
     if (per_wave <= 4) return launch_mfma<RB, TMV, NW, 4, true, BM, L>(a, stream);
     if (kDeep && per_wave <= 8 && a.ids == nullptr) return launch_mfma<RB, TMV, NW, (kDeep ? 8 : 4), true, BM, L>(a, stream);  // (the batch mode has 128 registers)
+    // Wide inputs at decode sizes: all chunks of a wave in flight at once here too (up to 12288 columns; the registers are there since
+    // a wave has one output block at most): the loop over groups of four exposed the memory latency once per group.  11008 -> 4096,
+    // T = 8: r = 16 9.4 -> 9.0 us, r = 32 14.1 -> 11.7, r = 64 18.5 -> 17.2 (5.3 of it the vector ALU's: 11008 x 64 signs per workgroup);
+    // T = 300, r = 16 12.9 -> 10.0.
+    constexpr int kOneShot = NW == 16 ? 6 : 12;
+    if constexpr (TMV == 8 && NW >= 8 && L == 1 && !kTraining) {
+        if (per_wave <= kOneShot) {
+            const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
+            if (a.ids != nullptr) {
+                if constexpr (NW == 16 && RB == 1) {  // (two to four rank blocks on 8 waves: no gain, 2 % slower at r = 64)
+                    if (tiles <= kFewPoolTiles && pool_split_blocks(a) <= NW) return launch_mfma_gm<RB, TMV, NW, kOneShot, true, BM, 5, L>(a, stream);
+                }
+            } else if (tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
+                return launch_mfma_gm<RB, TMV, NW, kOneShot, true, BM, 2, L>(a, stream);
+            }
+        }
+    }
     return launch_mfma<RB, TMV, NW, (TMV == 8 ? 4 : 2), false, BM, L>(a, stream);
 }
 
@@ -1215,7 +1268,8 @@ lordba_status forward_impl(const void* x, const uint32_t* packedA, const uint32_
     a.d_out = static_cast<int>(d_out);
     a.r = static_cast<int>(r);
     a.ell = L;
-    a.blocks_per_wg = 0;  // set per launch in grid mode 2
+    a.blocks_per_wg = 0;  // set per launch in the grid modes that split blocks
+    a.by_xcd = 0;
     a.ids = batched ? ids : nullptr;
     a.n_adapters = static_cast<int>(n_adapters);
     a.t_out = t_out;
