@@ -169,6 +169,33 @@ def load_library():
     return lib
 
 
+_current_raw_stream = None
+
+
+def _stream_handle(tensor, stream):
+    """The hipStream_t to enqueue on, as an integer: `stream` itself (a torch stream or a handle), or torch's current stream of
+    the tensor's device.  The current stream's handle is asked for directly: a torch.cuda.Stream object around it, of which
+    only the handle was used, took 1.9 of the 9.6 microseconds that a small call spent on the host."""
+    global _current_raw_stream
+    if stream is not None:
+        return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
+    device = tensor.get_device()
+    if _current_raw_stream is None or device < 0:
+        import torch
+
+        if device < 0 or not hasattr(torch._C, "_cuda_getCurrentRawStream"):
+            return torch.cuda.current_stream(tensor.device).cuda_stream
+        _current_raw_stream = torch._C._cuda_getCurrentRawStream
+    return _current_raw_stream(device)
+
+
+def _need(dtype, what: str, names: Tuple[str, ...], *tensors) -> None:
+    """Raises a TypeError that names the first of the tensors that is not a contiguous CUDA tensor of this type."""
+    for t_ in tensors:
+        if t_.dtype is not dtype or not t_.is_cuda or not t_.is_contiguous():
+            raise TypeError("%s must be a contiguous %s" % (names[[u is t_ for u in tensors].index(True)], what))
+
+
 def lordba_status_string(status: int) -> str:
     return load_library().lordba_status_string(int(status)).decode()
 
@@ -226,12 +253,10 @@ def lordba_forward(x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out=None,
 
     lib = load_library()
     if check:
-        for name, t_ in (("x", x), ("s_in", s_in), ("s_rank", s_rank), ("s_out", s_out), ("y_base", y_base)):
-            if t_.dtype != torch.float16 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous float16 CUDA tensor" % name)
-        for name, t_ in (("packedA", packedA), ("packedB", packedB)):
-            if t_.dtype != torch.int32 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous int32 CUDA tensor holding the packed words" % name)
+        _need(torch.float16, "float16 CUDA tensor", ("x", "s_in", "s_rank", "s_out", "y_base"),
+              x, s_in, s_rank, s_out, y_base)
+        _need(torch.int32, "int32 CUDA tensor holding the packed words", ("packedA", "packedB"),
+              packedA, packedB)
         if x.dim() != 2 or y_base.dim() != 2 or x.shape[0] != y_base.shape[0]:
             raise ValueError("x must be [T, d_in] and y_base [T, d_out]")
     T, d_in = x.shape
@@ -247,12 +272,9 @@ def lordba_forward(x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out=None,
     elif check and (y_out.dtype != torch.float16 or not y_out.is_cuda or not y_out.is_contiguous()
                     or y_out.shape != y_base.shape):
         raise TypeError("y_out must be a contiguous float16 CUDA tensor shaped like y_base")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     args = (x.data_ptr(), packedA.data_ptr(), packedB.data_ptr(), s_in.data_ptr(), s_rank.data_ptr(), s_out.data_ptr(),
-            y_base.data_ptr(), y_out.data_ptr(), T, d_in, d_out, r, ctypes.c_void_p(stream))
+            y_base.data_ptr(), y_out.data_ptr(), T, d_in, d_out, r, stream)
     # the library's own choice of kernel goes through the entry point of that name; a selector through its _algo twin
     st = lib.lordba_forward(*args) if int(algo) == ALGO_AUTO else lib.lordba_forward_algo(*args, int(algo))
     if st != 0:
@@ -268,12 +290,10 @@ def lordba_forward_multi(x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out
 
     lib = load_library()
     if check:
-        for name, t_ in (("x", x), ("s_in", s_in), ("s_rank", s_rank), ("s_out", s_out), ("y_base", y_base)):
-            if t_.dtype != torch.float16 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous float16 CUDA tensor" % name)
-        for name, t_ in (("packedA", packedA), ("packedB", packedB)):
-            if t_.dtype != torch.int32 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous int32 CUDA tensor holding the packed words" % name)
+        _need(torch.float16, "float16 CUDA tensor", ("x", "s_in", "s_rank", "s_out", "y_base"),
+              x, s_in, s_rank, s_out, y_base)
+        _need(torch.int32, "int32 CUDA tensor holding the packed words", ("packedA", "packedB"),
+              packedA, packedB)
         if x.dim() != 2 or y_base.dim() != 2 or x.shape[0] != y_base.shape[0]:
             raise ValueError("x must be [T, d_in] and y_base [T, d_out]")
         if s_in.dim() != 2 or s_rank.dim() != 2 or s_out.dim() != 2:
@@ -291,12 +311,9 @@ def lordba_forward_multi(x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out
     elif check and (y_out.dtype != torch.float16 or not y_out.is_cuda or not y_out.is_contiguous()
                     or y_out.shape != y_base.shape):
         raise TypeError("y_out must be a contiguous float16 CUDA tensor shaped like y_base")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     args = (x.data_ptr(), packedA.data_ptr(), packedB.data_ptr(), s_in.data_ptr(), s_rank.data_ptr(), s_out.data_ptr(),
-            y_base.data_ptr(), y_out.data_ptr(), T, d_in, d_out, r, ell, ctypes.c_void_p(stream))
+            y_base.data_ptr(), y_out.data_ptr(), T, d_in, d_out, r, ell, stream)
     st = lib.lordba_forward_multi(*args) if int(algo) == ALGO_AUTO else lib.lordba_forward_multi_algo(*args, int(algo))
     if st != 0:
         raise LordbaError(st, "lordba_forward_multi")
@@ -319,13 +336,10 @@ def lordba_forward_batched(x, packedA_pool, packedB_pool, s_in_pool, s_rank_pool
 
     lib = load_library()
     if check:
-        for name, t_ in (("x", x), ("s_in_pool", s_in_pool), ("s_rank_pool", s_rank_pool), ("s_out_pool", s_out_pool),
-                         ("y_base", y_base)):
-            if t_.dtype != torch.float16 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous float16 CUDA tensor" % name)
-        for name, t_ in (("packedA_pool", packedA_pool), ("packedB_pool", packedB_pool), ("adapter_of_row", adapter_of_row)):
-            if t_.dtype != torch.int32 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous int32 CUDA tensor" % name)
+        _need(torch.float16, "float16 CUDA tensor", ("x", "s_in_pool", "s_rank_pool", "s_out_pool", "y_base"),
+              x, s_in_pool, s_rank_pool, s_out_pool, y_base)
+        _need(torch.int32, "int32 CUDA tensor", ("packedA_pool", "packedB_pool", "adapter_of_row"),
+              packedA_pool, packedB_pool, adapter_of_row)
         if x.dim() != 2 or y_base.dim() != 2 or x.shape[0] != y_base.shape[0] or adapter_of_row.numel() != x.shape[0]:
             raise ValueError("x must be [T, d_in], y_base [T, d_out], adapter_of_row [T]")
         if s_rank_pool.dim() != 2 or packedA_pool.dim() != 2 or packedB_pool.dim() != 2:
@@ -343,13 +357,10 @@ def lordba_forward_batched(x, packedA_pool, packedB_pool, s_in_pool, s_rank_pool
     elif check and (y_out.dtype != torch.float16 or not y_out.is_cuda or not y_out.is_contiguous()
                     or y_out.shape != y_base.shape):
         raise TypeError("y_out must be a contiguous float16 CUDA tensor shaped like y_base")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     args = (x.data_ptr(), packedA_pool.data_ptr(), packedB_pool.data_ptr(), s_in_pool.data_ptr(), s_rank_pool.data_ptr(),
             s_out_pool.data_ptr(), adapter_of_row.data_ptr(), y_base.data_ptr(), y_out.data_ptr(), T, d_in, d_out, r, n,
-            ctypes.c_void_p(stream))
+            stream)
     st = lib.lordba_forward_batched(*args) if int(algo) == ALGO_AUTO else lib.lordba_forward_batched_algo(*args, int(algo))
     if st != 0:
         raise LordbaError(st, "lordba_forward_batched")
@@ -363,12 +374,10 @@ def lordba_forward_batched_multi(x, packedA_pool, packedB_pool, s_in_pool, s_ran
     import torch
 
     lib = load_library()
-    for name, t_ in (("x", x), ("s_in_pool", s_in_pool), ("s_rank_pool", s_rank_pool), ("s_out_pool", s_out_pool), ("y_base", y_base)):
-        if t_.dtype != torch.float16 or not t_.is_cuda or not t_.is_contiguous():
-            raise TypeError("%s must be a contiguous float16 CUDA tensor" % name)
-    for name, t_ in (("packedA_pool", packedA_pool), ("packedB_pool", packedB_pool), ("adapter_of_row", adapter_of_row)):
-        if t_.dtype != torch.int32 or not t_.is_cuda or not t_.is_contiguous():
-            raise TypeError("%s must be a contiguous int32 CUDA tensor" % name)
+    _need(torch.float16, "float16 CUDA tensor", ("x", "s_in_pool", "s_rank_pool", "s_out_pool", "y_base"),
+          x, s_in_pool, s_rank_pool, s_out_pool, y_base)
+    _need(torch.int32, "int32 CUDA tensor", ("packedA_pool", "packedB_pool", "adapter_of_row"),
+          packedA_pool, packedB_pool, adapter_of_row)
     if x.dim() != 2 or y_base.dim() != 2 or x.shape[0] != y_base.shape[0] or adapter_of_row.numel() != x.shape[0]:
         raise ValueError("x must be [T, d_in], y_base [T, d_out], adapter_of_row [T]")
     if s_rank_pool.dim() != 3:
@@ -382,13 +391,10 @@ def lordba_forward_batched_multi(x, packedA_pool, packedB_pool, s_in_pool, s_ran
         raise ValueError("packed pool shapes do not match")
     if y_out is None:
         y_out = torch.empty_like(y_base)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     args = (x.data_ptr(), packedA_pool.data_ptr(), packedB_pool.data_ptr(), s_in_pool.data_ptr(), s_rank_pool.data_ptr(),
             s_out_pool.data_ptr(), adapter_of_row.data_ptr(), y_base.data_ptr(), y_out.data_ptr(), T, d_in, d_out, r, ell, n,
-            ctypes.c_void_p(stream))
+            stream)
     st = lib.lordba_forward_batched_multi(*args) if int(algo) == ALGO_AUTO else lib.lordba_forward_batched_multi_algo(*args, int(algo))
     if st != 0:
         raise LordbaError(st, "lordba_forward_batched_multi")
@@ -428,13 +434,10 @@ def lordba_pack_latents(latentA, latentB, stream=None, transposed: bool = True):
     new = lambda n: torch.empty(n, dtype=torch.int32, device=latentA.device)
     pA, pB = new(wA), new(wB)
     pAt, pBt = (new(wA), new(wB)) if transposed else (None, None)
-    if stream is None:
-        stream = torch.cuda.current_stream(latentA.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(latentA, stream)
     ptr = lambda t_: None if t_ is None else t_.data_ptr()
     st = lib.lordba_pack_latents(latentA.contiguous().data_ptr(), latentB.contiguous().data_ptr(), pA.data_ptr(), pB.data_ptr(),
-                                 ptr(pAt), ptr(pBt), d_in, d_out, r, ctypes.c_void_p(stream))
+                                 ptr(pAt), ptr(pBt), d_in, d_out, r, stream)
     if st != 0:
         raise LordbaError(st, "lordba_pack_latents")
     return pA, pB, pAt, pBt
@@ -460,14 +463,11 @@ def lordba_forward_save_t(x, packedA, packedB, s_in, s_rank, s_out, y_base=None,
         t_out = torch.empty((r, stride), dtype=torch.float32, device=x.device)
     if y_base is not None and y_out is None:
         y_out = torch.empty_like(y_base)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     ptr = lambda t_: None if t_ is None else t_.data_ptr()
     st = lib.lordba_forward_save_t(x.data_ptr(), packedA.data_ptr(), packedB.data_ptr(), s_in.data_ptr(), s_rank.data_ptr(),
                                    s_out.data_ptr(), ptr(y_base), ptr(y_out), t_out.data_ptr(), stride, T, d_in, d_out, r,
-                                   ctypes.c_void_p(stream))
+                                   stream)
     if st != 0:
         raise LordbaError(st, "lordba_forward_save_t")
     return y_out, t_out
@@ -486,12 +486,10 @@ def lordba_backward(x, g, packedA, packedAt, packedBt, s_in, s_rank, s_out, late
 
     lib = load_library()
     if check:
-        for name, t_ in (("x", x), ("g", g), ("s_in", s_in), ("s_rank", s_rank), ("s_out", s_out)):
-            if t_.dtype != torch.float16 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous float16 CUDA tensor" % name)
-        for name, t_ in (("packedA", packedA), ("packedAt", packedAt), ("packedBt", packedBt)):
-            if t_.dtype != torch.int32 or not t_.is_cuda or not t_.is_contiguous():
-                raise TypeError("%s must be a contiguous int32 CUDA tensor holding the packed words" % name)
+        _need(torch.float16, "float16 CUDA tensor", ("x", "g", "s_in", "s_rank", "s_out"),
+              x, g, s_in, s_rank, s_out)
+        _need(torch.int32, "int32 CUDA tensor holding the packed words", ("packedA", "packedAt", "packedBt"),
+              packedA, packedAt, packedBt)
         if (latentA is None) != (latentB is None):
             raise ValueError("latentA and latentB come or go together (both None: frozen carriers, no latent gradients)")
         for name, t_ in (("latentA", latentA), ("latentB", latentB)):
@@ -522,17 +520,14 @@ def lordba_backward(x, g, packedA, packedAt, packedBt, s_in, s_rank, s_out, late
     if out is None:
         out = {"dx": dx, "d_s_in": f32(d_in), "d_s_rank": f32(r), "d_s_out": f32(d_out),
                "d_latentA": None if latentA is None else f32(r, d_in), "d_latentB": None if latentB is None else f32(d_out, r)}
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     ptr = lambda t_: None if t_ is None else t_.data_ptr()
     head = (x.data_ptr(), g.data_ptr(), packedA.data_ptr(), packedAt.data_ptr(), packedBt.data_ptr(),
             s_in.data_ptr(), s_rank.data_ptr(), s_out.data_ptr(), ptr(latentA), ptr(latentB),
             float(kappa), ptr(t_saved), 0 if t_saved is None else t_saved.shape[1],
             ptr(dx_base), ptr(dx), out["d_s_in"].data_ptr(), out["d_s_rank"].data_ptr(),
             out["d_s_out"].data_ptr(), ptr(out["d_latentA"]), ptr(out["d_latentB"]))
-    tail = (T, d_in, d_out, r, ctypes.c_void_p(stream))
+    tail = (T, d_in, d_out, r, stream)
     if _noalloc:
         st = lib.lordba_backward_noalloc(*head, *tail)
     else:
@@ -567,14 +562,11 @@ def lordba_forward_multi_save_t(x, packedA, packedB, s_in, s_rank, s_out, y_base
         t_out = torch.empty((ell, r, saved_t_stride(T)), dtype=torch.float32, device=x.device)
     if y_base is not None and y_out is None:
         y_out = torch.empty_like(y_base)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     ptr = lambda t_: None if t_ is None else t_.data_ptr()
     st = lib.lordba_forward_multi_save_t(x.data_ptr(), packedA.data_ptr(), packedB.data_ptr(), s_in.data_ptr(), s_rank.data_ptr(),
                                          s_out.data_ptr(), ptr(y_base), ptr(y_out), t_out.data_ptr(), t_out.shape[2], T, d_in, d_out, r,
-                                         ell, ctypes.c_void_p(stream))
+                                         ell, stream)
     if st != 0:
         raise LordbaError(st, "lordba_forward_multi_save_t")
     return y_out, t_out
@@ -600,17 +592,14 @@ def lordba_backward_multi(x, g, packedA, packedAt, packedBt, s_in, s_rank, s_out
     f32 = lambda *shape: torch.empty(shape, dtype=torch.float32, device=x.device)
     out = {"dx": dx, "d_s_in": f32(ell, d_in), "d_s_rank": f32(ell, r), "d_s_out": f32(ell, d_out),
            "d_latentA": None if latentA is None else f32(r, d_in), "d_latentB": None if latentB is None else f32(d_out, r)}
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(x, stream)
     ptr = lambda t_: None if t_ is None else t_.data_ptr()
     st = lib.lordba_backward_multi(x.data_ptr(), g.data_ptr(), packedA.data_ptr(), packedAt.data_ptr(), packedBt.data_ptr(),
                                    s_in.data_ptr(), s_rank.data_ptr(), s_out.data_ptr(), ptr(latentA), ptr(latentB), float(kappa),
                                    ptr(t_saved), 0 if t_saved is None else t_saved.shape[2],
                                    ptr(dx_base), ptr(dx), out["d_s_in"].data_ptr(), out["d_s_rank"].data_ptr(),
                                    out["d_s_out"].data_ptr(), ptr(out["d_latentA"]), ptr(out["d_latentB"]),
-                                   workspace.data_ptr(), workspace.numel(), T, d_in, d_out, r, ell, ctypes.c_void_p(stream))
+                                   workspace.data_ptr(), workspace.numel(), T, d_in, d_out, r, ell, stream)
     if st != 0:
         raise LordbaError(st, "lordba_backward_multi")
     return out
@@ -655,15 +644,12 @@ def lordba_ptq(A_star, B_star, R: int, K: int = 100, tau: float = 2.0, mu: float
         "s_out": torch.empty(max(M, 1), dtype=torch.float16, device=dev),
         "info": torch.empty(8 + max(K, 0), dtype=torch.float64, device=dev),
     }
-    if stream is None:
-        stream = torch.cuda.current_stream(dev).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
+    stream = _stream_handle(A_star, stream)
     st = lib.lordba_ptq_sweeps(A_star.contiguous().data_ptr(), B_star.contiguous().data_ptr(), out["packedA"].data_ptr(),
                                out["packedB"].data_ptr(), out["alpha"].data_ptr(), out["beta"].data_ptr(), out["gamma"].data_ptr(),
                                out["s_in"].data_ptr(), out["s_rank"].data_ptr(), out["s_out"].data_ptr(), out["info"].data_ptr(),
                                workspace.data_ptr(), workspace.numel() * workspace.element_size(), N, M, R, r0, K, t_begin, t_end,
-                               tau, mu, ctypes.c_void_p(stream))
+                               tau, mu, stream)
     if st != 0:
         raise LordbaError(st, "lordba_ptq_sweeps")
     off2 = (N * R + 31) // 32 * 32
@@ -683,11 +669,8 @@ def lordba_ptq_beta_solve(G, h, stream=None):
     if tuple(G.shape) != (R, R) or G.dtype != torch.float64 or h.dtype != torch.float64 or not G.is_contiguous() or not h.is_contiguous():
         raise ValueError("need contiguous float64 G [R, R] and h [R]")
     beta = torch.empty(R, dtype=torch.float64, device=G.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(G.device).cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
-    st = lib.lordba_ptq_beta_solve(G.data_ptr(), h.data_ptr(), beta.data_ptr(), R, ctypes.c_void_p(stream))
+    stream = _stream_handle(G, stream)
+    st = lib.lordba_ptq_beta_solve(G.data_ptr(), h.data_ptr(), beta.data_ptr(), R, stream)
     if st != 0:
         raise LordbaError(st, "lordba_ptq_beta_solve")
     return beta
