@@ -12,12 +12,15 @@
 // [M, R] row-major, which is also the layout of S_B.  All arithmetic is fp64; sums run in a fixed order (no atomics), so
 // a call is reproducible bit for bit.
 //
-// Each row kernel works on blocks of 32 rows and ends by writing its block's share of its side's Gram pair; a small
-// kernel adds the shares up (each workgroup of a row kernel doing so itself would pull every share through its own
-// compute unit's 64 B/clk path to L2: measured 9 us per launch against 4.8 us for the extra launch).  A sweep is nine
-// launches: two Tikhonov steps (each followed at once by the sign and dual update of its rows, which needs nothing
-// else), alpha, gamma, each with its totals kernel, and beta with the penalty control.  A flag in device memory ends the
-// loop: once the sign matrices repeat, the remaining launches return at once, so the host never waits on the device
+// Each row kernel works on blocks of 32 rows and ends by writing its block's share of its side's Gram pair.  The last block of a
+// group of 16 to do so adds the group's shares up, and the readers add up to 16 such sums (each workgroup of a row kernel
+// adding up every share itself would pull them through its own compute unit's 64 B/clk path to L2, 9 us per launch).  Sides of
+// more than 256 blocks or with more than 1024 values per share leave it to a small kernel of its own.  A sweep is four
+// launches: two Tikhonov steps (each followed at once by the sign and dual update of its rows, which needs nothing else),
+// alpha, and gamma, whose last block goes on with beta and the penalty control.  Enqueued as one call of 100 sweeps the host's
+// launch rate was the limit: 4096^2, R = r0 = 16 3.73 ms with the nine launches per sweep that separate totals and beta kernels
+// take, 2.25 ms with four (as a graph 2.74 and 2.22; the sweeps that were run alone 1.67 and 1.74).  A flag in device memory
+// ends the loop: once the sign matrices repeat, the remaining launches return at once, so the host never waits on the device
 // inside the loop (lordba_ptq_sweeps lets a caller that is willing to wait enqueue the run in pieces instead).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -35,6 +38,7 @@ constexpr int kRows = 32;      // rows of one side per workgroup
 constexpr int kThreads = 256;  // four waves: the warm-start and export kernels
 constexpr int kRowThreads = 512;  // eight waves: the kernels of a sweep
 static_assert(LORDBA_PTQ_MAX_RANK == 32, "the Tikhonov kernel is instantiated for ranks up to 16 and up to 32");
+constexpr int kGroup = 16, kMaxGroups = 16;   // blocks whose shares are added up together, and groups of a side (see add_up_group)
 constexpr double kRankFloor = 1e-12;  // a singular value of the update below this fraction of the largest counts as zero
 constexpr int kInfoHead = 8;   // info[0..7]: sweeps, frozen, rho, ||T||_F^2, degenerate, reserved; then one objective per sweep
 
@@ -53,9 +57,13 @@ struct PtqArgs {
     double* part[2];     // per block shares of each side, [nb, pstride]: S (R*R), K (R*r0), then the block's squared
                          // consensus gap and its number of sign changes in the sweep (written by the Tikhonov kernel only)
     int pstride;
-    double* tot[2];      // the shares of each side added up (same layout as one share), written by the totals kernel
+    double* tot[2];      // sides that are not grouped: the shares added up (same layout as one share), by the totals kernel
     double* Z[2];        // warm start: [r0, R] maps from factor rows to singular-vector entries
     double* ctrl;        // [kCtrlCount]
+    uint32_t* arrived;   // arrival counters of a launch, zero between launches: [0 .. 15] groups of blocks of side 0, [16 .. 31] of
+                         // side 1, [32] groups of side 1 (see add_up_group)
+    int grouped[2];      // the shares of a side are added up in groups of blocks by the kernel that writes them; else the totals
+                         // kernel does it
     double* info;
     int K;
     double tau, mu;
@@ -127,6 +135,12 @@ __device__ inline double group_solve(const double* H, int ld, int n, int l, int 
     return b;
 }
 
+// Shares of a block are written with agent-scope atomic stores and read by the last block with agent-scope atomic loads: such
+// accesses are coherent across the L2 caches of the XCDs by themselves, so that no block has to write its L2 back (a release at
+// device scope in each of the 128 blocks took 30 us per launch).
+__device__ inline void publish(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline double published(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // This block's share of a side's Gram pair from its rows in LDS: xs [kRows, R], cs [kRows] (0 past the end), fs [kRows, r0]
 // with row stride fstride.  The rows are first scaled in place (xs <- cs o xs; the callers are done with xs), then every
 // thread sums its output over the rows, eight rows' operands requested at a time.
@@ -151,7 +165,7 @@ __device__ inline void gram_share(double* xs, const double* cs, const double* fs
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc = fma(u[e], v[e], acc);
         }
-        out[o] = acc;
+        publish(out + o, acc);
     }
 }
 
@@ -193,9 +207,65 @@ __global__ __launch_bounds__(256) void lordba_ptq_totals_kernel(PtqArgs a, int s
     if (w == 0 && o < count) a.tot[side][o] = (partial[0][lane] + partial[1][lane]) + (partial[2][lane] + partial[3][lane]);
 }
 
-// The totals of a side into LDS.
-__device__ inline void load_totals(const double* tot, int count, double* dst) {
-    for (int o = threadIdx.x; o < count; o += blockDim.x) dst[o] = tot[o];
+// To be called by all threads of a block after its own published stores: true in every thread of the block that is the n-th to
+// arrive at `counter` in this launch.  Every wave waits for its own stores first (the wait makes them complete, at the agent's
+// point of coherence, before the barrier and hence before the block's arrival is counted); nobody waits for another block.
+__device__ inline bool arrive_last(uint32_t* counter, int n) {
+    __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = before + 1u == static_cast<uint32_t>(n);
+        if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return last != 0;
+}
+
+// Adding up the shares of a side without a launch of its own: the last block of a group of kGroup blocks to publish its share
+// adds the group's shares up, in block order whoever does it, and puts the sum in the place of the group's first share; the
+// readers add the up to kMaxGroups sums up (load_totals).  It takes about as long on the device as the totals kernel and its launch
+// (4.5 us); the last block of all adding up all 128 shares (526 KB through one compute unit) took 10 us.  Returns true in the block that is the last of its group, after publishing the sum.
+__device__ inline bool add_up_group(const PtqArgs& a, int side, int blk, int count) {
+    const int g = blk / kGroup, first = g * kGroup, size = a.nb[side] - first < kGroup ? a.nb[side] - first : kGroup;
+    if (!arrive_last(a.arrived + side * kMaxGroups + g, size)) return false;
+    for (int o = threadIdx.x; o < count; o += blockDim.x) {
+        double* part = a.part[side] + static_cast<int64_t>(first) * a.pstride + o;
+        double v[kGroup], acc = 0.0;
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) v[j] = published(part + static_cast<int64_t>(j < size ? j : size - 1) * a.pstride);
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) acc += j < size ? v[j] : 0.0;
+        publish(part, acc);
+    }
+    return true;
+}
+
+// The totals of a side (its first `count` values) into LDS.  NOW: the sums were published in this launch.
+template <bool NOW = false>
+__device__ inline void load_totals(const PtqArgs& a, int side, int count, double* dst) {
+    if (!a.grouped[side]) {
+        for (int o = threadIdx.x; o < count; o += blockDim.x) dst[o] = a.tot[side][o];
+        return;
+    }
+    const int ng = (a.nb[side] + kGroup - 1) / kGroup;
+    const int64_t stride = static_cast<int64_t>(kGroup) * a.pstride;
+    for (int o = threadIdx.x; o < count; o += blockDim.x) {
+        const double* part = a.part[side] + o;
+        double acc = 0.0;
+        for (int g0 = 0; g0 < ng; g0 += 8) {
+            double v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const double* p = part + (g0 + j < ng ? g0 + j : ng - 1) * stride;
+                v[j] = NOW ? published(p) : *p;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc += g0 + j < ng ? v[j] : 0.0;
+        }
+        dst[o] = acc;
+    }
 }
 
 // ---- warm start (Eq. (svd-init)) ----------------------------------------------------------------------------------
@@ -404,6 +474,7 @@ __global__ __launch_bounds__(64) void lordba_ptq_svd_kernel(PtqArgs a, const dou
         a.ctrl[kFrozen] = 0.0;
         a.ctrl[kDegenerate] = good ? 0.0 : 1.0;
         a.ctrl[7] = 0.0;
+        for (int i = 0; i <= 2 * kMaxGroups; ++i) a.arrived[i] = 0u;
     }
     wave_sync();
     if (l < R) a.beta[l] = sig[idx[l]];
@@ -458,6 +529,7 @@ __global__ __launch_bounds__(kThreads) void lordba_ptq_init_rows_kernel(PtqArgs 
     }
     __syncthreads();
     gram_share(xs, cs, fs, r0, R, r0, a.part[side] + static_cast<int64_t>(blk) * a.pstride);
+    if (side == 1 && a.grouped[1]) add_up_group(a, 1, blk, R * R + R * r0);   // (all that alpha needs)
 }
 
 // ---- one sweep ----------------------------------------------------------------------------------------------------
@@ -556,7 +628,7 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
     const int64_t n = a.n[side], row0 = static_cast<int64_t>(blk) * kRows;
     const RowLds s = carve_rows(R, r0);
     const int count = R * R + R * r0;
-    load_totals(a.tot[other], count, s.So);  // So and Ko are adjacent
+    load_totals(a, other, count, s.So);  // So and Ko are adjacent
     for (int k = threadIdx.x; k < R; k += blockDim.x) s.bs[k] = a.beta[k];
     load_factor_rows(a.F[side], n, r0, row0, s.fs, s.fstride);
     for (int row = threadIdx.x; row < kRows; row += blockDim.x) s.cs[row] = row0 + row < n ? a.scale[side][row0 + row] : 0.0;
@@ -621,62 +693,10 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
     if (threadIdx.x == 0) {
         double gsum = 0.0, fsum = 0.0;
         for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) { gsum += red[2 * w]; fsum += red[2 * w + 1]; }
-        share[count] = gsum;
-        share[count + 1] = fsum;
+        publish(share + count, gsum);
+        publish(share + count + 1, fsum);
     }
-}
-
-// Eq. (alpha-update) (side 0) / Eq. (gamma-update) (side 1): per row, with v = u o beta, <T_i, D_i> = v . (Ko f) and
-// ||D_i||^2 = v^T So v; 0 where the denominator is 0.
-__global__ __launch_bounds__(kRowThreads) void lordba_ptq_scale_kernel(PtqArgs a, int side) {
-    if (a.ctrl[kDone] != 0.0) return;
-    const int R = a.R, r0 = a.r0, other = 1 - side, blk = blockIdx.x;
-    const int64_t n = a.n[side], row0 = static_cast<int64_t>(blk) * kRows;
-    const RowLds s = carve_rows(R, r0);
-    load_totals(a.tot[other], R * R + R * r0, s.So);
-    for (int k = threadIdx.x; k < R; k += blockDim.x) s.bs[k] = a.beta[k];
-    load_factor_rows(a.F[side], n, r0, row0, s.fs, s.fstride);
-    for (int o = threadIdx.x; o < kRows * R; o += blockDim.x) s.xs[o] = row0 + o / R < n ? a.X[side][row0 * R + o] : 0.0;
-    __syncthreads();
-    factor_products(s, R, r0);
-    __syncthreads();
-    const int gs = group_size_for(R), groups = 64 / gs, waves = blockDim.x >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int g = lane / gs, l = lane - g * gs;
-    const int rows_per_pass = waves * groups;
-    for (int pass = 0; pass < kRows / rows_per_pass; ++pass) {
-        const int row = pass * rows_per_pass + wave * groups + g;
-        double num = 0.0, den = 0.0;
-        if (l < R) {
-            const double v = s.xs[row * R + l] * s.bs[l];
-            const double kf = s.kfs[row * R + l];
-            double sv = 0.0;   // (So v)_l: So is symmetric, so lane l walks column l (consecutive lanes, consecutive words)
-            for (int m0 = 0; m0 < R; m0 += 8) {
-                double so[8], xv[8], bv[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int m = m0 + e < R ? m0 + e : R - 1;
-                    so[e] = s.So[m * R + l];
-                    xv[e] = s.xs[row * R + m];
-                    bv[e] = s.bs[m];
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) sv += (m0 + e < R) ? so[e] * (xv[e] * bv[e]) : 0.0;
-            }
-            num = v * kf;
-            den = v * sv;
-        }
-        num = group_sum(num, gs);
-        den = group_sum(den, gs);
-        const double c = den > 0.0 ? num / den : 0.0;
-        const bool in = row0 + row < n;
-        if (l == 0) {
-            s.cs[row] = in ? c : 0.0;
-            if (in) a.scale[side][row0 + row] = c;
-        }
-    }
-    __syncthreads();
-    gram_share(s.xs, s.cs, s.fs, s.fstride, R, r0, a.part[side] + static_cast<int64_t>(blk) * a.pstride);
+    if (a.grouped[side]) add_up_group(a, side, blk, count + 2);
 }
 
 // beta = pinv(G) h for a symmetric positive semidefinite R x R matrix G, by one wave (Eq. (beta-pinv)).  G [R, ld] and hv [R]
@@ -776,8 +796,8 @@ __device__ inline void beta_pinv_solve(double* G, int ld, double* hv, double* N2
 // f = (||T||_F^2 - 2 beta.h + beta^T G beta) / 2.  Then the end of the sweep: residual balancing of the penalty (first
 // half of the run) from the consensus gaps and sign changes the Tikhonov kernels left in their shares, and the end of
 // the loop when no sign changed.
-__global__ __launch_bounds__(kRowThreads) void lordba_ptq_beta_kernel(PtqArgs a, int t) {
-    if (a.ctrl[kDone] != 0.0) return;
+// By a whole block; P1 and P2 at the start of `lds` are loaded by the caller, and the block synchronised.
+__device__ inline void beta_update(const PtqArgs& a, int t) {
     const int R = a.R, r0 = a.r0, ld = R + 1, count = R * R + R * r0;
     double* P1 = lds;              // S1, K1, gap, sign changes of side 0
     double* P2 = P1 + count + 2;   // the same of side 1
@@ -788,9 +808,6 @@ __global__ __launch_bounds__(kRowThreads) void lordba_ptq_beta_kernel(PtqArgs a,
     double* h0 = hv + R;           // [R]
     double* bt = h0 + R;           // [R] result
     int* perm = reinterpret_cast<int*>(bt + R);
-    load_totals(a.tot[0], count + 2, P1);
-    load_totals(a.tot[1], count + 2, P2);
-    __syncthreads();
     for (int o = threadIdx.x; o < R * R; o += blockDim.x) G[(o / R) * ld + o % R] = P1[o] * P2[o];
     for (int k = threadIdx.x; k < R; k += blockDim.x) {
         double acc = 0.0;
@@ -826,6 +843,78 @@ __global__ __launch_bounds__(kRowThreads) void lordba_ptq_beta_kernel(PtqArgs a,
     a.ctrl[kYfac] = yfac;
     a.ctrl[kSweeps] = t + 1;
     if (f0 + f1 == 0.0) { a.ctrl[kFrozen] = 1.0; a.ctrl[kDone] = 1.0; }
+}
+
+__global__ __launch_bounds__(kRowThreads) void lordba_ptq_beta_kernel(PtqArgs a, int t) {
+    if (a.ctrl[kDone] != 0.0) return;
+    const int count = a.R * a.R + a.R * a.r0 + 2;
+    load_totals(a, 0, count, lds);
+    load_totals(a, 1, count, lds + count);
+    __syncthreads();
+    beta_update(a, t);
+}
+
+// Eq. (alpha-update) (side 0) / Eq. (gamma-update) (side 1): per row, with v = u o beta, <T_i, D_i> = v . (Ko f) and
+// ||D_i||^2 = v^T So v; 0 where the denominator is 0.
+__global__ __launch_bounds__(kRowThreads) void lordba_ptq_scale_kernel(PtqArgs a, int side, int t) {
+    if (a.ctrl[kDone] != 0.0) return;
+    const int R = a.R, r0 = a.r0, other = 1 - side, blk = blockIdx.x;
+    const int64_t n = a.n[side], row0 = static_cast<int64_t>(blk) * kRows;
+    const RowLds s = carve_rows(R, r0);
+    load_totals(a, other, R * R + R * r0, s.So);
+    for (int k = threadIdx.x; k < R; k += blockDim.x) s.bs[k] = a.beta[k];
+    load_factor_rows(a.F[side], n, r0, row0, s.fs, s.fstride);
+    for (int o = threadIdx.x; o < kRows * R; o += blockDim.x) s.xs[o] = row0 + o / R < n ? a.X[side][row0 * R + o] : 0.0;
+    __syncthreads();
+    factor_products(s, R, r0);
+    __syncthreads();
+    const int gs = group_size_for(R), groups = 64 / gs, waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane / gs, l = lane - g * gs;
+    const int rows_per_pass = waves * groups;
+    for (int pass = 0; pass < kRows / rows_per_pass; ++pass) {
+        const int row = pass * rows_per_pass + wave * groups + g;
+        double num = 0.0, den = 0.0;
+        if (l < R) {
+            const double v = s.xs[row * R + l] * s.bs[l];
+            const double kf = s.kfs[row * R + l];
+            double sv = 0.0;   // (So v)_l: So is symmetric, so lane l walks column l (consecutive lanes, consecutive words)
+            for (int m0 = 0; m0 < R; m0 += 8) {
+                double so[8], xv[8], bv[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int m = m0 + e < R ? m0 + e : R - 1;
+                    so[e] = s.So[m * R + l];
+                    xv[e] = s.xs[row * R + m];
+                    bv[e] = s.bs[m];
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sv += (m0 + e < R) ? so[e] * (xv[e] * bv[e]) : 0.0;
+            }
+            num = v * kf;
+            den = v * sv;
+        }
+        num = group_sum(num, gs);
+        den = group_sum(den, gs);
+        const double c = den > 0.0 ? num / den : 0.0;
+        const bool in = row0 + row < n;
+        if (l == 0) {
+            s.cs[row] = in ? c : 0.0;
+            if (in) a.scale[side][row0 + row] = c;
+        }
+    }
+    __syncthreads();
+    gram_share(s.xs, s.cs, s.fs, s.fstride, R, r0, a.part[side] + static_cast<int64_t>(blk) * a.pstride);
+    if (!a.grouped[side]) return;
+    const int count = R * R + R * r0;
+    if (!add_up_group(a, side, blk, count)) return;
+    // The gap and sign-change sums of the sweep stay where the Tikhonov kernel's groups left them, behind the Gram pair.
+    if (side == 1 && t >= 0 && arrive_last(a.arrived + 2 * kMaxGroups, (a.nb[1] + kGroup - 1) / kGroup)) {
+        load_totals(a, 0, count + 2, lds);   // both sides' totals are known now: the rest of the sweep here too
+        load_totals<true>(a, 1, count + 2, lds + count + 2);
+        __syncthreads();
+        beta_update(a, t);
+    }
 }
 
 // The beta update on its own (lordba_ptq_beta_solve): G [R, R] row-major and h [R] from memory, beta [R] to memory.
@@ -865,35 +954,26 @@ __device__ inline __half half_from_double(double x) {
     return __float2half_rn(f);
 }
 
+// A wave packs 64 consecutive bits of a carrier's stream with one ballot (one entry per lane: with a word's 32 entries in one
+// thread eight workgroups did all of it, 16 us at 4096^2); the waves behind those take the scales and the control words.
 __global__ __launch_bounds__(kThreads) void lordba_ptq_export_kernel(PtqArgs a, ExportArgs e) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    const int64_t N = a.n[0], M = a.n[1];
+    const int lane = threadIdx.x & 63;
+    const int64_t N = a.n[0], M = a.n[1], wavesA = (e.wordsA + 1) / 2, wavesB = (e.wordsB + 1) / 2;
+    int64_t w = static_cast<int64_t>(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
     const int R = a.R;
-    // a word's 32 entries are requested together (from a clamped position), then tested
-    if (i < e.wordsA) {
-        double v[32];
-#pragma unroll
-        for (int bit = 0; bit < 32; ++bit) {
-            const int nbit = static_cast<int>(i * 32 + bit < N * R ? i * 32 + bit : N * R - 1);   // (N R <= 2^27)
-            const int k = nbit / static_cast<int>(N), row = nbit - k * static_cast<int>(N);
-            v[bit] = a.Mm[0][row * R + k];
-        }
-        uint32_t w = 0;
-#pragma unroll
-        for (int bit = 0; bit < 32; ++bit)
-            if (i * 32 + bit < N * R && v[bit] < 0.0) w |= 1u << bit;
-        e.packedA[i] = w;
+    if (w < wavesA + wavesB) {
+        const bool is_a = w < wavesA;
+        if (!is_a) w -= wavesA;
+        const int total = static_cast<int>((is_a ? N : M) * R);   // (<= 2^27)
+        const int nbit = static_cast<int>(w) * 64 + lane, nc = nbit < total ? nbit : total - 1;
+        const int k = is_a ? nc / static_cast<int>(N) : 0;
+        const double v = is_a ? a.Mm[0][(nc - k * static_cast<int>(N)) * R + k] : a.Mm[1][nc];
+        const uint64_t bits = __builtin_amdgcn_ballot_w64(nbit < total && v < 0.0);   // pad bits are 0
+        if (lane < 2 && 2 * w + lane < (is_a ? e.wordsA : e.wordsB))
+            (is_a ? e.packedA : e.packedB)[2 * w + lane] = static_cast<uint32_t>(bits >> (32 * lane));
+        return;
     }
-    if (i < e.wordsB) {
-        double v[32];
-#pragma unroll
-        for (int bit = 0; bit < 32; ++bit) v[bit] = a.Mm[1][i * 32 + bit < M * R ? i * 32 + bit : M * R - 1];
-        uint32_t w = 0;
-#pragma unroll
-        for (int bit = 0; bit < 32; ++bit)
-            if (i * 32 + bit < M * R && v[bit] < 0.0) w |= 1u << bit;
-        e.packedB[i] = w;
-    }
+    const int64_t i = (w - wavesA - wavesB) * 64 + lane;
     if (e.s_in && i < N) e.s_in[i] = half_from_double(a.scale[0][i]);
     if (e.s_out && i < M) e.s_out[i] = half_from_double(a.scale[1][i]);
     if (e.s_rank && i < R) e.s_rank[i] = half_from_double(a.beta[i]);
@@ -927,7 +1007,7 @@ Layout make_layout(int64_t N, int64_t M, int64_t R, int64_t r0) {
     for (int s = 0; s < 2; ++s) L.part[s] = take(static_cast<size_t>(L.nb[s]) * L.pstride);
     for (int s = 0; s < 2; ++s) L.tot[s] = take(L.pstride);
     for (int s = 0; s < 2; ++s) L.z[s] = take(r0 * R);
-    L.ctrl = take(kCtrlCount);
+    L.ctrl = take(kCtrlCount + kMaxGroups + 1);   // and the arrival counters
     L.total = off * sizeof(double);
     return L;
 }
@@ -1005,6 +1085,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     a.beta = beta;
     a.pstride = L.pstride;
     a.ctrl = ws + L.ctrl;
+    a.arrived = reinterpret_cast<uint32_t*>(ws + L.ctrl + kCtrlCount);
     a.info = info;
     a.K = static_cast<int>(K);
     a.tau = tau;
@@ -1024,6 +1105,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     while (solve_waves > 1 && lds_fixed + solve_waves * lds_wave > 160 * 1024) solve_waves >>= 1;
     const size_t lds_rows = lds_fixed + solve_waves * lds_wave;
     const size_t lds_beta = sizeof(double) * (2 * (iR * iR + iR * ir0 + 2) + iR * ldR + (iR * ldR > 288 ? iR * ldR : 288) + 3 * iR) + sizeof(int) * iR;
+    const size_t lds_scale = lds_fixed > lds_beta ? lds_fixed : lds_beta;   // (its last block may run the beta update)
     const int nb01 = a.nb[0] + a.nb[1];
 
     {   // More than 64 KiB of LDS per workgroup has to be asked for; the largest request so far is remembered per device and
@@ -1035,7 +1117,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
             {reinterpret_cast<const void*>(lordba_ptq_qr_kernel), lds_qr, 0}, {reinterpret_cast<const void*>(lordba_ptq_svd_kernel), lds_svd, 1},
             {reinterpret_cast<const void*>(lordba_ptq_init_rows_kernel), lds_init, 2},
             {reinterpret_cast<const void*>(iR <= 16 ? lordba_ptq_ustep_kernel<16> : lordba_ptq_ustep_kernel<32>), lds_rows, iR <= 16 ? 3 : 4},
-            {reinterpret_cast<const void*>(lordba_ptq_scale_kernel), lds_fixed, 5}, {reinterpret_cast<const void*>(lordba_ptq_beta_kernel), lds_beta, 6}};
+            {reinterpret_cast<const void*>(lordba_ptq_scale_kernel), lds_scale, 5}, {reinterpret_cast<const void*>(lordba_ptq_beta_kernel), lds_beta, 6}};
         std::lock_guard<std::mutex> guard(mu);
         for (const auto& b : big) {
             if (b.bytes > 160 * 1024) return LORDBA_ERR_DIM;
@@ -1053,7 +1135,10 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     bool launch_failed = false;
     auto launched = [&]() { if (hipGetLastError() != hipSuccess) launch_failed = true; };
     const int count = iR * iR + iR * ir0;
+    // (beyond 8192 rows the readers would add up too many sums each; beyond 1024 values a share is more than one block's work)
+    for (int s = 0; s < 2; ++s) a.grouped[s] = (a.nb[s] + kGroup - 1) / kGroup <= kMaxGroups && count <= 1024 ? 1 : 0;
     auto totals = [&](int side, int n, int always) {
+        if (a.grouped[side]) return;
         hipLaunchKernelGGL(lordba_ptq_totals_kernel, dim3((n + 63) / 64), dim3(256), 0, stream, a, side, n, always);
     };
     if (t_begin == 0) {   // the warm start; a later call continues from the state the workspace holds
@@ -1093,9 +1178,9 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
         hipLaunchKernelGGL(lordba_ptq_init_rows_kernel, dim3(nb01), dim3(kThreads), lds_init, stream, a);
         launched();
         totals(1, count, 0);
-        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[0]), dim3(kRowThreads), lds_fixed, stream, a, 0);
+        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[0]), dim3(kRowThreads), lds_fixed, stream, a, 0, -1);
         totals(0, count, 0);
-        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[1]), dim3(kRowThreads), lds_fixed, stream, a, 1);
+        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[1]), dim3(kRowThreads), lds_fixed, stream, a, 1, -1);
         totals(1, count, 0);
         launched();
         if (launch_failed) return LORDBA_ERR_LAUNCH;
@@ -1108,11 +1193,11 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
                 hipLaunchKernelGGL(lordba_ptq_ustep_kernel<32>, dim3(a.nb[side]), dim3(ustep_threads), lds_rows, stream, a, side, solve_waves);
             totals(side, count + 2, 0);
         }
-        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[0]), dim3(kRowThreads), lds_fixed, stream, a, 0);
+        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[0]), dim3(kRowThreads), lds_scale, stream, a, 0, t);
         totals(0, count, 0);
-        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[1]), dim3(kRowThreads), lds_fixed, stream, a, 1);
+        hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[1]), dim3(kRowThreads), lds_scale, stream, a, 1, t);
         totals(1, count, 0);
-        hipLaunchKernelGGL(lordba_ptq_beta_kernel, dim3(1), dim3(kRowThreads), lds_beta, stream, a, t);
+        if (!a.grouped[1]) hipLaunchKernelGGL(lordba_ptq_beta_kernel, dim3(1), dim3(kRowThreads), lds_beta, stream, a, t);
         launched();
         if (launch_failed) return LORDBA_ERR_LAUNCH;
     }
@@ -1124,11 +1209,10 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     e.s_out = static_cast<__half*>(s_out);
     e.wordsA = static_cast<int64_t>(wordsA);
     e.wordsB = static_cast<int64_t>(wordsB);
-    int64_t most = static_cast<int64_t>(wordsA > wordsB ? wordsA : wordsB);
-    if (N > most) most = N;
-    if (M > most) most = M;
-    if (most < kCtrlCount) most = kCtrlCount;
-    hipLaunchKernelGGL(lordba_ptq_export_kernel, dim3(static_cast<unsigned>((most + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, a, e);
+    int64_t most = N > M ? N : M;   // (at least R and the control words too)
+    if (most < 64) most = 64;
+    const int64_t waves = (e.wordsA + 1) / 2 + (e.wordsB + 1) / 2 + (most + 63) / 64;
+    hipLaunchKernelGGL(lordba_ptq_export_kernel, dim3(static_cast<unsigned>((waves * 64 + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, a, e);
     return hipGetLastError() == hipSuccess ? LORDBA_OK : LORDBA_ERR_LAUNCH;
 }
 

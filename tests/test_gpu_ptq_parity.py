@@ -106,6 +106,18 @@ def test_full_run_matches_oracle(torch_cuda, seed, N, M, R, r0):
     compare(res, ref, K)
 
 
+# Rows at the edges of the groups of 16 blocks of 32 rows whose shares are added up together: one group, one block more, the
+# most groups, one block too many on one side (its shares are then added up by a kernel of its own); and a share of more values
+# than a group takes
+@pytest.mark.parametrize("N,M,R,r0", [(512, 513, 4, 6), (31, 8192, 3, 4), (8193, 40, 3, 4), (40, 8193, 3, 4), (545, 600, 16, 49)])
+def test_groups_of_blocks(torch_cuda, N, M, R, r0):
+    d = inputs.make_ptq_inputs(61, N, M, r0)
+    say("  case %dx%d R %d r0 %d" % (N, M, R, r0))
+    K = 12
+    ref = P.ptq(d["A_star"], d["B_star"], R, K=K)
+    compare(run_gpu(torch_cuda, d, R, K=K), ref, K)
+
+
 @pytest.mark.parametrize("K", [1, 2, 3, 7])
 def test_first_sweeps_match_oracle(torch_cuda, K):
     # a run of K sweeps (its penalty window is the first half of those K) pins every update of the early sweeps
