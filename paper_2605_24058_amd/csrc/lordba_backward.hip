@@ -38,12 +38,13 @@ constexpr int kWgradWaves = 4;        // waves per workgroup of the wgrad kernel
 // Workgroups the wgrad grid aims at: two per CU once the token ranges are long (measured 3-4 % faster from T = 4096 on),
 // one per CU below that, where a second one only doubles the partial sums the finish kernel has to read.
 constexpr int kWgradTargetWgsLong = 512, kWgradTargetWgsShort = 256;
-// 32-row steps a wave of the wgrad kernel keeps in flight: one (two from three rank blocks on).  Deeper requests per wave
+// 32-row steps a wave of the wgrad kernel keeps in flight: one.  Deeper requests per wave
 // were slower wherever they were tried (four steps against one: 4 to 5 % of the whole call at T = 8192, 1 to 6 % below 4096);
 // a kernel that only reads the same column stripes shows the same (5120 columns, 8192 rows, 240 workgroups: 4.4 TB/s with
 // four steps in flight per wave, 5.9 with one or two): a wave that requests 128 rows at a time spreads its requests over
 // more DRAM pages than one that walks 32 rows at a time.
-constexpr int kWgradGroup = 1, kWgradGroupWide = 2;
+constexpr int kWgradGroup = 1;
+constexpr int kShortBatch = 4096;     // token rows from which a batch counts as long
 
 struct BwdPlan {
     int rp;          // ranks padded to a multiple of 16
@@ -52,7 +53,7 @@ struct BwdPlan {
     int dcols;       // columns of one partial-sum plane: (nbx + nbg) * 128
     int tw;          // token rows per wave of the wgrad kernel (multiple of 128)
     int splits;      // workgroups along the token axis of the wgrad kernel
-    int waves;       // waves per workgroup of the wgrad kernel: 4, or 8 on short batches (see make_plan)
+    int waves;       // waves per workgroup of the wgrad kernel: 4, or 8 on short batches with one rank block (see make_plan)
     // workspace layout, in 4-byte words
     size_t off_t, off_du, off_dbeta, off_part, words;
 };
@@ -67,13 +68,11 @@ BwdPlan make_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, int64_t ell
     p.nbg = static_cast<int>((d_out + 127) / 128);
     p.dcols = (p.nbx + p.nbg) * 128;
     // Below 4096 token rows a wave of a 4-wave workgroup would have little to overlap with: such batches run 8 waves (two
-    // per SIMD), up to two rank blocks (registers).
-    const bool narrow = p.rp * ell_fused <= 32;
-    const bool short_batch = T < 4096 && narrow;
-    p.waves = short_batch ? 2 * kWgradWaves : kWgradWaves;
-    const int group_rows = 32 * (narrow ? kWgradGroup : kWgradGroupWide);
+    // per SIMD); from two rank blocks on their workgroups share a compute unit instead (see launch_all).
+    p.waves = T < kShortBatch && p.rp * ell_fused <= 16 ? 2 * kWgradWaves : kWgradWaves;
+    const int group_rows = 32 * kWgradGroup;
     const int groups = p.t_pad / group_rows;  // a wave takes whole groups of steps (t_pad is a multiple of 128)
-    const int target = T >= 4096 ? kWgradTargetWgsLong : kWgradTargetWgsShort;
+    const int target = T >= kShortBatch ? kWgradTargetWgsLong : kWgradTargetWgsShort;
     int splits = target / (p.nbx + p.nbg);   // rounded down: a grid just above the target would start another round
     const int max_splits = (groups + p.waves - 1) / p.waves;  // at least one group per wave
     splits = splits > max_splits ? max_splits : splits;
@@ -131,7 +130,7 @@ __global__ void bwd_zero_kernel(float* p, int64_t n) {
 // G steps are in flight per wave: the loads of a group are issued without any condition (past the end of the wave's range
 // they re-read valid addresses and are not used), so that every wait counts exactly the loads issued after the one it
 // needs; the last group is consumed without issuing anything.
-template <int RB, int G, int W>
+template <int RB, int G, int W, int Z>
 __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     static_assert(W == 4 || W == 8, "the final sums are dealt to 4 or 8 waves");
     __shared__ __align__(16) float red[W][8][64][4];
@@ -139,7 +138,14 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     // MFMA instructions ignore the EXEC mask, so they must never sit under a vector-predicated branch.
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, q = lane >> 4;
-    const int cb = blockIdx.x;
+    const int rbe = a.rp >> 4, blocks = a.ell * rbe;  // rank blocks per envelope, and in all
+    int cb = blockIdx.x, rb0 = 0;   // column block, first rank block
+    if constexpr (Z > 1) {
+        // workgroups are dealt to the 8 XCDs in turn: the Z that read the same x (or g) are 8 apart, on one XCD
+        rb0 = (cb >> 3) % Z * RB;
+        cb = (cb / (8 * Z)) * 8 + (cb & 7);
+        if (cb >= a.nbx + a.nbg) return;   // (the whole workgroup, before any barrier)
+    }
     const int tk_begin = (static_cast<int>(blockIdx.y) * W + wave) * a.tw;
     int tk_end = tk_begin + a.tw;
     tk_end = tk_end < a.t_pad ? tk_end : a.t_pad;
@@ -151,12 +157,11 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     const float* small = is_x ? a.duT : a.tT;   // dt = beta du meets x, u = beta t meets g
     const int sstride = is_x ? a.du_stride : a.t_stride;
 
-    const int rbe = a.rp >> 4;  // rank blocks per envelope
     float beta[RB];
     int row_of[RB];  // the lane's row in the small arrays: envelope * r + rank, clamped to a rank that exists (its values are then masked)
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {   // block rb: envelope rb / (rp / 16), ranks 16 (rb % (rp / 16)) ..
-        const int en = rb / rbe, rk = (rb - en * rbe) * 16 + li;
+    for (int rb = 0; rb < RB; ++rb) {   // block b: envelope b / (rp / 16), ranks 16 (b % (rp / 16)) ..  (past the last block: it again)
+        const int b = rb0 + rb < blocks ? rb0 + rb : blocks - 1, en = b / rbe, rk = (b - en * rbe) * 16 + li;
         row_of[rb] = en * a.r + (rk < a.r ? rk : a.r - 1);
         beta[rb] = rk < a.r ? static_cast<float>(a.s_rank[row_of[rb]]) : 0.f;
     }
@@ -287,11 +292,12 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     // tile back to true scale; the tiles are summed in wave order; with 4 waves wave w sums register i = w of all 8
     // accumulators and so ends up with 8 consecutive columns, with 8 waves it sums register i = w mod 4 of accumulators
     // 4 (w / 4) .. 4 (w / 4) + 3: 4 consecutive columns.
-    float* out = a.part + static_cast<size_t>(blockIdx.y) * (RB * 16) * a.dcols + static_cast<size_t>(cb) * 128;
+    float* out = a.part + (static_cast<size_t>(blockIdx.y) * blocks + rb0) * 16 * a.dcols + static_cast<size_t>(cb) * 128;
     constexpr int NE = W == 4 ? 8 : 4;
     const int ri = wave & 3, e0 = W == 4 ? 0 : 4 * (wave >> 2);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
+        if (Z > 1 && rb0 + rb >= blocks) break;   // (uniform)
         if (rb > 0) __syncthreads();
         const float inv = __uint_as_float(static_cast<uint32_t>(cur_e[rb] - 13) << 23);
 #pragma unroll
@@ -319,7 +325,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         float* sums = &red[0][0][0][0];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const int en = rb / rbe, rk = (rb - en * rbe) * 16 + li;
+            const int b = rb0 + rb < blocks ? rb0 + rb : blocks - 1, en = b / rbe, rk = (b - en * rbe) * 16 + li;
             float s = 0.f;
             const int row = en * a.r + (rk < a.r ? rk : a.r - 1);  // a rank that exists; the result of a padded rank is dropped below
             const float* dup = a.duT + static_cast<size_t>(row) * a.du_stride + 8 * q;
@@ -338,11 +344,11 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
             if (q == 0) sums[(rb * 16 + li) * W + wave] = s;
         }
         __syncthreads();
-        if (tid < RB * 16) {
+        if (tid < RB * 16 && (rb0 + (tid >> 4)) < blocks) {
             float tot = 0.f;
 #pragma unroll
             for (int w = 0; w < W; ++w) tot += sums[tid * W + w];
-            a.dbeta_part[static_cast<size_t>(blockIdx.y) * (RB * 16) + tid] = tot;
+            a.dbeta_part[(static_cast<size_t>(blockIdx.y) * blocks + rb0) * 16 + tid] = tot;
         }
     }
 }
@@ -356,15 +362,19 @@ __device__ __forceinline__ float smooth_sign_factor(float latent, float kappa) {
 }
 
 // One workgroup per group of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out, d_latentB), plus one for
-// d_s_rank.  Thread (c, kq) takes column c of the group and ranks kq, kq + 8, ...; every sum has a fixed order.
-__global__ __launch_bounds__(256) void lordba_bwd_finish_kernel(BwdArgs a) {
-    __shared__ float sh[LORDBA_MAX_ENVELOPES][256];
+// d_s_rank.  Thread (c, kq) takes column c of the group and ranks kq, kq + KQ, ...; every sum has a fixed order.  KQ is the
+// padded rank up to 32: a thread then has one or two dependent rounds of requests instead of r / 8 (the whole backward call at
+// T = 512, 4096 -> 4096, r = 16 18.7 -> 16.5 us; T = 2048, r = 64 54.1 -> 47.7).
+template <int KQ>
+__global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
+    constexpr int NT = 32 * KQ;
+    __shared__ float sh[LORDBA_MAX_ENVELOPES][NT];
     __shared__ float lat[32 * LORDBA_MAX_RANK];
     const int gx = a.d_in >> 5, gg = a.d_out >> 5;
     const int tid = threadIdx.x;
     const int r = a.r, ell = a.ell, rows = ell * a.rp;   // rows of one token range's plane of partial sums: all envelopes' rank blocks
     if (static_cast<int>(blockIdx.x) == gx + gg) {
-        for (int o = tid; o < ell * r; o += 256) {  // d_beta of every envelope: the shares of the token ranges, in their order
+        for (int o = tid; o < ell * r; o += NT) {  // d_beta of every envelope: the shares of the token ranges, in their order
             const int en = o / r, k = o - en * r;
             float tot = 0.f;
             for (int sp = 0; sp < a.splits; ++sp) tot += a.dbeta_part[static_cast<size_t>(sp) * rows + en * a.rp + k];
@@ -387,12 +397,12 @@ __global__ __launch_bounds__(256) void lordba_bwd_finish_kernel(BwdArgs a) {
         dscale[en] = 0.f;
     }
     if (!is_x && a.d_latB != nullptr) {  // latentB [d_out, r]: the group's 32 rows are 32 r contiguous floats; through LDS for coalesced accesses
-        for (int e = tid; e < 32 * r; e += 256) lat[e] = a.latB[static_cast<size_t>(grp) * 32 * r + e];
+        for (int e = tid; e < 32 * r; e += NT) lat[e] = a.latB[static_cast<size_t>(grp) * 32 * r + e];
         __syncthreads();
     }
     const bool with_lat = a.d_latA != nullptr;   // (null: the carriers are frozen, only the scale gradients are wanted)
     const bool lat_x = with_lat && is_x, add_x = lat_x && a.accumulate;
-    for (int k = kq; k < r; k += 8) {
+    for (int k = kq; k < r; k += KQ) {
         // Everything this rank needs is requested before anything is used: the shares of the token ranges (eight at a
         // time, from a clamped index), the carrier word, the latent and, when accumulating, the gradient so far.  The
         // last two come from a harmless address when they are not wanted, so that no request hides behind a branch.
@@ -431,14 +441,14 @@ __global__ __launch_bounds__(256) void lordba_bwd_finish_kernel(BwdArgs a) {
     for (int en = 0; en < LORDBA_MAX_ENVELOPES; ++en) sh[en][tid] = dscale[en];
     __syncthreads();
     if (!is_x && a.d_latB != nullptr)
-        for (int e = tid; e < 32 * r; e += 256) {
+        for (int e = tid; e < 32 * r; e += NT) {
             float* dst = a.d_latB + static_cast<size_t>(grp) * 32 * r + e;
             *dst = a.accumulate ? *dst + lat[e] : lat[e];
         }
-    if (kq < ell) {   // wave pair kq sums envelope kq's eight partial sums of every column
+    if (kq < ell) {   // wave pair kq sums envelope kq's partial sums of every column
         float tot = 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) tot += sh[kq][j * 32 + c];
+        for (int j = 0; j < KQ; ++j) tot += sh[kq][j * 32 + c];
         (is_x ? a.d_s_in : a.d_s_out)[static_cast<size_t>(kq) * d + col] = tot;
     }
 }
@@ -512,20 +522,41 @@ lordba_status launch_general(const BwdArgs& a, hipStream_t st) {
 // ------------------------------------------------------------------------------------------ host side ----
 bool aligned_to(const void* p, size_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
 
-template <int RB>
+template <int RB, int W, int Z>
+void launch_wgrad(const BwdArgs& a, hipStream_t st) {
+    const int nb = a.nbx + a.nbg;
+    hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z>), dim3(Z > 1 ? (nb + 7) / 8 * 8 * Z : nb, a.splits), dim3(W * 64), 0, st, a);
+}
+
 lordba_status launch_all(const BwdArgs& a, hipStream_t st) {
-    // (steps in flight and waves as make_plan laid the token ranges out)
-    const dim3 grid(a.nbx + a.nbg, a.splits);
-    if constexpr (RB <= 2) {
-        if (a.waves == 2 * kWgradWaves)
-            hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, 2 * kWgradWaves>), grid, dim3(2 * kWgradWaves * 64), 0, st, a);
-        else
-            hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, kWgradWaves>), grid, dim3(kWgradWaves * 64), 0, st, a);
-    } else {
-        hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroupWide, kWgradWaves>), grid, dim3(kWgradWaves * 64), 0, st, a);
+    // Rank blocks of all envelopes together over workgroups (Z) and inside one (RB).  A workgroup that held three or four blocks
+    // left one wave per SIMD (462 registers) with nothing to overlap its conversions, products and requests with; two
+    // workgroups with two blocks each read x and g twice, the second time out of the L2 they share (us of the whole backward call,
+    // one workgroup for all blocks in brackets: 2048 x 5120 x 5120, two envelopes at r = 32 49.4 (60.4); 4096 -> 4096, r = 64, T = 2048
+    // 43.5 (53.7), T = 64 22.3 (34.2); T = 8192, 5120^2 135 (152)).  Short batches gain from single blocks too (T = 2048, r = 32 29.9
+    // (31.5), r = 48 38.5 (41.3 with two)), but not four of them (r = 64 46.0), and long ones, which the streams bind, lose (T = 8192, r = 32
+    // 111 (97)).
+    const bool short_batch = a.T < kShortBatch;
+    switch (a.ell * (a.rp / 16)) {
+        case 1:
+            if (a.waves == 2 * kWgradWaves) launch_wgrad<1, 2 * kWgradWaves, 1>(a, st);
+            else launch_wgrad<1, kWgradWaves, 1>(a, st);
+            break;
+        case 2:
+            if (short_batch) launch_wgrad<1, kWgradWaves, 2>(a, st);
+            else launch_wgrad<2, kWgradWaves, 1>(a, st);
+            break;
+        case 3:
+            if (short_batch) launch_wgrad<1, kWgradWaves, 3>(a, st);
+            else launch_wgrad<2, kWgradWaves, 2>(a, st);
+            break;
+        default: launch_wgrad<2, kWgradWaves, 2>(a, st); break;
     }
     if (hipGetLastError() != hipSuccess) return LORDBA_ERR_LAUNCH;
-    hipLaunchKernelGGL(lordba_bwd_finish_kernel, dim3((a.d_in >> 5) + (a.d_out >> 5) + 1), dim3(256), 0, st, a);
+    const dim3 groups((a.d_in >> 5) + (a.d_out >> 5) + 1);
+    if (a.r <= 8) hipLaunchKernelGGL(lordba_bwd_finish_kernel<8>, groups, dim3(256), 0, st, a);
+    else if (a.r <= 16) hipLaunchKernelGGL(lordba_bwd_finish_kernel<16>, groups, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL(lordba_bwd_finish_kernel<32>, groups, dim3(1024), 0, st, a);
     return hipGetLastError() == hipSuccess ? LORDBA_OK : LORDBA_ERR_LAUNCH;
 }
 
@@ -692,12 +723,7 @@ lordba_status backward_impl(const void* x, const void* g,
         if (!fast) {
             s = r <= 8 ? launch_general<8>(a, st) : r <= 16 ? launch_general<16>(a, st) : r <= 32 ? launch_general<32>(a, st) : launch_general<64>(a, st);
         } else {
-            switch (a.ell * (p.rp / 16)) {   // rank blocks held at once
-                case 1: s = launch_all<1>(a, st); break;
-                case 2: s = launch_all<2>(a, st); break;
-                case 3: s = launch_all<3>(a, st); break;
-                default: s = launch_all<4>(a, st); break;
-            }
+            s = launch_all(a, st);
         }
         if (s != LORDBA_OK) return s;
     }

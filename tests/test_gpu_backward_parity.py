@@ -174,6 +174,15 @@ def test_uneven_rank_scales(torch_cuda):
     assert got["d_s_rank"][4] != 0
 
 
+# Rank blocks dealt over workgroups: two and three blocks on short batches, three (one workgroup with a block to spare) and four on
+# long ones, column blocks that are no multiple of 8, r below a whole block
+@pytest.mark.parametrize("shape", [(37, 96, 64, 32), (100, 1056, 96, 48), (45, 640, 512, 33), (4100, 256, 384, 48), (4099, 160, 96, 64),
+                                   (4096, 1184, 32, 40)], ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_rank_blocks_over_workgroups(torch_cuda, shape):
+    T, d_in, d_out, r = shape
+    check(torch_cuda, inputs.make_backward_inputs(26, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
+
+
 @pytest.mark.parametrize("kappa", [0.0, 1.0, 25.0, 400.0])
 def test_temperatures(torch_cuda, kappa):
     d = inputs.make_backward_inputs(26, 50, 512, 512, 8)
