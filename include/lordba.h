@@ -232,8 +232,8 @@ lordba_status lordba_forward_multi_save_t(const void* x, const uint32_t* packedA
  *             the carriers are taken from these bits, which the caller keeps equal to the signs of the latents)
  *   t_saved : the rank-r intermediate that lordba_forward_save_t wrote for this x and adapter, with its t_stride >= T
  *             (entries past T are ignored); or NULL: it is recomputed from x (one more pass over x).  The matrix-core
- *             kernels take it only with a t_stride that is a multiple of 4 and at least T rounded up to a multiple of
- *             128 (they read the rows in whole steps), 16-byte aligned.
+ *             kernels take it only with a t_stride of at least T rounded up to a multiple of 128 (they read the rows in
+ *             whole steps), and run fastest with one that is a multiple of 4, 16-byte aligned.
  *   d_latentA == NULL and d_latentB == NULL together: the carriers are frozen and only the scales are trained (the
  *   "QAT Freeze" mode of Sec. 3.2): no latent gradients are computed; latentA, latentB and kappa are then ignored.
  *   dx_base fp16 [T, d_in]: the input gradient of the base path, to which the branch's is added; dx may be the same
@@ -244,8 +244,9 @@ lordba_status lordba_forward_multi_save_t(const void* x, const uint32_t* packedA
  * No output, nor the workspace, may overlap an input or another output (dx == dx_base excepted): LORDBA_ERR_ALIAS.
  * Shapes: any d_in, d_out >= 1 and 1 <= r <= 64, every pointer aligned to its element (the workspace to 16 bytes), as
  * lordba_forward and lordba_forward_save_t; else LORDBA_ERR_DIM / LORDBA_ERR_ALIGN.  With d_in and d_out multiples of 32
- * and 16-byte aligned activations, scales and packed carriers the matrix-core kernels run; anything else takes a slower
- * general kernel with the same results (one thread per column).  T == 0: the parameter gradients are set to zero.
+ * and 16-byte aligned activations, scales and packed carriers the calls run fastest; other widths from 8 columns on and
+ * tensors aligned to their elements take variants of the same kernels for them; fewer than 8 columns, or a t_saved whose rows
+ * end before T rounded up to a multiple of 128, a slow general kernel with the same results (one thread per column).  T == 0: the parameter gradients are set to zero.
  * The call only enqueues kernels on `stream`; it never synchronises, allocates or frees.  Results are deterministic
  * (fixed summation order).  Arithmetic: fp16 inputs at their exact values, fp32 accumulation; every gradient array is
  * within 1e-3 relative L2 (per token row for dx, per rank for the latents, whole vector for the scales) of the exact result. */

@@ -117,6 +117,7 @@ struct BwdArgs {
     // with different small operands).  s_in, s_rank, s_out and the scale gradients then have ell rows, tT and duT one
     // [r, stride] block per envelope, and the wgrad kernel's rank blocks are the ell * rp / 16 blocks of all envelopes.
     int ell;
+    int any;               // widths that are no multiples of 32, or tensors aligned to their elements only
 };
 
 __global__ void bwd_zero_kernel(float* p, int64_t n) {
@@ -130,7 +131,9 @@ __global__ void bwd_zero_kernel(float* p, int64_t n) {
 // G steps are in flight per wave: the loads of a group are issued without any condition (past the end of the wave's range
 // they re-read valid addresses and are not used), so that every wait counts exactly the loads issued after the one it
 // needs; the last group is consumed without issuing anything.
-template <int RB, int G, int W, int Z>
+// ANY: any widths from 8 columns on, accesses without an alignment; a last group of 8 columns that reaches past the row is read 8
+// columns from its end and moved into place (columns past the end are zeros).
+template <int RB, int G, int W, int Z, bool ANY>
 __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     static_assert(W == 4 || W == 8, "the final sums are dealt to 4 or 8 waves");
     __shared__ __align__(16) float red[W][8][64][4];
@@ -166,7 +169,8 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         beta[rb] = rk < a.r ? static_cast<float>(a.s_rank[row_of[rb]]) : 0.f;
     }
     int col = cc * 128 + li * 8;
-    col = col < d ? col : d - 8;  // past the end: a valid column group is re-read, its sums are never used
+    const int back = ANY && col > d - 8 ? col - (d - 8) : 0;   // columns that a ragged group was moved back by
+    col = ANY ? col - back : (col < d ? col : d - 8);  // past the end: a valid column group is re-read, its sums are never used
 
     f4 acc[RB][8];
 #pragma unroll
@@ -190,7 +194,8 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         for (int e = 0; e < 8; ++e) {
             int row = tk + 8 * q + e;
             row = row < a.T ? row : a.T - 1;  // rows past T meet dt = u = 0
-            xb[i][e] = load16_stream(src + static_cast<size_t>(row) * d + col);
+            const _Float16* p = src + static_cast<size_t>(row) * d + col;
+            xb[i][e] = ANY ? load16_any_stream(p) : load16_stream(p);
         }
     };
     auto issue_small = [&](int tk0) {  // all G steps of the group that starts at token tk0
@@ -202,8 +207,8 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
             for (int rb = 0; rb < RB; ++rb) {
                 // 32 bytes inside the row's t_pad entries; the array is defined for token < T only, the rest is masked
                 const float* p = small + static_cast<size_t>(row_of[rb]) * sstride + tk + 8 * q;
-                sb[i][rb][0] = load16(p);
-                sb[i][rb][1] = load16(p + 4);
+                sb[i][rb][0] = ANY ? load16_word(p) : load16(p);
+                sb[i][rb][1] = ANY ? load16_word(p + 4) : load16(p + 4);
             }
         }
     };
@@ -251,6 +256,12 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         }
     };
     auto consume_x = [&](int i) {
+        if constexpr (ANY) {
+            if (cc * 128 + 128 > d) {   // scalar: the last column block
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xb[i][e] = drop_halves(xb[i][e], back);
+            }
+        }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             // column e of the lane's 8 x 8 block: token pairs (0,1), (2,3), (4,5), (6,7)
@@ -331,7 +342,8 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
             const float* dup = a.duT + static_cast<size_t>(row) * a.du_stride + 8 * q;
             const float* tp = a.tT + static_cast<size_t>(row) * a.t_stride + 8 * q;
             for (int tk = tk_begin; tk < tk_end; tk += 32) {  // 32 bytes of each array per lane and step, inside t_pad entries
-                const u4 d0 = load16(dup + tk), d1 = load16(dup + tk + 4), t0 = load16(tp + tk), t1 = load16(tp + tk + 4);
+                auto ld = [](const float* p) { return ANY ? load16_word(p) : load16(p); };
+                const u4 d0 = ld(dup + tk), d1 = ld(dup + tk + 4), t0 = ld(tp + tk), t1 = ld(tp + tk + 4);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float dv = __uint_as_float(e < 4 ? d0[e & 3] : d1[e & 3]), tv = __uint_as_float(e < 4 ? t0[e & 3] : t1[e & 3]);
@@ -365,12 +377,12 @@ __device__ __forceinline__ float smooth_sign_factor(float latent, float kappa) {
 // d_s_rank.  Thread (c, kq) takes column c of the group and ranks kq, kq + KQ, ...; every sum has a fixed order.  KQ is the
 // padded rank up to 32: a thread then has one or two dependent rounds of requests instead of r / 8 (the whole backward call at
 // T = 512, 4096 -> 4096, r = 16 18.7 -> 16.5 us; T = 2048, r = 64 54.1 -> 47.7).
-template <int KQ>
+template <int KQ, bool ANY>
 __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
     constexpr int NT = 32 * KQ;
     __shared__ float sh[LORDBA_MAX_ENVELOPES][NT];
     __shared__ float lat[32 * LORDBA_MAX_RANK];
-    const int gx = a.d_in >> 5, gg = a.d_out >> 5;
+    const int gx = (a.d_in + 31) >> 5, gg = (a.d_out + 31) >> 5;
     const int tid = threadIdx.x;
     const int r = a.r, ell = a.ell, rows = ell * a.rp;   // rows of one token range's plane of partial sums: all envelopes' rank blocks
     if (static_cast<int>(blockIdx.x) == gx + gg) {
@@ -386,7 +398,8 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
     const int grp = is_x ? blockIdx.x : blockIdx.x - gx;
     const int d = is_x ? a.d_in : a.d_out;
     const int c = tid & 31, kq = tid >> 5;
-    const int col = grp * 32 + c;
+    const bool live = !ANY || grp * 32 + c < d;   // (ANY: the last group may have fewer than 32 columns)
+    const int col = live ? grp * 32 + c : d - 1;
     const float* plane = a.part + (is_x ? col : a.nbx * 128 + col);
     const uint32_t* pk = is_x ? a.pA : a.pBt;   // both [r, d]: the group's 32 bits of rank k are one word
     float scale[LORDBA_MAX_ENVELOPES], dscale[LORDBA_MAX_ENVELOPES];
@@ -396,8 +409,9 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
         scale[en] = static_cast<float>(is_x ? a.s_in[static_cast<size_t>(ec) * d + col] : a.s_out[static_cast<size_t>(ec) * d + col]);
         dscale[en] = 0.f;
     }
+    const int lat_n = (ANY && d - grp * 32 < 32 ? d - grp * 32 : 32) * r;
     if (!is_x && a.d_latB != nullptr) {  // latentB [d_out, r]: the group's 32 rows are 32 r contiguous floats; through LDS for coalesced accesses
-        for (int e = tid; e < 32 * r; e += NT) lat[e] = a.latB[static_cast<size_t>(grp) * 32 * r + e];
+        for (int e = tid; e < lat_n; e += NT) lat[e] = a.latB[static_cast<size_t>(grp) * 32 * r + e];
         __syncthreads();
     }
     const bool with_lat = a.d_latA != nullptr;   // (null: the carriers are frozen, only the scale gradients are wanted)
@@ -407,10 +421,10 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
         // time, from a clamped index), the carrier word, the latent and, when accumulating, the gradient so far.  The
         // last two come from a harmless address when they are not wanted, so that no request hides behind a branch.
         const size_t n = static_cast<size_t>(k) * d + col;
-        const uint32_t word = pk[k * (d >> 5) + grp];
+        const uint32_t word = ANY ? pk[n >> 5] : pk[k * (d >> 5) + grp];
         const float latent = *(lat_x ? a.latA + n : plane);
         const float so_far = *(add_x ? a.d_latA + n : plane);
-        const uint32_t bit = (word >> c) & 1u;
+        const uint32_t bit = (word >> (ANY ? static_cast<int>(n & 31) : c)) & 1u;
         float weighted = 0.f;   // sum over the envelopes of scale_e * (Q_e or P_e)[k, col]: dL/dS[k, col]
 #pragma unroll
         for (int en = 0; en < LORDBA_MAX_ENVELOPES; ++en) {
@@ -432,8 +446,8 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
         }
         if (lat_x) {
             const float val = weighted * smooth_sign_factor(latent, a.kappa);
-            a.d_latA[n] = add_x ? so_far + val : val;
-        } else if (with_lat) {
+            if (live) a.d_latA[n] = add_x ? so_far + val : val;
+        } else if (with_lat && live) {
             lat[c * r + k] = weighted * smooth_sign_factor(lat[c * r + k], a.kappa);
         }
     }
@@ -441,11 +455,11 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
     for (int en = 0; en < LORDBA_MAX_ENVELOPES; ++en) sh[en][tid] = dscale[en];
     __syncthreads();
     if (!is_x && a.d_latB != nullptr)
-        for (int e = tid; e < 32 * r; e += NT) {
+        for (int e = tid; e < lat_n; e += NT) {
             float* dst = a.d_latB + static_cast<size_t>(grp) * 32 * r + e;
             *dst = a.accumulate ? *dst + lat[e] : lat[e];
         }
-    if (kq < ell) {   // wave pair kq sums envelope kq's partial sums of every column
+    if (kq < ell && live) {   // wave pair kq sums envelope kq's partial sums of every column
         float tot = 0.f;
 #pragma unroll
         for (int j = 0; j < KQ; ++j) tot += sh[kq][j * 32 + c];
@@ -454,10 +468,11 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
 }
 
 // --------------------------------------------------------------------------------------- general kernel ----
-// Q, P and everything that follows from them for any shape and alignment, on the vector ALU: one thread per column of x
+// Q, P and everything that follows from them for widths below 8 columns and for a kept t whose rows end before the padded token
+// count, on the vector ALU: one thread per column of x
 // (Q[:, i], then d_s_in[i] and d_latentA[:, i]) or of g (P[:, j], d_s_out[j], d_latentB[j, :]) walks all token rows with
 // its r sums in registers; r more threads take d_s_rank.  No partial sums, fixed order.  Slow (a column's T x r
-// multiply-adds in one thread) but it is what a shape outside the matrix-core path gets, as in the forward pass.
+// multiply-adds in one thread) but it takes every shape.
 template <int RP>
 __global__ __launch_bounds__(256) void lordba_bwd_general_kernel(BwdArgs a) {
     __shared__ float beta_s[RP];
@@ -522,10 +537,19 @@ lordba_status launch_general(const BwdArgs& a, hipStream_t st) {
 // ------------------------------------------------------------------------------------------ host side ----
 bool aligned_to(const void* p, size_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
 
+template <int KQ>
+void launch_finish(const BwdArgs& a, hipStream_t st) {
+    const dim3 groups((a.d_in + 31) / 32 + (a.d_out + 31) / 32 + 1);
+    if (a.any) hipLaunchKernelGGL((lordba_bwd_finish_kernel<KQ, true>), groups, dim3(32 * KQ), 0, st, a);
+    else hipLaunchKernelGGL((lordba_bwd_finish_kernel<KQ, false>), groups, dim3(32 * KQ), 0, st, a);
+}
+
 template <int RB, int W, int Z>
 void launch_wgrad(const BwdArgs& a, hipStream_t st) {
     const int nb = a.nbx + a.nbg;
-    hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z>), dim3(Z > 1 ? (nb + 7) / 8 * 8 * Z : nb, a.splits), dim3(W * 64), 0, st, a);
+    const dim3 grid(Z > 1 ? (nb + 7) / 8 * 8 * Z : nb, a.splits);
+    if (a.any) hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z, true>), grid, dim3(W * 64), 0, st, a);
+    else hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z, false>), grid, dim3(W * 64), 0, st, a);
 }
 
 lordba_status launch_all(const BwdArgs& a, hipStream_t st) {
@@ -553,10 +577,9 @@ lordba_status launch_all(const BwdArgs& a, hipStream_t st) {
         default: launch_wgrad<2, kWgradWaves, 2>(a, st); break;
     }
     if (hipGetLastError() != hipSuccess) return LORDBA_ERR_LAUNCH;
-    const dim3 groups((a.d_in >> 5) + (a.d_out >> 5) + 1);
-    if (a.r <= 8) hipLaunchKernelGGL(lordba_bwd_finish_kernel<8>, groups, dim3(256), 0, st, a);
-    else if (a.r <= 16) hipLaunchKernelGGL(lordba_bwd_finish_kernel<16>, groups, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL(lordba_bwd_finish_kernel<32>, groups, dim3(1024), 0, st, a);
+    if (a.r <= 8) launch_finish<8>(a, st);
+    else if (a.r <= 16) launch_finish<16>(a, st);
+    else launch_finish<32>(a, st);
     return hipGetLastError() == hipSuccess ? LORDBA_OK : LORDBA_ERR_LAUNCH;
 }
 
@@ -611,12 +634,15 @@ lordba_status backward_impl(const void* x, const void* g,
         !aligned_to(d_latentA, 4) || !aligned_to(d_latentB, 4) || !aligned_to(workspace, 16) || !aligned_to(t_saved, 4) ||
         !aligned_to(dx_base, 2) || !aligned_to(dx, 2))
         return LORDBA_ERR_ALIGN;
-    // The matrix-core wgrad and the finish kernel need widths that are multiples of 32, 16-byte aligned activations and
-    // carriers, and a kept t whose rows reach the padded token count (it is read in whole 32-row steps); anything else
-    // takes the general kernel.
+    // The plain matrix-core wgrad and finish kernels need widths that are multiples of 32, 16-byte aligned activations and
+    // carriers, and a kept t whose rows reach the padded token count (it is read in whole 32-row steps).
     const bool fast = fast_shape(d_in, d_out) && aligned_to(x, 16) && aligned_to(g, 16) && aligned_to(s_in, 16) && aligned_to(s_out, 16) &&
                       aligned_to(packedA, 16) && aligned_to(packedAt, 16) && aligned_to(dx_base, 16) && aligned_to(dx, 16) &&
                       (t_saved == nullptr || (aligned_to(t_saved, 16) && t_stride % 4 == 0 && t_stride >= (T + 127) / 128 * 128));
+    // The same kernels with element-aligned accesses take everything else that has a whole group of 8 columns on either side, with
+    // a kept t whose rows reach the padded token count (us, the general kernel's time in brackets: 300 x 1000 -> 3001, r = 12 17.2
+    // (362); 600 x 4728 -> 11055, r = 32 37 (1902); 4000 x 999 -> 1001, r = 16 21.6 (7178); 64 x 33 -> 17, r = 3 10.8 (30.9).
+    const bool any_ok = d_in >= 8 && d_out >= 8 && (t_saved == nullptr || t_stride >= (T + 127) / 128 * 128);
     // Several envelopes: with room for the partial sums of all of them (lordba_backward_multi_workspace_bytes) and at most
     // four rank blocks in all, one wgrad and one finish pass serve every envelope (x and g are read once); otherwise one
     // pass per envelope.
@@ -720,7 +746,8 @@ lordba_status backward_impl(const void* x, const void* g,
         a.waves = p.waves;
         a.accumulate = e > 0 ? 1 : 0;
         a.ell = fused ? static_cast<int>(ell) : 1;
-        if (!fast) {
+        a.any = fast ? 0 : 1;
+        if (!fast && !any_ok) {
             s = r <= 8 ? launch_general<8>(a, st) : r <= 16 ? launch_general<16>(a, st) : r <= 32 ? launch_general<32>(a, st) : launch_general<64>(a, st);
         } else {
             s = launch_all(a, st);

@@ -22,6 +22,7 @@ typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u1_any __attribute__((aligned(2)));
 typedef uint32_t u4_word __attribute__((ext_vector_type(4), aligned(4)));  // (packed words: aligned to a word)
 __device__ __forceinline__ u4 load16_any(const void* p) { return *static_cast<const u4_any*>(p); }
+__device__ __forceinline__ u4 load16_word(const void* p) { return *static_cast<const u4_word*>(p); }
 __device__ __forceinline__ u4 load16_any_stream(const void* p) { return __builtin_nontemporal_load(static_cast<const u4_any*>(p)); }
 __device__ __forceinline__ void store16_any_stream(void* p, u4 v) { __builtin_nontemporal_store(static_cast<u4_any>(v), static_cast<u4_any*>(p)); }
 // Eight halves moved down by n (0 .. 8 or more) places, zeros from above: entry e becomes entry e + n.

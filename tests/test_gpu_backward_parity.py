@@ -183,6 +183,15 @@ def test_rank_blocks_over_workgroups(torch_cuda, shape):
     check(torch_cuda, inputs.make_backward_inputs(26, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
 
 
+# Widths around the edges of groups (8), words (32) and column blocks (128) on the element-aligned kernels, every rank-block count,
+# short and long batches
+@pytest.mark.parametrize("shape", [(70, 25, 41, 5), (33, 129, 127, 64), (300, 1000, 3001, 12), (45, 1055, 257, 33), (4100, 135, 250, 17),
+                                   (4097, 90, 129, 48)], ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_odd_widths(torch_cuda, shape):
+    T, d_in, d_out, r = shape
+    check(torch_cuda, inputs.make_backward_inputs(27, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
+
+
 @pytest.mark.parametrize("kappa", [0.0, 1.0, 25.0, 400.0])
 def test_temperatures(torch_cuda, kappa):
     d = inputs.make_backward_inputs(26, 50, 512, 512, 8)
