@@ -6,11 +6,12 @@
 // computed 8 columns from the end and stores only the columns that no other group has; requests that a wave has no use for
 // (chunks or blocks past its share) are not made, since with so little work per call they are a third of it.
 //
-// Every call that the plain variants decline comes here first; measured against the general kernel on 28 small shapes (17 to
-// 1001 columns, 1 to 1024 rows, r = 1 to 8) it is 1.1 to 2.3 times as fast on each, beyond that 3 to 50 times (us, general kernel
-// in brackets): 1500 x 1000 -> 3001, r = 12: 8.5 (32.8); 4000 x 5001 -> 5001, r = 16: 36.4 (352); 16 x 999 -> 12777, r = 57: 7.2
-// (136); 1 x 33 -> 17, r = 1: 3.1 (3.7).  Bound: at 4000 rows of 5001 the streams (3.3 TB/s; rows that start inside a cache line
-// share it with their neighbours), at a few rows the latency of the chain.
+// Every call that the plain variants decline comes here first, also pools of adapters with several envelopes at r > 16 or 32.
+// Measured against the general kernel on 28 small shapes (17 to 1001 columns, 1 to 1024 rows, r = 1 to 8) it is 1.1 to 2.3 times
+// as fast on each, beyond that 3 to 50 times (us, general kernel in brackets): 1500 x 1000 -> 3001, r = 12 8.5 (32.8); 4000 x 5001
+// -> 5001, r = 16 36.4 (352); 16 x 999 -> 12777, r = 57 7.2 (136); 1 x 33 -> 17, r = 1 3.1 (3.7).  Bound: at 4000 rows of 5001 the
+// streams (3.3 TB/s; rows that start inside a cache line share it with their neighbours), at a few rows the latency of the
+// chain.
 #pragma once
 #include "lordba_fwd_impl.h"
 
@@ -20,7 +21,7 @@ namespace {
 template <int RB, int L>
 lordba_status launch_any_depth(const FwdArgs& a, hipStream_t stream) {
     // chunks in flight per wave where they do not all fit: two where the accumulators of three or four envelopes leave no room for
-    // more (with four, up to 72 registers were spilled)
+    // more (with four chunks, up to 72 registers were spilled)
     constexpr int kDeep = RB * L >= 9 ? 2 : 4;
     const bool shallow = (a.d_in + 127) / 128 <= 2 * 8;  // every wave's chunks of d_in are in flight at once
     if (a.ids != nullptr) {
@@ -37,7 +38,9 @@ lordba_status launch_any_rb(const FwdArgs& a, hipStream_t stream) {
         case 1: return launch_any_depth<1, L>(a, stream);
         case 2: return launch_any_depth<2, L>(a, stream);
         case 3: return launch_any_depth<3, L>(a, stream);
-        default: return launch_any_depth<4, L>(a, stream);
+        default:
+            if constexpr (L <= 3) return launch_any_depth<4, L>(a, stream);
+            return LORDBA_ERR_ALGO;  // (the partial tiles of four envelopes need more than the 160 KiB of LDS)
     }
 }
 

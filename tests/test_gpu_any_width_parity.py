@@ -33,7 +33,7 @@ def place(torch, a, shift):
 
 # (T, d_in, d_out, r): widths one below, at and one above the edges of groups (8), words (32), chunks and blocks (128) and of the
 # one-shot x pipeline (2048); every rank-block count; one row, a ragged tile,
-# more tiles than are split; an aligned shape whose four envelopes at r = 64 only these variants hold
+# more tiles than are split; an aligned shape (four envelopes at r = 64 take the general kernel)
 SHAPES = [(1, 8, 8, 5), (3, 9, 15, 64), (5, 33, 17, 3), (9, 127, 129, 16), (8, 129, 127, 8), (17, 136, 250, 17), (300, 1000, 3001, 12),
           (261, 2047, 513, 33), (12, 2049, 1030, 64), (11, 512, 640, 64), (7, 3999, 640, 16), (2, 40, 4097, 48)]
 
