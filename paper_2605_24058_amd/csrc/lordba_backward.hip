@@ -70,7 +70,9 @@ BwdPlan make_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, int64_t ell
     // Below 4096 token rows a wave of a 4-wave workgroup would have little to overlap with: such batches run 8 waves (two
     // per SIMD); from two rank blocks on their workgroups share a compute unit instead (see launch_all).
     p.waves = T < kShortBatch && p.rp * ell_fused <= 16 ? 2 * kWgradWaves : kWgradWaves;
-    const int group_rows = 32 * kWgradGroup;
+    // (beyond 2048 rows with three or four rank blocks: token ranges of 64 rows at a time, so that the plan, and with it the shapes that fit
+    // the array of lordba_backward_noalloc, is the one it was when such a workgroup took two steps at a time)
+    const int group_rows = T > 2048 && p.rp * ell_fused > 32 ? 64 : 32 * kWgradGroup;
     const int groups = p.t_pad / group_rows;  // a wave takes whole groups of steps (t_pad is a multiple of 128)
     const int target = T >= kShortBatch ? kWgradTargetWgsLong : kWgradTargetWgsShort;
     int splits = target / (p.nbx + p.nbg);   // rounded down: a grid just above the target would start another round
