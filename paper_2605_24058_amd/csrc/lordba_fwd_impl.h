@@ -314,8 +314,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // gridDim.y workgroups may share a token tile (small T: most of the chip would idle otherwise): each repeats stages 1
     // and 2, which costs no extra HBM traffic worth naming at such T, and takes its own contiguous range of blocks.
     const int nblk_all = (d_out + 127) >> 7;
-    const int per_wg = GM == 1 ? nblk_all : a.blocks_per_wg;
-    const int b_first = GM == 1 ? 0 : static_cast<int>(POOL ? blockIdx.z : blockIdx.y) * per_wg;
+    constexpr bool WHOLE = GM == 1 || (GM == 0 && TMV != 8);   // (only 8-row tiles are ever split)
+    const int per_wg = WHOLE ? nblk_all : a.blocks_per_wg;
+    const int b_first = WHOLE ? 0 : static_cast<int>(POOL ? blockIdx.z : blockIdx.y) * per_wg;
     const int nblk = nblk_all - b_first < per_wg ? (nblk_all - b_first > 0 ? nblk_all - b_first : 0) : per_wg;
     // A wave owns CONSECUTIVE blocks (its blocks in flight are then one contiguous piece of each row: 512 bytes per row at
     // the headline shape instead of two pieces 4 KiB apart: C2 9.99 -> 9.61 us, 4096 -> 11008 at T = 4096 42.1 -> 39.7),
@@ -842,7 +843,7 @@ __global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && !ANY && (
     extern __shared__ __align__(16) unsigned char smem[];
     if constexpr (GM < 4) {
         const int64_t t0 = static_cast<int64_t>(blockIdx.x) * TMV;
-        if (GM != 1 && t0 >= a.T) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
+        if (GM != 1 && TMV == 8 && t0 >= a.T) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
         const int last = static_cast<int>(a.T - 1 - t0 < TMV - 1 ? a.T - 1 - t0 : TMV - 1);  // last live row of the tile
         fwd_tile<RB, TMV, NW, D1, OS, BM, GM, L, TR, ANY>(a, smem, t0, 0, last);
     } else {
