@@ -93,9 +93,15 @@ lordba_status lordba_unpack_signs(const uint32_t* packedA, const uint32_t* packe
  * Arithmetic: fp16 inputs at their exact values, products s_in*x exact, fp32 accumulation, one
  * round-to-nearest-even to fp16 at the end; every token row is within 1e-3 relative L2 of the
  * exact result.  Shapes with d_in % 32 == 0, d_out % 8 == 0 and 16-byte aligned pointers run
- * fastest; other widths from 8 columns on and tensors aligned to their elements take variants of the same matrix-core
- * kernel for them; fewer than 8 columns take a general kernel.  Same results up to the order of fp32 sums.
- * Non-finite inputs propagate by IEEE rules; nothing is clamped. */
+ * fastest; other widths from 8 columns on and tensors aligned to their elements take variants of
+ * the same matrix-core kernel for them; fewer than 8 columns, r * d_in <= 32, and four envelopes at
+ * r > 48 take a general kernel.  The matrix-core kernels hold u = s_rank * t to 22
+ * bits of its row's largest entry, the general kernel in fp32; the results agree up to that and
+ * the order of fp32 sums (error against 64 bits on 40 odd shapes: the same to 1e-6 of itself).
+ * Non-finite inputs: nothing is clamped, and what depends on a NaN is NaN.  Infinities propagate by
+ * IEEE rules in the general kernel and the variants for element-aligned tensors; on the fastest
+ * path an infinite x, s_in or s_rank makes the token rows that it reaches NaN.
+ */
 lordba_status lordba_forward(const void* x, const uint32_t* packedA, const uint32_t* packedB,
                              const void* s_in, const void* s_rank, const void* s_out,
                              const void* y_base, void* y_out,

@@ -562,6 +562,8 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
                 }
                 if constexpr (TR) tkeep[rb * L + en] = part[0];  // training: t is written out at the very end (see export_t)
                 u[rb] = part[0] * sr[rb][en];
+                // (ANY: the padded ranks repeat the last rank's t, which may be infinite, and meet a scale of 0)
+                if constexpr (ANY) u[rb] = rb * 16 + li < r ? u[rb] : 0.f;
                 amax = fmaxf(amax, fabsf(u[rb]));
             }
             const float rowmax = row_max16(amax);  // over the 16 ranks of a block; amax already spans the blocks
@@ -573,7 +575,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
             for (int rb = 0; rb < RB; ++rb) {
                 const float up = u[rb] * mul;
                 const _Float16 hi = static_cast<_Float16>(up);
-                const _Float16 lo = static_cast<_Float16>(up - static_cast<float>(hi));
+                _Float16 lo = static_cast<_Float16>(up - static_cast<float>(hi));
+                // (ANY: infinities propagate as in the general kernel, whose calls these variants took over: no inf - inf)
+                if constexpr (ANY) lo = fabsf(up) < INFINITY ? lo : static_cast<_Float16>(0.f);
                 us[((rb * L + en) * 16 + q * 4 + i) * kURow + li] = hi;
                 us[((rb * L + en) * 16 + q * 4 + i) * kURow + 16 + li] = lo;
             }

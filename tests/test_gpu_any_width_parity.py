@@ -121,3 +121,42 @@ def test_a_row_of_nan_stays_in_its_row(torch_cuda):
     for row in (0, 1, 2, 5):
         assert np.array_equal(y[row], y0[row]), row
     assert np.isnan(y[3]).all() and np.isinf(y[4]).all()
+
+
+def same_with_infinities(got, want, label):
+    """Infinities of the same sign and NaN in the same places; finite values within one rounding to fp16."""
+    with np.errstate(over="ignore"):
+        w16 = want.astype(np.float16)
+    assert np.array_equal(np.isnan(got), np.isnan(w16)), label
+    assert np.array_equal(np.isposinf(got), np.isposinf(w16)) and np.array_equal(np.isneginf(got), np.isneginf(w16)), label
+    ok = np.isfinite(w16)
+    # half a unit of fp16 and the fp32 sums
+    assert np.abs(got[ok].astype(np.float64) - want[ok]).max(initial=0.0) <= 2.0 ** -10 * max(np.abs(want[ok]).max(initial=0.0), 2.0 ** -14), label
+
+
+@pytest.mark.parametrize("ell", [1, 2, 3])
+@pytest.mark.parametrize("r", [1, 5, 16, 17, 50])
+@pytest.mark.parametrize("where", ["x", "x_end", "s_in", "s_rank", "s_out"])
+def test_infinities(torch_cuda, where, r, ell):
+    """An infinite input gives infinities where IEEE arithmetic does (one rank, or all ranks' signs agree) and NaN only where
+    infinities of both signs meet."""
+    torch = torch_cuda
+    d = inputs.make_inputs_multi(34, 6, 203, 77, r, ell)
+    place_of = {"x": ("x", (2, 3)), "x_end": ("x", (2, 202)), "s_in": ("s_in", (ell - 1, 7)), "s_rank": ("s_rank", (0, r // 2)), "s_out": ("s_out", (0, 75))}
+    name, index = place_of[where]
+    d[name][index] = np.inf
+    with np.errstate(invalid="ignore"):
+        want = oracle.forward_multi(d["x"], d["signsA"], d["signsB"], d["s_in"], d["s_rank"], d["s_out"], d["y_base"])
+    dev = binding.to_device(d)
+    args = [dev[k] for k in ("x", "packedA", "packedB", "s_in", "s_rank", "s_out", "y_base")]
+    for algo in (A_GEN, A_AUTO):
+        got = binding.lordba_forward_multi(*args, algo=algo).cpu().numpy()
+        same_with_infinities(got, want, (where, r, ell, algo))
+    # one adapter of a pool, whose other rows stay finite
+    ids = torch.tensor([0, 0, 1, 1, 0, 1], dtype=torch.int32, device="cuda")
+    clean = binding.to_device(inputs.make_inputs_multi(35, 6, 203, 77, r, ell))
+    pool = [torch.stack([clean[k], dev[k]]) for k in ("packedA", "packedB", "s_in", "s_rank", "s_out")]
+    got = binding.lordba_forward_batched_multi(dev["x"], *pool, ids, dev["y_base"]).cpu().numpy()
+    rows = [2, 3, 5]
+    same_with_infinities(got[rows], want[rows], (where, r, ell, "pool"))
+    assert np.isfinite(got[[0, 1, 4]]).all()
