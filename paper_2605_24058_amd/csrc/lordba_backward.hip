@@ -134,7 +134,8 @@ __global__ void bwd_zero_kernel(float* p, int64_t n) {
 // they re-read valid addresses and are not used), so that every wait counts exactly the loads issued after the one it
 // needs; the last group is consumed without issuing anything.
 // ANY: any widths from 8 columns on, accesses without an alignment; a last group of 8 columns that reaches past the row is read 8
-// columns from its end and moved into place (columns past the end are zeros).
+// columns from its end and moved into place (columns past the end are zeros).  Infinities propagate by IEEE rules, as in the general
+// kernel, which takes the calls that these variants decline.
 template <int RB, int G, int W, int Z, bool ANY>
 __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     static_assert(W == 4 || W == 8, "the final sums are dealt to 4 or 8 waves");
@@ -224,8 +225,8 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float raw = __uint_as_float(sb[i][rb][e >> 2][e & 3]);
-                    // select, not multiply: the padding rows and the ranks past r hold undefined values
-                    v[i][e] = (tk0 + 32 * i + 8 * q + e < a.T && beta[rb] != 0.f) ? raw * beta[rb] : 0.f;
+                    // select, not multiply: the padding rows hold undefined values
+                    v[i][e] = (tk0 + 32 * i + 8 * q + e < a.T && (ANY || beta[rb] != 0.f)) ? raw * beta[rb] : 0.f;
                     m = fmaxf(m, fabsf(v[i][e]));
                 }
             }
@@ -251,17 +252,25 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
                     h[1] = static_cast<_Float16>(v1);
                     l[0] = static_cast<_Float16>(v0 - static_cast<float>(h[0]));
                     l[1] = static_cast<_Float16>(v1 - static_cast<float>(h[1]));
+                    if constexpr (ANY) {   // (no inf - inf)
+                        l[0] = fabsf(v0) < INFINITY ? l[0] : static_cast<_Float16>(0.f);
+                        l[1] = fabsf(v1) < INFINITY ? l[1] : static_cast<_Float16>(0.f);
+                    }
                     hl[i][rb][0][w] = __builtin_bit_cast(uint32_t, h);
                     hl[i][rb][1][w] = __builtin_bit_cast(uint32_t, l);
                 }
             }
         }
     };
-    auto consume_x = [&](int i) {
+    auto consume_x = [&](int i, int tk) {
         if constexpr (ANY) {
             if (cc * 128 + 128 > d) {   // scalar: the last column block
 #pragma unroll
                 for (int e = 0; e < 8; ++e) xb[i][e] = drop_halves(xb[i][e], back);
+            }
+            if (tk + 32 > a.T) {        // scalar: the last rows (they repeat row T - 1, which may hold infinities)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xb[i][e] = tk + 8 * q + e < a.T ? xb[i][e] : u4{0u, 0u, 0u, 0u};
             }
         }
 #pragma unroll
@@ -272,10 +281,13 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr)
                 col8[pr] = __builtin_amdgcn_perm(xb[i][2 * pr + 1][e >> 1], xb[i][2 * pr][e >> 1], sel);
+            // ANY: what is not finite in x is counted with the hi operand; the lo operand, whose sign may differ, meets the largest
+            // finite number in its place
+            const h8 fin8 = ANY ? clamp_finite(as_h8(col8)) : as_h8(col8);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 acc[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(col8), as_h8(hl[i][rb][0]), acc[rb][e], 0, 0, 0);
-                acc[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(col8), as_h8(hl[i][rb][1]), acc[rb][e], 0, 0, 0);
+                acc[rb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fin8, as_h8(hl[i][rb][1]), acc[rb][e], 0, 0, 0);
             }
         }
     };
@@ -292,13 +304,13 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
             issue_small(tk + 32 * G);
 #pragma unroll
             for (int i = 0; i < G; ++i) {
-                consume_x(i);
+                consume_x(i, tk + 32 * i);
                 issue_x(i, tk + 32 * (G + i));
             }
         }
         convert(tk);
 #pragma unroll
-        for (int i = 0; i < G; ++i) consume_x(i);
+        for (int i = 0; i < G; ++i) consume_x(i, tk + 32 * i);
     }
 
     // Accumulator e, register i of lane (li, q): rank rb*16 + li, column 8 (4q + i) + e of the block.  Each wave brings its

@@ -34,6 +34,12 @@ __device__ __forceinline__ u4 drop_halves(u4 v, int n) {
     v = (n & 1) ? one : v;
     return n < 8 ? v : u4{0u, 0u, 0u, 0u};
 }
+// Infinities and NaN become the largest finite number (NaN whichever of the two).
+__device__ __forceinline__ h8 clamp_finite(h8 v) {
+    const _Float16 top = static_cast<_Float16>(65504.f);
+    const h8 hi = {top, top, top, top, top, top, top, top};
+    return __builtin_elementwise_min(__builtin_elementwise_max(v, -hi), hi);
+}
 // Address = uniform base (kept in scalar registers) + unsigned 32-bit byte offset per lane: one add-free addressing
 // mode, no 64-bit vector arithmetic.
 __device__ __forceinline__ const void* at(const void* base, uint32_t byte_off) { return static_cast<const char*>(base) + byte_off; }

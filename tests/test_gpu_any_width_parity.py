@@ -160,3 +160,40 @@ def test_infinities(torch_cuda, where, r, ell):
     rows = [2, 3, 5]
     same_with_infinities(got[rows], want[rows], (where, r, ell, "pool"))
     assert np.isfinite(got[[0, 1, 4]]).all()
+
+
+def backward_both_ways(torch, d):
+    """The parameter gradients and dx by the element-aligned matrix-core kernels (kept t in rows of the padded token count) and by
+    the general kernel (rows of T, no multiple of 128), from the same t."""
+    T = d["x"].shape[0]
+    cu = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    w = lambda a: cu(a.view(np.int32))
+    pA, pB = map(w, binding.lordba_pack_signs(d["signsA"], d["signsB"]))
+    pAt, pBt = map(w, binding.lordba_pack_transposed(d["signsA"], d["signsB"]))
+    x, scales = cu(d["x"]), tuple(cu(d[k]) for k in ("s_in", "s_rank", "s_out"))
+    _, t = binding.lordba_forward_save_t(x, pA, pB, *scales)
+    out = []
+    for t_saved in (t, t[:, :T].contiguous()):
+        got = binding.lordba_backward(x, cu(d["g"]), pA, pAt, pBt, *scales, cu(d["latA"]), cu(d["latB"]), 100.0,
+                                      dx_base=cu(d["dx_base"]), t_saved=t_saved)
+        out.append({k: v.cpu().numpy() for k, v in got.items()})
+    return out
+
+
+# (the last row and column: what a ragged group or a padded row repeats; a rank scale of zero; g, whose du is then infinite)
+@pytest.mark.parametrize("r", [1, 5, 17, 50])
+@pytest.mark.parametrize("where", [("x", (3, 7)), ("x", (44, 56)), ("g", (2, 32)), ("g", (44, 1)), ("s_rank", (0,)), ("s_out", (4,))],
+                         ids=lambda w: "%s_%s" % (w[0], "_".join(map(str, w[1]))))
+def test_infinities_in_the_backward(torch_cuda, where, r):
+    """Infinite and NaN gradients where the general kernel, which adds up each column by itself, has them; the rest as it has them
+    (fp32 sums of 45 terms in another order: 45 half units of 2^-24 of the largest partial sum, taken as 1e-5 of the norm)."""
+    d = inputs.make_backward_inputs(36, 45, 57, 33, r)
+    d[where[0]][where[1]] = np.inf
+    d["s_rank"][r // 2] = 0 if where[0] != "s_rank" else d["s_rank"][r // 2]
+    any_, general = backward_both_ways(torch_cuda, d)
+    for k in general:
+        a, b = any_[k].astype(np.float64), general[k].astype(np.float64)
+        assert np.array_equal(np.isnan(a), np.isnan(b)), (k, where, r)
+        assert np.array_equal(np.isposinf(a), np.isposinf(b)) and np.array_equal(np.isneginf(a), np.isneginf(b)), (k, where, r)
+        ok = np.isfinite(b)
+        assert np.linalg.norm(a[ok] - b[ok]) <= 1e-5 * np.linalg.norm(b[ok]), (k, where, r)
