@@ -197,3 +197,17 @@ def test_infinities_in_the_backward(torch_cuda, where, r):
         assert np.array_equal(np.isposinf(a), np.isposinf(b)) and np.array_equal(np.isneginf(a), np.isneginf(b)), (k, where, r)
         ok = np.isfinite(b)
         assert np.linalg.norm(a[ok] - b[ok]) <= 1e-5 * np.linalg.norm(b[ok]), (k, where, r)
+
+
+@pytest.mark.parametrize("shape", [(57, 33, 50), (129, 200, 33), (1000, 77, 64)], ids=lambda s: "%dx%d_r%d" % s)
+def test_gradients_keep_24_bits(torch_cuda, shape):
+    """One row of x and g that holds powers of two: a latent gradient is then alpha * dt * smooth-sign factor with exact products
+    by 2^n, and the fp32 dt must come through whole, as in the general kernel."""
+    d_in, d_out, r = shape
+    d = inputs.make_backward_inputs(37, 1, d_in, d_out, r)
+    rng = np.random.default_rng(38)
+    for k in ("x", "g"):
+        d[k] = np.ldexp(np.where(rng.random(d[k].shape) < 0.5, -1.0, 1.0), rng.integers(-3, 4, d[k].shape)).astype(np.float16)
+    any_, general = backward_both_ways(torch_cuda, d)
+    for k in ("d_latentA", "d_latentB"):
+        assert general[k].any() and np.array_equal(any_[k], general[k]), k
