@@ -34,11 +34,14 @@ __device__ __forceinline__ u4 drop_halves(u4 v, int n) {
     v = (n & 1) ? one : v;
     return n < 8 ? v : u4{0u, 0u, 0u, 0u};
 }
-// Infinities and NaN become the largest finite number (NaN whichever of the two).
+// Infinities and NaN become the largest finite number of their sign.  On the bits: as unsigned numbers the negative ones that are not
+// finite are the largest, as signed numbers the positive ones (two packed minima; the fp16 minimum and maximum need a third
+// instruction to quiet NaN).
 __device__ __forceinline__ h8 clamp_finite(h8 v) {
-    const _Float16 top = static_cast<_Float16>(65504.f);
-    const h8 hi = {top, top, top, top, top, top, top, top};
-    return __builtin_elementwise_min(__builtin_elementwise_max(v, -hi), hi);
+    typedef uint16_t us8 __attribute__((ext_vector_type(8)));
+    typedef int16_t s8 __attribute__((ext_vector_type(8)));
+    const us8 neg = __builtin_elementwise_min(__builtin_bit_cast(us8, v), static_cast<us8>(static_cast<uint16_t>(0xFBFF)));
+    return __builtin_bit_cast(h8, __builtin_elementwise_min(__builtin_bit_cast(s8, neg), static_cast<s8>(static_cast<int16_t>(0x7BFF))));
 }
 // Address = uniform base (kept in scalar registers) + unsigned 32-bit byte offset per lane: one add-free addressing
 // mode, no 64-bit vector arithmetic.
