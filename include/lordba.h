@@ -238,8 +238,9 @@ lordba_status lordba_forward_multi_save_t(const void* x, const uint32_t* packedA
  *             the carriers are taken from these bits, which the caller keeps equal to the signs of the latents)
  *   t_saved : the rank-r intermediate that lordba_forward_save_t wrote for this x and adapter, with its t_stride >= T
  *             (entries past T are ignored); or NULL: it is recomputed from x (one more pass over x).  The matrix-core
- *             kernels take it only with a t_stride of at least T rounded up to a multiple of 128 (they read the rows in
- *             whole steps), and run fastest with one that is a multiple of 4, 16-byte aligned.
+ *             kernels take it only with a t_stride of at least T rounded up to a multiple of 128, and run fastest with one
+ *             that is a multiple of 4, 16-byte aligned: on the fastest path (see Shapes) every row, the last one too, is
+ *             read up to T rounded up to a multiple of 128; off it no row is read past T.
  *   d_latentA == NULL and d_latentB == NULL together: the carriers are frozen and only the scales are trained (the
  *   "QAT Freeze" mode of Sec. 3.2): no latent gradients are computed; latentA, latentB and kappa are then ignored.
  *   dx_base fp16 [T, d_in]: the input gradient of the base path, to which the branch's is added; dx may be the same

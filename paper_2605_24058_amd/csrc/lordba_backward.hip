@@ -31,6 +31,7 @@
 
 #include "lordba.h"
 #include "lordba_dev_util.h"
+#include "lordba_rows.h"
 
 namespace {
 
@@ -214,9 +215,15 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 // 32 bytes inside the row's t_pad entries; the array is defined for token < T only, the rest is masked
-                const float* p = small + static_cast<size_t>(row_of[rb]) * sstride + tk + 8 * q;
-                sb[i][rb][0] = ANY ? load16_word(p) : load16(p);
-                sb[i][rb][1] = ANY ? load16_word(p + 4) : load16(p + 4);
+                const float* p = small + static_cast<size_t>(row_of[rb]) * sstride;
+                const int tok = tk + 8 * q;
+                if constexpr (ANY) {   // (nothing past the row's T entries is read: a kept t may end there; see convert)
+                    sb[i][rb][0] = load16_word(p + row_piece(tok, a.T));
+                    sb[i][rb][1] = load16_word(p + row_piece(tok + 4, a.T));
+                } else {
+                    sb[i][rb][0] = load16(p + tok);
+                    sb[i][rb][1] = load16(p + tok + 4);
+                }
             }
         }
     };
@@ -227,6 +234,15 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
             float m = 0.f;
 #pragma unroll
             for (int i = 0; i < G; ++i) {
+                if constexpr (ANY) {
+                    if (tk0 + 32 * i + 32 > a.T) {   // scalar: the row's last entries may have been read from its end
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const int tok = tk0 + 32 * i + 8 * q + 4 * h;
+                            sb[i][rb][h] = drop_words(sb[i][rb][h], tok - row_piece(tok, a.T));
+                        }
+                    }
+                }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float raw = __uint_as_float(sb[i][rb][e >> 2][e & 3]);
@@ -366,11 +382,15 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
             const int b = rb0 + rb < blocks ? rb0 + rb : blocks - 1, en = b / rbe, rk = (b - en * rbe) * 16 + li;
             float s = 0.f;
             const int row = en * a.r + (rk < a.r ? rk : a.r - 1);  // a rank that exists; the result of a padded rank is dropped below
-            const float* dup = a.duT + static_cast<size_t>(row) * a.du_stride + 8 * q;
-            const float* tp = a.tT + static_cast<size_t>(row) * a.t_stride + 8 * q;
-            for (int tk = tk_begin; tk < tk_end; tk += 32) {  // 32 bytes of each array per lane and step, inside t_pad entries
-                auto ld = [](const float* p) { return ANY ? load16_word(p) : load16(p); };
-                const u4 d0 = ld(dup + tk), d1 = ld(dup + tk + 4), t0 = ld(tp + tk), t1 = ld(tp + tk + 4);
+            const float* dup = a.duT + static_cast<size_t>(row) * a.du_stride;
+            const float* tp = a.tT + static_cast<size_t>(row) * a.t_stride;
+            for (int tk = tk_begin; tk < tk_end; tk += 32) {  // 32 bytes of each array per lane and step, inside t_pad entries (ANY: inside T)
+                const int tok = tk + 8 * q;
+                auto ld = [&](const float* p, int at) {
+                    if constexpr (!ANY) return load16(p + at);
+                    else return drop_words(load16_word(p + row_piece(at, a.T)), at - row_piece(at, a.T));
+                };
+                const u4 d0 = ld(dup, tok), d1 = ld(dup, tok + 4), t0 = ld(tp, tok), t1 = ld(tp, tok + 4);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float dv = __uint_as_float(e < 4 ? d0[e & 3] : d1[e & 3]), tv = __uint_as_float(e < 4 ? t0[e & 3] : t1[e & 3]);
@@ -669,7 +689,8 @@ lordba_status backward_impl(const void* x, const void* g,
     // The same kernels with element-aligned accesses take everything else that has a whole group of 8 columns on either side, with
     // a kept t whose rows reach the padded token count (us, the general kernel's time in brackets: 300 x 1000 -> 3001, r = 12 17.2
     // (362); 600 x 4728 -> 11055, r = 32 37 (1902); 4000 x 999 -> 1001, r = 16 21.6 (7178); 64 x 33 -> 17, r = 3 10.8 (30.9).
-    const bool any_ok = d_in >= 8 && d_out >= 8 && (t_saved == nullptr || t_stride >= (T + 127) / 128 * 128);
+    // (A kept t of fewer than four rows may be shorter than the four entries that they read at once.)
+    const bool any_ok = d_in >= 8 && d_out >= 8 && (t_saved == nullptr || (T >= 4 && t_stride >= (T + 127) / 128 * 128));
     // Several envelopes: with room for the partial sums of all of them (lordba_backward_multi_workspace_bytes) and at most
     // four rank blocks in all, one wgrad and one finish pass serve every envelope (x and g are read once); otherwise one
     // pass per envelope.

@@ -34,6 +34,12 @@ __device__ __forceinline__ u4 drop_halves(u4 v, int n) {
     v = (n & 1) ? one : v;
     return n < 8 ? v : u4{0u, 0u, 0u, 0u};
 }
+// Four words moved down by n (0 .. 3) places: entry e becomes entry e + n.  What comes in from above means nothing (so all of it
+// for other n).
+__device__ __forceinline__ u4 drop_words(u4 v, int n) {
+    v = (n & 2) ? u4{v[2], v[3], v[2], v[3]} : v;
+    return (n & 1) ? u4{v[1], v[2], v[3], v[3]} : v;
+}
 // Infinities and NaN become the largest finite number of their sign.  On the bits: as unsigned numbers the negative ones that are not
 // finite are the largest, as signed numbers the positive ones (two packed minima; the fp16 minimum and maximum need a third
 // instruction to quiet NaN).
