@@ -218,8 +218,8 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
                 const float* p = small + static_cast<size_t>(row_of[rb]) * sstride;
                 const int tok = tk + 8 * q;
                 if constexpr (ANY) {   // (nothing past the row's T entries is read: a kept t may end there; see convert)
-                    sb[i][rb][0] = load16_word(p + row_piece(tok, a.T));
-                    sb[i][rb][1] = load16_word(p + row_piece(tok + 4, a.T));
+                    sb[i][rb][0] = load16_word(p + row_piece(tok, a.T, row_of[rb]));
+                    sb[i][rb][1] = load16_word(p + row_piece(tok + 4, a.T, row_of[rb]));
                 } else {
                     sb[i][rb][0] = load16(p + tok);
                     sb[i][rb][1] = load16(p + tok + 4);
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
                             const int tok = tk0 + 32 * i + 8 * q + 4 * h;
-                            sb[i][rb][h] = drop_words(sb[i][rb][h], tok - row_piece(tok, a.T));
+                            sb[i][rb][h] = drop_words(sb[i][rb][h], tok - row_piece(tok, a.T, row_of[rb]));
                         }
                     }
                 }
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
                 const int tok = tk + 8 * q;
                 auto ld = [&](const float* p, int at) {
                     if constexpr (!ANY) return load16(p + at);
-                    else return drop_words(load16_word(p + row_piece(at, a.T)), at - row_piece(at, a.T));
+                    else return drop_words(load16_word(p + row_piece(at, a.T, row)), at - row_piece(at, a.T, row));
                 };
                 const u4 d0 = ld(dup, tok), d1 = ld(dup, tok + 4), t0 = ld(tp, tok), t1 = ld(tp, tok + 4);
 #pragma unroll
@@ -515,10 +515,9 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
 }
 
 // --------------------------------------------------------------------------------------- general kernel ----
-// Q, P and everything that follows from them for widths below 8 columns and for a kept t whose rows end before the padded token
-// count, on the vector ALU: one thread per column of x
-// (Q[:, i], then d_s_in[i] and d_latentA[:, i]) or of g (P[:, j], d_s_out[j], d_latentB[j, :]) walks all token rows with
-// its r sums in registers; r more threads take d_s_rank.  No partial sums, fixed order.  Slow (a column's T x r
+// Q, P and everything that follows from them for widths below 8 columns, for a kept t whose rows end before the padded token
+// count (backward_impl), on the vector ALU: one thread per column of x (Q[:, i], then d_s_in[i] and
+// d_latentA[:, i]) or of g (P[:, j], d_s_out[j], d_latentB[j, :]) walks all token rows with its r sums in registers; r more threads take d_s_rank.  No partial sums, fixed order.  Slow (a column's T x r
 // multiply-adds in one thread) but it takes every shape.
 template <int RP>
 __global__ __launch_bounds__(256) void lordba_bwd_general_kernel(BwdArgs a) {
@@ -687,10 +686,11 @@ lordba_status backward_impl(const void* x, const void* g,
                       aligned_to(packedA, 16) && aligned_to(packedAt, 16) && aligned_to(dx_base, 16) && aligned_to(dx, 16) &&
                       (t_saved == nullptr || (aligned_to(t_saved, 16) && t_stride % 4 == 0 && t_stride >= (T + 127) / 128 * 128));
     // The same kernels with element-aligned accesses take everything else that has a whole group of 8 columns on either side, with
-    // a kept t whose rows reach the padded token count (us, the general kernel's time in brackets: 300 x 1000 -> 3001, r = 12 17.2
-    // (362); 600 x 4728 -> 11055, r = 32 37 (1902); 4000 x 999 -> 1001, r = 16 21.6 (7178); 64 x 33 -> 17, r = 3 10.8 (30.9).
-    // (A kept t of fewer than four rows may be shorter than the four entries that they read at once.)
-    const bool any_ok = d_in >= 8 && d_out >= 8 && (t_saved == nullptr || (T >= 4 && t_stride >= (T + 127) / 128 * 128));
+    // a kept t whose rows reach the padded token count (us, the general kernel's time in brackets: 300 x 1000 -> 3001, r = 12 17.4
+    // (362); 600 x 4728 -> 11055, r = 32 37.8 (1902); 4000 x 999 -> 1001, r = 16 21.9 (7178); 64 x 33 -> 17, r = 3 11.1 (19.4).
+    const bool any_ok = d_in >= 8 && d_out >= 8 && (t_saved == nullptr || t_stride >= (T + 127) / 128 * 128);
+    // (One rank and fewer than four rows: row_piece counts on a second row.)
+    const bool general = !fast && (!any_ok || (r == 1 && T < 4));
     // Several envelopes: with room for the partial sums of all of them (lordba_backward_multi_workspace_bytes) and at most
     // four rank blocks in all, one wgrad and one finish pass serve every envelope (x and g are read once); otherwise one
     // pass per envelope.
@@ -795,7 +795,7 @@ lordba_status backward_impl(const void* x, const void* g,
         a.accumulate = e > 0 ? 1 : 0;
         a.ell = fused ? static_cast<int>(ell) : 1;
         a.any = fast ? 0 : 1;
-        if (!fast && !any_ok) {
+        if (general) {
             s = r <= 8 ? launch_general<8>(a, st) : r <= 16 ? launch_general<16>(a, st) : r <= 32 ? launch_general<32>(a, st) : launch_general<64>(a, st);
         } else {
             s = launch_all(a, st);

@@ -1,5 +1,5 @@
-"""The element-aligned backward kernel reads a kept t four entries at a time: every read must lie inside the row's T entries, and
-every token below T must come out of the words read (no GPU: the index function is compiled for the host)."""
+"""The element-aligned backward kernel reads a kept t four entries at a time: no read may lie outside an array that ends
+with the last row's token T - 1, and every token below T must come out of the words read (no GPU: the index function is compiled for the host)."""
 import os
 import subprocess
 
@@ -9,17 +9,18 @@ PROGRAM = r"""
 #include <cstdio>
 #include "lordba_rows.h"
 int main() {
-    for (int T = 4; T <= 700; ++T)
-        for (int tok = 0; tok < (T + 127) / 128 * 128; tok += 4) {
-            const int at = row_piece(tok, T);
-            if (at < 0 || at + 4 > T) { std::printf("T %d, token %d: reads %d .. %d\n", T, tok, at, at + 3); return 1; }
-            for (int e = 0; e < 4 && tok + e < T; ++e) {
-                const int word = tok + e - at, n = tok - at;   // the kernel moves the words down by n, which must not exceed 3
-                if (word < 0 || word > 3 || n > 3) { std::printf("T %d, token %d: word %d\n", T, tok + e, word); return 1; }
+    for (int row = 0; row < 3; ++row)
+        for (int T = 1; T <= 700; ++T) {
+            const int stride = (T + 127) / 128 * 128, end = 2 * stride + T;   // an array that ends with token T - 1 of the last row
+            for (int tok = 0; tok < stride; tok += 4) {
+                const int at = row * stride + row_piece(tok, T, row);
+                if (at < 0 || at + 4 > end) { std::printf("T %d, row %d, token %d: reads from %d\n", T, row, tok, at); return 1; }
+                for (int e = 0; e < 4 && tok + e < T; ++e) {
+                    const int n = row * stride + tok - at, word = n + e;   // the kernel moves the words down by n, which must not exceed 3
+                    if (word < 0 || word > 3 || n > 3) { std::printf("T %d, row %d, token %d: word %d\n", T, row, tok + e, word); return 1; }
+                }
             }
         }
-    for (int T = 1; T < 4; ++T)
-        if (row_piece(0, T) != 0) return 1;
     return 0;
 }
 """
