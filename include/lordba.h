@@ -253,7 +253,7 @@ lordba_status lordba_forward_multi_save_t(const void* x, const uint32_t* packedA
  * lordba_forward and lordba_forward_save_t; else LORDBA_ERR_DIM / LORDBA_ERR_ALIGN.  With d_in and d_out multiples of 32
  * and 16-byte aligned activations, scales and packed carriers the calls run fastest; other widths from 8 columns on and
  * tensors aligned to their elements take variants of the same kernels for them; fewer than 8 columns, a t_saved whose rows
- * end before T rounded up to a multiple of 128, and off the fastest path one rank and fewer than four rows a general kernel with one thread per column.  T == 0: the parameter gradients are set to zero.
+ * end before T rounded up to a multiple of 128, and off the fastest path the fewest rows at r <= 8 (r T <= 20) a general kernel with one thread per column.  T == 0: the parameter gradients are set to zero.
  * Off the fastest path infinities propagate by IEEE rules; on it a parameter gradient that depends on one may be NaN instead.
  * The call only enqueues kernels on `stream`; it never synchronises, allocates or frees.  Results are deterministic
  * (fixed summation order).  Arithmetic: fp16 inputs at their exact values, fp32 accumulation; every gradient array is

@@ -516,7 +516,7 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
 
 // --------------------------------------------------------------------------------------- general kernel ----
 // Q, P and everything that follows from them for widths below 8 columns, for a kept t whose rows end before the padded token
-// count (backward_impl), on the vector ALU: one thread per column of x (Q[:, i], then d_s_in[i] and
+// count and for the fewest rows (backward_impl), on the vector ALU: one thread per column of x (Q[:, i], then d_s_in[i] and
 // d_latentA[:, i]) or of g (P[:, j], d_s_out[j], d_latentB[j, :]) walks all token rows with its r sums in registers; r more threads take d_s_rank.  No partial sums, fixed order.  Slow (a column's T x r
 // multiply-adds in one thread) but it takes every shape.
 template <int RP>
@@ -689,8 +689,14 @@ lordba_status backward_impl(const void* x, const void* g,
     // a kept t whose rows reach the padded token count (us, the general kernel's time in brackets: 300 x 1000 -> 3001, r = 12 17.4
     // (362); 600 x 4728 -> 11055, r = 32 37.8 (1902); 4000 x 999 -> 1001, r = 16 21.9 (7178); 64 x 33 -> 17, r = 3 11.1 (19.4).
     const bool any_ok = d_in >= 8 && d_out >= 8 && (t_saved == nullptr || t_stride >= (T + 127) / 128 * 128);
-    // (One rank and fewer than four rows: row_piece counts on a second row.)
-    const bool general = !fast && (!any_ok || (r == 1 && T < 4));
+    // Not where a column's r T multiply-adds are so few that one launch which does them one after the other is over before the two
+    // launches of the matrix-core path are: the general kernel takes about 6 us and 0.25 (r = 1), 0.4 (3, 4), 0.5 (5), 0.65 (8) more
+    // per row, the others about 10.7 whatever the rows (us, matrix-core path in brackets: one row of 33 -> 17, r = 3 6.3 (10.5),
+    // 1001 -> 1003, r = 4 8.2 (10.7), 999 -> 12777, r = 8 15.7 (18.4); 5 x 101 -> 65, r = 5 9.2 (10.7) but 9 rows 11.2 (10.8); from
+    // r = 9 on it needs twice the registers and loses at one row: 513 -> 515, r = 12 13.0 (11.2)).
+    // (One rank and fewer than four rows have to stay among these: row_piece counts on a second row.)
+    const bool few = r <= 8 && r * T <= 20;
+    const bool general = !fast && (few || !any_ok);
     // Several envelopes: with room for the partial sums of all of them (lordba_backward_multi_workspace_bytes) and at most
     // four rank blocks in all, one wgrad and one finish pass serve every envelope (x and g are read once); otherwise one
     // pass per envelope.
