@@ -1023,6 +1023,8 @@ constexpr bool kTraining = LORDBA_FWD_TRAINING != 0;
 
 // Output blocks per workgroup of a call whose tiles do not fill the chip: its tiles' blocks are split over several workgroups
 // (each repeats stages 1 and 2; nothing is exchanged), at least kSplitBlocks for each, up to one workgroup per compute unit.
+// (A call that wants t alone has no blocks to share: every workgroup would do all of it.  lordba_backward without a kept t, T = 273,
+// 5120 -> 2048, r = 1 27.7 -> 23.5 us, T = 200, 4097 -> 4095, r = 32 38.5 -> 35.7.)
 // Up to 128 tiles, where that is two workgroups per tile (us, whole tiles in brackets): T = 512, 4096 -> 4096 6.1 (7.1), 4096 ->
 // 11008 7.6 (13.7), 11008 -> 4096 11.7 (13.2), r = 64 9.9 (15.0); T = 1000, 4096 -> 11008 13.1 (16.0), 4096 -> 4096 7.2 (7.6).
 // Where that leaves a wave at most one block, the variants for it (grid modes 2 and 3) make no request for a second: T = 8,
@@ -1032,7 +1034,7 @@ template <int TMV, int NW, bool ANY>
 int split_blocks(const FwdArgs& a) {
     const unsigned nblk = static_cast<unsigned>((a.d_out + 127) / 128);
     const unsigned tiles = static_cast<unsigned>((static_cast<int64_t>(a.T) + TMV - 1) / TMV);
-    if (TMV != 8 || NW < 8 || (!ANY && tiles > kFewTiles)) return static_cast<int>(nblk);
+    if (TMV != 8 || NW < 8 || (!ANY && tiles > kFewTiles) || a.y_out == nullptr) return static_cast<int>(nblk);
     // (ANY: two workgroups per compute unit where a workgroup is mostly stage 3: 1500 rows of 1000 -> 3001 8.5 against 9.9 us; where
     // the repeated reads of x weigh as much they lose, 500 rows of 5001 -> 5001 11.6 against 9.1)
     const unsigned cap = (ANY && a.d_out >= 2 * a.d_in ? 512 : 256) / tiles;
@@ -1132,7 +1134,7 @@ lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
         if (tiles >= 128) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 1, L>(a, stream);
     }
     if constexpr (TMV == 8 && NW >= 8) {
-        if (tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {  // at most one block per wave
+        if (tiles <= kFewTiles && (a.y_out == nullptr || split_blocks<TMV, NW, false>(a) <= NW)) {  // at most one block per wave
             if (a.T < TMV) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 3, L>(a, stream);
             return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 2, L>(a, stream);
         }
