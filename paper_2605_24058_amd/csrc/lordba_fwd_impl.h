@@ -345,8 +345,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
         int j0 = b * 128 + li * 8;
         j0 = (ANY ? j0 <= d_out - 8 : j0 < d_out) ? j0 : d_out - 8;  // (ANY: a ragged last group takes the last 8 columns)
         if constexpr (BM == 0) {
-            const uint32_t w = (static_cast<uint32_t>(j0) * static_cast<uint32_t>(r)) >> 5;
-            if ((static_cast<uint32_t>(b) * 128u + 127u) * static_cast<uint32_t>(r) / 32u + NB <= words_b) {  // scalar: whole block
+            // (what is not the wave's comes from the start of the stream: past the last block it would be read word by word)
+            const uint32_t w = mine ? (static_cast<uint32_t>(j0) * static_cast<uint32_t>(r)) >> 5 : 0u;
+            if ((mine ? (static_cast<uint32_t>(b) * 128u + 127u) * static_cast<uint32_t>(r) / 32u : 0u) + NB <= words_b) {  // scalar: whole block
 #pragma unroll
                 for (int v = 0; v < RB; ++v) {
                     const u4_word g = *static_cast<const u4_word*>(static_cast<const void*>(a.pB + w + 4 * v));
@@ -481,10 +482,14 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // TR (training instantiation): t is also written, and with y_out == nullptr nothing else is computed.  The inference
     // instantiation carries none of this.
     const bool with_y = !TR || a.y_out != nullptr;  // uniform: a kernel argument
+    // Whether a wave without a block for a slot leaves the request out.  Under a branch the later waits are for everything in
+    // flight, but with one block per wave, or few blocks and the bits of a general rank, the requests weigh more (T = 8, 4096 -> 4096
+    // 4.83 -> 4.67 us, r = 64 8.6 -> 8.4; training, T = 188, 1952 -> 256, r = 4, three envelopes 6.1 -> 5.3).
+    constexpr bool kMineOnly = ANY || ONE || (TR && L >= 3 && BM == 0);
     if (with_y) {
 #pragma unroll
         for (int slot = 0; slot < D2; ++slot)
-            if (!(ANY || ONE) || slot < my_b) issue_y(slot, slot);
+            if (!kMineOnly || slot < my_b) issue_y(slot, slot);
     }
 
     // ---------------------------------------------------------------- stage 2: reduce, scale, split -
@@ -1134,7 +1139,10 @@ lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
         if (tiles >= 128) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 1, L>(a, stream);
     }
     if constexpr (TMV == 8 && NW >= 8) {
-        if (tiles <= kFewTiles && (a.y_out == nullptr || split_blocks<TMV, NW, false>(a) <= NW)) {  // at most one block per wave
+        // At most one block per wave.  Three and four envelopes hold four blocks in flight per wave, which with the sign bits of a
+        // general rank is a lot to request for nothing: 2678 x 256 -> 256, r = 30, three envelopes 16.2 us against 9.2.
+        const bool narrow = L >= 3 && BM == 0 && (a.d_out + 127) / 128 <= NW;
+        if (narrow || (tiles <= kFewTiles && (a.y_out == nullptr || split_blocks<TMV, NW, false>(a) <= NW))) {
             if (a.T < TMV) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 3, L>(a, stream);
             return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 2, L>(a, stream);
         }
