@@ -911,6 +911,7 @@ __global__ __launch_bounds__(NW * 64, (GM == 4 && NW == 8 && L == 1 && !ANY && (
             else pass_through(first, end);
             first = skip_runs(end + 1, stride - 1);
         }
+        if constexpr (GM == 5) return;  // (a workgroup for each of up to eight runs)
         while (first <= last) {
             const int end = run_end(first), id = __builtin_amdgcn_readlane(my_id, first);
             __syncthreads();  // the previous run's last LDS reads are over
@@ -1109,6 +1110,7 @@ lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
         const bool big = tiles > kFewPoolTiles;
         b.by_xcd = big ? 1 : 0;
         b.blocks_per_wg = pool_split_blocks(a);
+        if (GM == 5 && big) return LORDBA_ERR_ALGO;  // (the dispatch sends no such call: grid mode 5 has a workgroup per run)
         grid = big ? dim3((tiles + 7u) & ~7u, 2) : dim3(tiles, TMV, (nblk + b.blocks_per_wg - 1) / b.blocks_per_wg);
     }
     hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, stream, b);
