@@ -1108,10 +1108,15 @@ lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
     }
     if constexpr (GM == 4 || GM == 5) {  // see the kernel
         const bool big = tiles > kFewPoolTiles;
+        // Workgroups that share a tile's runs: see the kernel.  Element-aligned tensors up to 1024 rows keep one per run: the general
+        // kernel that took them before has a workgroup per row (us, two per tile and the general kernel in brackets: 289 x 1353 -> 140,
+        // r = 2, every row its own adapter 6.0 (13.3, 7.1), sorted 5.1 (6.9, 7.2); 600 x 2000 -> 777, r = 8 12.1 (18.1, 14.0), sorted 7.1
+        // (9.0, 14.4)); beyond that sorted batches, which have one or two runs per tile, lose (4000 x 515 -> 517, r = 40 23.5 (19.1)).
+        const unsigned runs = !big || (ANY && tiles <= kFewTiles) ? TMV : 2;
         b.by_xcd = big ? 1 : 0;
         b.blocks_per_wg = pool_split_blocks(a);
         if (GM == 5 && big) return LORDBA_ERR_ALGO;  // (the dispatch sends no such call: grid mode 5 has a workgroup per run)
-        grid = big ? dim3((tiles + 7u) & ~7u, 2) : dim3(tiles, TMV, (nblk + b.blocks_per_wg - 1) / b.blocks_per_wg);
+        grid = big ? dim3((tiles + 7u) & ~7u, runs) : dim3(tiles, runs, (nblk + b.blocks_per_wg - 1) / b.blocks_per_wg);
     }
     hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, stream, b);
     return hipGetLastError() == hipSuccess ? LORDBA_OK : LORDBA_ERR_LAUNCH;
