@@ -1170,17 +1170,28 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
     // Wide inputs at decode sizes: all chunks of a wave in flight at once here too (up to 12288 columns; the registers are there since
     // a wave has one output block at most): the loop over groups of four exposed the memory latency once per group.  11008 -> 4096,
     // T = 8: r = 16 9.4 -> 9.0 us, r = 32 14.1 -> 11.7, r = 64 18.5 -> 17.2 (5.3 of it the vector ALU's: 11008 x 64 signs per workgroup);
-    // T = 300, r = 16 12.9 -> 10.0.
+    // T = 300, r = 16 12.9 -> 10.0.  (Wider inputs, such as 13824 columns, stay with the loop: variants with more slots were not built.)
     constexpr int kOneShot = NW == 16 ? 6 : 12;
-    if constexpr (TMV == 8 && NW >= 8 && L == 1 && !kTraining) {
-        if (per_wave <= kOneShot) {
-            const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
-            if (a.ids != nullptr) {
-                if constexpr (NW == 16 && RB == 1) {  // (two to four rank blocks on 8 waves: no gain, 2 % slower at r = 64)
-                    if (tiles <= kFewPoolTiles && pool_split_blocks(a) <= NW) return launch_mfma_gm<RB, TMV, NW, kOneShot, true, BM, 5, L>(a, stream);
-                }
-            } else if (tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
-                return launch_mfma_gm<RB, TMV, NW, kOneShot, true, BM, 2, L>(a, stream);
+    if constexpr (TMV == 8 && L == 1 && !kTraining && (NW == 16 || (NW == 8 && RB >= 3))) {  // (one and two rank blocks run on 16 waves)
+        const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
+        if (a.ids != nullptr) {
+            // (Where a run's blocks are split over workgroups: a single workgroup of at most four blocks gains nothing and loses 2 to
+            // 6 %, 64 rows, 12288 -> 256, r = 8 10.4 -> 10.9 us.  Two to four rank blocks on 8 waves: no gain, 2 % slower at r = 64.)
+            if constexpr (NW == 16 && RB == 1) {
+                const int per_wg = pool_split_blocks(a);
+                if (per_wave <= kOneShot && tiles <= kFewPoolTiles && per_wg <= NW && per_wg < (a.d_out + 127) / 128)
+                    return launch_mfma_gm<RB, TMV, NW, kOneShot, true, BM, 5, L>(a, stream);
+            }
+        } else if (per_wave <= kOneShot && tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
+            // Slots that a wave has no chunk for repeat a request, so the loop keeps the counts of which few waves have a chunk beyond
+            // whole groups of four (us, one-shot against the loop; d_out 1024: 33 chunks, T = 64, r = 48 9.2 : 8.6, 36 9.3 : 9.5, 40 10.1 :
+            // 11.0; 65 chunks, T = 8, r = 64 15.1 : 13.9, 66 15.1 : 15.4, 80 17.6 : 18.8; T = 64, r = 48 66 13.4 : 12.8, 80 15.4 : 15.5; r = 8 72
+            // 8.8 : 7.9, 80 9.4 : 9.7; d_out 4096, T = 8, r = 32 66 10.5 : 11.2).  Up to 64 chunks eight slots are enough for 8 waves (40
+            // chunks, T = 8, r = 64 11.5 us, with twelve 13.1).
+            if (nchunks > 64) {
+                if (nchunks >= (RB % 2 == 1 ? 76 : 66)) return launch_mfma_gm<RB, TMV, NW, kOneShot, true, BM, 2, L>(a, stream);
+            } else if constexpr (NW == 8) {
+                if (nchunks >= 36) return launch_mfma_gm<RB, TMV, NW, 8, true, BM, 2, L>(a, stream);
             }
         }
     }
