@@ -484,8 +484,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     const bool with_y = !TR || a.y_out != nullptr;  // uniform: a kernel argument
     // Whether a wave without a block for a slot leaves the request out.  Under a branch the later waits are for everything in
     // flight, but with one block per wave, or few blocks and the bits of a general rank, the requests weigh more (T = 8, 4096 -> 4096
-    // 4.83 -> 4.67 us, r = 64 8.6 -> 8.4; training, T = 188, 1952 -> 256, r = 4, three envelopes 6.1 -> 5.3).
-    constexpr bool kMineOnly = ANY || ONE || (TR && L >= 3 && BM == 0);
+    // 4.83 -> 4.67 us, r = 64 8.6 -> 8.4; training, T = 188, 1952 -> 256, r = 4, three envelopes 6.1 -> 5.3); not at three and four
+    // rank blocks behind at most two chunks of x per wave (T = 8, 512 -> 512, r = 64 4.9 -> 5.2).
+    constexpr bool kMineOnly = ANY || (ONE && (RB < 3 || D1 > 2)) || (TR && L >= 3 && BM == 0);
     if (with_y) {
 #pragma unroll
         for (int slot = 0; slot < D2; ++slot)
