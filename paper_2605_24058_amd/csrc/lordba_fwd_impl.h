@@ -1132,8 +1132,9 @@ lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
     const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
     if (a.ids != nullptr) {
         // (two rank blocks on 16 waves would spill a few registers in the batch mode's second copy of the tile code: 8 waves)
-        // Pools of adapters with several envelopes run the 8-wave variants (one workgroup per compute unit) up to r = 32 (r = 16 with four envelopes); beyond
-        // that the registers do not hold the batch mode's two copies of the tile code, and the general kernel runs.
+        // Pools of adapters with several envelopes run the 8-wave variants (one workgroup per compute unit) up to r = 32 (r = 16 with four
+        // envelopes); beyond that the registers do not hold the batch mode's two copies of the tile code, and the element-aligned
+        // variants run (four envelopes at r > 48: the general kernel).
         if constexpr (TMV == 8 && D1 <= 4 && ((L == 1 && (NW == 8 || (NW == 16 && RB == 1))) || (L > 1 && NW == 8 && (RB == 1 || (RB == 2 && L <= 3))))) {
             if (tiles <= kFewPoolTiles && pool_split_blocks(a) <= NW) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 5, L>(a, stream);
             return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 4, L>(a, stream);
