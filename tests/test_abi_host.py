@@ -125,7 +125,7 @@ def test_backward_validation_needs_no_device(lib):
     T, d_in, d_out, r = 4, 64, 96, 8
     need = lib.lordba_backward_workspace_bytes(T, d_in, d_out, r)
     assert need > 0 and need % 4 == 0
-    assert lib.lordba_backward_workspace_bytes(T, 72, d_out, r) > 0           # any width (the general kernel takes odd ones)
+    assert lib.lordba_backward_workspace_bytes(T, 72, d_out, r) > 0           # any width
     assert lib.lordba_backward_workspace_bytes(T, 0, d_out, r) == 0 and lib.lordba_backward_workspace_bytes(T, d_in, (1 << 24) + 1, r) == 0
     assert lib.lordba_backward_workspace_bytes(T, d_in, d_out, 0) == 0
     assert lib.lordba_backward_workspace_bytes(0, d_in, d_out, r) > 0

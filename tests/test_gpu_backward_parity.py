@@ -126,7 +126,7 @@ SHAPES = [
     (33, 512, 1024, 64),
     (130, 32, 96, 5),         # the smallest widths, a rank that is not a multiple of 8
     (519, 2048, 1536, 16),    # several 32-row steps per wave
-    # widths that are no multiples of 32: the general (vector ALU) kernel, as in the forward pass
+    # widths that are no multiples of 32: the element-aligned variants, as in the forward pass
     (7, 100, 60, 5),
     (9, 100, 36, 5),
     (50, 33, 17, 3),
@@ -192,6 +192,46 @@ def test_odd_widths(torch_cuda, shape):
     check(torch_cuda, inputs.make_backward_inputs(27, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
 
 
+def lifted(d):
+    """With a handful of columns the branch's share of dx alone would land among the subnormals of fp16: lift it out."""
+    d["s_in"] = (d["s_in"].astype(np.float32) * 2.0 ** 8).astype(np.float16)
+    return d
+
+
+# The general kernel: widths below 8 columns on either side at every padded rank (8, 16, 32, 64), and the fewest rows of other
+# odd widths at r <= 8 (r T <= 20) with the shapes just beyond, which the element-aligned kernels take
+@pytest.mark.parametrize("shape", [(33, 5, 7, 3), (70, 6, 100, 8), (33, 7, 40, 16), (45, 100, 4, 24), (20, 6, 40, 64),
+                                   (1, 33, 17, 3), (5, 101, 65, 4), (4, 101, 65, 5), (2, 513, 35, 8), (20, 9, 11, 1), (21, 9, 11, 1),
+                                   (3, 513, 35, 8), (1, 40, 33, 12)], ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_narrow_widths_and_few_rows(torch_cuda, shape):
+    T, d_in, d_out, r = shape
+    check(torch_cuda, lifted(inputs.make_backward_inputs(28, T, d_in, d_out, r)), "T%d_%dx%d_r%d" % shape)
+
+
+# A kept t whose rows end with token T - 1 sends odd and even widths to the general kernel; with rows of the padded token count
+# it is read four entries at a time by the element-aligned kernels, below four rows from before a row's start
+@pytest.mark.parametrize("shape", [(37, 256, 96, 8), (130, 57, 40, 8), (45, 64, 96, 32), (37, 130, 57, 33), (50, 96, 64, 64),
+                                   (1, 57, 33, 12), (2, 130, 40, 50), (3, 57, 33, 9), (4, 57, 33, 6), (127, 57, 33, 2), (129, 33, 57, 17)],
+                         ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_kept_t_by_either_stride(torch_cuda, shape):
+    torch = torch_cuda
+    T, d_in, d_out, r = shape
+    d = lifted(inputs.make_backward_inputs(29, T, d_in, d_out, r))
+    want = oracle_backward(d)
+    cu = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    w = lambda a: cu(a.view(np.int32))
+    pA, pB = map(w, binding.lordba_pack_signs(d["signsA"], d["signsB"]))
+    pAt, pBt = map(w, binding.lordba_pack_transposed(d["signsA"], d["signsB"]))
+    scales = [cu(d[k]) for k in ("s_in", "s_rank", "s_out")]
+    for stride in (T, binding.saved_t_stride(T)):
+        t = torch.full((r, stride), float("nan"), dtype=torch.float32, device="cuda:0")
+        binding.lordba_forward_save_t(cu(d["x"]), pA, pB, *scales, t_out=t)
+        out = binding.lordba_backward(cu(d["x"]), cu(d["g"]), pA, pAt, pBt, *scales, cu(d["latA"]), cu(d["latB"]), KAPPA,
+                                      dx_base=cu(d["dx_base"]), t_saved=t)
+        torch.cuda.synchronize()
+        compare({k: v.cpu().numpy() for k, v in out.items()}, want, "T%d_%dx%d_r%d" % shape + " stride %d" % stride)
+
+
 @pytest.mark.parametrize("kappa", [0.0, 1.0, 25.0, 400.0])
 def test_temperatures(torch_cuda, kappa):
     d = inputs.make_backward_inputs(26, 50, 512, 512, 8)
@@ -234,7 +274,7 @@ def test_deterministic_and_workspace_reuse(torch_cuda):
 @pytest.mark.parametrize("shape", [(9, 100, 36, 5), (3, 513, 77, 16), (3, 512, 384, 16), (20, 4096, 4096, 64)],
                          ids=lambda s: "T%d_%dx%d_r%d" % s)
 def test_forward_that_keeps_t_other_kernels(torch_cuda, shape):
-    """The same export through the general kernel (unaligned widths) and through the small-T grid modes (a single partial
+    """The same export through the element-aligned kernel (unaligned widths) and through the small-T grid modes (a single partial
     tile; a few tiles whose output blocks are split over workgroups, each of which writes the same t)."""
     torch = torch_cuda
     T, d_in, d_out, r = shape
@@ -282,10 +322,10 @@ def test_forward_that_keeps_t(torch_cuda, shape):
         assert np.array_equal(a[k], b[k]), k
 
 
-def test_unaligned_tensors_and_any_kept_t_take_the_general_kernel(torch_cuda):
+def test_unaligned_tensors_and_any_kept_t(torch_cuda):
     """Widths that would fit the matrix-core kernels, but x starts 2 bytes past a 16-byte boundary, or the kept t has a row
-    stride of exactly T (no multiple of 4): the call is accepted (as lordba_forward accepts such tensors) and takes the
-    general kernel; same bar against the oracle."""
+    stride of exactly T (no multiple of 4): the call is accepted (as lordba_forward accepts such tensors); the first takes the
+    element-aligned kernels, the second the general one; same bar against the oracle."""
     torch = torch_cuda
     T, d_in, d_out, r = 37, 256, 384, 16
     d = inputs.make_backward_inputs(38, T, d_in, d_out, r)
@@ -374,7 +414,8 @@ def test_frozen_carriers_scale_gradients_only(torch_cuda):
 
 
 @pytest.mark.parametrize("case", [(2, 203, 1056, 2080, 16), (3, 70, 1024, 768, 32), (4, 45, 512, 640, 8), (2, 4100, 256, 384, 16),
-                                  (1, 37, 512, 512, 16), (3, 21, 100, 60, 5), (4, 33, 72, 200, 16)],   # the last two: general kernel
+                                  (1, 37, 512, 512, 16), (3, 21, 100, 60, 5), (4, 33, 72, 200, 16),   # (the last two: element-aligned kernels)
+                                  (2, 33, 6, 600, 24), (3, 4, 340, 90, 5)],   # (general kernel)
                          ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
 def test_several_envelopes(torch_cuda, case):
     """lordba_backward_multi against the oracle: per-envelope scale gradients (whole vector each), dx per token row (as
@@ -497,7 +538,7 @@ def test_argument_errors(torch_cuda):
     with pytest.raises(binding.LordbaError) as e:
         gpu_backward(torch, d, ws=new_workspace(torch, need), ws_bytes=need - 16)
     assert e.value.status == 9
-    assert binding.lordba_backward_workspace_bytes(16, 250, 256, 8) > 0       # any width (general kernel)
+    assert binding.lordba_backward_workspace_bytes(16, 250, 256, 8) > 0       # any width
     assert binding.lordba_backward_workspace_bytes(16, 0, 256, 8) == 0
     assert binding.lordba_backward_workspace_bytes(16, 256, 256, 65) == 0
 

@@ -83,8 +83,8 @@ CASES = [
     (29, 512, 256, 32, 4, "decode"),            # two rank blocks
     (26, 256, 512, 64, 3, "segments"),          # four rank blocks: 8 waves
     (45, 256, 384, 12, 4, "mixed"),             # generic carrier fetch; 384 * 12 is a multiple of 128
-    (30, 160, 136, 16, 3, "segments"),          # pool rows of sign(B) not 16-byte aligned: general kernel
-    (9, 33, 17, 3, 2, "decode"),                # nothing aligned: general kernel
+    (30, 160, 136, 16, 3, "segments"),          # pool rows of sign(B) not 16-byte aligned: element-aligned kernel
+    (9, 33, 17, 3, 2, "decode"),                # nothing aligned: element-aligned kernel
     (1, 4096, 4096, 16, 2, "segments"),
     (8, 2048, 1024, 16, 8, "decode"),
     # more than 32 tiles: two 8-wave workgroups per tile share its runs (the second and later runs of a workgroup go through
@@ -250,10 +250,10 @@ MULTI_CASES = [
     (40, 256, 256, 16, 40, 4, "decode"),         # every row its own adapter
     (33, 640, 384, 8, 3, 2, "segments"),         # r = 8
     (29, 512, 256, 32, 4, 3, "decode"),          # two rank blocks
-    (27, 512, 256, 32, 4, 4, "decode"),          # two rank blocks with four envelopes: general kernel
-    (26, 256, 512, 64, 3, 2, "segments"),        # four rank blocks: general kernel
+    (27, 512, 256, 32, 4, 4, "decode"),          # two rank blocks with four envelopes: element-aligned kernel
+    (26, 256, 512, 64, 3, 2, "segments"),        # four rank blocks: element-aligned kernel
     (45, 256, 384, 12, 4, 2, "mixed"),           # generic carrier fetch
-    (9, 33, 17, 3, 2, 3, "decode"),              # nothing aligned: general kernel
+    (9, 33, 17, 3, 2, 3, "decode"),              # nothing aligned: element-aligned kernel
     (301, 512, 640, 16, 9, 2, "decode"),         # more than 32 tiles: two workgroups per tile, looped later runs
     (333, 384, 512, 16, 6, 4, "mixed"),
     (290, 8192, 384, 16, 3, 3, "segments"),      # looped x pipeline

@@ -99,7 +99,7 @@ SMALL = [
     (inputs.Shape("T31_512x640_r64", 31, 512, 640, 64), 2),
     (inputs.Shape("T12_2048x2048_r7", 12, 2048, 2048, 7), 2),
     (inputs.Shape("T20_4096x1024_r16", 20, 4096, 1024, 16), 4),     # looped stage 1 with four envelopes
-    (inputs.Shape("odd_T5_33x17_r3", 5, 33, 17, 3), 2),             # general kernel only
+    (inputs.Shape("odd_T5_33x17_r3", 5, 33, 17, 3), 2),             # element-aligned kernel
     (inputs.Shape("odd_T4_40x36_r9", 4, 40, 36, 9), 3),
     (inputs.Shape("odd_T3_1x1_r1", 3, 1, 1, 1), 4),
 ]

@@ -152,16 +152,16 @@ def test_tall_batches_every_workgroup_shape(torch_cuda, sh):
             assert e.status == 8 and algo in A_VARIANTS, (algo, e.status)
 
 
-GENERAL_ONLY = [
-    inputs.Shape("odd_T5_33x17_r3", 5, 33, 17, 3),         # nothing aligned: general kernel, scalar path
+UNALIGNED = [
+    inputs.Shape("odd_T5_33x17_r3", 5, 33, 17, 3),         # nothing aligned: element-aligned kernel; general kernel, scalar path
     inputs.Shape("odd_T7_100x60_r5", 7, 100, 60, 5),
-    inputs.Shape("odd_T3_1x1_r1", 3, 1, 1, 1),
+    inputs.Shape("odd_T3_1x1_r1", 3, 1, 1, 1),             # fewer than 8 columns: general kernel in both
     inputs.Shape("odd_T4_40x36_r9", 4, 40, 36, 9),          # d_in % 8 == 0 but not % 32: vector x path of the general kernel
 ]
 
 
-@pytest.mark.parametrize("sh", GENERAL_ONLY, ids=lambda s: s.name)
-def test_unaligned_shapes_take_the_general_kernel(torch_cuda, sh):
+@pytest.mark.parametrize("sh", UNALIGNED, ids=lambda s: s.name)
+def test_unaligned_shapes(torch_cuda, sh):
     d = inputs.make_inputs_for(sh, 7)
     # with so few input channels the branch alone (~1e-4) would land in the fp16 subnormal range, where the
     # output format itself cannot hold 1e-3 relative accuracy: lift it into the normal range
