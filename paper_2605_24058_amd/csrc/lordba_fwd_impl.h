@@ -1148,9 +1148,10 @@ lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
         if (tiles >= 128) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 1, L>(a, stream);
     }
     if constexpr (TMV == 8 && NW >= 8) {
-        // At most one block per wave.  Three and four envelopes hold four blocks in flight per wave, which with the sign bits of a
-        // general rank is a lot to request for nothing: 2678 x 256 -> 256, r = 30, three envelopes 16.2 us against 9.2.
-        const bool narrow = L >= 3 && BM == 0 && (a.d_out + 127) / 128 <= NW;
+        // At most one block per wave.  Several envelopes hold two to four blocks in flight per wave, which with the sign bits of a general
+        // rank is a lot to request for nothing (us, against the variants for any number of blocks: 2558 x 1024 -> 128, r = 2, two
+        // envelopes 8.0 : 9.6; 1100 x 512 -> 512, r = 12 5.3 : 5.8; 2678 x 256 -> 256, r = 30, three 9.1 : 11.3).
+        const bool narrow = L >= 2 && BM == 0 && (a.d_out + 127) / 128 <= NW;
         if (narrow || (tiles <= kFewTiles && (a.y_out == nullptr || split_blocks<TMV, NW, false>(a) <= NW))) {
             if (a.T < TMV) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 3, L>(a, stream);
             return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 2, L>(a, stream);
