@@ -52,7 +52,7 @@ struct BwdPlan {
     int t_pad;       // token rows padded to a multiple of 128 (whole groups of steps of the wgrad kernel, whole 16-byte pieces of t and du)
     int nbx, nbg;    // 128-column blocks of d_in and of d_out
     int dcols;       // columns of one partial-sum plane: (nbx + nbg) * 128
-    int tw;          // token rows per wave of the wgrad kernel (multiple of 128)
+    int tw;          // token rows per wave of the wgrad kernel (a multiple of 32, or of 64: see group_rows)
     int splits;      // workgroups along the token axis of the wgrad kernel
     int waves;       // waves per workgroup of the wgrad kernel: 4, or 8 on short batches with one rank block (see make_plan)
     // workspace layout, in 4-byte words
@@ -438,7 +438,8 @@ __device__ __forceinline__ float smooth_sign_factor(float latent, float kappa) {
 // One workgroup per group of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out, d_latentB), plus one for
 // d_s_rank.  Thread (c, kq) takes column c of the group and ranks kq, kq + KQ, ...; every sum has a fixed order.  KQ is the
 // padded rank up to 32: a thread then has one or two dependent rounds of requests instead of r / 8 (the whole backward call at
-// T = 512, 4096 -> 4096, r = 16 18.7 -> 16.5 us; T = 2048, r = 64 54.1 -> 47.7).
+// T = 512, 4096 -> 4096, r = 16 18.7 -> 16.5 us; T = 2048, r = 64 54.1 -> 47.7; long batches gain too, KQ = 8 in brackets: T = 4096,
+// 4096^2, r = 16 37.4 (38.3), r = 32 47.6 (49.6); T = 8192, 5120^2 83.7 (84.5), r = 64 136 (140), 13824 -> 5120 165.0 (165.7)).
 template <int KQ, bool ANY>
 __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
     constexpr int NT = 32 * KQ;

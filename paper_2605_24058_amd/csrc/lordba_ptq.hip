@@ -9,8 +9,8 @@
 //     side 2 (columns j of U2, factor rows b*_j, scale gamma): S2 = sum_j gamma_j^2 v_j v_j^T,        K2 = sum_j gamma_j v_j b*_j^T
 // e.g. the Tikhonov step of row i of U1 is (alpha_i^2 (beta beta^T o S2) + rho_1 I) u = alpha_i beta o (K2 a*_i) + rho_1 (M1 - Y1)_i.
 // The two sides are mirror images (the transposed target swaps them), so one kernel serves both.  U2 is held transposed,
-// [M, R] row-major, which is also the layout of S_B.  All arithmetic is fp64; sums run in a fixed order (no atomics), so
-// a call is reproducible bit for bit.
+// [M, R] row-major, which is also the layout of S_B.  All arithmetic is fp64; sums run in a fixed order (atomics only
+// publish shares and count arrivals), so a call is reproducible bit for bit.
 //
 // Each row kernel works on blocks of 32 rows and ends by writing its block's share of its side's Gram pair.  The last block of a
 // group of 16 to do so adds the group's shares up, and the readers add up to 16 such sums (each workgroup of a row kernel
@@ -182,8 +182,8 @@ extern __shared__ double lds[];
 // tot[side][o] = sum over the blocks of part[side][b][o], o < count: 64 outputs per workgroup of 256 threads.  Wave w adds
 // up the shares b = w, w + 4, w + 8, ... (32 loads in flight per thread), and the four partial sums are added in the
 // order of w: a fixed order, whatever the timing.
-__global__ __launch_bounds__(256) void lordba_ptq_totals_kernel(PtqArgs a, int side, int count, int always) {
-    if (!always && a.ctrl[kDone] != 0.0) return;
+__global__ __launch_bounds__(256) void lordba_ptq_totals_kernel(PtqArgs a, int side, int count) {
+    if (a.ctrl[kDone] != 0.0) return;
     __shared__ double partial[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int o = blockIdx.x * 64 + lane;
@@ -208,8 +208,10 @@ __global__ __launch_bounds__(256) void lordba_ptq_totals_kernel(PtqArgs a, int s
 }
 
 // To be called by all threads of a block after its own published stores: true in every thread of the block that is the n-th to
-// arrive at `counter` in this launch.  Every wave waits for its own stores first (the wait makes them complete, at the agent's
-// point of coherence, before the barrier and hence before the block's arrival is counted); nobody waits for another block.
+// arrive at `counter` in this launch.  Every wave waits for its own stores first, so that they are complete before the barrier
+// and hence before the block's arrival is counted; nobody waits for another block.  That this orders the shares before the
+// count is a rule of the hardware, not of the language, in which relaxed atomics order nothing: on gfx950 an agent-scope store
+// counts in vmcnt until it is complete at the agent's point of coherence, and agent-scope loads read there.
 __device__ inline bool arrive_last(uint32_t* counter, int n) {
     __shared__ int last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1137,9 +1139,9 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     const int count = iR * iR + iR * ir0;
     // (beyond 8192 rows the readers would add up too many sums each; beyond 1024 values a share is more than one block's work)
     for (int s = 0; s < 2; ++s) a.grouped[s] = (a.nb[s] + kGroup - 1) / kGroup <= kMaxGroups && count <= 1024 ? 1 : 0;
-    auto totals = [&](int side, int n, int always) {
+    auto totals = [&](int side, int n) {
         if (a.grouped[side]) return;
-        hipLaunchKernelGGL(lordba_ptq_totals_kernel, dim3((n + 63) / 64), dim3(256), 0, stream, a, side, n, always);
+        hipLaunchKernelGGL(lordba_ptq_totals_kernel, dim3((n + 63) / 64), dim3(256), 0, stream, a, side, n);
     };
     if (t_begin == 0) {   // the warm start; a later call continues from the state the workspace holds
         hipLaunchKernelGGL(lordba_ptq_fill_kernel, dim3((kInfoHead + K + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, info,
@@ -1177,11 +1179,11 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
         hipLaunchKernelGGL(lordba_ptq_svd_kernel, dim3(1), dim3(64), lds_svd, stream, a, Rfinal[0], Rfinal[1]);
         hipLaunchKernelGGL(lordba_ptq_init_rows_kernel, dim3(nb01), dim3(kThreads), lds_init, stream, a);
         launched();
-        totals(1, count, 0);
+        totals(1, count);
         hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[0]), dim3(kRowThreads), lds_fixed, stream, a, 0, -1);
-        totals(0, count, 0);
+        totals(0, count);
         hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[1]), dim3(kRowThreads), lds_fixed, stream, a, 1, -1);
-        totals(1, count, 0);
+        totals(1, count);
         launched();
         if (launch_failed) return LORDBA_ERR_LAUNCH;
     }
@@ -1191,12 +1193,12 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
                 hipLaunchKernelGGL(lordba_ptq_ustep_kernel<16>, dim3(a.nb[side]), dim3(kRowThreads), lds_rows, stream, a, side, solve_waves);
             else
                 hipLaunchKernelGGL(lordba_ptq_ustep_kernel<32>, dim3(a.nb[side]), dim3(ustep_threads), lds_rows, stream, a, side, solve_waves);
-            totals(side, count + 2, 0);
+            totals(side, count + 2);
         }
         hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[0]), dim3(kRowThreads), lds_scale, stream, a, 0, t);
-        totals(0, count, 0);
+        totals(0, count);
         hipLaunchKernelGGL(lordba_ptq_scale_kernel, dim3(a.nb[1]), dim3(kRowThreads), lds_scale, stream, a, 1, t);
-        totals(1, count, 0);
+        totals(1, count);
         if (!a.grouped[1]) hipLaunchKernelGGL(lordba_ptq_beta_kernel, dim3(1), dim3(kRowThreads), lds_beta, stream, a, t);
         launched();
         if (launch_failed) return LORDBA_ERR_LAUNCH;
