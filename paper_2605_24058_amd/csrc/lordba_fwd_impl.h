@@ -485,8 +485,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // Whether a wave without a block for a slot leaves the request out.  Under a branch the later waits are for everything in
     // flight, but with one block per wave, or few blocks and the bits of a general rank, the requests weigh more (T = 8, 4096 -> 4096
     // 4.83 -> 4.67 us, r = 64 8.6 -> 8.4; training, T = 188, 1952 -> 256, r = 4, three envelopes 6.1 -> 5.3); not at three and four
-    // rank blocks behind at most two chunks of x per wave (T = 8, 512 -> 512, r = 64 4.9 -> 5.2).
-    constexpr bool kMineOnly = ANY || (ONE && (RB < 3 || D1 > 2)) || (TR && L >= 3 && BM == 0);
+    // rank blocks behind at most two chunks of x per wave (T = 8, 512 -> 512, r = 64 4.9 -> 5.2), unless the rank is a general one
+    // (T = 300, 128 -> 128, r = 50 5.2 -> 5.0).
+    constexpr bool kMineOnly = ANY || (ONE && (RB < 3 || D1 > 2 || BM == 0)) || (TR && L >= 3 && BM == 0);
     if (with_y) {
 #pragma unroll
         for (int slot = 0; slot < D2; ++slot)
@@ -1148,10 +1149,12 @@ lordba_status launch_mfma(const FwdArgs& a, hipStream_t stream) {
         if (tiles >= 128) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 1, L>(a, stream);
     }
     if constexpr (TMV == 8 && NW >= 8) {
-        // At most one block per wave.  Several envelopes hold two to four blocks in flight per wave, which with the sign bits of a general
-        // rank is a lot to request for nothing (us, against the variants for any number of blocks: 2558 x 1024 -> 128, r = 2, two
-        // envelopes 8.0 : 9.6; 1100 x 512 -> 512, r = 12 5.3 : 5.8; 2678 x 256 -> 256, r = 30, three 9.1 : 11.3).
-        const bool narrow = L >= 2 && BM == 0 && (a.d_out + 127) / 128 <= NW;
+        // At most one block per wave, also where the tiles are not few: at a general rank, whose sign bits are requested with each block,
+        // the variants for any number of blocks request a lot for nothing there (us, those in brackets, in square ones before the
+        // bits were requested ahead: 2558 x 128 -> 128, r = 50 6.2 (9.6) [10.3]; 3500 x 256 -> 256, r = 30 5.4 (7.4) [6.3]; 2558 x 4096 ->
+        // 1024, r = 40 13.1 (17.5) [23.2]; two envelopes, 2558 x 1024 -> 128, r = 2 8.0 (9.6) [9.3]; three, 2678 x 256 -> 256, r = 30 9.1
+        // (11.3) [11.1]).
+        const bool narrow = BM == 0 && (a.d_out + 127) / 128 <= NW;
         if (narrow || (tiles <= kFewTiles && (a.y_out == nullptr || split_blocks<TMV, NW, false>(a) <= NW))) {
             if (a.T < TMV) return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 3, L>(a, stream);
             return launch_mfma_gm<RB, TMV, NW, D1, OS, BM, 2, L>(a, stream);

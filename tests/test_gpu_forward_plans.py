@@ -48,6 +48,8 @@ PLANS = [
     (601, 512, 11008, 16, 1), (1000, 512, 4224, 64, 1), (601, 96, 11008, 33, 1), (1021, 160, 4168, 24, 1), (1029, 512, 4224, 64, 1),
     # fewer blocks than waves at three and four rank blocks behind few chunks
     (8, 512, 512, 64, 1), (3, 128, 5120, 48, 1), (16, 256, 1032, 33, 1), (1, 64, 128, 64, 1),
+    # a general rank on more than 128 tiles: up to one block per wave (16 and 8 waves), and one block more
+    (1031, 96, 2048, 2, 1), (1030, 96, 2056, 20, 1), (2055, 160, 1024, 30, 1), (2051, 160, 1032, 50, 1), (5001, 96, 1000, 12, 1),
     # several envelopes at a general rank: up to one block per wave, and one block more
     (1100, 256, 256, 30, 3), (1031, 96, 1024, 2, 4), (1029, 160, 1032, 20, 3), (5, 160, 136, 30, 4), (1027, 64, 72, 1, 3), (300, 256, 2056, 44, 3),
 ]
