@@ -1045,7 +1045,10 @@ int split_blocks(const FwdArgs& a) {
     if (TMV != 8 || NW < 8 || (!ANY && tiles > kFewTiles) || a.y_out == nullptr) return static_cast<int>(nblk);
     // (ANY: two workgroups per compute unit where a workgroup is mostly stage 3: 1500 rows of 1000 -> 3001 8.5 against 9.9 us; where
     // the repeated reads of x weigh as much they lose, 500 rows of 5001 -> 5001 11.6 against 9.1)
-    const unsigned cap = (ANY && a.d_out >= 2 * a.d_in ? 512 : 256) / tiles;
+    // The workgroups of a tile share an XCD of 32 compute units, which has every eighth tile: counted by the padded extent, or the first
+    // XCDs get a second round (81 tiles, 3 workgroups each: 33 on the first; 643 rows of 4096 -> 2048 8.4 us, with 2 each 5.9;
+    // 400 of 4096 -> 4096 9.1 and 5.8; one row of 4096 -> 28672, 56 and 32 workgroups on one XCD, 7.8 and 4.8).
+    const unsigned cap = (ANY && a.d_out >= 2 * a.d_in ? 512 : 256) / ((tiles + 7u) & ~7u);
     unsigned split = (nblk + kSplitBlocks - 1) / kSplitBlocks;
     split = split < cap ? split : cap;
     split = split < 1 ? 1 : split;

@@ -45,6 +45,7 @@ PLANS = [
     # six slots on 16 waves, and the loop
     (9, 9760, 640, 16, 1), (300, 11008, 512, 12, 1), (9, 8480, 512, 32, 1), (9, 9600, 512, 16, 1), (9, 8352, 512, 8, 1),
     # a tile's blocks split over workgroups with more than one block per wave, on 16 and on 8 waves; all of them in one workgroup
+    (264, 96, 11008, 16, 1), (401, 160, 4096, 16, 1), (643, 96, 2048, 16, 1), (1, 160, 28680, 16, 1),
     (601, 512, 11008, 16, 1), (1000, 512, 4224, 64, 1), (601, 96, 11008, 33, 1), (1021, 160, 4168, 24, 1), (1029, 512, 4224, 64, 1),
     # fewer blocks than waves at three and four rank blocks behind few chunks
     (8, 512, 512, 64, 1), (3, 128, 5120, 48, 1), (16, 256, 1032, 33, 1), (1, 64, 128, 64, 1),
