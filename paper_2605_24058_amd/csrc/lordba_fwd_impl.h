@@ -107,8 +107,8 @@ __host__ __device__ constexpr size_t mfma_lds_bytes(int RB, int TMV, int NW, int
 //      loads), 2 = r is 8 (one aligned 8-byte load, one byte per column), 0 = any r (two dwords per operand)
 // GM   grid mode.  1 (grids that fill the chip): the waves that do not run stage 2 build their first block's sign
 //      operands during stage 2 instead of before it.  0: the same without that; gridDim.y workgroups may share a token tile and
-//      split its output blocks; the x extent of such a grid is padded to a multiple of 8 and padding workgroups exit.  2 (tiles
-//      that do not fill the chip): as 0, with at most one output block per wave, so that no request is made for a second one.
+//      split its output blocks; the x extent of such a grid is padded to a multiple of 8 and padding workgroups exit.  2 (few
+//      tiles, or narrow outputs at a general rank): as 0, with at most one output block per wave and no request for a second one.
 //      3 (fewer token rows than a tile): as 2, and rows past T are not requested at all.  4: multi-adapter batch, the
 //      gridDim.y workgroups of a tile share its runs of rows that use the same adapter (rows outside a run are not
 //      requested), gridDim.z workgroups share a run's output blocks.  5: as 4, with at most one output block per wave.
