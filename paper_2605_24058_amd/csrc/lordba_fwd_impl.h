@@ -486,8 +486,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // flight, but with one block per wave, or few blocks and the bits of a general rank, the requests weigh more (T = 8, 4096 -> 4096
     // 4.83 -> 4.67 us, r = 64 8.6 -> 8.4; training, T = 188, 1952 -> 256, r = 4, three envelopes 6.1 -> 5.3); not at three and four
     // rank blocks behind at most two chunks of x per wave (T = 8, 512 -> 512, r = 64 4.9 -> 5.2), unless the rank is a general one
-    // (T = 300, 128 -> 128, r = 50 5.2 -> 5.0) or t is kept (T = 2, 1024 -> 5120, r = 64 6.5 -> 5.9).
-    constexpr bool kMineOnly = ANY || (ONE && (RB < 3 || D1 > 2 || BM == 0 || TR)) || (TR && L >= 3 && BM == 0);
+    // (T = 300, 128 -> 128, r = 50 5.2 -> 5.0), t is kept (T = 2, 1024 -> 5120, r = 64 6.5 -> 5.9) or
+    // there are several envelopes (T = 168, 1024 -> 4096, r = 64, two 7.1 -> 6.9).
+    constexpr bool kMineOnly = ANY || (ONE && (RB < 3 || D1 > 2 || BM == 0 || TR || L > 1)) || (TR && L >= 3 && BM == 0);
     if (with_y) {
 #pragma unroll
         for (int slot = 0; slot < D2; ++slot)
