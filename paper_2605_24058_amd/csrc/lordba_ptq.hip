@@ -568,7 +568,77 @@ __device__ inline void factor_products(const RowLds& s, int R, int r0) {
     }
 }
 
-// Solves H x = b for a symmetric positive definite RMAX x RMAX matrix by the RMAX lanes of one group (the wave's lanes
+// The value of lane K of each row of 16 lanes, in every lane of the row.
+template <int K>
+__device__ inline double row_lane(double v) {
+    constexpr int ctrl = 0x150 + K;   // row_newbcast:K
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xf, 0xf, false));
+}
+// a += (lane K's a) * f for one, two or four numbers: the 64-bit multiply-add takes its first operand from another lane
+// of the row by itself, where the compiler would move both halves first.  The wait states are those between any vector instruction
+// and one that reads its result across lanes; the compiler sees the block as one instruction and adds none.
+template <int K>
+__device__ inline void fma_own_row_lane(double& a, double f) {
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%c2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(f), "n"(K));
+}
+template <int K>
+__device__ inline void fma_own_row_lane(double& a, double& b, double f) {
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf"
+        : "+&v"(a), "+&v"(b) : "v"(f), "n"(K));
+}
+template <int K>
+__device__ inline void fma_own_row_lane(double& a, double& b, double& c, double& d, double f) {
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf"
+        : "+&v"(a), "+&v"(b), "+&v"(c), "+&v"(d) : "v"(f), "n"(K));
+}
+
+// Solves H x = b for a symmetric positive definite 16 x 16 matrix by the 16 lanes of one row of the wave (a smaller system is
+// passed padded with an identity block; R says how many pivots are its own).  Lane l passes column l of H and entry l of b, and
+// receives entry l of x.  Right-looking L D L^T factorisation with the columns in registers and no LDS: lane k's column reaches
+// the others inside the multiply-add, and entry l of it, which scales lane l's update, is by symmetry lane l's own entry k.  The
+// right-hand side rides along, which makes the forward substitution part of the factorisation.  No square root, one reciprocal per
+// column (hardware estimate and two Newton steps).  Bound: sixteen dependent reciprocals and their first update.  With the columns
+// published in LDS (up to 17 reads per column, for which eight waves shared the LDS of a compute unit) a Tikhonov step of 4096 rows took
+// 5.5 us more (the sweeps of 4096^2, R = 16 as a graph 1725 against 1482 us).  Returns the smallest of the first R pivots in *min_pivot.
+template <int K>
+__device__ inline void ldlt_step(double (&col)[16], double& b, double& ipl, double& minp, int R, int l) {
+    const double pk = row_lane<K>(col[K]);
+    minp = fmin(minp, K < R ? pk : INFINITY);
+    double ipk = __builtin_amdgcn_rcp(pk);
+    ipk = fma(fma(-pk, ipk, 1.0), ipk, ipk);
+    ipk = fma(fma(-pk, ipk, 1.0), ipk, ipk);
+    ipl = (l == K) ? ipk : ipl;
+    const double f = (l > K) ? -(col[K] * ipk) : 0.0;   // -L'[l][K] for the lanes below the diagonal
+    constexpr int n = 15 - K, i1 = K + 1, i2 = i1 + (n & 1), i4 = i2 + (n & 2);
+    if constexpr ((n & 1) != 0) fma_own_row_lane<K>(col[i1], f);
+    if constexpr ((n & 2) != 0) fma_own_row_lane<K>(col[i2], col[i2 + 1], f);
+    if constexpr (n >= 4) fma_own_row_lane<K>(col[i4], col[i4 + 1], col[i4 + 2], col[i4 + 3], f);
+    if constexpr (n >= 8) fma_own_row_lane<K>(col[i4 + 4], col[i4 + 5], col[i4 + 6], col[i4 + 7], f);
+    if constexpr (n >= 12) fma_own_row_lane<K>(col[i4 + 8], col[i4 + 9], col[i4 + 10], col[i4 + 11], f);
+    fma_own_row_lane<K>(b, f);
+    if constexpr (K < 15) ldlt_step<K + 1>(col, b, ipl, minp, R, l);
+}
+template <int K>
+__device__ inline void ldlt_back(const double (&col)[16], double& b, double ipl, int l) {
+    const double f = (l < K) ? -(col[K] * ipl) : 0.0;   // -L'[K][l]: lane l's own column, entry K, over its pivot
+    fma_own_row_lane<K>(b, f);
+    if constexpr (K > 1) ldlt_back<K - 1>(col, b, ipl, l);
+}
+__device__ inline double row_ldlt_solve(double (&col)[16], double b, int R, int l, double* min_pivot) {
+    double minp = INFINITY, ipl = 0.0;
+    ldlt_step<0>(col, b, ipl, minp, R, l);
+    b *= ipl;   // H = L' D L'^T with D the pivots and L' unit lower triangular; b held entry l of L'^{-1} b
+    ldlt_back<15>(col, b, ipl, l);
+    *min_pivot = minp;
+    return b;
+}
+
+// The same for more than 16 lanes: an RMAX x RMAX matrix by the RMAX lanes of one group (the wave's lanes
 // base .. base + RMAX - 1; a smaller system is passed padded with an identity block, and R says how many pivots are its
 // own).  Lane l passes column l of H in col[] (entries i >= l are used) and entry l of b, and receives entry l of x.
 // Right-looking L D L^T factorisation with the columns in registers: a finished column is published once, unscaled, to
@@ -618,10 +688,8 @@ __device__ inline double group_ldlt_solve(double (&col)[RMAX], double b, double*
 
 // Eq. (u-step-1) / Eq. (u-step-2) for one side: per row, (c^2 (beta beta^T o So) + rho_k I) u = c beta o (Ko f) + rho_k (M - Y),
 // then Eq. (m-y-step) for the same row: M = sign(u + Y), Y += u - M (a pending rescaling of Y after a penalty change is
-// applied on the way).  A group of lanes solves one row: lane l keeps column l of the matrix in registers through a
-// right-looking L D L^T factorisation; a finished column is published once, unscaled, to LDS together with the
-// reciprocal of its pivot, and the other lanes fold the scaling into their updates (no square root, one reciprocal).
-// `solve_waves` of the block's waves take part (as many as the LDS holds matrices for).
+// applied on the way).  A group of lanes solves one row, lane l with column l of the matrix in registers (row_ldlt_solve,
+// group_ldlt_solve).  `solve_waves` of the block's waves take part (beyond 16 lanes as many as the LDS holds matrices for).
 template <int RMAX>  // the carrier rank is at most RMAX (16 or 32): lanes per row and length of the register-resident column; the
                      // larger one runs with half the threads per block, so that a lane may hold twice the registers
 __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lordba_ptq_ustep_kernel(PtqArgs a, int side, int solve_waves) {
@@ -648,7 +716,7 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
     const int g = lane / gs, l = lane - g * gs, base = g * gs;
     double gap = 0.0, flips = 0.0;
     if (wave < solve_waves) {
-        double* H = s.H + (wave * groups + g) * (RMAX * ld + RMAX);
+        double* H = s.H + (RMAX == 16 ? 0 : (wave * groups + g) * (RMAX * ld + RMAX));
         double* zrow = H + RMAX * ld;
         const int rows_per_pass = solve_waves * groups;
         const bool act = l < R;       // the other lanes of the group carry the identity block that pads the system
@@ -667,7 +735,8 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
                 col[i] = (act && i < R) ? own : (i == l ? 1.0 : 0.0);
             }
             double min_pivot;   // positive: the matrix is a Gram matrix plus rho_k I
-            b = group_ldlt_solve<RMAX>(col, b, H, zrow, R, l, base, &min_pivot);
+            if constexpr (RMAX == 16) b = row_ldlt_solve(col, b, R, l, &min_pivot);
+            else b = group_ldlt_solve<RMAX>(col, b, H, zrow, R, l, base, &min_pivot);
             if (act) {
                 const double x = b;
                 const double mn = (x + y_old) < 0.0 ? -1.0 : 1.0;
@@ -702,7 +771,7 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
 }
 
 // beta = pinv(G) h for a symmetric positive semidefinite R x R matrix G, by one wave (Eq. (beta-pinv)).  G [R, ld] and hv [R]
-// are in LDS and are overwritten; N2 is an LDS area of max(R ld, 16 * 17 + 16) doubles; perm [R] must hold the identity.
+// are in LDS and are overwritten; N2 is an LDS area of R ld doubles; perm [R] must hold the identity.
 // The result goes to bt [R].  A factorisation without pivoting is tried first (ranks up to 16: its columns stay in
 // registers) and kept if every pivot clears the rank tolerance 64 eps max_k G_kk; otherwise a Cholesky factorisation with
 // diagonal pivoting stops at the numerical rank: with G = L L^T, L of full column rank, pinv(G) = L (L^T L)^{-2} L^T (at
@@ -712,7 +781,7 @@ __device__ inline void beta_pinv_solve(double* G, int ld, double* hv, double* N2
     for (int m = 32; m >= 1; m >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, m, 64));
     const double tol = 64.0 * 2.220446049250313e-16 * dmax;
     // Fast path: G is positive definite whenever both sides' iterates have full column rank, so try the factorisation
-    // without pivoting first (columns in registers, N2 as its LDS area) and keep its result if every pivot clears the rank
+    // without pivoting first (columns in registers) and keep its result if every pivot clears the rank
     // tolerance; G itself is left untouched for the pivoted factorisation below.
     bool solved = false;
     double x = 0.0;
@@ -727,7 +796,7 @@ __device__ inline void beta_pinv_solve(double* G, int ld, double* hv, double* N2
             col[i] = (i < R && lg < R) ? own : (i == lg ? 1.0 : 0.0);
         }
         double min_pivot;
-        const double xf = group_ldlt_solve<16>(col, lg < R ? hv[lc] : 0.0, N2, N2 + 16 * 17, R, lg, l & ~15, &min_pivot);
+        const double xf = row_ldlt_solve(col, lg < R ? hv[lc] : 0.0, R, lg, &min_pivot);
         wave_sync();
         if (min_pivot > tol) { solved = true; x = xf; }
     }
@@ -804,9 +873,8 @@ __device__ inline void beta_update(const PtqArgs& a, int t) {
     double* P1 = lds;              // S1, K1, gap, sign changes of side 0
     double* P2 = P1 + count + 2;   // the same of side 1
     double* G = P2 + count + 2;    // [R, ld]
-    double* N2 = G + R * ld;       // [R, ld]; the unpivoted attempt uses it as its 16 x 17 area plus the 16-entry extra row
-    const int n2 = R * ld > 16 * 17 + 16 ? R * ld : 16 * 17 + 16;
-    double* hv = N2 + n2;          // [R] permuted right-hand side
+    double* N2 = G + R * ld;       // [R, ld]
+    double* hv = N2 + R * ld;      // [R] permuted right-hand side
     double* h0 = hv + R;           // [R]
     double* bt = h0 + R;           // [R] result
     int* perm = reinterpret_cast<int*>(bt + R);
@@ -923,9 +991,8 @@ __global__ __launch_bounds__(kRowThreads) void lordba_ptq_scale_kernel(PtqArgs a
 __global__ __launch_bounds__(64) void lordba_ptq_beta_solve_kernel(const double* Gin, const double* hin, double* out, int R) {
     const int ld = R + 1, l = threadIdx.x;
     double* G = lds;
-    const int n2 = R * ld > 16 * 17 + 16 ? R * ld : 16 * 17 + 16;
     double* N2 = G + R * ld;
-    double* hv = N2 + n2;
+    double* hv = N2 + R * ld;
     double* bt = hv + R;
     int* perm = reinterpret_cast<int*>(bt + R);
     for (int o = l; o < R * R; o += 64) G[(o / R) * ld + o % R] = Gin[o];
@@ -1101,12 +1168,12 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     // the Tikhonov kernel: as many waves solve rows at once as the LDS has room for their matrices (8, 4, 2 or 1); the scale
     // kernel has the same layout without the matrices
     const size_t lds_fixed = sizeof(double) * (iR * iR + iR * ir0 + iR + kRows * (ir0 + 1) + 3 * kRows * iR + kRows);
-    const size_t lds_wave = sizeof(double) * (64 / gs) * (gs * (gs + 1) + gs);   // (systems are padded to the group's 16 or 32 lanes)
+    const size_t lds_wave = iR <= 16 ? 0 : sizeof(double) * (64 / gs) * (gs * (gs + 1) + gs);   // (padded to the group's 32 lanes)
     const int ustep_threads = iR <= 16 ? kRowThreads : kRowThreads / 2;
     int solve_waves = ustep_threads / 64;
     while (solve_waves > 1 && lds_fixed + solve_waves * lds_wave > 160 * 1024) solve_waves >>= 1;
     const size_t lds_rows = lds_fixed + solve_waves * lds_wave;
-    const size_t lds_beta = sizeof(double) * (2 * (iR * iR + iR * ir0 + 2) + iR * ldR + (iR * ldR > 288 ? iR * ldR : 288) + 3 * iR) + sizeof(int) * iR;
+    const size_t lds_beta = sizeof(double) * (2 * (iR * iR + iR * ir0 + 2) + 2 * iR * ldR + 3 * iR) + sizeof(int) * iR;
     const size_t lds_scale = lds_fixed > lds_beta ? lds_fixed : lds_beta;   // (its last block may run the beta update)
     const int nb01 = a.nb[0] + a.nb[1];
 
@@ -1236,7 +1303,7 @@ extern "C" lordba_status lordba_ptq_beta_solve(const double* G, const double* h,
     const lordba_status ds = check_device();
     if (ds != LORDBA_OK) return ds;
     const int iR = static_cast<int>(R), ld = iR + 1;
-    const size_t lds_bytes = sizeof(double) * (iR * ld + (iR * ld > 288 ? iR * ld : 288) + 2 * iR) + sizeof(int) * iR;
+    const size_t lds_bytes = sizeof(double) * (2 * iR * ld + 2 * iR) + sizeof(int) * iR;
     hipLaunchKernelGGL(lordba_ptq_beta_solve_kernel, dim3(1), dim3(64), lds_bytes, static_cast<hipStream_t>(stream), G, h, beta, iR);
     return hipGetLastError() == hipSuccess ? LORDBA_OK : LORDBA_ERR_LAUNCH;
 }
