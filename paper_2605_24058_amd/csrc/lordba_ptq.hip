@@ -12,14 +12,15 @@
 // [M, R] row-major, which is also the layout of S_B.  All arithmetic is fp64; sums run in a fixed order (atomics only
 // publish shares and count arrivals), so a call is reproducible bit for bit.
 //
+// Carrier ranks up to 16 with factor ranks up to 32 make all sweeps in one launch (lordba_ptq_run.h).  The others, whose rows and Gram
+// pairs do not fit that kernel's registers and LDS, take launches per sweep:
+//
 // Each row kernel works on blocks of 32 rows and ends by writing its block's share of its side's Gram pair.  The last block of a
 // group of 16 to do so adds the group's shares up, and the readers add up to 16 such sums (each workgroup of a row kernel
 // adding up every share itself would pull them through its own compute unit's 64 B/clk path to L2, 9 us per launch).  Sides of
 // more than 256 blocks or with more than 1024 values per share leave it to a small kernel of its own.  A sweep is four
 // launches: two Tikhonov steps (each followed at once by the sign and dual update of its rows, which needs nothing else),
-// alpha, and gamma, whose last block goes on with beta and the penalty control.  Enqueued as one call of 100 sweeps the host's
-// launch rate was the limit: 4096^2, R = r0 = 16 3.73 ms with the nine launches per sweep that separate totals and beta kernels
-// take, 2.25 ms with four (as a graph 2.74 and 2.22; the sweeps that were run alone 1.67 and 1.74).  A flag in device memory
+// alpha, and gamma, whose last block goes on with beta and the penalty control.  A flag in device memory
 // ends the loop: once the sign matrices repeat, the remaining launches return at once, so the host never waits on the device
 // inside the loop (lordba_ptq_sweeps lets a caller that is willing to wait enqueue the run in pieces instead).
 #include <hip/hip_runtime.h>
@@ -38,6 +39,8 @@ constexpr int kRows = 32;      // rows of one side per workgroup
 constexpr int kThreads = 256;  // four waves: the warm-start and export kernels
 constexpr int kRowThreads = 512;  // eight waves: the kernels of a sweep
 static_assert(LORDBA_PTQ_MAX_RANK == 32, "the Tikhonov kernel is instantiated for ranks up to 16 and up to 32");
+constexpr int kSyncStride = 32;               // counters of the run kernel lie 128 bytes apart
+constexpr int kSyncWords = 6 * kSyncStride;   // next block, workgroups that have left, arrivals of the four kinds of step
 constexpr int kGroup = 16, kMaxGroups = 16;   // blocks whose shares are added up together, and groups of a side (see add_up_group)
 constexpr double kRankFloor = 1e-12;  // a singular value of the update below this fraction of the largest counts as zero
 constexpr int kInfoHead = 8;   // info[0..7]: sweeps, frozen, rho, ||T||_F^2, degenerate, reserved; then one objective per sweep
@@ -64,6 +67,7 @@ struct PtqArgs {
                          // side 1, [32] groups of side 1 (see add_up_group)
     int grouped[2];      // the shares of a side are added up in groups of blocks by the kernel that writes them; else the totals
                          // kernel does it
+    uint32_t* sync;      // counters of the run kernel, [kSyncWords], zero between launches
     double* info;
     int K;
     double tau, mu;
@@ -177,7 +181,7 @@ __device__ inline void load_factor_rows(const __half* F, int64_t n, int r0, int6
     }
 }
 
-extern __shared__ double lds[];
+extern __shared__ __align__(16) double lds[];
 
 // tot[side][o] = sum over the blocks of part[side][b][o], o < count: 64 outputs per workgroup of 256 threads.  Wave w adds
 // up the shares b = w, w + 4, w + 8, ... (32 loads in flight per thread), and the four partial sums are added in the
@@ -478,6 +482,7 @@ __global__ __launch_bounds__(64) void lordba_ptq_svd_kernel(PtqArgs a, const dou
         a.ctrl[7] = 0.0;
         for (int i = 0; i <= 2 * kMaxGroups; ++i) a.arrived[i] = 0u;
     }
+    for (int i = l; i < kSyncWords; i += 64) a.sync[i] = 0u;
     wave_sync();
     if (l < R) a.beta[l] = sig[idx[l]];
     for (int side = 0; side < 2; ++side) {
@@ -606,7 +611,8 @@ __device__ inline void fma_own_row_lane(double& a, double& b, double& c, double&
 // published in LDS (up to 17 reads per column, for which eight waves shared the LDS of a compute unit) a Tikhonov step of 4096 rows took
 // 5.5 us more (the sweeps of 4096^2, R = 16 as a graph 1725 against 1482 us).  Returns the smallest of the first R pivots in *min_pivot.
 template <int K>
-__device__ inline void ldlt_step(double (&col)[16], double& b, double& ipl, double& minp, int R, int l) {
+__device__ __forceinline__ void ldlt_step(double (&col)[16], double& b, double& ipl, double& minp, int R, int l) {
+    asm volatile("" : "+v"(l));   // (the comparisons with the lane are made where they are needed: kept, they overflow the scalar registers)
     const double pk = row_lane<K>(col[K]);
     minp = fmin(minp, K < R ? pk : INFINITY);
     double ipk = __builtin_amdgcn_rcp(pk);
@@ -624,12 +630,13 @@ __device__ inline void ldlt_step(double (&col)[16], double& b, double& ipl, doub
     if constexpr (K < 15) ldlt_step<K + 1>(col, b, ipl, minp, R, l);
 }
 template <int K>
-__device__ inline void ldlt_back(const double (&col)[16], double& b, double ipl, int l) {
+__device__ __forceinline__ void ldlt_back(const double (&col)[16], double& b, double ipl, int l) {
+    asm volatile("" : "+v"(l));
     const double f = (l < K) ? -(col[K] * ipl) : 0.0;   // -L'[K][l]: lane l's own column, entry K, over its pivot
     fma_own_row_lane<K>(b, f);
     if constexpr (K > 1) ldlt_back<K - 1>(col, b, ipl, l);
 }
-__device__ inline double row_ldlt_solve(double (&col)[16], double b, int R, int l, double* min_pivot) {
+__device__ __forceinline__ double row_ldlt_solve(double (&col)[16], double b, int R, int l, double* min_pivot) {
     double minp = INFINITY, ipl = 0.0;
     ldlt_step<0>(col, b, ipl, minp, R, l);
     b *= ipl;   // H = L' D L'^T with D the pivots and L' unit lower triangular; b held entry l of L'^{-1} b
@@ -776,7 +783,7 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
 // registers) and kept if every pivot clears the rank tolerance 64 eps max_k G_kk; otherwise a Cholesky factorisation with
 // diagonal pivoting stops at the numerical rank: with G = L L^T, L of full column rank, pinv(G) = L (L^T L)^{-2} L^T (at
 // full rank the ordinary solve).
-__device__ inline void beta_pinv_solve(double* G, int ld, double* hv, double* N2, int* perm, double* bt, int R, int l) {
+__device__ __forceinline__ void beta_pinv_solve(double* G, int ld, double* hv, double* N2, int* perm, double* bt, int R, int l) {
     double dmax = (l < R) ? G[l * ld + l] : 0.0;
     for (int m = 32; m >= 1; m >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, m, 64));
     const double tol = 64.0 * 2.220446049250313e-16 * dmax;
@@ -868,7 +875,7 @@ __device__ inline void beta_pinv_solve(double* G, int ld, double* hv, double* N2
 // half of the run) from the consensus gaps and sign changes the Tikhonov kernels left in their shares, and the end of
 // the loop when no sign changed.
 // By a whole block; P1 and P2 at the start of `lds` are loaded by the caller, and the block synchronised.
-__device__ inline void beta_update(const PtqArgs& a, int t) {
+__device__ __forceinline__ void beta_update(const PtqArgs& a, int t) {
     const int R = a.R, r0 = a.r0, ld = R + 1, count = R * R + R * r0;
     double* P1 = lds;              // S1, K1, gap, sign changes of side 0
     double* P2 = P1 + count + 2;   // the same of side 1
@@ -987,6 +994,8 @@ __global__ __launch_bounds__(kRowThreads) void lordba_ptq_scale_kernel(PtqArgs a
     }
 }
 
+#include "lordba_ptq_run.h"
+
 // The beta update on its own (lordba_ptq_beta_solve): G [R, R] row-major and h [R] from memory, beta [R] to memory.
 __global__ __launch_bounds__(64) void lordba_ptq_beta_solve_kernel(const double* Gin, const double* hin, double* out, int R) {
     const int ld = R + 1, l = threadIdx.x;
@@ -1058,8 +1067,9 @@ __global__ __launch_bounds__(kThreads) void lordba_ptq_fill_kernel(double* p, in
 }
 
 struct Layout {
-    size_t x[2], m[2], y[2], part[2], tot[2], z[2], ctrl, total;
+    size_t x[2], m[2], y[2], part[2], tot[2], z[2], ctrl, sync, slot, gf, total;
     int nb[2], pstride;
+    RunBlocks u[2], s[2];   // blocks of the run kernel
 };
 
 Layout make_layout(int64_t N, int64_t M, int64_t R, int64_t r0) {
@@ -1073,10 +1083,18 @@ Layout make_layout(int64_t N, int64_t M, int64_t R, int64_t r0) {
     for (int s = 0; s < 2; ++s) L.x[s] = take(n[s] * R);   // the iterates come first: U1 [N, R], then U2^T [M, R]
     for (int s = 0; s < 2; ++s) L.m[s] = take(n[s] * R);
     for (int s = 0; s < 2; ++s) L.y[s] = take(n[s] * R);
-    for (int s = 0; s < 2; ++s) L.part[s] = take(static_cast<size_t>(L.nb[s]) * L.pstride);
+    for (int s = 0; s < 2; ++s) {   // (the run kernel keeps its shares in the same place: those of the Tikhonov blocks, then the scale blocks')
+        L.u[s] = run_blocks(n[s], kRunRows);
+        L.s[s] = run_blocks(n[s], kRunScaleRows);
+        const size_t rows = static_cast<size_t>(L.nb[s]) * L.pstride, run = static_cast<size_t>(L.u[s].nb + L.s[s].nb) * (R * R + R * r0);
+        L.part[s] = take(rows > run ? rows : run);
+    }
     for (int s = 0; s < 2; ++s) L.tot[s] = take(L.pstride);
     for (int s = 0; s < 2; ++s) L.z[s] = take(r0 * R);
     L.ctrl = take(kCtrlCount + kMaxGroups + 1);   // and the arrival counters
+    L.sync = take(kSyncWords / 2);
+    L.slot = take(2 * kSlot);
+    L.gf = take(2 * 2 * kRunMaxBlocks * 2);
     L.total = off * sizeof(double);
     return L;
 }
@@ -1155,6 +1173,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     a.pstride = L.pstride;
     a.ctrl = ws + L.ctrl;
     a.arrived = reinterpret_cast<uint32_t*>(ws + L.ctrl + kCtrlCount);
+    a.sync = reinterpret_cast<uint32_t*>(ws + L.sync);
     a.info = info;
     a.K = static_cast<int>(K);
     a.tau = tau;
@@ -1177,16 +1196,23 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     const size_t lds_scale = lds_fixed > lds_beta ? lds_fixed : lds_beta;   // (its last block may run the beta update)
     const int nb01 = a.nb[0] + a.nb[1];
 
+    // One launch for all sweeps where a row's ranks fit the 16 lanes of a row and the Gram pair's tiles the LDS (us per call, launches per
+    // sweep in brackets: 4096^2, R = r0 = 16 1444 (1990), 400 x 500, R = 4 665 (1565), R = 16, r0 = 32 2780 (3260), 16384^2 2590 (4250)).
+    const bool one_launch = iR <= 16 && ir0 <= 32;
+    const void* run_fn = ir0 <= 16 ? reinterpret_cast<const void*>(lordba_ptq_run_kernel<1>) : reinterpret_cast<const void*>(lordba_ptq_run_kernel<2>);
+    const size_t lds_run = sizeof(double) * run_lds_doubles(ir0 <= 16 ? 1 : 2);
+
     {   // More than 64 KiB of LDS per workgroup has to be asked for; the largest request so far is remembered per device and
         // kernel, so that a call whose shapes the process has already seen makes no runtime call besides its launches
         // (it can then be captured into a HIP graph).
         static std::mutex mu;
-        static size_t granted[64][7];
+        static size_t granted[64][9];
         const struct { const void* fn; size_t bytes; int slot; } big[] = {
             {reinterpret_cast<const void*>(lordba_ptq_qr_kernel), lds_qr, 0}, {reinterpret_cast<const void*>(lordba_ptq_svd_kernel), lds_svd, 1},
             {reinterpret_cast<const void*>(lordba_ptq_init_rows_kernel), lds_init, 2},
             {reinterpret_cast<const void*>(iR <= 16 ? lordba_ptq_ustep_kernel<16> : lordba_ptq_ustep_kernel<32>), lds_rows, iR <= 16 ? 3 : 4},
-            {reinterpret_cast<const void*>(lordba_ptq_scale_kernel), lds_scale, 5}, {reinterpret_cast<const void*>(lordba_ptq_beta_kernel), lds_beta, 6}};
+            {reinterpret_cast<const void*>(lordba_ptq_scale_kernel), lds_scale, 5}, {reinterpret_cast<const void*>(lordba_ptq_beta_kernel), lds_beta, 6},
+            {run_fn, one_launch ? lds_run : 0, ir0 <= 16 ? 7 : 8}};
         std::lock_guard<std::mutex> guard(mu);
         for (const auto& b : big) {
             if (b.bytes > 160 * 1024) return LORDBA_ERR_DIM;
@@ -1244,6 +1270,33 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
             }
         }
         hipLaunchKernelGGL(lordba_ptq_svd_kernel, dim3(1), dim3(64), lds_svd, stream, a, Rfinal[0], Rfinal[1]);
+        launched();
+        if (launch_failed) return LORDBA_ERR_LAUNCH;
+    }
+    if (one_launch) {
+        PtqRunArgs args;
+        args.a = a;
+        PtqRun& g = args.g;
+        int most = 0;
+        for (int s = 0; s < 2; ++s) {
+            g.nbU[s] = L.u[s].nb;
+            g.passU[s] = L.u[s].pass;
+            g.nbS[s] = L.s[s].nb;
+            g.passS[s] = L.s[s].pass;
+            g.partU[s] = a.part[s];
+            g.partS[s] = a.part[s] + static_cast<size_t>(g.nbU[s]) * count;
+            most = g.nbU[s] + 1 > most ? g.nbU[s] + 1 : most;
+        }
+        g.gf = ws + L.gf;
+        g.slot = ws + L.slot;
+        g.sync = a.sync;
+        g.t_begin = static_cast<int>(t_begin);
+        g.t_end = static_cast<int>(t_end);
+        if (ir0 <= 16) hipLaunchKernelGGL(lordba_ptq_run_kernel<1>, dim3(most), dim3(kRunThreads), lds_run, stream, args);
+        else hipLaunchKernelGGL(lordba_ptq_run_kernel<2>, dim3(most), dim3(kRunThreads), lds_run, stream, args);
+        launched();
+        if (launch_failed) return LORDBA_ERR_LAUNCH;
+    } else if (t_begin == 0) {
         hipLaunchKernelGGL(lordba_ptq_init_rows_kernel, dim3(nb01), dim3(kThreads), lds_init, stream, a);
         launched();
         totals(1, count);
@@ -1254,7 +1307,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
         launched();
         if (launch_failed) return LORDBA_ERR_LAUNCH;
     }
-    for (int t = static_cast<int>(t_begin); t < static_cast<int>(t_end); ++t) {
+    for (int t = static_cast<int>(t_begin); t < static_cast<int>(t_end) && !one_launch; ++t) {
         for (int side = 0; side < 2; ++side) {
             if (iR <= 16)
                 hipLaunchKernelGGL(lordba_ptq_ustep_kernel<16>, dim3(a.nb[side]), dim3(kRowThreads), lds_rows, stream, a, side, solve_waves);

@@ -1,0 +1,503 @@
+// The sweeps of a quantisation run as ONE launch (carrier rank up to 16, factor rank up to 32).
+//
+// A sweep is a chain of four steps - Tikhonov step and duals of U1, the same of U2, alpha, gamma - each of which needs the Gram
+// pair of all rows of the side before it.  As launches of their own the steps of 4096^2, R = 16 took 57 us per sweep, of which
+// the arithmetic is a fraction, and a run that ends after 22 of its 100 sweeps paid 0.5 ms for the launches behind its end.
+// Here the blocks of all steps of all sweeps are numbered in order, and every workgroup takes the next number that nobody has
+// taken (one counter), waits until the step before is complete (one arrival counter per kind of step), does the block,
+// publishes its share of the Gram pair and goes on.  A block waits for blocks with smaller numbers only, and whoever took a
+// number does it before anything else, so the smallest unfinished one is always being worked on: the launch ends whatever the
+// number of workgroups that run at a time, also beside other work on the device, and none of them has to be there.
+// (No result depends on who does which block; sums run in a fixed order.)
+//
+// What one workgroup writes and another reads goes through agent-scope accesses (see `publish`); an arrival is counted after
+// every wave's stores have completed (see `arrive_last`).  Buffers that a later step overwrites have no reader left by then:
+// a step starts when the step before it is complete, and readers are at most three steps behind their writer; what is read
+// longer (beta, penalty, consensus gaps) is kept twice, by the parity of the sweep.
+//
+// Blocks: 64 rows of a Tikhonov step (16 waves, four rows each; a lane group per row as in row_ldlt_solve), 256 rows of a
+// scale step (16 waves, 16 rows each), more per block beyond 4096 or 16384 rows, so that a step has at most 64 blocks whose
+// shares every reader adds up.  Gram pairs and the products with them are 64-bit MFMAs whose operands are the registers the
+// rows are in: S = sum over rows of (c u)(c u)^T with lane (rank, row) as both operands.
+#pragma once
+
+constexpr int kRunThreads = 1024, kRunWaves = kRunThreads / 64;
+constexpr int kRunRows = 64, kRunScaleRows = 256, kRunMaxBlocks = 64;
+constexpr int kSlot = 32;            // doubles per parity: beta [16], rho, pending factor of Y
+constexpr uint32_t kStop = 0x80000000u;
+
+struct PtqRun {
+    double* partU[2];   // shares of the blocks of a Tikhonov step, [nbU, count]
+    double* partS[2];   // the same of a scale step, [nbS, count]
+    double* gf;         // [parity][side][nbU of the side, up to kRunMaxBlocks][2]: consensus gap and sign changes of a block
+    double* slot;       // [parity][kSlot]
+    uint32_t* sync;     // [kSyncWords], zero between launches
+    int nbU[2], nbS[2], passU[2], passS[2];
+    int t_begin, t_end;
+};
+
+struct PtqRunArgs {
+    PtqArgs a;
+    PtqRun g;
+};
+
+struct RunBlocks { int nb, pass; };
+inline RunBlocks run_blocks(int64_t n, int rows) {
+    RunBlocks b;
+    b.pass = static_cast<int>((n + static_cast<int64_t>(rows) * kRunMaxBlocks - 1) / (static_cast<int64_t>(rows) * kRunMaxBlocks));
+    b.nb = static_cast<int>((n + static_cast<int64_t>(rows) * b.pass - 1) / (static_cast<int64_t>(rows) * b.pass));
+    return b;
+}
+// LDS of the run kernel in doubles: the two totals, the operands, beta and its work area, scales, the waves' shares.
+constexpr int run_lds_doubles(int RT) {
+    return 2 * (256 + 256 * RT) + 256 + 256 * RT + 16 + (2 * 16 * 17 + 3 * 16 + 8) + kRunWaves * 16 + 2 * kRunWaves + 8 + kRunWaves * 256 * (1 + RT);
+}
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// acc[e] += (lane K + e's `from`) * f[e], e = 0..3
+template <int K>
+__device__ inline void fma_row_lanes4(double (&acc)[4], double from, const double (&f)[4]) {
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %4, %5 row_newbcast:%c9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %4, %6 row_newbcast:%c10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %7 row_newbcast:%c11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %4, %8 row_newbcast:%c12 row_mask:0xf bank_mask:0xf"
+        : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
+        : "v"(from), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "n"(K), "n"(K + 1), "n"(K + 2), "n"(K + 3));
+}
+
+// sum over c < 16 of M[c][l] * (lane c's f), M in LDS as pairs of rows
+template <int C = 0>
+__device__ inline void row_products(const double* M, double f, int l, double (&acc)[4]) {
+    const d2 a = *reinterpret_cast<const d2*>(M + (C >> 1) * 32 + l * 2), b = *reinterpret_cast<const d2*>(M + ((C >> 1) + 1) * 32 + l * 2);
+    const double m[4] = {a[0], a[1], b[0], b[1]};
+    fma_row_lanes4<C>(acc, f, m);
+    if constexpr (C < 12) row_products<C + 4>(M, f, l, acc);
+}
+
+template <int RT>   // factor rank at most 16 RT
+__global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs) {
+    constexpr int NT = 1 + RT;              // 16 x 16 tiles of a Gram pair
+    constexpr int NV = 256 * NT;            // values of a padded pair
+    constexpr int H = NV <= 512 ? 2 : 1;    // threads that share the sum of one value
+    typedef const __attribute__((address_space(4))) PtqRunArgs KernelArgs;   // (constant memory: read into scalar registers)
+    KernelArgs* arg = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    const int R = arg->a.R, r0 = arg->a.r0, RR = R * R, count = RR + R * r0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double* T1 = lds;                  // totals of side 0 and of side 1, as they are stored (for beta)
+    double* T2 = T1 + NV;
+    double* G = T2 + NV;               // S as pairs of rows: entry (i, j) at (i / 2) * 32 + 2 j + i % 2, zeros beyond R
+    double* Kt = G + 256;              // K transposed [16 RT, 16], the same way
+    double* bs = Kt + 256 * RT;        // beta
+    double* bw = bs + 16;              // beta_pinv_solve's areas
+    double* cs = bw + 2 * 16 * 17 + 3 * 16 + 8;   // [waves][16]
+    double* gfs = cs + kRunWaves * 16;            // [waves][2]
+    double* ctl = gfs + 2 * kRunWaves;            // rho, factor of Y, done
+    double* red = ctl + 8;                        // [waves][NV]
+    __shared__ uint32_t sh_number, sh_stop[2], place[NV];
+    int waits = 0;   // (two flags in turn: the next wait's must not be set before every wave has read this one's)
+
+    // Value o of a Gram pair as it is stored: whether there is one (bit 0) and it belongs to S (1), its row and column up to 16 (2..5, 6..9), its
+    // place in G and Kt (10..19) and in a wave's share (20..29).
+    for (int o = threadIdx.x; o < NV; o += kRunThreads) {
+        const bool is_s = o < RR;
+        const int vi = is_s ? o / R : (o - RR) / r0, vj = is_s ? o - vi * R : (o - RR) - vi * r0;
+        const int at = is_s ? (vi >> 1) * 32 + vj * 2 + (vi & 1) : 256 + (vj >> 1) * 32 + vi * 2 + (vj & 1);
+        const int rpos = is_s ? vi * 16 + vj : (1 + (vj >> 4)) * 256 + vi * 16 + (vj & 15);
+        place[o] = o < count ? 1u | (is_s ? 2u : 0u) | vi << 2 | (vj & 15) << 6 | at << 10 | static_cast<uint32_t>(rpos) << 20 : 0u;
+        G[o] = 0.0;   // (Kt follows G)
+    }
+    if (threadIdx.x < 16) bs[threadIdx.x] = 0.0;
+    __syncthreads();
+    auto arrivals = [&](int p) { return arg->g.sync + (2 + p) * kSyncStride; };
+    const bool init = arg->g.t_begin == 0;
+    auto per = [&](int p) { return p == 0 ? arg->g.nbU[0] + 1 : p == 1 ? arg->g.nbU[1] : arg->g.nbS[p & 1]; };   // (the first step has a keeper: beta and the penalty)
+    const uint32_t per_sweep = static_cast<uint32_t>(per(0) + per(1) + per(2) + per(3));
+    const uint32_t n_init = init ? per_sweep - 1u : 0u;
+    const uint32_t sweeps = static_cast<uint32_t>(arg->g.t_end - arg->g.t_begin);
+    // An update that has no carriers (or a run whose signs have repeated) makes no sweeps; the iterates are still set.
+    const bool ended = arg->a.ctrl[kDone] != 0.0;
+    auto need = [&](int p, int t) {   // arrivals of step p through sweep t
+        const int base = !init ? 0 : p == 0 ? per(0) - 1 : per(p);
+        return static_cast<uint32_t>(base + (t - arg->g.t_begin + 1) * per(p));
+    };
+    // Lane-derived values and arguments are taken anew in every block, from numbers that the compiler cannot follow: kept over the whole
+    // kernel, with the lane masks of every phase that follow from them, they take more registers than there are, scalar ones above all.
+    int tid = threadIdx.x;
+    auto wait_for = [&](int p, int t) {   // true: the run is over
+        uint32_t* stop = &sh_stop[waits++ & 1];
+        if (tid == 0) {
+            const uint32_t want = need(p, t);
+            uint32_t v;
+            while ((v = __hip_atomic_load(arrivals(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < want) __builtin_amdgcn_s_sleep(1);
+            *stop = v & kStop;   // (with the stop bit the count is beyond any other)
+        }
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(*stop) != 0u;
+    };
+    auto arrive = [&](int p) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) __hip_atomic_fetch_add(arrivals(p), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto gather = [&](const double* part, int nb) {   // this thread's share of the sum over the blocks
+        double acc = 0.0;
+        const int o = H == 2 ? tid & (NV - 1) : tid, h = H == 2 ? tid / NV : 0;
+        if (o < count) {
+            const int lo = H == 2 && h == 1 ? nb >> 1 : 0, hi = H == 2 && h == 0 ? nb >> 1 : nb;
+            for (int b0 = lo; b0 < hi; b0 += 16) {
+                double v[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) v[j] = published(part + static_cast<int64_t>(b0 + j < hi ? b0 + j : hi - 1) * count + o);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) acc += b0 + j < hi ? v[j] : 0.0;
+            }
+        }
+        return acc;
+    };
+    auto combine = [&](double acc) {   // the whole sum, in the threads below NV (contains a barrier)
+        if constexpr (H == 2) {
+            if (tid >= NV) red[tid - NV] = acc;
+            __syncthreads();
+            if (tid < NV) acc += red[tid];
+        }
+        return acc;
+    };
+    // the waves' shares added up and published (contains a barrier)
+    auto share = [&](const d4 (&s)[NT], double* part) {
+#pragma unroll
+        for (int e = 0; e < NT; ++e) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave * NV + e * 256 + r * 64 + (tid & 63)] = s[e][r];
+        }
+        __syncthreads();
+        if (tid < count) {
+            const double* at = red + (place[tid] >> 20);
+            double v[kRunWaves], acc = 0.0;
+#pragma unroll
+            for (int w = 0; w < kRunWaves; ++w) v[w] = at[w * NV];
+#pragma unroll
+            for (int w = 0; w < kRunWaves; ++w) acc += v[w];
+            publish(part + tid, acc);
+        }
+    };
+
+    for (;;) {
+        asm volatile("" : "+v"(tid));
+        asm volatile("" : "+s"(arg));
+        const int lane = tid & 63, li = lane & 15, q = lane >> 4;
+        if (tid == 0) sh_number = __hip_atomic_fetch_add(arg->g.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        uint32_t rest = __builtin_amdgcn_readfirstlane(sh_number);
+        int t = -1, p = 0;
+        if (rest >= n_init) {
+            rest -= n_init;
+            const uint32_t s = rest / per_sweep;
+            rest -= s * per_sweep;
+            // (behind the last sweep comes one more number: beta and the penalty of that sweep)
+            if (ended || sweeps == 0u || s > sweeps || (s == sweeps && rest != 0u)) break;
+            t = arg->g.t_begin + static_cast<int>(s);
+        } else {
+            ++rest;   // (the warm start has no keeper)
+        }
+        for (; rest >= static_cast<uint32_t>(per(p)); ++p) rest -= static_cast<uint32_t>(per(p));
+        if (ended && p >= 2) break;
+        // The keeper comes first: the blocks behind it may leave when they see that the run is over, it tells the others.
+        const bool keeper = p == 0 && rest == 0u;
+        const int blk = static_cast<int>(rest) - (p == 0 && !keeper ? 1 : 0), side = p & 1;
+        const int64_t n = arg->a.n[side];
+        const __half* F = arg->a.F[side];
+        auto factor = [&](int64_t row, int c) {   // entry c of a factor row; zeros beyond the rows and the rank
+            const bool in = row < n && c < r0;
+            const float v = __half2float(F[in ? row * r0 + c : 0]);
+            return in ? static_cast<double>(v) : 0.0;
+        };
+
+        if (p < 2 && t < 0) {   // ---- warm start: U = M = sign(factor row . Z), Y = 0, scale = 1
+            d4 s[NT];
+#pragma unroll
+            for (int e = 0; e < NT; ++e) s[e] = d4{0.0, 0.0, 0.0, 0.0};
+            for (int pass = 0; pass < arg->g.passU[side]; ++pass) {
+                const int64_t row = (static_cast<int64_t>(blk) * arg->g.passU[side] + pass) * kRunRows + wave * 4 + q;
+                const bool in = row < n, act = in && li < R;
+                double acc = 0.0;
+                for (int c = 0; c < r0; ++c) acc += factor(row, c) * arg->a.Z[side][c * R + (li < R ? li : 0)];
+                const double v = act ? (acc < 0.0 ? -1.0 : 1.0) : 0.0;
+                if (act) {
+                    publish(arg->a.X[side] + row * R + li, v);
+                    publish(arg->a.Mm[side] + row * R + li, v);
+                    publish(arg->a.Y[side] + row * R + li, 0.0);
+                }
+                if (in && li == 0) publish(arg->a.scale[side] + row, 1.0);
+                s[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, s[0], 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < RT; ++e) s[1 + e] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, factor(row, e * 16 + li), s[1 + e], 0, 0, 0);
+            }
+            if (side == 1) share(s, arg->g.partU[1] + static_cast<int64_t>(blk) * count);   // (all that alpha needs)
+            arrive(p);
+            continue;
+        }
+        if (p < 2) {   // ---- Tikhonov step of a side, signs and duals; before U1's, beta and the penalty of the sweep before
+            const bool update = p == 0 && t > arg->g.t_begin;
+            if (wait_for(p + 2, t - 1)) break;
+            // what the rows need is there already: requested ahead of the wait for the totals
+            const int passes = keeper ? 0 : arg->g.passU[side];
+            double m_old = 0.0, y_old = 0.0, c = 0.0, f[RT];
+            auto request = [&](int pass) {
+                const int64_t row = (static_cast<int64_t>(blk) * passes + pass) * kRunRows + wave * 4 + q;
+                const bool in = row < n && passes > 0;
+                const int64_t at = in ? row * R + (li < R ? li : 0) : 0;
+                m_old = published(arg->a.Mm[side] + at);
+                y_old = published(arg->a.Y[side] + at);
+                c = published(arg->a.scale[side] + (in ? row : 0));
+#pragma unroll
+                for (int e = 0; e < RT; ++e) f[e] = factor(in ? row : n, e * 16 + li);
+                c = in ? c : 0.0;
+            };
+            request(0);
+            double acc1 = 0.0;
+            if (update) {
+                acc1 = combine(gather(arg->g.partS[0], arg->g.nbS[0]));
+                if (tid < count) T1[tid] = acc1;
+                if (wave == 1) {   // consensus gaps and sign changes of both sides
+                    double gap = 0.0, f0 = 0.0, f1 = 0.0;
+                    const double* gf = arg->g.gf + ((t - 1) & 1) * 4 * kRunMaxBlocks;
+                    if (lane < arg->g.nbU[0]) { gap += published(gf + 2 * lane); f0 = published(gf + 2 * lane + 1); }
+                    gf += 2 * kRunMaxBlocks;
+                    if (lane < arg->g.nbU[1]) { gap += published(gf + 2 * lane); f1 = published(gf + 2 * lane + 1); }
+                    gap = group_sum(gap, 64);
+                    f0 = group_sum(f0, 64);
+                    f1 = group_sum(f1, 64);
+                    if (lane == 0) {
+                        const double* slot = arg->g.slot + ((t - 1) & 1) * kSlot;
+                        double rho = published(slot + 16), yfac = 1.0;
+                        if (2 * static_cast<int64_t>(t - 1) < arg->a.K) {   // residual balancing in the first half of the run
+                            const double rho0 = rho / (static_cast<double>(arg->a.n[0]) * R), rho1 = rho / (static_cast<double>(arg->a.n[1]) * R);
+                            const double rp = sqrt(gap), sd = sqrt(rho0 * rho0 * 4.0 * f0 + rho1 * rho1 * 4.0 * f1);
+                            if (rp > arg->a.mu * sd) { rho *= arg->a.tau; yfac = 1.0 / arg->a.tau; }
+                            else if (sd > arg->a.mu * rp) { rho /= arg->a.tau; yfac = arg->a.tau; }
+                        }
+                        ctl[0] = rho;
+                        ctl[1] = yfac;
+                        ctl[2] = f0 + f1 == 0.0 ? 1.0 : 0.0;
+                    }
+                }
+            }
+            if (p == 0 ? wait_for(3, t - 1) : wait_for(0, t)) break;
+            double total = gather(p == 0 ? arg->g.partS[1] : arg->g.partU[0], p == 0 ? arg->g.nbS[1] : arg->g.nbU[0]);
+            if (!update && tid < 18) {   // beta, rho, factor of Y
+                double v;
+                if (p == 0) v = tid < 16 ? (tid < R ? arg->a.beta[tid] : 0.0) : arg->a.ctrl[tid == 16 ? kRho : kYfac];
+                else v = published(arg->g.slot + (t & 1) * kSlot + tid);
+                if (tid < 16) bs[tid] = v;
+                else ctl[tid - 16] = v;
+            }
+            total = combine(total);
+            if (H == 1) __syncthreads();
+            if (update) {
+                if (tid < count) T2[tid] = total;
+                __syncthreads();
+                if (wave == 0) {   // Eq. (beta-gram), Eq. (beta-pinv): beta = pinv(S1 o S2) h, h_k = K1[k, :] . K2[k, :]
+                    double* Gb = bw;
+                    double* N2 = Gb + 16 * 17;
+                    double* hv = N2 + 16 * 17;
+                    double* bt = hv + 16;
+                    int* perm = reinterpret_cast<int*>(bt + 16);
+                    const int ld = R + 1, l = lane;
+                    double h0 = 0.0;
+                    if (l < R) {
+                        for (int i = 0; i < R; ++i) Gb[i * ld + l] = T1[i * R + l] * T2[i * R + l];
+                        for (int e = 0; e < r0; ++e) h0 += T1[RR + l * r0 + e] * T2[RR + l * r0 + e];
+                        hv[l] = h0;
+                        perm[l] = l;
+                    }
+                    wave_sync();
+                    beta_pinv_solve(Gb, ld, hv, N2, perm, bt, R, l);
+                    if (l < R) bs[l] = bt[l];
+                }
+                __syncthreads();
+            }
+            if (tid < count) {
+                const uint32_t w = place[tid];
+                G[w >> 10 & 0x3ffu] = total * (bs[w >> 2 & 15u] * (w & 2u ? bs[w >> 6 & 15u] : 1.0));
+            }
+            if (keeper) {
+                const bool done = update && ctl[2] != 0.0, last = done || t == arg->g.t_end;
+                if (tid < 18) publish(arg->g.slot + (t & 1) * kSlot + tid, tid < 16 ? bs[tid] : ctl[tid - 16]);
+                if (update && wave == 0) {   // objective of Eq. (admm-problem): (||T||_F^2 - 2 beta . h + beta^T G beta) / 2
+                    double lin = 0.0, quad = 0.0;
+                    if (lane < R) {
+                        const double bl = bs[lane];
+                        for (int e = 0; e < r0; ++e) lin += T1[RR + lane * r0 + e] * T2[RR + lane * r0 + e];
+                        lin *= bl;
+                        for (int i = 0; i < R; ++i) quad += bl * bs[i] * (T1[lane * R + i] * T2[lane * R + i]);
+                    }
+                    lin = group_sum(lin, 64);
+                    quad = group_sum(quad, 64);
+                    if (lane == 0) arg->a.info[kInfoHead + t - 1] = 0.5 * (arg->a.ctrl[kNormT2] - 2.0 * lin + quad);
+                    if (last) {
+                        if (lane < R) arg->a.beta[lane] = bs[lane];
+                        if (lane == 0) {
+                            arg->a.ctrl[kRho] = ctl[0];
+                            arg->a.ctrl[kYfac] = ctl[1];
+                            arg->a.ctrl[kSweeps] = t;
+                            if (done) { arg->a.ctrl[kFrozen] = 1.0; arg->a.ctrl[kDone] = 1.0; }
+                        }
+                    }
+                }
+                if (last) {   // nobody arrives at this step any more
+                    if (tid < 4) __hip_atomic_fetch_or(arrivals(tid), kStop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                arrive(0);
+                continue;
+            }
+            if (update && ctl[2] != 0.0) break;
+            __syncthreads();
+            const double rho_k = ctl[0] / (static_cast<double>(n) * R), yfac = ctl[1];
+            d4 s[NT];
+#pragma unroll
+            for (int e = 0; e < NT; ++e) s[e] = d4{0.0, 0.0, 0.0, 0.0};
+            double gap = 0.0, flips = 0.0;
+            const bool act = li < R;
+            for (int pass = 0; pass < passes; ++pass) {
+                const int64_t row = (static_cast<int64_t>(blk) * passes + pass) * kRunRows + wave * 4 + q;
+                const bool in = row < n;
+                double kb[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int e = 0; e < RT; ++e) row_products(Kt + e * 256, f[e], li, kb);
+                const double y = yfac * y_old, mo = m_old, cc = c;
+                double b = act ? cc * ((kb[0] + kb[1]) + (kb[2] + kb[3])) + rho_k * (mo - y) : 0.0;
+                const double c2 = cc * cc, diag = act ? rho_k : 1.0;
+                double col[16];
+                int l = li;
+#pragma unroll
+                for (int i = 0; i < 16; i += 2) {
+                    asm volatile("" : "+v"(l));   // (see row_ldlt_solve)
+                    const d2 gg = *reinterpret_cast<const d2*>(G + (i >> 1) * 32 + l * 2);
+                    col[i] = fma(c2, gg[0], l == i ? diag : 0.0);
+                    col[i + 1] = fma(c2, gg[1], l == i + 1 ? diag : 0.0);
+                }
+                double fr[RT];
+#pragma unroll
+                for (int e = 0; e < RT; ++e) fr[e] = f[e];
+                if (pass + 1 < passes) request(pass + 1);
+                double min_pivot;   // positive: the matrix is a Gram matrix plus rho_k I
+                const double x = row_ldlt_solve(col, b, R, li, &min_pivot);
+                const double mn = (x + y) < 0.0 ? -1.0 : 1.0;
+                const bool live = in && act;
+                if (live) {
+                    publish(arg->a.X[side] + row * R + li, x);
+                    publish(arg->a.Mm[side] + row * R + li, mn);
+                    publish(arg->a.Y[side] + row * R + li, y + x - mn);
+                    gap += (x - mn) * (x - mn);
+                    flips += mn != mo ? 1.0 : 0.0;
+                }
+                const double v = live ? cc * x : 0.0;
+                s[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, s[0], 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < RT; ++e) s[1 + e] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, fr[e], s[1 + e], 0, 0, 0);
+            }
+            gap = group_sum(gap, 64);
+            flips = group_sum(flips, 64);
+            if (lane == 0) { gfs[2 * wave] = gap; gfs[2 * wave + 1] = flips; }
+            share(s, arg->g.partU[side] + static_cast<int64_t>(blk) * count);
+            if (tid >= kRunThreads - 64 && lane < 2) {   // (a wave without a value to add up where there are 512)
+                double sum = 0.0;
+#pragma unroll
+                for (int w = 0; w < kRunWaves; ++w) sum += gfs[2 * w + lane];
+                publish(arg->g.gf + (((t & 1) * 2 + side) * kRunMaxBlocks + blk) * 2 + lane, sum);
+            }
+            arrive(p);
+            continue;
+        }
+        // ---- Eq. (alpha-update), Eq. (gamma-update): per row, with v = u o beta, (v . (K f)) / (v^T S v), 0 where the denominator is 0
+        if (p == 2 ? wait_for(0, t) : wait_for(1, t)) break;
+        const int passes = arg->g.passS[side];
+        double xr[4], xk[4], fr[RT][4], fk[RT][4];   // the wave's 16 rows by lane (row, ranks 4 s + q) and by lane (rank, rows 4 s + q)
+        auto request = [&](int pass) {
+            const int64_t row0 = (static_cast<int64_t>(blk) * passes + pass) * kRunScaleRows + wave * 16;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int64_t r1 = row0 + li, r2 = row0 + 4 * s + q;
+                const int k = 4 * s + q;
+                const bool in1 = r1 < n && k < R, in2 = r2 < n && li < R;
+                xr[s] = published(arg->a.X[side] + (in1 ? r1 * R + k : 0));
+                xk[s] = published(arg->a.X[side] + (in2 ? r2 * R + li : 0));
+                xr[s] = in1 ? xr[s] : 0.0;
+                xk[s] = in2 ? xk[s] : 0.0;
+#pragma unroll
+                for (int e = 0; e < RT; ++e) {
+                    fr[e][s] = factor(r1, e * 16 + k);
+                    fk[e][s] = factor(r2, e * 16 + li);
+                }
+            }
+        };
+        request(0);
+        if (tid < 16) bs[tid] = t < 0 ? (tid < R ? arg->a.beta[tid] : 0.0) : published(arg->g.slot + (t & 1) * kSlot + tid);
+        if (wait_for(p - 1, t)) break;
+        {
+            const double total = combine(gather(p == 2 ? arg->g.partU[1] : arg->g.partS[0], p == 2 ? arg->g.nbU[1] : arg->g.nbS[0]));
+            if (tid < count) G[place[tid] >> 10 & 0x3ffu] = total;
+        }
+        __syncthreads();
+        d4 s[NT];
+#pragma unroll
+        for (int e = 0; e < NT; ++e) s[e] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int pass = 0; pass < passes; ++pass) {
+            const int64_t row = (static_cast<int64_t>(blk) * passes + pass) * kRunScaleRows + wave * 16 + li;
+            d4 sv = {0.0, 0.0, 0.0, 0.0}, kf = {0.0, 0.0, 0.0, 0.0};
+            double v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {   // ranks 4 e + q: operand (rank, q) of S, which is symmetric, and of K
+                const int k = 4 * e + q;
+                v[e] = xr[e] * bs[k];
+                sv = __builtin_amdgcn_mfma_f64_16x16x4f64(G[(k >> 1) * 32 + li * 2 + (k & 1)], v[e], sv, 0, 0, 0);
+#pragma unroll
+                for (int w = 0; w < RT; ++w)
+                    kf = __builtin_amdgcn_mfma_f64_16x16x4f64(Kt[w * 256 + (k >> 1) * 32 + li * 2 + (k & 1)], fr[w][e], kf, 0, 0, 0);
+            }
+            double num = 0.0, den = 0.0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                num = fma(v[e], kf[e], num);
+                den = fma(v[e], sv[e], den);
+            }
+            num += __shfl_xor(num, 16, 64);
+            den += __shfl_xor(den, 16, 64);
+            num += __shfl_xor(num, 32, 64);
+            den += __shfl_xor(den, 32, 64);
+            const double c = den > 0.0 ? num / den : 0.0;
+            const bool in = row < n;
+            wave_sync();
+            if (q == 0) {
+                cs[wave * 16 + li] = in ? c : 0.0;
+                if (in) publish(arg->a.scale[side] + row, c);
+            }
+            wave_sync();
+            double u[4], fv[RT][4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                u[e] = cs[wave * 16 + 4 * e + q] * xk[e];
+#pragma unroll
+                for (int w = 0; w < RT; ++w) fv[w][e] = fk[w][e];
+            }
+            if (pass + 1 < passes) request(pass + 1);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[e], u[e], s[0], 0, 0, 0);
+#pragma unroll
+                for (int w = 0; w < RT; ++w) s[1 + w] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[e], fv[w][e], s[1 + w], 0, 0, 0);
+            }
+        }
+        share(s, arg->g.partS[side] + static_cast<int64_t>(blk) * count);
+        arrive(p);
+    }
+    // The last workgroup to leave sets the counters back for the next launch: by then nobody reads them.
+    if (tid == 0) {
+        if (__hip_atomic_fetch_add(arg->g.sync + kSyncStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x) {
+            for (int e = 0; e < 6; ++e) __hip_atomic_store(arg->g.sync + e * kSyncStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
