@@ -1,5 +1,6 @@
-"""ctypes binding of liblordba.so (argument marshalling only; every step of the path runs in the
-library's HIP kernels).  Names and argument order follow include/lordba.h.
+"""Binding of liblordba.so (argument marshalling only; every step of the path runs in the library's HIP kernels): ctypes, and
+for the plain cases of the calls that training and serving make a small C++ module (csrc/lordba_torch.cpp).  Names and
+argument order follow include/lordba.h.
 
 torch is used for device memory and streams only: tensors are passed as raw device pointers and
 the current torch stream is passed as the hipStream_t.
@@ -10,6 +11,7 @@ import ctypes
 import os
 import subprocess
 import sys
+import sysconfig
 from typing import Optional, Tuple
 
 import numpy as np
@@ -23,6 +25,8 @@ _SOURCES = ("lordba_forward.hip", "lordba_forward_train.hip", "lordba_forward_an
             "lordba_forward_multi_l2.hip", "lordba_forward_multi_l3.hip", "lordba_forward_multi_l4.hip",
             "lordba_forward_multi_train.hip", "lordba_forward_multi.hip", "lordba_backward.hip", "lordba_ptq.hip", "lordba_pack_device.hip", "lordba_pack.cpp")
 _lib = None
+_TORCH_MODULE_PATH = os.path.join(_PKG, "_lordba_torch.so")
+_torch_module = None
 
 ALGO_AUTO, ALGO_GENERAL, ALGO_MFMA_T8, ALGO_MFMA_T16 = 0, 1, 2, 3
 
@@ -51,25 +55,54 @@ def build_library(verbose: bool = False) -> str:
             print(" ".join(cmd), file=sys.stderr)
         objs.append(obj)
         procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
+    obj, cmd = _torch_module_command(tag)
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    objs.append(obj)
+    procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
     outs = [p.communicate()[0] for p in procs]
     tmp = _LIB_PATH + tag
     try:
         for p, out in zip(procs, outs):
             out = "\n".join(l for l in out.splitlines() if "not a recognized feature for this target" not in l)
             if p.returncode != 0:
-                raise RuntimeError("hipcc failed:\n" + out)
+                raise RuntimeError("compilation failed:\n" + out)
             if verbose and out.strip():
                 print(out, file=sys.stderr)
-        link = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp],
-                              stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        if link.returncode != 0:
-            raise RuntimeError("link failed:\n" + link.stdout)
-        os.replace(tmp, _LIB_PATH)
+        _link([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs[:-1], tmp, _LIB_PATH)
+        _link_torch_module(obj, tmp)
     finally:
         for f in objs + [tmp]:
             if os.path.exists(f):
                 os.remove(f)
     return _LIB_PATH
+
+
+def _link(cmd, tmp: str, target: str) -> None:
+    link = subprocess.run(cmd + ["-o", tmp], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if link.returncode != 0:
+        raise RuntimeError("link failed:\n" + link.stdout)
+    os.replace(tmp, target)
+
+
+def _torch_module_command(tag: str):
+    """The object file of the module that takes torch tensors, and the command that compiles it (host code only)."""
+    import torch
+
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    obj = os.path.join(_PKG, "lordba_torch.cpp" + tag + ".o")
+    return obj, [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                 "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(_ROOT, "include"),
+                 "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"), "-I", "/opt/rocm/include",
+                 "-I", sysconfig.get_paths()["include"], "-c", os.path.join(_CSRC, "lordba_torch.cpp"), "-o", obj]
+
+
+def _link_torch_module(obj: str, tmp: str) -> None:
+    import torch
+
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _link([os.environ.get("CXX", "g++"), "-shared", obj, "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-L", _PKG,
+           "-l:" + os.path.basename(_LIB_PATH), "-Wl,-rpath,$ORIGIN"], tmp, _TORCH_MODULE_PATH)
 
 
 _BENCH_LIB_PATH = os.path.join(_PKG, "libmembench.so")
@@ -169,6 +202,33 @@ def load_library():
     return lib
 
 
+def _load_torch_module():
+    """The C++ module that takes torch tensors.  As for the library there is no fallback: not built is an error."""
+    global _torch_module
+    load_library()
+    if not os.path.exists(_TORCH_MODULE_PATH):
+        raise RuntimeError("_lordba_torch.so is not built: run __graft_entry__.build() first")
+    import torch  # noqa: F401  (its libraries have to be in the process)
+    from . import _lordba_torch
+
+    _torch_module = _lordba_torch
+    return _lordba_torch
+
+
+def _plain_call(name: str, *args):
+    """The call through the C++ module: its result, or None where the arguments are not the plain case, which the caller then
+    takes (and checks) itself."""
+    res = getattr(_torch_module or _load_torch_module(), name)(*args)
+    if type(res) is int:
+        raise LordbaError(res, "lordba_" + name)
+    return res
+
+
+def _handle(stream):
+    """A stream argument for _plain_call: None (the current one) or a handle."""
+    return stream if stream is None else getattr(stream, "cuda_stream", stream)
+
+
 _current_raw_stream = None
 
 
@@ -249,6 +309,10 @@ def lordba_forward(x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out=None,
     x [T, d_in] f16, packedA / packedB int32 (the uint32 words, reinterpreted), s_in [d_in], s_rank [r],
     s_out [d_out], y_base [T, d_out] f16.  y_out defaults to a new tensor; pass y_base itself for in-place.
     Enqueues on `stream` (default: torch's current stream) and returns y_out without synchronising."""
+    if algo == ALGO_AUTO:
+        res = _plain_call("forward", x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out, _handle(stream))
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
@@ -286,6 +350,10 @@ def lordba_forward_multi(x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out
                          algo: int = ALGO_AUTO, check: bool = True):
     """y_out = y_base + the branch of an adapter with ell scale envelopes over the same carriers, on the GPU.
     As lordba_forward, with s_in [ell, d_in], s_rank [ell, r], s_out [ell, d_out] (float16, contiguous)."""
+    if algo == ALGO_AUTO:
+        res = _plain_call("forward_multi", x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out, _handle(stream))
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
@@ -332,6 +400,11 @@ def lordba_forward_batched(x, packedA_pool, packedB_pool, s_in_pool, s_rank_pool
     """y_out[t] = y_base[t] + the branch of adapter adapter_of_row[t] of a pool, on the GPU.  Pools are torch CUDA tensors
     stacked over the adapter index: packedA_pool / packedB_pool int32 [n, words], s_*_pool float16 [n, .];
     adapter_of_row int32 [T] (an index outside [0, n) = no adapter)."""
+    if algo == ALGO_AUTO:
+        res = _plain_call("forward_batched", x, packedA_pool, packedB_pool, s_in_pool, s_rank_pool, s_out_pool, adapter_of_row,
+                          y_base, y_out, _handle(stream))
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
@@ -371,6 +444,11 @@ def lordba_forward_batched_multi(x, packedA_pool, packedB_pool, s_in_pool, s_ran
                                  y_out=None, stream=None, algo: int = ALGO_AUTO):
     """lordba_forward_batched for a pool whose adapters have ell scale envelopes each: s_in_pool [n, ell, d_in],
     s_rank_pool [n, ell, r], s_out_pool [n, ell, d_out] (float16 CUDA tensors); everything else as lordba_forward_batched."""
+    if algo == ALGO_AUTO:
+        res = _plain_call("forward_batched_multi", x, packedA_pool, packedB_pool, s_in_pool, s_rank_pool, s_out_pool, adapter_of_row,
+                          y_base, y_out, _handle(stream))
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
@@ -423,6 +501,9 @@ def lordba_pack_latents(latentA, latentB, stream=None, transposed: bool = True):
     """Device-side binarisation and packing of the latent carriers (torch CUDA float32 tensors latentA [r, d_in],
     latentB [d_out, r]).  Returns int32 CUDA tensors (packedA, packedB, packedAt, packedBt); the last two are None unless
     `transposed`."""
+    res = _plain_call("pack_latents", latentA, latentB, _handle(stream), transposed)
+    if res is not None:
+        return res
     import torch
 
     lib = load_library()
@@ -452,6 +533,10 @@ def lordba_forward_save_t(x, packedA, packedB, s_in, s_rank, s_out, y_base=None,
     """The training forward: lordba_forward that also writes the rank-r intermediate t = (x diag(s_in)) S_A^T, fp32,
     rank-major [r, saved_t_stride(T)] (entries past T untouched).  y_base = None: only t is computed.
     Returns (y_out or None, t_out)."""
+    if y_base is not None and y_out is None and t_out is None:
+        res = _plain_call("forward_save_t", x, packedA, packedB, s_in, s_rank, s_out, y_base, _handle(stream))
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
@@ -482,6 +567,11 @@ def lordba_backward(x, g, packedA, packedAt, packedBt, s_in, s_rank, s_out, late
     for this x, or None (recomputed).  workspace: a uint8 CUDA tensor of at least
     lordba_backward_workspace_bytes(...) bytes (allocated here if None).  Returns a dict of new tensors dx (or None),
     d_s_in, d_s_rank, d_s_out, d_latentA, d_latentB; enqueues on `stream` without synchronising."""
+    if dx is None and out is None and not _noalloc:
+        res = _plain_call("backward", x, g, packedA, packedAt, packedBt, s_in, s_rank, s_out, latentA, latentB, kappa, dx_base,
+                          workspace, _handle(stream), t_saved)
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
@@ -552,6 +642,10 @@ def lordba_backward_noalloc(x, g, packedA, packedAt, packedBt, s_in, s_rank, s_o
 def lordba_forward_multi_save_t(x, packedA, packedB, s_in, s_rank, s_out, y_base=None, y_out=None, t_out=None, stream=None):
     """lordba_forward_save_t for ell envelopes (s_in [ell, d_in], s_rank [ell, r], s_out [ell, d_out]): t_out float32
     [ell, r, saved_t_stride(T)].  Returns (y_out or None, t_out)."""
+    if y_base is not None and y_out is None and t_out is None:
+        res = _plain_call("forward_multi_save_t", x, packedA, packedB, s_in, s_rank, s_out, y_base, _handle(stream))
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
@@ -576,6 +670,11 @@ def lordba_backward_multi(x, g, packedA, packedAt, packedBt, s_in, s_rank, s_out
                           dx_base=None, dx=None, workspace=None, stream=None, t_saved=None) -> dict:
     """lordba_backward for ell envelopes: s_in [ell, d_in], s_rank [ell, r], s_out [ell, d_out] (float16 CUDA tensors); the
     scale gradients come back with the same leading envelope index."""
+    if dx is None:
+        res = _plain_call("backward_multi", x, g, packedA, packedAt, packedBt, s_in, s_rank, s_out, latentA, latentB, kappa, dx_base,
+                          workspace, _handle(stream), t_saved)
+        if res is not None:
+            return res
     import torch
 
     lib = load_library()
