@@ -29,6 +29,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "lordba.h"
 #include "lordba_host_util.h"
@@ -1277,7 +1278,9 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
         PtqRunArgs args;
         args.a = a;
         PtqRun& g = args.g;
-        int most = 0;
+        // A workgroup for every block of a sweep: each waits, its rows requested, when its step begins (with one for every block of a
+        // Tikhonov step some took their next block late: a call of 4096^2, R = 16 1446 us, so 1377).
+        int most = 1;
         for (int s = 0; s < 2; ++s) {
             g.nbU[s] = L.u[s].nb;
             g.passU[s] = L.u[s].pass;
@@ -1285,7 +1288,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
             g.passS[s] = L.s[s].pass;
             g.partU[s] = a.part[s];
             g.partS[s] = a.part[s] + static_cast<size_t>(g.nbU[s]) * count;
-            most = g.nbU[s] + 1 > most ? g.nbU[s] + 1 : most;
+            most += g.nbU[s] + g.nbS[s];
         }
         g.gf = ws + L.gf;
         g.slot = ws + L.slot;

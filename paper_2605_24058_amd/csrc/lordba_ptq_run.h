@@ -15,14 +15,15 @@
 // a step starts when the step before it is complete, and readers are at most three steps behind their writer; what is read
 // longer (beta, penalty, consensus gaps) is kept twice, by the parity of the sweep.
 //
-// Blocks: 64 rows of a Tikhonov step (16 waves, four rows each; a lane group per row as in row_ldlt_solve), 256 rows of a
-// scale step (16 waves, 16 rows each), more per block beyond 4096 or 16384 rows, so that a step has at most 64 blocks whose
+// Blocks: 64 rows of a Tikhonov step (16 waves, four rows each; a lane group per row as in row_ldlt_solve), 128 rows of a
+// scale step (8 of the waves, 16 rows each: 256 rows per block kept 64-bit MFMAs of four waves waiting for each other, 64 gave
+// readers too many shares: a call 1377, 1364, 1505 us), more per block beyond 4096 or 8192 rows, so that a step has at most 64 blocks whose
 // shares every reader adds up.  Gram pairs and the products with them are 64-bit MFMAs whose operands are the registers the
 // rows are in: S = sum over rows of (c u)(c u)^T with lane (rank, row) as both operands.
 #pragma once
 
 constexpr int kRunThreads = 1024, kRunWaves = kRunThreads / 64;
-constexpr int kRunRows = 64, kRunScaleRows = 256, kRunMaxBlocks = 64;
+constexpr int kRunRows = 64, kRunScaleRows = 128, kRunMaxBlocks = 64;
 constexpr int kSlot = 32;            // doubles per parity: beta [16], rho, pending factor of Y
 constexpr uint32_t kStop = 0x80000000u;
 
@@ -50,7 +51,7 @@ inline RunBlocks run_blocks(int64_t n, int rows) {
 }
 // LDS of the run kernel in doubles: the two totals, the operands, beta and its work area, scales, the waves' shares.
 constexpr int run_lds_doubles(int RT) {
-    return 2 * (256 + 256 * RT) + 256 + 256 * RT + 16 + (2 * 16 * 17 + 3 * 16 + 8) + kRunWaves * 16 + 2 * kRunWaves + 8 + kRunWaves * 256 * (1 + RT);
+    return 2 * (256 + 256 * RT) + 256 + 256 * RT + 16 + (2 * 16 * 17 + 3 * 16 + 8) + 16 * (16 * RT + 1) + kRunWaves * 16 + 2 * kRunWaves + 8 + kRunWaves * 256 * (1 + RT);
 }
 
 typedef double d2 __attribute__((ext_vector_type(2)));
@@ -76,6 +77,13 @@ __device__ inline void row_products(const double* M, double f, int l, double (&a
     if constexpr (C < 12) row_products<C + 4>(M, f, l, acc);
 }
 
+// p[i] by a 32-bit byte offset from a uniform pointer: one address register per lane
+template <class T>
+__device__ inline T* at32(T* p, uint32_t i) {
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type Byte;
+    return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + i * static_cast<uint32_t>(sizeof(T)));
+}
+
 template <int RT>   // factor rank at most 16 RT
 __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs) {
     constexpr int NT = 1 + RT;              // 16 x 16 tiles of a Gram pair
@@ -91,7 +99,8 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
     double* Kt = G + 256;              // K transposed [16 RT, 16], the same way
     double* bs = Kt + 256 * RT;        // beta
     double* bw = bs + 16;              // beta_pinv_solve's areas
-    double* cs = bw + 2 * 16 * 17 + 3 * 16 + 8;   // [waves][16]
+    double* hp = bw + 2 * 16 * 17 + 3 * 16 + 8;   // [16][16 RT + 1]: K1 o K2
+    double* cs = hp + 16 * (16 * RT + 1);         // [waves][16]
     double* gfs = cs + kRunWaves * 16;            // [waves][2]
     double* ctl = gfs + 2 * kRunWaves;            // rho, factor of Y, done
     double* red = ctl + 8;                        // [waves][NV]
@@ -142,17 +151,16 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         if (tid == 0) __hip_atomic_fetch_add(arrivals(p), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     auto gather = [&](const double* part, int nb) {   // this thread's share of the sum over the blocks
+        const int o = H == 2 ? tid & (NV - 1) : tid, h = H == 2 ? wave / (NV / 64) : 0;
+        const int lo = h == 1 ? nb >> 1 : 0, hi = H == 2 && h == 0 ? nb >> 1 : nb;
+        if (o >= count) return 0.0;
         double acc = 0.0;
-        const int o = H == 2 ? tid & (NV - 1) : tid, h = H == 2 ? tid / NV : 0;
-        if (o < count) {
-            const int lo = H == 2 && h == 1 ? nb >> 1 : 0, hi = H == 2 && h == 0 ? nb >> 1 : nb;
-            for (int b0 = lo; b0 < hi; b0 += 16) {
-                double v[16];
+        for (int b0 = lo; b0 < hi; b0 += 16) {
+            double v[16];
 #pragma unroll
-                for (int j = 0; j < 16; ++j) v[j] = published(part + static_cast<int64_t>(b0 + j < hi ? b0 + j : hi - 1) * count + o);
+            for (int j = 0; j < 16; ++j) v[j] = published(at32(part + (b0 + j < hi ? b0 + j : hi - 1) * count, static_cast<uint32_t>(o)));
 #pragma unroll
-                for (int j = 0; j < 16; ++j) acc += b0 + j < hi ? v[j] : 0.0;
-            }
+            for (int j = 0; j < 16; ++j) acc += b0 + j < hi ? v[j] : 0.0;
         }
         return acc;
     };
@@ -296,25 +304,36 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
             total = combine(total);
             if (H == 1) __syncthreads();
             if (update) {
-                if (tid < count) T2[tid] = total;
+                double* Gb = bw;
+                double* N2 = Gb + 16 * 17;
+                double* hv = N2 + 16 * 17;
+                double* bt = hv + 16;
+                int* perm = reinterpret_cast<int*>(bt + 16);
+                const int ld = R + 1;
+                // Eq. (beta-gram), Eq. (beta-pinv): beta = pinv(S1 o S2) h, h_k = K1[k, :] . K2[k, :]
+                if (tid < count) {
+                    const uint32_t w = place[tid];
+                    const int i = w >> 2 & 15u;
+                    T2[tid] = total;
+                    *(w & 2u ? Gb + i * ld + (w >> 6 & 15u) : hp + i * (16 * RT + 1) + (tid - RR - i * r0)) = acc1 * total;
+                }
                 __syncthreads();
-                if (wave == 0) {   // Eq. (beta-gram), Eq. (beta-pinv): beta = pinv(S1 o S2) h, h_k = K1[k, :] . K2[k, :]
-                    double* Gb = bw;
-                    double* N2 = Gb + 16 * 17;
-                    double* hv = N2 + 16 * 17;
-                    double* bt = hv + 16;
-                    int* perm = reinterpret_cast<int*>(bt + 16);
-                    const int ld = R + 1, l = lane;
-                    double h0 = 0.0;
-                    if (l < R) {
-                        for (int i = 0; i < R; ++i) Gb[i * ld + l] = T1[i * R + l] * T2[i * R + l];
-                        for (int e = 0; e < r0; ++e) h0 += T1[RR + l * r0 + e] * T2[RR + l * r0 + e];
-                        hv[l] = h0;
-                        perm[l] = l;
+                if (wave == 0) {
+                    const int k = lane >> 2;   // four lanes per entry of h
+                    double h = 0.0;
+#pragma unroll
+                    for (int c = 0; c < 4 * RT; ++c) {
+                        const int at = (lane & 3) + 4 * c;
+                        const double v = hp[k * (16 * RT + 1) + at];
+                        h += at < r0 ? v : 0.0;
                     }
+                    h += __shfl_xor(h, 1, 64);
+                    h += __shfl_xor(h, 2, 64);
+                    if (k < R && (lane & 3) == 0) hv[k] = h;
+                    if (lane < R) perm[lane] = lane;
                     wave_sync();
-                    beta_pinv_solve(Gb, ld, hv, N2, perm, bt, R, l);
-                    if (l < R) bs[l] = bt[l];
+                    beta_pinv_solve(Gb, ld, hv, N2, perm, bt, R, lane);
+                    if (lane < R) bs[lane] = bt[lane];
                 }
                 __syncthreads();
             }
@@ -434,7 +453,8 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                 }
             }
         };
-        request(0);
+        const bool rows_here = wave < kRunScaleRows / 16;   // (the other waves only add shares up)
+        if (rows_here) request(0);
         if (tid < 16) bs[tid] = t < 0 ? (tid < R ? arg->a.beta[tid] : 0.0) : published(arg->g.slot + (t & 1) * kSlot + tid);
         if (wait_for(p - 1, t)) break;
         {
@@ -445,7 +465,7 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         d4 s[NT];
 #pragma unroll
         for (int e = 0; e < NT; ++e) s[e] = d4{0.0, 0.0, 0.0, 0.0};
-        for (int pass = 0; pass < passes; ++pass) {
+        for (int pass = 0; pass < passes && rows_here; ++pass) {
             const int64_t row = (static_cast<int64_t>(blk) * passes + pass) * kRunScaleRows + wave * 16 + li;
             d4 sv = {0.0, 0.0, 0.0, 0.0}, kf = {0.0, 0.0, 0.0, 0.0};
             double v[4];
