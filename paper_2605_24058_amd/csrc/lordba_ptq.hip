@@ -91,15 +91,53 @@ __device__ inline double row_rotate16(double v) {
                             __builtin_amdgcn_update_dpp(0, lo, ctrl, 0xf, 0xf, false));
 }
 
-// Sum over each group of gs consecutive lanes (gs = 16, 32 or 64), returned in every lane of the group.  Within rows of 16
-// lanes the partial sums travel by rotation, across rows by lane exchange.
+template <int CTRL>
+__device__ inline double dpp_move(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false));
+}
+
+// Sum over each group of gs consecutive lanes (gs = 8, 16, 32 or 64), returned in every lane of the group.  Within rows of 16
+// lanes the partial sums travel by rotation (within 8 by exchange of neighbours, pairs and quads), across rows by lane exchange.
 __device__ inline double group_sum(double v, int gs) {
+    if (gs == 8) {
+        v += dpp_move<0xb1>(v);    // quad_perm 1, 0, 3, 2
+        v += dpp_move<0x4e>(v);    // quad_perm 2, 3, 0, 1
+        return v + dpp_move<0x141>(v);   // row_half_mirror
+    }
     for (int m = gs >> 1; m >= 16; m >>= 1) v += __shfl_xor(v, m, 64);
     v += row_rotate16<8>(v);
     v += row_rotate16<4>(v);
     v += row_rotate16<2>(v);
     v += row_rotate16<1>(v);
     return v;
+}
+
+// The value of lane K of each row of 16 lanes, in every lane of the row.
+template <int K>
+__device__ inline double row_lane(double v) {
+    return dpp_move<0x150 + K>(v);   // row_newbcast:K
+}
+// a += (lane K's a) * f for one, two or four numbers: the 64-bit multiply-add takes its first operand from another lane
+// of the row by itself, where the compiler would move both halves first.  The wait states are those between any vector instruction
+// and one that reads its result across lanes; the compiler sees the block as one instruction and adds none.
+template <int K>
+__device__ inline void fma_own_row_lane(double& a, double f) {
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%c2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(f), "n"(K));
+}
+template <int K>
+__device__ inline void fma_own_row_lane(double& a, double& b, double f) {
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf"
+        : "+&v"(a), "+&v"(b) : "v"(f), "n"(K));
+}
+template <int K>
+__device__ inline void fma_own_row_lane(double& a, double& b, double& c, double& d, double f) {
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf"
+        : "+&v"(a), "+&v"(b), "+&v"(c), "+&v"(d) : "v"(f), "n"(K));
 }
 
 __device__ inline int group_size_for(int R) { return R <= 16 ? 16 : (R <= 32 ? 32 : 64); }
@@ -364,12 +402,107 @@ __global__ __launch_bounds__(256) void lordba_ptq_qr_kernel(PtqArgs a, QrLevel l
     }
 }
 
+// The same for up to 16 columns, one wave per panel with the panel in registers: lane (j, q) holds rows 4 s + q of column j, and
+// column K reaches the other columns by broadcasts inside the multiply-adds.  No barrier and no LDS; bound: 64-bit vector arithmetic of one
+// wave, 128 multiply-adds per column, and the chain of sums, square root and divisions between them.  Two levels at 4096 rows,
+// 16 columns: 15 us each (45 with the panel in LDS and two barriers per column).
+constexpr int kQrSlots = kQrRows / 4;
+template <int K>
+__device__ __forceinline__ void qr_column(double (&P)[kQrSlots], double* dst, int n, int j, int q) {
+    if (K >= n) return;   // (uniform)
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {   // (the rows up to K are finished)
+        double below = 4 * s + q > K ? P[s] : 0.0;
+        acc[s] = row_lane<K>(below) * below;
+    }
+#pragma unroll
+    for (int s = 4; s < kQrSlots; s += 4)
+        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %4, %4 row_newbcast:%c8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %1, %5, %5 row_newbcast:%c8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %2, %6, %6 row_newbcast:%c8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %3, %7, %7 row_newbcast:%c8 row_mask:0xf bank_mask:0xf"
+            : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
+            : "v"(P[s]), "v"(P[s + 1]), "v"(P[s + 2]), "v"(P[s + 3]), "n"(K));
+    double dot = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    dot += __shfl_xor(dot, 16, 64);
+    dot += __shfl_xor(dot, 32, 64);
+    const double pkj = __shfl(P[K >> 2], (K & 3) * 16 + j, 64);   // row K
+    const double alpha = row_lane<K>(pkj), below2 = row_lane<K>(dot);
+    double f = 0.0, out = j == K ? alpha : pkj;
+    if (below2 > 0.0) {   // (uniform: the reflector as in the kernel above)
+        const double norm = sqrt(fma(alpha, alpha, below2)), beta = alpha < 0.0 ? norm : -norm;
+        const double inv = 1.0 / (alpha - beta), tau = (beta - alpha) / beta;
+        const double tw = tau * fma(dot, inv, pkj);
+        out = j == K ? beta : pkj - tw;
+        f = j > K ? -(tw * inv) : 0.0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double fs = 4 * s + q > K ? f : 0.0;
+            fma_own_row_lane<K>(P[s], fs);
+        }
+#pragma unroll
+        for (int s = 4; s < kQrSlots; s += 4) fma_own_row_lane<K>(P[s], P[s + 1], P[s + 2], P[s + 3], f);
+    }
+    if (q == 0 && j < n) dst[K * n + j] = j < K ? 0.0 : out;
+    if constexpr (K < 15) qr_column<K + 1>(P, dst, n, j, q);
+}
+
+__global__ __launch_bounds__(64) void lordba_ptq_qr16_kernel(PtqArgs a, QrLevel lv) {
+    const int side = static_cast<int>(blockIdx.x) < lv.count_out[0] ? 0 : 1;
+    const int blk = side == 0 ? blockIdx.x : blockIdx.x - lv.count_out[0];
+    const int n = a.r0, j = threadIdx.x & 15, q = threadIdx.x >> 4, jc = j < n ? j : 0;
+    double P[kQrSlots];
+    if (lv.level == 0) {
+        const int64_t row0 = static_cast<int64_t>(blk) * kQrRows, rows = a.n[side] - row0;
+        const __half* F = a.F[side] + row0 * n;
+#pragma unroll
+        for (int s = 0; s < kQrSlots; ++s) {
+            const int row = 4 * s + q;
+            const bool in = row < rows && j < n;
+            const float v = __half2float(F[in ? row * n + jc : 0]);
+            P[s] = in ? static_cast<double>(v) : 0.0;
+        }
+    } else {
+        const int64_t first = static_cast<int64_t>(blk) * lv.group;
+        const double* src = lv.src[side] + first * n * n;
+        const int have = static_cast<int>(lv.count_in[side] - first < lv.group ? lv.count_in[side] - first : lv.group) * n;
+#pragma unroll
+        for (int s = 0; s < kQrSlots; ++s) {
+            const int row = 4 * s + q;
+            const bool in = row < have && j < n;
+            const double v = src[in ? row * n + jc : 0];
+            P[s] = in ? v : 0.0;
+        }
+    }
+    qr_column<0>(P, lv.dst[side] + static_cast<int64_t>(blk) * n * n, n, j, q);
+}
+
+// 1 / sqrt(x) and 1 / x for positive normal x: hardware estimate and Newton steps, the last few bits left to rounding (a rotation is
+// as good with a tangent that is a few last places off, as long as its sine and cosine come from the same one).
+__device__ inline double newton_rsqrt(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double e = fma(-x * y, y, 1.0);
+        y = fma(y * e, fma(0.375, e, 0.5), y);
+    }
+    return y;
+}
+__device__ inline double newton_rcp(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+
 // One-sided Jacobi iteration on the n x n matrix W (n <= 64) by one wave: plane rotations of column pairs, accumulated
 // in V (which the caller sets to the identity), until all columns of W are orthogonal: W V_acc = (orthogonal columns).
 // Round-robin order: the n / 2 column pairs of a round are disjoint, so groups of lanes rotate several pairs at once
-// (lane i of a group owns row i of W and of V for the group's pair).
+// (lane i of a group owns rows i and i + gsz of W and of V for the group's pair).  Bound: the chain of one rotation, from the reads
+// of its columns to the writes; with two rows per lane all eight pairs of n = 16 make theirs at once (with one row per lane, four
+// pairs at a time, the kernel took 97 us).
 __device__ inline void jacobi_onesided(double* W, double* V, int n, int ld, int l) {
-    const int gsz = n <= 16 ? 16 : (n <= 32 ? 32 : 64), ngroups = 64 / gsz;
+    const int gsz = n <= 16 ? 8 : (n <= 32 ? 16 : 32), ngroups = 64 / gsz;
     const int g = l / gsz, i = l - g * gsz;
     const int ne = n + (n & 1);  // an even number of players; with n odd, player n is a bye
     for (int sweep = 0; sweep < 60; ++sweep) {
@@ -380,27 +513,40 @@ __device__ inline void jacobi_onesided(double* W, double* V, int n, int ld, int 
                 int p = 0, q = 0;
                 bool valid = m < ne / 2;
                 if (valid) {
-                    const int lo = (round + m) % (ne - 1);
-                    const int hi = m == 0 ? ne - 1 : (round + ne - 1 - m) % (ne - 1);
+                    int lo = round + m, hi = round + ne - 1 - m;   // modulo ne - 1
+                    lo = lo >= ne - 1 ? lo - (ne - 1) : lo;
+                    hi = m == 0 ? ne - 1 : (hi >= ne - 1 ? hi - (ne - 1) : hi);
                     p = lo < hi ? lo : hi;
                     q = lo < hi ? hi : lo;
                     valid = q < n;
                 }
-                const bool mine = valid && i < n;
-                const double wp = mine ? W[i * ld + p] : 0.0, wq = mine ? W[i * ld + q] : 0.0;
-                const double app = group_sum(wp * wp, gsz), aqq = group_sum(wq * wq, gsz), apq = group_sum(wp * wq, gsz);
+                const bool mine = valid && i < n, two = valid && i + gsz < n;
+                double* wi = W + i * ld;
+                double* wj = W + (i + gsz) * ld;
+                const double wp = mine ? wi[p] : 0.0, wq = mine ? wi[q] : 0.0, xp = two ? wj[p] : 0.0, xq = two ? wj[q] : 0.0;
+                double* vi = V + i * ld;
+                double* vj = V + (i + gsz) * ld;
+                const double vp = mine ? vi[p] : 0.0, vq = mine ? vi[q] : 0.0, up = two ? vj[p] : 0.0, uq = two ? vj[q] : 0.0;
+                const double app = group_sum(fma(wp, wp, xp * xp), gsz), aqq = group_sum(fma(wq, wq, xq * xq), gsz),
+                             apq = group_sum(fma(wp, wq, xp * xq), gsz);
                 const bool rot = valid && apq * apq > 1e-30 * (app * aqq);   // |apq| > 1e-15 sqrt(app aqq)
                 if (rot && mine) {
                     // tangent of the rotation angle: with zeta = (aqq - app) / (2 apq), t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)),
                     // written with one square root and one division: t = sign(d) h / (|d| + sqrt(d^2 + h^2)), d = aqq - app, h = 2 apq
                     const double d = aqq - app, h = 2.0 * apq;
-                    const double t = (signbit(d) ? -h : h) / (fabs(d) + sqrt(d * d + h * h));
-                    const double cs = rsqrt(1.0 + t * t), sn = cs * t;
-                    W[i * ld + p] = cs * wp - sn * wq;
-                    W[i * ld + q] = sn * wp + cs * wq;
-                    const double vp = V[i * ld + p], vq = V[i * ld + q];
-                    V[i * ld + p] = cs * vp - sn * vq;
-                    V[i * ld + q] = sn * vp + cs * vq;
+                    const double s = fma(d, d, h * h), den = fma(s, newton_rsqrt(s), fabs(d));
+                    const double t = (signbit(d) ? -h : h) * newton_rcp(den);
+                    const double cs = newton_rsqrt(fma(t, t, 1.0)), sn = cs * t;
+                    wi[p] = cs * wp - sn * wq;
+                    wi[q] = sn * wp + cs * wq;
+                    vi[p] = cs * vp - sn * vq;
+                    vi[q] = sn * vp + cs * vq;
+                    if (two) {
+                        wj[p] = cs * xp - sn * xq;
+                        wj[q] = sn * xp + cs * xq;
+                        vj[p] = cs * up - sn * uq;
+                        vj[q] = sn * up + cs * uq;
+                    }
                 }
                 rotated = rotated || (__builtin_amdgcn_ballot_w64(rot) != 0);
                 wave_sync();
@@ -410,12 +556,13 @@ __device__ inline void jacobi_onesided(double* W, double* V, int n, int ld, int 
     }
 }
 
-// norms[p] = the 2-norm of column p of the n x n matrix W (one wave; every lane returns after the values are in LDS).
+// norms[p] = the 2-norm of column p of the n x n matrix W (one wave, a column per lane; every lane returns after the values are in LDS).
 __device__ inline void column_norms(const double* W, int n, int ld, int l, double* norms) {
-    for (int p = 0; p < n; ++p) {
-        const double wp = l < n ? W[l * ld + p] : 0.0;
-        const double s2 = __shfl(group_sum(wp * wp, 64), 0, 64);
-        if (l == 0) norms[p] = sqrt(s2);
+    if (l < n) {
+        double s2 = 0.0;
+#pragma unroll 8
+        for (int i = 0; i < n; ++i) s2 = fma(W[i * ld + l], W[i * ld + l], s2);
+        norms[l] = sqrt(s2);
     }
     wave_sync();
 }
@@ -435,21 +582,20 @@ __global__ __launch_bounds__(64) void lordba_ptq_svd_kernel(PtqArgs a, const dou
     double* W = Rb + r0 * ld;
     double* V = W + r0 * ld;
     double* sig = V + r0 * ld;
-    double* zs = sig + r0;   // [r0, R] one side's map before it goes to memory
-    int* idx = reinterpret_cast<int*>(zs + r0 * R);
+    int* idx = reinterpret_cast<int*>(sig + r0);
     for (int o = l; o < r0 * r0; o += 64) {
         Ra[(o / r0) * ld + o % r0] = RaG[o];
         Rb[(o / r0) * ld + o % r0] = RbG[o];
     }
     wave_sync();
-    // core W = Ra Rb^T (both upper triangular), V = I; lane i owns row i of both from here on
-    if (l < r0) {
-        for (int j = 0; j < r0; ++j) {
-            double acc = 0.0;
-            for (int k = (l > j ? l : j); k < r0; ++k) acc = fma(Ra[l * ld + k], Rb[j * ld + k], acc);
-            W[l * ld + j] = acc;
-            V[l * ld + j] = (l == j) ? 1.0 : 0.0;
-        }
+    // core W = Ra Rb^T (both upper triangular), V = I
+    for (int o = l; o < r0 * r0; o += 64) {
+        const int i = o / r0, j = o - i * r0;
+        double acc = 0.0;
+#pragma unroll 8
+        for (int k = (i > j ? i : j); k < r0; ++k) acc = fma(Ra[i * ld + k], Rb[j * ld + k], acc);
+        W[i * ld + j] = acc;
+        V[i * ld + j] = (i == j) ? 1.0 : 0.0;
     }
     wave_sync();
     jacobi_onesided(W, V, r0, ld, l);
@@ -489,17 +635,13 @@ __global__ __launch_bounds__(64) void lordba_ptq_svd_kernel(PtqArgs a, const dou
     for (int side = 0; side < 2; ++side) {
         const double* Rt = side == 0 ? Rb : Ra;   // the OTHER factor's triangle, transposed: Z[i, l] = sum_{j <= i} Rt[j, i] src[j, c]
         const double* src = side == 0 ? V : W;
-        if (l < R) {   // lane l: column l of the side's map, built in LDS (zs, [r0, R])
-            const int c = idx[l];
-            for (int i = 0; i < r0; ++i) {
-                double acc = 0.0;
-                for (int j = 0; j <= i; ++j) acc = fma(Rt[j * ld + i], src[j * ld + c], acc);
-                zs[i * R + l] = acc;
-            }
+        for (int o = l; o < r0 * R; o += 64) {
+            const int i = o / R, c = idx[o - i * R];
+            double acc = 0.0;
+#pragma unroll 8
+            for (int j = 0; j <= i; ++j) acc = fma(Rt[j * ld + i], src[j * ld + c], acc);
+            a.Z[side][o] = acc;
         }
-        wave_sync();
-        for (int o = l; o < r0 * R; o += 64) a.Z[side][o] = zs[o];
-        wave_sync();
     }
 }
 
@@ -572,35 +714,6 @@ __device__ inline void factor_products(const RowLds& s, int R, int r0) {
         for (int q = 0; q < r0; ++q) acc += s.Ko[k * r0 + q] * s.fs[row * s.fstride + q];
         s.kfs[row * R + k] = acc;
     }
-}
-
-// The value of lane K of each row of 16 lanes, in every lane of the row.
-template <int K>
-__device__ inline double row_lane(double v) {
-    constexpr int ctrl = 0x150 + K;   // row_newbcast:K
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xf, 0xf, false),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xf, 0xf, false));
-}
-// a += (lane K's a) * f for one, two or four numbers: the 64-bit multiply-add takes its first operand from another lane
-// of the row by itself, where the compiler would move both halves first.  The wait states are those between any vector instruction
-// and one that reads its result across lanes; the compiler sees the block as one instruction and adds none.
-template <int K>
-__device__ inline void fma_own_row_lane(double& a, double f) {
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%c2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(f), "n"(K));
-}
-template <int K>
-__device__ inline void fma_own_row_lane(double& a, double& b, double f) {
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf"
-        : "+&v"(a), "+&v"(b) : "v"(f), "n"(K));
-}
-template <int K>
-__device__ inline void fma_own_row_lane(double& a, double& b, double& c, double& d, double f) {
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%c5 row_mask:0xf bank_mask:0xf"
-        : "+&v"(a), "+&v"(b), "+&v"(c), "+&v"(d) : "v"(f), "n"(K));
 }
 
 // Solves H x = b for a symmetric positive definite 16 x 16 matrix by the 16 lanes of one row of the wave (a smaller system is
@@ -1182,7 +1295,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
 
     const int iR = a.R, ir0 = a.r0, ld0 = ir0 + 1, ldR = iR + 1;
     const size_t lds_qr = sizeof(double) * (kQrRows * ir0 + 256 + ir0);
-    const size_t lds_svd = sizeof(double) * (4 * ir0 * ld0 + ir0 + ir0 * iR) + sizeof(int) * ir0;
+    const size_t lds_svd = sizeof(double) * (4 * ir0 * ld0 + ir0) + sizeof(int) * ir0;
     const size_t lds_init = sizeof(double) * (kRows * ir0 + kRows * iR + kRows + ir0 * iR);
     const int gs = iR <= 16 ? 16 : 32;
     // the Tikhonov kernel: as many waves solve rows at once as the LDS has room for their matrices (8, 4, 2 or 1); the scale
@@ -1260,7 +1373,9 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
                     lv.count_out[s] = Rfinal[s] != nullptr ? 0 : (level == 0 ? count[s] : (count[s] + group - 1) / group);
                     lv.dst[s] = a.part[s] + ((level & 1) ? c0[s] * ir0 * ir0 : 0);
                 }
-                hipLaunchKernelGGL(lordba_ptq_qr_kernel, dim3(lv.count_out[0] + lv.count_out[1]), dim3(256), lds_qr, stream, a, lv);
+                const dim3 panels(lv.count_out[0] + lv.count_out[1]);
+                if (ir0 <= 16) hipLaunchKernelGGL(lordba_ptq_qr16_kernel, panels, dim3(64), 0, stream, a, lv);
+                else hipLaunchKernelGGL(lordba_ptq_qr_kernel, panels, dim3(256), lds_qr, stream, a, lv);
                 launched();
                 for (int s = 0; s < 2; ++s) {
                     if (lv.count_out[s] == 0) continue;

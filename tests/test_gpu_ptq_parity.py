@@ -118,6 +118,17 @@ def test_groups_of_blocks(torch_cuda, N, M, R, r0):
     compare(run_gpu(torch_cuda, d, R, K=K), ref, K)
 
 
+# Rows at the edges of the 256-row panels of the triangular factors (one, one and a row, sixteen and a row: a third level) and of the
+# blocks of 128 and 64 rows of a run, with factor ranks at which a panel's columns fill their 16 lanes or leave some out
+@pytest.mark.parametrize("N,M,R,r0", [(256, 257, 16, 16), (4097, 129, 4, 16), (127, 4096, 3, 5), (128, 65, 15, 15), (17, 64, 1, 1)])
+def test_panels_and_blocks(torch_cuda, N, M, R, r0):
+    d = inputs.make_ptq_inputs(62, N, M, r0)
+    say("  case %dx%d R %d r0 %d" % (N, M, R, r0))
+    K = 12
+    ref = P.ptq(d["A_star"], d["B_star"], R, K=K)
+    compare(run_gpu(torch_cuda, d, R, K=K), ref, K)
+
+
 @pytest.mark.parametrize("K", [1, 2, 3, 7])
 def test_first_sweeps_match_oracle(torch_cuda, K):
     # a run of K sweeps (its penalty window is the first half of those K) pins every update of the early sweeps
