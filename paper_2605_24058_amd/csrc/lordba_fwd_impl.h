@@ -1075,9 +1075,9 @@ template <int RB, int TMV, int NW, int D1, bool OS, int BM, int GM, int L, bool 
 lordba_status launch_mfma_gm(const FwdArgs& a, hipStream_t stream) {
     constexpr bool TR = kTraining;
     if ((a.t_out != nullptr) != TR) return LORDBA_ERR_ALGO;  // (an entry point of the other kind of unit)
-    // With several envelopes only the plain grid mode of the 8-row, 8-wave variants has a training instantiation (the
-    // dispatch sends such calls there); the multi-adapter batch has none.
-    if constexpr (TR && !((L == 1 && GM < 4) || (L > 1 && GM == 0 && TMV == 8 && NW == 8) || (ANY && GM == 2))) {
+    // With several envelopes only the plain grid mode of the 8-row variants has a training instantiation (the dispatch sends
+    // such calls there); the multi-adapter batch has none.
+    if constexpr (TR && !((L == 1 && GM < 4) || (L > 1 && GM == 0 && TMV == 8 && (NW == 8 || L == 2)) || (ANY && GM == 2))) {
         return LORDBA_ERR_ALGO;
     } else {
     const size_t lds = mfma_lds_bytes(RB, TMV, NW, D1, L);
@@ -1175,6 +1175,22 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
     const int nchunks = (a.d_in + 127) / 128;
     const int per_wave = (nchunks + NW - 1) / NW;
     if (per_wave <= 2) return launch_mfma<RB, TMV, NW, 2, true, BM, L>(a, stream);
+    // As many x slots as the waves have chunks for, 5120 to 6144 columns: three on 16 waves, where the slots without a chunk repeat a
+    // request, and six on 8 with two to four rank blocks instead of the loop over groups of four, which waits for memory once per group (us,
+    // four slots or the loop in brackets; 5120 -> 5120: T = 2048, r = 16 14.6 (15.4), training 14.0 (15.7), r = 32 16.3 (17.2), two
+    // envelopes 16.1 (17.3), at r = 32 19.9 (20.6); T = 3000, r = 32 24.2 (28.5), r = 64 39.6 (43.3); T = 8192, 5120 -> 8192, r = 64 114
+    // (121)).  Not below 40 chunks (4608 -> 2048, T = 3900, r = 32 19.5 (19.1)), and several envelopes on 8 waves gain nothing.
+    if constexpr (TMV == 8 && ((NW == 16 && L <= 2) || (NW == 8 && L == 1 && RB >= 2))) {
+        const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
+        const bool narrow = BM == 0 && (a.d_out + 127) / 128 <= NW;   // (see launch_mfma)
+        constexpr int kSlots = NW == 16 ? 3 : 6;
+        // (Narrow outputs and calls for t alone too: the loop sums a wave's chunks in another order, and t is the same whichever call
+        // keeps it.)
+        if (nchunks >= 40 && per_wave <= kSlots && a.ids == nullptr && tiles > kFewTiles) {
+            if (!narrow) return launch_mfma_gm<RB, TMV, NW, kSlots, true, BM, RB == 1 && BM != 0 && L == 1 ? 1 : 0, L>(a, stream);
+            if constexpr (NW == 8 && BM == 0) return launch_mfma_gm<RB, TMV, NW, kSlots, true, BM, 2, L>(a, stream);
+        }
+    }
     if (per_wave <= 4) return launch_mfma<RB, TMV, NW, 4, true, BM, L>(a, stream);
     if (kDeep && per_wave <= 8 && a.ids == nullptr) return launch_mfma<RB, TMV, NW, (kDeep ? 8 : 4), true, BM, L>(a, stream);  // (the batch mode has 128 registers)
     // Wide inputs at decode sizes: all chunks of a wave in flight at once here too (up to 12288 columns; the registers are there since
@@ -1212,7 +1228,7 @@ template <int TMV, int NW, int L>
 lordba_status launch_mfma_rb(const FwdArgs& a, hipStream_t stream) {
     // Rank blocks a variant holds in registers without spilling.  16 waves: 128 registers per lane.  Several envelopes
     // keep L accumulator sets per block: 16-row tiles then only fit two envelopes of at most two rank blocks.
-    constexpr int kMaxRb = NW == 16 ? (L == 1 ? (TMV == 8 ? 2 : 1) : (L == 2 && TMV == 8 ? 1 : 0))
+    constexpr int kMaxRb = NW == 16 ? (L == 1 ? (TMV == 8 ? 2 : 1) : (L == 2 && TMV == 8 ? 2 : 0))
                            : L == 1 ? 4
                            : TMV == 16 ? (L == 2 ? 2 : 1)
                            : (L == 4 ? 3 : 4);
@@ -1388,15 +1404,21 @@ lordba_status forward_impl(const void* x, const uint32_t* packedA, const uint32_
             if (batched && s == LORDBA_ERR_ALGO) s = launch_mfma_rb<8, 8, 1>(a, st);
         }
     } else {
-        if (t_out != nullptr) {
-            s = launch_mfma_rb<8, 8, L>(a, st);  // the variant family that has a training instantiation
+        // Two envelopes of up to two rank blocks take 116 registers: where there is one 8-row tile per compute unit, 16 waves hide more
+        // latency than 8 (us, 8 waves in brackets; training, 4096 -> 4096, T = 2048: r = 16 11.7 (14.8), r = 32 14.2 (17.0); T = 1500,
+        // r = 20 13.1 (15.4); 6144 -> 4096, r = 32 16.5 (19.3); 4096 -> 11008 27.7 (28.8)).  Not where waves go without a chunk or a
+        // block, or with few of them (1100 rows of 2048 -> 2048, r = 16 8.2 (6.7), 2048 rows of 5120 -> 2048 11.1 (10.7)).
+        const bool one_per_cu = (T + 7) / 8 > kFewTiles && (T + 7) / 8 <= 256 && d_in >= 3072 && d_out >= 3072;
+        if (t_out != nullptr) {   // (8-row tiles and the plain grid mode have training instantiations)
+            s = L == 2 && one_per_cu ? launch_mfma_rb<8, 16, L>(a, st) : LORDBA_ERR_ALGO;
+            if (s == LORDBA_ERR_ALGO) s = launch_mfma_rb<8, 8, L>(a, st);
         } else if (tall) {
             s = launch_mfma_rb<16, 8, L>(a, st);
             if (s == LORDBA_ERR_ALGO && algo == LORDBA_ALGO_AUTO) s = launch_mfma_rb<8, 8, L>(a, st);
         } else {
-            // a pair of envelopes with one rank block fits the registers of 16 waves (the pair shares an accumulator set);
-            // anything more, or the tuning value 6, runs 8 waves
-            s = algo == 6 ? LORDBA_ERR_ALGO : launch_mfma_rb<8, 16, L>(a, st);
+            // a pair of envelopes with one rank block runs 16 waves (the pair shares an accumulator set), with two where one_per_cu says
+            // so; anything more, or the tuning value 6, runs 8 waves
+            s = algo == 6 || (rb > 1 && !one_per_cu) ? LORDBA_ERR_ALGO : launch_mfma_rb<8, 16, L>(a, st);
             if (s == LORDBA_ERR_ALGO) s = launch_mfma_rb<8, 8, L>(a, st);
         }
     }
