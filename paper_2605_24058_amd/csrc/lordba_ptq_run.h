@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
     double* gfs = cs + kRunWaves * 16;            // [waves][2]
     double* ctl = gfs + 2 * kRunWaves;            // rho, factor of Y, done
     double* red = ctl + 8;                        // [waves][NV]
-    __shared__ uint32_t sh_number, sh_stop[2], place[NV];
+    __shared__ uint32_t sh_number, sh_numbers, sh_stop[2], place[NV];
     int waits = 0;   // (two flags in turn: the next wait's must not be set before every wave has read this one's)
 
     // Value o of a Gram pair as it is stored: whether there is one (bit 0) and it belongs to S (1), its row and column up to 16 (2..5, 6..9), its
@@ -118,15 +118,21 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         G[o] = 0.0;   // (Kt follows G)
     }
     if (threadIdx.x < 16) bs[threadIdx.x] = 0.0;
-    __syncthreads();
     auto arrivals = [&](int p) { return arg->g.sync + (2 + p) * kSyncStride; };
     const bool init = arg->g.t_begin == 0;
     auto per = [&](int p) { return p == 0 ? arg->g.nbU[0] + 1 : p == 1 ? arg->g.nbU[1] : arg->g.nbS[p & 1]; };   // (the first step has a keeper: beta and the penalty)
     const uint32_t per_sweep = static_cast<uint32_t>(per(0) + per(1) + per(2) + per(3));
     const uint32_t n_init = init ? per_sweep - 1u : 0u;
-    const uint32_t sweeps = static_cast<uint32_t>(arg->g.t_end - arg->g.t_begin);
-    // An update that has no carriers (or a run whose signs have repeated) makes no sweeps; the iterates are still set.
-    const bool ended = arg->a.ctrl[kDone] != 0.0;
+    // How many numbers there are.  An update that has no carriers (or a run whose signs have repeated) makes no sweeps; the iterates are
+    // still set.  Behind the last sweep comes one more number: beta and the penalty of that sweep.  One thread reads the end flag for the
+    // workgroup: the keeper of this launch sets it too, and a workgroup that starts as the run ends must leave whole or stay whole (it may
+    // see either value: everything before its number is done by then, and what it would wait for carries the stop bit or soon will).
+    if (threadIdx.x == 0) {
+        const uint32_t sweeps = static_cast<uint32_t>(arg->g.t_end - arg->g.t_begin);
+        if (published(arg->a.ctrl + kDone) != 0.0) sh_numbers = init ? n_init - static_cast<uint32_t>(per(2) + per(3)) : 0u;
+        else sh_numbers = n_init + (sweeps == 0u ? 0u : sweeps * per_sweep + 1u);
+    }
+    __syncthreads();
     auto need = [&](int p, int t) {   // arrivals of step p through sweep t
         const int base = !init ? 0 : p == 0 ? per(0) - 1 : per(p);
         return static_cast<uint32_t>(base + (t - arg->g.t_begin + 1) * per(p));
@@ -198,19 +204,17 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         if (tid == 0) sh_number = __hip_atomic_fetch_add(arg->g.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         uint32_t rest = __builtin_amdgcn_readfirstlane(sh_number);
+        if (rest >= __builtin_amdgcn_readfirstlane(sh_numbers)) break;
         int t = -1, p = 0;
         if (rest >= n_init) {
             rest -= n_init;
             const uint32_t s = rest / per_sweep;
             rest -= s * per_sweep;
-            // (behind the last sweep comes one more number: beta and the penalty of that sweep)
-            if (ended || sweeps == 0u || s > sweeps || (s == sweeps && rest != 0u)) break;
             t = arg->g.t_begin + static_cast<int>(s);
         } else {
             ++rest;   // (the warm start has no keeper)
         }
         for (; rest >= static_cast<uint32_t>(per(p)); ++p) rest -= static_cast<uint32_t>(per(p));
-        if (ended && p >= 2) break;
         // The keeper comes first: the blocks behind it may leave when they see that the run is over, it tells the others.
         const bool keeper = p == 0 && rest == 0u;
         const int blk = static_cast<int>(rest) - (p == 0 && !keeper ? 1 : 0), side = p & 1;

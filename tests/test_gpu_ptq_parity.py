@@ -371,6 +371,31 @@ def test_calls_are_reproducible_and_reuse_a_workspace(torch_cuda):
                                                torch.equal(torch.nan_to_num(first[k]), torch.nan_to_num(b[k]))), k
 
 
+# More workgroups in flight than the device holds, some of which start as their run ends (rank-one updates end after a sweep)
+@pytest.mark.parametrize("shapes", [[(1500, 1100, 16, 16), (900, 2100, 4, 9), (700, 130, 1, 1)], [(1300, 700, 12, 32), (2500, 300, 3, 17)]],
+                         ids=["r0_16", "r0_32"])
+def test_runs_in_flight_on_several_streams(torch_cuda, shapes):
+    torch = torch_cuda
+    cu = lambda d: (torch.from_numpy(d["A_star"]).cuda(), torch.from_numpy(d["B_star"]).cuda())
+    runs = [(cu(inputs.make_ptq_inputs(70 + i, N, M, r0)), R) for i, (N, M, R, r0) in enumerate(shapes)]
+    alone = []
+    for (A, B), R in runs:
+        alone.append(binding.lordba_ptq(A, B, R, K=40))
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    for rep in range(3):
+        held = []
+        for i, s in enumerate(streams):
+            (A, B), R = runs[i % len(runs)]
+            with torch.cuda.stream(s):
+                held.append((i % len(runs), binding.lordba_ptq(A, B, R, K=40)))
+        torch.cuda.synchronize()
+        say("  streams, pass %d" % rep)
+        for i, out in held:
+            for k in ("packedA", "packedB", "alpha", "beta", "gamma", "info", "U1", "U2t"):
+                assert torch.equal(out[k], alone[i][k]), (rep, i, k)
+
+
 def test_a_run_enqueued_in_pieces_is_the_same_run(torch_cuda):
     # lordba_ptq_sweeps: [0, 5) + [5, 6) + [6, 40) against one call of 40 sweeps, bit for bit; the outputs after the first
     # piece are those of the run stopped there (same penalty schedule: K stays 40)
