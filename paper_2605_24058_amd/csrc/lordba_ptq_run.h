@@ -369,8 +369,9 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                         }
                     }
                 }
-                if (last) {   // nobody arrives at this step any more
-                    if (tid < 4) __hip_atomic_fetch_or(arrivals(tid), kStop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (last) {   // nobody arrives at this step any more; where the run is over, the others may be waiting
+                    if (done && tid < 4) __hip_atomic_fetch_or(arrivals(tid), kStop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (before this workgroup counts as gone: whoever leaves last sets the bits back)
                     break;
                 }
                 arrive(0);
@@ -518,7 +519,8 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         share(s, arg->g.partS[side] + static_cast<int64_t>(blk) * count);
         arrive(p);
     }
-    // The last workgroup to leave sets the counters back for the next launch: by then nobody reads them.
+    // The last workgroup to leave sets the counters back for the next launch: by then nobody reads them, and nothing written to them is
+    // still under way.
     if (tid == 0) {
         if (__hip_atomic_fetch_add(arg->g.sync + kSyncStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x) {
             for (int e = 0; e < 6; ++e) __hip_atomic_store(arg->g.sync + e * kSyncStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -418,6 +418,23 @@ def test_a_run_enqueued_in_pieces_is_the_same_run(torch_cuda):
     assert int(whole["info"][0].item()) == ref["sweeps"]
 
 
+# Every sweep a piece of its own, on sides of more blocks than one pass makes and of few, and pieces behind the end of the run
+@pytest.mark.parametrize("N,M,R,r0,K", [(9000, 70, 4, 5, 12), (260, 5000, 5, 17, 12), (100, 80, 16, 32, 20)])
+def test_many_pieces_of_one_sweep(torch_cuda, N, M, R, r0, K):
+    say("  case %dx%d R %d r0 %d" % (N, M, R, r0))
+    torch = torch_cuda
+    d = inputs.make_ptq_inputs(23, N, M, r0)
+    A, B = torch.from_numpy(d["A_star"]).cuda(), torch.from_numpy(d["B_star"]).cuda()
+    whole = binding.lordba_ptq(A, B, R, K=K)
+    part = None
+    for t in range(K):
+        part = binding.lordba_ptq(A, B, R, K=K, sweeps=(t, t + 1), out=part)
+    torch.cuda.synchronize()
+    assert whole["info"][0].item() > 1
+    for k in ("packedA", "packedB", "alpha", "beta", "gamma", "s_in", "s_rank", "s_out", "info", "U1", "U2t"):
+        assert torch.equal(part[k], whole[k]), k
+
+
 def test_graph_replay_matches_eager(torch_cuda):
     # a warmed-up call only launches kernels (no clearing by memset, no allocation, no wait): it can be captured; replays,
     # with eager work of the same library in between, must give the eager result bit for bit

@@ -22,3 +22,15 @@ def test_one_thread_reads_the_end_flag_for_its_workgroup():
     assert not any("}" in line for line in lines[guard:reads[0]])   # (still inside the block of one thread)
     used = [i for i, line in enumerate(lines) if re.search(r"readfirstlane\(sh_numbers\)", line)]
     assert len(used) == 1 and "__syncthreads();" in lines[reads[0]:used[0]]
+
+
+def test_stop_bits_are_written_before_their_workgroup_counts_as_gone():
+    # The last workgroup to leave zeroes the counters; a stop bit that landed after that would end the next piece of the run.
+    lines = _kernel()
+    bits = [i for i, line in enumerate(lines) if "__hip_atomic_fetch_or(" in line]
+    gone = [i for i, line in enumerate(lines) if "__hip_atomic_fetch_add(arg->g.sync + kSyncStride" in line]
+    assert len(bits) == 1 and len(gone) == 1 and bits[0] < gone[0]
+    waits = [i for i in range(bits[0], gone[0]) if "s_waitcnt vmcnt(0)" in lines[i]]
+    leaves = [i for i in range(bits[0], gone[0]) if lines[i].startswith("break;")]
+    assert waits and leaves and waits[0] < leaves[0]
+    assert re.match(r"if \(done && ", lines[bits[0]])   # (at the end of a piece nobody waits: no bits at all)
