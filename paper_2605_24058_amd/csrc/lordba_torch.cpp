@@ -9,6 +9,7 @@
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -50,8 +51,9 @@ bool stream_of(PyObject* o, const at::Tensor* t, void** out) {
     return true;
 }
 
-// Nobody watches torch's own functions (a mode that does would miss the allocations made here).
-bool unwatched() { return at::impl::PythonTorchFunctionTLS::stack_len() == 0; }
+// Nobody watches or replaces torch's own functions (a mode that does would miss the allocations made here, or hand out tensors that have
+// no memory).
+bool unwatched() { return at::impl::PythonTorchFunctionTLS::stack_len() == 0 && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
 at::Tensor empty(const at::Tensor* like, at::ScalarType type, std::initializer_list<int64_t> s) {
     return at::empty(at::IntArrayRef(s), at::TensorOptions().dtype(type).device(like->device()));
@@ -91,7 +93,17 @@ struct Forward {   // what the four forward calls share: x, packedA, packedB, s_
 
 PyObject* result(const at::Tensor& t, int st) { return st == LORDBA_OK ? THPVariable_Wrap(t) : PyLong_FromLong(st); }
 
-#define CALL(st, expr) int st; Py_BEGIN_ALLOW_THREADS st = expr; Py_END_ALLOW_THREADS
+// f(a...) without the interpreter's lock.  The arguments are evaluated while it is held: a tensor may refuse its pointer, and an
+// exception that passes must find the lock.
+struct Unlocked {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <class F, class... A>
+int unlocked(F* f, A... a) {
+    Unlocked here;
+    return f(a...);
+}
 
 // (x, packedA, packedB, s_in, s_rank, s_out, y_base, y_out, stream)
 PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -101,8 +113,8 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* st;
     at::Tensor y;
     NEED(n == 9 && unwatched() && f.read(a, a[6]) && f.single(&r) && stream_of(a[8], f.x, &st) && output_like(a[7], f.yb, &y));
-    CALL(rc, lordba_forward(ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si), ptr<void>(f.sr), ptr<void>(f.so),
-                            ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r, st));
+    const int rc = unlocked(lordba_forward, ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si), ptr<void>(f.sr),
+                            ptr<void>(f.so), ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r, st);
     return result(y, rc);
     END_HANDLE_TH_ERRORS
 }
@@ -114,8 +126,8 @@ PyObject* forward_multi(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* st;
     at::Tensor y;
     NEED(n == 9 && unwatched() && f.read(a, a[6]) && f.multi(&ell, &r) && stream_of(a[8], f.x, &st) && output_like(a[7], f.yb, &y));
-    CALL(rc, lordba_forward_multi(ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si), ptr<void>(f.sr),
-                                  ptr<void>(f.so), ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r, ell, st));
+    const int rc = unlocked(lordba_forward_multi, ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si),
+                            ptr<void>(f.sr), ptr<void>(f.so), ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r, ell, st);
     return result(y, rc);
     END_HANDLE_TH_ERRORS
 }
@@ -132,8 +144,9 @@ PyObject* forward_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t na = f.sr->size(0), r = f.sr->size(1);
     NEED(shaped(f.si, {na, f.d_in}) && shaped(f.so, {na, f.d_out}) && shaped(f.pA, {na, words(r, f.d_in)}) &&
          shaped(f.pB, {na, words(f.d_out, r)}) && stream_of(a[9], f.x, &st) && output_like(a[8], f.yb, &y));
-    CALL(rc, lordba_forward_batched(ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si), ptr<void>(f.sr),
-                                    ptr<void>(f.so), ptr<int32_t>(ids), ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r, na, st));
+    const int rc = unlocked(lordba_forward_batched, ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si),
+                            ptr<void>(f.sr), ptr<void>(f.so), ptr<int32_t>(ids), ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r,
+                            na, st);
     return result(y, rc);
     END_HANDLE_TH_ERRORS
 }
@@ -149,9 +162,9 @@ PyObject* forward_batched_multi(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t na = f.sr->size(0), ell = f.sr->size(1), r = f.sr->size(2);
     NEED(shaped(f.si, {na, ell, f.d_in}) && shaped(f.so, {na, ell, f.d_out}) && shaped(f.pA, {na, words(r, f.d_in)}) &&
          shaped(f.pB, {na, words(f.d_out, r)}) && stream_of(a[9], f.x, &st) && output_like(a[8], f.yb, &y));
-    CALL(rc, lordba_forward_batched_multi(ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si), ptr<void>(f.sr),
-                                          ptr<void>(f.so), ptr<int32_t>(ids), ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r, ell,
-                                          na, st));
+    const int rc = unlocked(lordba_forward_batched_multi, ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si),
+                            ptr<void>(f.sr), ptr<void>(f.so), ptr<int32_t>(ids), ptr<void>(f.yb), ptr<void>(y), f.T, f.d_in, f.d_out, r,
+                            ell, na, st);
     return result(y, rc);
     END_HANDLE_TH_ERRORS
 }
@@ -167,9 +180,9 @@ PyObject* pack_latents(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t r = A->size(0), d_in = A->size(1), d_out = B->size(0), wA = words(r, d_in), wB = words(d_out, r);
     at::Tensor out[4];
     for (int i = 0; i < (a[3] == Py_True ? 4 : 2); ++i) out[i] = empty(A, kI32, {i & 1 ? wB : wA});
-    CALL(rc, lordba_pack_latents(ptr<float>(A), ptr<float>(B), ptr<uint32_t>(out[0]), ptr<uint32_t>(out[1]),
-                                 out[2].defined() ? ptr<uint32_t>(out[2]) : nullptr, out[3].defined() ? ptr<uint32_t>(out[3]) : nullptr, d_in,
-                                 d_out, r, st));
+    const int rc = unlocked(lordba_pack_latents, ptr<float>(A), ptr<float>(B), ptr<uint32_t>(out[0]), ptr<uint32_t>(out[1]),
+                            out[2].defined() ? ptr<uint32_t>(out[2]) : nullptr, out[3].defined() ? ptr<uint32_t>(out[3]) : nullptr, d_in,
+                            d_out, r, st);
     if (rc != LORDBA_OK) return PyLong_FromLong(rc);
     PyObject* t = PyTuple_New(4);
     for (int i = 0; t && i < 4; ++i) PyTuple_SET_ITEM(t, i, THPVariable_Wrap(out[i]));   // (an undefined tensor becomes None)
@@ -185,11 +198,12 @@ PyObject* save_t(PyObject* const* a, Py_ssize_t n, bool many) {
     NEED(n == 8 && unwatched() && f.read(a, a[6]) && (many ? f.multi(&ell, &r) : f.single(&r)) && stream_of(a[7], f.x, &st));
     const int64_t stride = (f.T + 127) / 128 * 128;
     at::Tensor t = many ? empty(f.x, kF32, {ell, r, stride}) : empty(f.x, kF32, {r, stride}), y = at::empty_like(*f.yb);
-    CALL(rc, many ? lordba_forward_multi_save_t(ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si), ptr<void>(f.sr),
-                                                ptr<void>(f.so), ptr<void>(f.yb), ptr<void>(y), ptr<float>(t), stride, f.T, f.d_in, f.d_out, r,
-                                                ell, st)
-                  : lordba_forward_save_t(ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si), ptr<void>(f.sr),
-                                          ptr<void>(f.so), ptr<void>(f.yb), ptr<void>(y), ptr<float>(t), stride, f.T, f.d_in, f.d_out, r, st));
+    const int rc = many ? unlocked(lordba_forward_multi_save_t, ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB),
+                                   ptr<void>(f.si), ptr<void>(f.sr), ptr<void>(f.so), ptr<void>(f.yb), ptr<void>(y), ptr<float>(t),
+                                   stride, f.T, f.d_in, f.d_out, r, ell, st)
+                        : unlocked(lordba_forward_save_t, ptr<void>(f.x), ptr<uint32_t>(f.pA), ptr<uint32_t>(f.pB), ptr<void>(f.si),
+                                   ptr<void>(f.sr), ptr<void>(f.so), ptr<void>(f.yb), ptr<void>(y), ptr<float>(t), stride, f.T, f.d_in,
+                                   f.d_out, r, st);
     if (rc != LORDBA_OK) return PyLong_FromLong(rc);
     PyObject* out = PyTuple_New(2);
     if (out) {
@@ -252,13 +266,14 @@ PyObject* backward_any(PyObject* const* a, Py_ssize_t n, bool many) {
     for (int i = 0; i < 5; ++i) gp[i] = out[i].defined() ? ptr<float>(out[i]) : nullptr;
     const float kappa = static_cast<float>(PyFloat_AS_DOUBLE(a[10]));
     const int64_t stride = ts ? ts->size(many ? 2 : 1) : 0;
-    CALL(rc, many ? lordba_backward_multi(ptr<void>(x), ptr<void>(g), ptr<uint32_t>(pA), ptr<uint32_t>(pAt), ptr<uint32_t>(pBt), ptr<void>(si),
-                                          ptr<void>(sr), ptr<void>(so), ptr<float>(lA), ptr<float>(lB), kappa, ptr<float>(ts), stride,
-                                          ptr<void>(dxb), dxp, gp[0], gp[1], gp[2], gp[3], gp[4], ptr<void>(ws), ws->numel(), T, d_in, d_out,
-                                          r, ell, st)
-                  : lordba_backward(ptr<void>(x), ptr<void>(g), ptr<uint32_t>(pA), ptr<uint32_t>(pAt), ptr<uint32_t>(pBt), ptr<void>(si),
-                                    ptr<void>(sr), ptr<void>(so), ptr<float>(lA), ptr<float>(lB), kappa, ptr<float>(ts), stride, ptr<void>(dxb),
-                                    dxp, gp[0], gp[1], gp[2], gp[3], gp[4], ptr<void>(ws), ws->numel(), T, d_in, d_out, r, st));
+    const int rc = many ? unlocked(lordba_backward_multi, ptr<void>(x), ptr<void>(g), ptr<uint32_t>(pA), ptr<uint32_t>(pAt),
+                                   ptr<uint32_t>(pBt), ptr<void>(si), ptr<void>(sr), ptr<void>(so), ptr<float>(lA), ptr<float>(lB),
+                                   kappa, ptr<float>(ts), stride, ptr<void>(dxb), dxp, gp[0], gp[1], gp[2], gp[3], gp[4], ptr<void>(ws),
+                                   ws->numel(), T, d_in, d_out, r, ell, st)
+                        : unlocked(lordba_backward, ptr<void>(x), ptr<void>(g), ptr<uint32_t>(pA), ptr<uint32_t>(pAt),
+                                   ptr<uint32_t>(pBt), ptr<void>(si), ptr<void>(sr), ptr<void>(so), ptr<float>(lA), ptr<float>(lB),
+                                   kappa, ptr<float>(ts), stride, ptr<void>(dxb), dxp, gp[0], gp[1], gp[2], gp[3], gp[4], ptr<void>(ws),
+                                   ws->numel(), T, d_in, d_out, r, st);
     if (rc != LORDBA_OK) return PyLong_FromLong(rc);
     static PyObject* const names[6] = {PyUnicode_InternFromString("dx"),      PyUnicode_InternFromString("d_s_in"),
                                        PyUnicode_InternFromString("d_s_rank"), PyUnicode_InternFromString("d_s_out"),

@@ -104,3 +104,47 @@ def test_training_calls(monkeypatch, ell):
             a, b = _both(monkeypatch, lambda: back(x, gy, pA, pAt, pBt, *s, *lat, 100.0, **kw))
             assert _same(a, b), kw.keys()
     assert isinstance(_both(monkeypatch, lambda: back(x, gy, pA, pAt, pBt, *s, latA, latB, 100, dx_base=dxb))[0], dict)   # an int kappa
+
+
+@pytest.mark.gpu
+def test_tensors_that_refuse_their_pointer(monkeypatch):
+    # The exception rises where the call is about to give the interpreter's lock away; for every call
+    def refusing(t):
+        t = t.clone()
+        torch._C._set_throw_on_mutable_data_ptr(t)
+        return t
+
+    for name, ell, pool in (("lordba_forward", 1, False), ("lordba_forward_multi", 2, False), ("lordba_forward_batched", 1, True),
+                            ("lordba_forward_batched_multi", 2, True)):
+        p = _case(ell, pool)
+        for k in range(len(p)):
+            q = p[:k] + [refusing(p[k])] + p[k + 1:]
+            assert _both(monkeypatch, lambda: getattr(binding, name)(*q)) == [RuntimeError, RuntimeError], (name, k)
+        assert _both(monkeypatch, lambda: getattr(binding, name)(*p, y_out=refusing(p[-1]))) == [RuntimeError, RuntimeError], name
+    x, pA, pB, si, sr, so, yb = _case(1, False)
+    assert _both(monkeypatch, lambda: binding.lordba_forward_save_t(x, pA, refusing(pB), si, sr, so, y_base=yb)) == [RuntimeError] * 2
+    lat = torch.ones(8, 64).cuda(), torch.ones(48, 8).cuda()
+    assert _both(monkeypatch, lambda: binding.lordba_pack_latents(lat[0], refusing(lat[1]))) == [RuntimeError] * 2
+    args = [x, yb, pA, pA, pB, si, sr, so, *lat, 100.0]
+    for k in range(10):
+        q = args[:k] + [refusing(args[k])] + args[k + 1:]
+        assert _both(monkeypatch, lambda: binding.lordba_backward(*q, dx_base=x.clone())) == [RuntimeError] * 2, k
+
+
+@pytest.mark.gpu
+def test_modes_that_see_torchs_functions_get_the_bindings_own_way():
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Watch(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    m, p = binding._load_torch_module(), _case(1, False)
+    assert isinstance(m.forward(*p, None, None), torch.Tensor)
+    with Watch():
+        assert m.forward(*p, None, None) is None
+        under = binding.lordba_forward(*p)
+    assert _same(under, binding.lordba_forward(*p))
+    with FakeTensorMode(allow_non_fake_inputs=True):
+        assert m.forward(*p, None, None) is None   # (its output would have no memory)
