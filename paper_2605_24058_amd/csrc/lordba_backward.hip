@@ -770,10 +770,13 @@ lordba_status backward_impl(const void* x, const void* g,
     s = lordba_forward_multi_save_t(g, packedBt, packedAt, s_out, s_rank, s_in, dx_base, dx, duT, p.t_pad, T, d_out, d_in, r, ell, stream);
     if (s != LORDBA_OK) return s;
     if (t_saved == nullptr) {
-        // t of every envelope: the forward branch of the adapter itself, stopped after its rank-r intermediate (its second
-        // carrier is not read; packedAt stands in as a valid [d_in, r] carrier)
-        s = lordba_forward_multi_save_t(x, packedA, packedAt, s_in, s_rank, s_in, nullptr, nullptr, t_own, p.t_pad, T, d_in, d_in, r, ell,
-                                        stream);
+        // t of every envelope: the forward branch of the adapter itself, stopped after its rank-r intermediate.  Its second carrier and
+        // s_out are not read: with several envelopes it gets the adapter's own d_out, which the forward that keeps t chooses its number of
+        // waves by, so that the sums are the same (packedBt stands in as a carrier of as many bits); with one, and for what the plain
+        // matrix-core kernels do not take, d_in (packedAt).
+        const bool own = ell > 1 && fast && aligned_to(packedBt, 16);
+        s = lordba_forward_multi_save_t(x, packedA, own ? packedBt : packedAt, s_in, s_rank, own ? s_out : s_in, nullptr, nullptr, t_own, p.t_pad,
+                                        T, d_in, own ? d_out : d_in, r, ell, stream);
         if (s != LORDBA_OK) return s;
     }
     for (int64_t e = 0; e < (fused ? 1 : ell); ++e) {

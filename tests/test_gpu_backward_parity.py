@@ -394,6 +394,25 @@ def test_several_envelopes_in_one_pass(torch_cuda, case):
     assert np.array_equal(results["by_envelope"]["dx"], results["one_pass"]["dx"])
 
 
+# Where the forward that keeps t chooses its number of waves: d_out on either side of the line and on it, one 8-row tile per compute unit
+# and one more
+@pytest.mark.parametrize("case", [(2, 2048, 4096, 2048, 16), (2, 1033, 3072, 512, 30), (2, 1500, 3072, 3072, 32), (2, 1100, 1024, 4096, 8),
+                                  (2, 2049, 4096, 2048, 16), (3, 1200, 4096, 512, 16)], ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
+def test_a_kept_t_of_several_envelopes_is_the_recomputed_one(torch_cuda, case):
+    torch = torch_cuda
+    ell, T, d_in, d_out, r = case
+    g = torch.Generator().manual_seed(5)
+    half = lambda *shape: torch.randn(shape, generator=g).half().cuda()
+    lat = torch.randn(r, d_in, generator=g).cuda(), torch.randn(d_out, r, generator=g).cuda()
+    pA, pB, pAt, pBt = binding.lordba_pack_latents(*lat)
+    x, gy, scales = half(T, d_in), half(T, d_out), (half(ell, d_in), half(ell, r), half(ell, d_out))
+    _, t = binding.lordba_forward_multi_save_t(x, pA, pB, *scales, y_base=half(T, d_out))
+    out = [binding.lordba_backward_multi(x, gy, pA, pAt, pBt, *scales, *lat, KAPPA, t_saved=kept) for kept in (None, t)]
+    torch.cuda.synchronize()
+    for k in ("d_s_in", "d_s_rank", "d_s_out", "d_latentA", "d_latentB"):
+        assert torch.equal(out[0][k], out[1][k]), k
+
+
 def test_frozen_carriers_scale_gradients_only(torch_cuda):
     """latentA = latentB = None (only the scales are trained): the scale gradients and dx are bit-identical to the full
     call's, and no latent gradient is produced."""
