@@ -8,10 +8,12 @@ the current torch stream is passed as the hipStream_t.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 from typing import Optional, Tuple
 
 import numpy as np
@@ -43,39 +45,54 @@ class LordbaError(RuntimeError):
 
 def build_library(verbose: bool = False) -> str:
     """Compile the HIP library for gfx950 with hipcc (cross-compiles without a GPU).  The translation units are
-    compiled side by side (the kernel templates take most of the time), then linked."""
+    compiled side by side (the kernel templates take most of the time), then linked.  The C++ module of this binding is
+    compiled beside them where there is a torch for ROCm (a C program needs the library alone), and linked behind it."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tag = ".tmp.%d" % os.getpid()
     flags = [f for f in HIPCC_FLAGS if f != "-shared"]
     objs, procs = [], []
     for src in _SOURCES:
         obj = os.path.join(_PKG, src + tag + ".o")
-        cmd = [hipcc] + flags + ["-I", os.path.join(_ROOT, "include"), "-c", os.path.join(_CSRC, src), "-o", obj]
-        if verbose:
-            print(" ".join(cmd), file=sys.stderr)
+        procs.append(_start([hipcc] + flags + ["-I", os.path.join(_ROOT, "include"), "-c", os.path.join(_CSRC, src), "-o", obj], verbose))
         objs.append(obj)
-        procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
-    obj, cmd = _torch_module_command(tag)
-    if verbose:
-        print(" ".join(cmd), file=sys.stderr)
-    objs.append(obj)
-    procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
-    outs = [p.communicate()[0] for p in procs]
+    module, started = _torch_module_command(tag), None
+    if module is not None:
+        started = _start(module[1], verbose)
     tmp = _LIB_PATH + tag
     try:
-        for p, out in zip(procs, outs):
-            out = "\n".join(l for l in out.splitlines() if "not a recognized feature for this target" not in l)
-            if p.returncode != 0:
-                raise RuntimeError("compilation failed:\n" + out)
-            if verbose and out.strip():
-                print(out, file=sys.stderr)
-        _link([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs[:-1], tmp, _LIB_PATH)
-        _link_torch_module(obj, tmp)
+        outs = [_finish(p, verbose) for p in procs]
+        failed = [out for p, out in zip(procs, outs) if p.returncode != 0]
+        if failed:
+            raise RuntimeError("compilation failed:\n" + "\n".join(failed))
+        _link([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs, tmp, _LIB_PATH)
+        if module is None:
+            print("no torch for ROCm: built without the module that takes its tensors", file=sys.stderr)
+        else:
+            out = _finish(started, verbose)
+            if started.returncode != 0:
+                raise RuntimeError("the library is built, its torch module is not; compilation failed:\n" + out)
+            _link_torch_module(module[0], tmp)
     finally:
-        for f in objs + [tmp]:
+        if started is not None and started.poll() is None:
+            started.communicate()
+        for f in objs + [tmp] + ([module[0]] if module else []):
             if os.path.exists(f):
                 os.remove(f)
     return _LIB_PATH
+
+
+def _start(cmd, verbose: bool):
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    return subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
+
+def _finish(proc, verbose: bool) -> str:
+    """The output of a compiler that has ended (hipcc's host pass warns that it does not know a feature of the GPU)."""
+    out = "\n".join(l for l in proc.communicate()[0].splitlines() if "not a recognized feature for this target" not in l)
+    if verbose and out.strip() and proc.returncode == 0:
+        print(out, file=sys.stderr)
+    return out
 
 
 def _link(cmd, tmp: str, target: str) -> None:
@@ -86,9 +103,14 @@ def _link(cmd, tmp: str, target: str) -> None:
 
 
 def _torch_module_command(tag: str):
-    """The object file of the module that takes torch tensors, and the command that compiles it (host code only)."""
-    import torch
-
+    """The object file of the module that takes torch tensors, and the command that compiles it (host code only); None where
+    there is no torch for ROCm."""
+    try:
+        import torch
+    except ImportError:
+        return None
+    if torch.version.hip is None:
+        return None
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
     obj = os.path.join(_PKG, "lordba_torch.cpp" + tag + ".o")
     return obj, [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
@@ -203,22 +225,24 @@ def load_library():
 
 
 def _load_torch_module():
-    """The C++ module that takes torch tensors.  As for the library there is no fallback: not built is an error."""
+    """The C++ module that takes torch tensors; False where it is not built or does not load (it was built for another torch):
+    every call then goes through ctypes, with the same results and about 3 us more of the host's time."""
     global _torch_module
     load_library()
-    if not os.path.exists(_TORCH_MODULE_PATH):
-        raise RuntimeError("_lordba_torch.so is not built: run __graft_entry__.build() first")
     import torch  # noqa: F401  (its libraries have to be in the process)
-    from . import _lordba_torch
-
-    _torch_module = _lordba_torch
-    return _lordba_torch
+    try:
+        _torch_module = importlib.import_module("._lordba_torch", __package__)
+    except ImportError as e:
+        warnings.warn("the binding's C++ module is not there, calls take longer on the host (run __graft_entry__.build()): %s" % e)
+        _torch_module = False
+    return _torch_module
 
 
 def _plain_call(name: str, *args):
-    """The call through the C++ module: its result, or None where the arguments are not the plain case, which the caller then
-    takes (and checks) itself."""
-    res = getattr(_torch_module or _load_torch_module(), name)(*args)
+    """The call through the C++ module: its result, or None where there is none or the arguments are not the plain case, which the
+    caller then takes (and checks) itself."""
+    module = _load_torch_module() if _torch_module is None else _torch_module
+    res = getattr(module, name)(*args) if module else None
     if type(res) is int:
         raise LordbaError(res, "lordba_" + name)
     return res
