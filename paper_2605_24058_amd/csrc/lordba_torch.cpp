@@ -12,6 +12,7 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/PyInterpreter.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "lordba.h"
@@ -52,8 +53,25 @@ bool stream_of(PyObject* o, const at::Tensor* t, void** out) {
 }
 
 // Nobody watches or replaces torch's own functions (a mode that does would miss the allocations made here, or hand out tensors that have
-// no memory).
-bool unwatched() { return at::impl::PythonTorchFunctionTLS::stack_len() == 0 && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
+// no memory).  Default devices are modes too (torch.set_default_device, `with torch.device(...)`) and concern nothing here: every
+// allocation names its device.
+PyObject* device_mode = nullptr;   // torch.utils._device.DeviceContext
+bool unwatched() {
+    for (int64_t i = at::impl::PythonTorchFunctionTLS::stack_len() - 1; i >= 0; --i) {
+        PyObject* mode = at::impl::PythonTorchFunctionTLS::get_stack_at(i)->ptr(getPyInterpreter());
+        if (reinterpret_cast<PyObject*>(Py_TYPE(mode)) != device_mode) return false;
+    }
+    return !c10::impl::TorchDispatchModeTLS::any_modes_set();
+}
+
+// A number of the kind that float() takes as it is: a float or an int (others go the binding's own way).
+bool number(PyObject* o, float* out) {
+    if (!PyFloat_Check(o) && !PyLong_Check(o)) return false;
+    const double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) { PyErr_Clear(); return false; }
+    *out = static_cast<float>(v);
+    return true;
+}
 
 at::Tensor empty(const at::Tensor* like, at::ScalarType type, std::initializer_list<int64_t> s) {
     return at::empty(at::IntArrayRef(s), at::TensorOptions().dtype(type).device(like->device()));
@@ -239,7 +257,8 @@ PyObject* backward_any(PyObject* const* a, Py_ssize_t n, bool many) {
     NEED(lat == (a[9] != Py_None));
     const at::Tensor *lA = lat ? plain(a[8], kF32) : nullptr, *lB = lat ? plain(a[9], kF32) : nullptr;
     NEED(!lat || (lA && lB && shaped(lA, {r, d_in}) && shaped(lB, {d_out, r})));
-    NEED(PyFloat_CheckExact(a[10]));
+    float kappa;
+    NEED(number(a[10], &kappa));
     const at::Tensor *dxb = a[11] == Py_None ? nullptr : plain(a[11], kF16), *ws = a[12] == Py_None ? nullptr : plain(a[12], at::kByte);
     const at::Tensor* ts = a[14] == Py_None ? nullptr : plain(a[14], kF32);
     NEED((dxb || a[11] == Py_None) && (ws || a[12] == Py_None) && (ts || a[14] == Py_None));
@@ -264,7 +283,6 @@ PyObject* backward_any(PyObject* const* a, Py_ssize_t n, bool many) {
     void* const dxp = dxb ? ptr<void>(dx) : nullptr;
     float* gp[5];
     for (int i = 0; i < 5; ++i) gp[i] = out[i].defined() ? ptr<float>(out[i]) : nullptr;
-    const float kappa = static_cast<float>(PyFloat_AS_DOUBLE(a[10]));
     const int64_t stride = ts ? ts->size(many ? 2 : 1) : 0;
     const int rc = many ? unlocked(lordba_backward_multi, ptr<void>(x), ptr<void>(g), ptr<uint32_t>(pA), ptr<uint32_t>(pAt),
                                    ptr<uint32_t>(pBt), ptr<void>(si), ptr<void>(sr), ptr<void>(so), ptr<float>(lA), ptr<float>(lB),
@@ -309,4 +327,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_lordba_torch", nullptr, -1, metho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__lordba_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__lordba_torch() {
+    if (PyObject* m = PyImport_ImportModule("torch.utils._device")) {
+        device_mode = PyObject_GetAttrString(m, "DeviceContext");
+        Py_DECREF(m);
+    }
+    PyErr_Clear();   // (a torch without it: such modes then go the binding's own way)
+    return PyModule_Create(&module);
+}

@@ -148,3 +148,39 @@ def test_modes_that_see_torchs_functions_get_the_bindings_own_way():
     assert _same(under, binding.lordba_forward(*p))
     with FakeTensorMode(allow_non_fake_inputs=True):
         assert m.forward(*p, None, None) is None   # (its output would have no memory)
+
+
+@pytest.mark.gpu
+def test_default_devices_and_whole_numbers_are_the_plain_case(monkeypatch):
+    from torch.overrides import TorchFunctionMode
+    from torch.utils._device import DeviceContext
+
+    class Watch(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    m, p = binding._load_torch_module(), _case(1, False)
+    want = m.forward(*p, None, None)
+    with torch.device("cpu"), torch.device("cuda"):
+        assert _same(m.forward(*p, None, None), want)
+    torch.set_default_device("cpu")
+    try:
+        assert _same(m.forward(*p, None, None), want)
+        with Watch():
+            assert m.forward(*p, None, None) is None
+    finally:
+        torch.set_default_device(None)
+    with Watch(), torch.device("cpu"):
+        assert m.forward(*p, None, None) is None
+    with type("Other", (DeviceContext,), {})(torch.device("cpu")):
+        assert m.forward(*p, None, None) is None
+
+    x, pA, pB, si, sr, so, yb = p
+    lat = torch.ones(8, 64).cuda(), torch.ones(48, 8).cuda()
+    back = lambda kappa: m.backward(x, yb, pA, pA, pB, si, sr, so, *lat, kappa, None, None, None, None)
+    for kappa in (100, 100.0, True, np.float64(25.0), 10**400, np.float32(3.0), "100", None):
+        got = back(kappa)
+        plain = isinstance(kappa, float) or (isinstance(kappa, int) and kappa < 10**300)
+        assert (got is not None) == plain, kappa
+        if plain:
+            assert _same(got, back(float(kappa))), kappa
