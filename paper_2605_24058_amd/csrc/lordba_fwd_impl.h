@@ -1407,8 +1407,11 @@ lordba_status forward_impl(const void* x, const uint32_t* packedA, const uint32_
         // Two envelopes of up to two rank blocks take 116 registers: where there is one 8-row tile per compute unit, 16 waves hide more
         // latency than 8 (us, 8 waves in brackets; training, 4096 -> 4096, T = 2048: r = 16 11.7 (14.8), r = 32 14.2 (17.0); T = 1500,
         // r = 20 13.1 (15.4); 6144 -> 4096, r = 32 16.5 (19.3); 4096 -> 11008 27.7 (28.8)).  Not where waves go without a chunk or a
-        // block, or with few of them (1100 rows of 2048 -> 2048, r = 16 8.2 (6.7), 2048 rows of 5120 -> 2048 11.1 (10.7)).
-        const bool one_per_cu = (T + 7) / 8 > kFewTiles && (T + 7) / 8 <= 256 && d_in >= 3072 && d_out >= 3072;
+        // block, or with few of them (1100 rows of 2048 -> 2048, r = 16 8.2 (6.7), 2048 rows of 5120 -> 2048 11.1 (10.7)); and only while the
+        // x pipeline of the 16 waves is one-shot, 64 chunks: 8192 -> 4096 gains 8 to 17 % at T = 1100 to 2048, beyond that both loop over groups
+        // of four and most calls lose (T = 1100, r = 32: 10240 -> 3072 19.6 (17.6), 11008 -> 8192 26.3 (25.4); T = 2048, 20480 -> 8192 41.1
+        // (39.0); the gains there are single blocks in training, 13824 -> 8192, r = 16 22.4 (25.0)).
+        const bool one_per_cu = (T + 7) / 8 > kFewTiles && (T + 7) / 8 <= 256 && d_in >= 3072 && d_in <= 8192 && d_out >= 3072;
         if (t_out != nullptr) {   // (8-row tiles and the plain grid mode have training instantiations)
             s = L == 2 && one_per_cu ? launch_mfma_rb<8, 16, L>(a, st) : LORDBA_ERR_ALGO;
             if (s == LORDBA_ERR_ALGO) s = launch_mfma_rb<8, 8, L>(a, st);

@@ -397,7 +397,7 @@ def test_several_envelopes_in_one_pass(torch_cuda, case):
 # Where the forward that keeps t chooses its number of waves: d_out on either side of the line and on it, one 8-row tile per compute unit
 # and one more
 @pytest.mark.parametrize("case", [(2, 2048, 4096, 2048, 16), (2, 1033, 3072, 512, 30), (2, 1500, 3072, 3072, 32), (2, 1100, 1024, 4096, 8),
-                                  (2, 2049, 4096, 2048, 16), (3, 1200, 4096, 512, 16)], ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
+                                  (2, 1030, 8224, 3072, 16), (2, 2049, 4096, 2048, 16), (3, 1200, 4096, 512, 16)], ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
 def test_a_kept_t_of_several_envelopes_is_the_recomputed_one(torch_cuda, case):
     torch = torch_cuda
     ell, T, d_in, d_out, r = case

@@ -54,8 +54,9 @@ PLANS = [
     # three slots on 16 waves and six on 8 (40 to 48 chunks, the last one whole or ragged), and the plans beside them
     (1033, 5120, 512, 16, 1), (2047, 6144, 264, 8, 1), (1033, 5088, 2056, 12, 1), (2049, 5120, 136, 32, 1), (1029, 6144, 1032, 50, 1),
     (1027, 5088, 512, 64, 1), (2051, 5120, 512, 20, 1), (1025, 4992, 512, 32, 1), (1030, 6176, 512, 48, 1),
-    # two envelopes on 16 waves, and on 8 beyond one tile per compute unit
-    (1033, 3072, 3080, 30, 2), (2048, 3104, 3072, 16, 2), (1025, 5120, 3072, 32, 2), (1026, 8352, 3080, 5, 2), (2049, 3072, 3072, 32, 2),
+    # two envelopes on 16 waves, and on 8 beyond one tile per compute unit and beyond four chunks per wave
+    (1033, 3072, 3080, 30, 2), (2048, 3104, 3072, 16, 2), (1025, 5120, 3072, 32, 2), (2049, 3072, 3072, 32, 2),
+    (1027, 8192, 3072, 20, 2), (1029, 8224, 3080, 32, 2), (1026, 8352, 3080, 5, 2),
     # several envelopes at a general rank: up to one block per wave, and one block more
     (1100, 256, 256, 30, 3), (1031, 96, 1024, 2, 4), (1029, 160, 1032, 20, 3), (5, 160, 136, 30, 4), (1027, 64, 72, 1, 3), (300, 256, 2056, 44, 3),
 ]
