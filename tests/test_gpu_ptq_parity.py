@@ -106,10 +106,12 @@ def test_full_run_matches_oracle(torch_cuda, seed, N, M, R, r0):
     compare(res, ref, K)
 
 
-# Rows at the edges of the groups of 16 blocks of 32 rows whose shares are added up together: one group, one block more, the
-# most groups, one block too many on one side (its shares are then added up by a kernel of its own); and a share of more values
-# than a group takes
-@pytest.mark.parametrize("N,M,R,r0", [(512, 513, 4, 6), (31, 8192, 3, 4), (8193, 40, 3, 4), (40, 8193, 3, 4), (545, 600, 16, 49)])
+# Rows at the edges of the groups of 16 blocks of 32 rows whose shares the row kernels of a sweep add up together (factor ranks beyond 32,
+# which take launches per sweep): one group, one block more, the most groups, one block too many on either side (its shares are then
+# added up by a kernel of its own); and a share of more values than a group takes.  At smaller factor ranks the same rows go through
+# the one launch for all sweeps: one pass of its blocks, and more than one.
+@pytest.mark.parametrize("N,M,R,r0", [(512, 513, 4, 6), (31, 8192, 3, 4), (8193, 40, 3, 4), (40, 8193, 3, 4), (545, 600, 16, 49),
+                                      (512, 513, 4, 40), (31, 8192, 3, 40), (8193, 40, 3, 40), (40, 8193, 3, 40)])
 def test_groups_of_blocks(torch_cuda, N, M, R, r0):
     d = inputs.make_ptq_inputs(61, N, M, r0)
     say("  case %dx%d R %d r0 %d" % (N, M, R, r0))
@@ -127,6 +129,16 @@ def test_panels_and_blocks(torch_cuda, N, M, R, r0):
     K = 12
     ref = P.ptq(d["A_star"], d["B_star"], R, K=K)
     compare(run_gpu(torch_cuda, d, R, K=K), ref, K)
+
+
+# Factor ranks from 17 to 32 in the one launch (two tiles of K per Gram pair), whole runs: the ranks' limits, a tile with one column, one
+# and several passes per block, fewer rows than a block
+@pytest.mark.parametrize("N,M,R,r0", [(300, 260, 16, 32), (200, 333, 5, 17), (4096, 65, 9, 24), (9001, 300, 8, 20), (70, 17000, 2, 32), (33, 40, 16, 31)])
+def test_two_tiles_of_factor_ranks(torch_cuda, N, M, R, r0):
+    say("  case %dx%d R %d r0 %d" % (N, M, R, r0))
+    d = inputs.make_ptq_inputs(63, N, M, r0)
+    ref = P.ptq(d["A_star"], d["B_star"], R, K=100)
+    compare(run_gpu(torch_cuda, d, R, K=100), ref, 100)
 
 
 @pytest.mark.parametrize("K", [1, 2, 3, 7])
