@@ -51,8 +51,16 @@ def _same(a, b):
     if isinstance(a, (tuple, list)):
         return len(a) == len(b) and all(_same(u, v) for u, v in zip(a, b))
     if isinstance(a, torch.Tensor):
-        return a.dtype == b.dtype and a.shape == b.shape and torch.equal(torch.nan_to_num(a.float()), torch.nan_to_num(b.float()))
+        if not isinstance(b, torch.Tensor) or a.dtype != b.dtype or a.shape != b.shape:
+            return False
+        bits = {torch.float16: torch.int16, torch.float32: torch.int32}.get(a.dtype, a.dtype)
+        return torch.equal(a.view(bits), b.view(bits))
     return a is b
+
+
+def test_the_comparison_is_by_bits():
+    a, b = torch.tensor([1.0, float("nan")]).half(), torch.tensor([1.0, 0.0]).half()
+    assert _same(a, a.clone()) and not _same(a, b) and not _same(b, -b) and not _same(a, None) and not _same(a, a.float())
 
 
 @pytest.mark.gpu
