@@ -1393,9 +1393,13 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
         PtqRunArgs args;
         args.a = a;
         PtqRun& g = args.g;
-        // A workgroup for every block of a sweep: each waits, its rows requested, when its step begins (with one for every block of a
-        // Tikhonov step some took their next block late: a call of 4096^2, R = 16 1446 us, so 1377).
-        int most = 1;
+        // A workgroup for every block of a sweep (each waits, its rows requested, when its step begins) up to 160 of them, beyond that one for
+        // every block of a Tikhonov step, at most 129: two runs on two streams then share the chip, where more workgroups of one keep the
+        // other's out while they wait.  ms per run, with all blocks in brackets: 8192^2, R = 16, alone 1.69 (1.73), two streams 0.92 (1.68),
+        // 16 0.95 (1.55; launches per sweep 1.42); 4096^2 1.25 (1.28), 0.67 (0.80), 0.66 (0.77); 3400^2, 163 blocks, 1.21 (1.23), 0.63 (0.64),
+        // 0.60 (0.64).  Smaller ones fit twice as they are, and alone the fewer workgroups lose: 2560^2, 121 blocks, 1.07 (1.02), 512^2
+        // 0.81 (0.80).
+        int rows = 1, all = 1;
         for (int s = 0; s < 2; ++s) {
             g.nbU[s] = L.u[s].nb;
             g.passU[s] = L.u[s].pass;
@@ -1403,8 +1407,10 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
             g.passS[s] = L.s[s].pass;
             g.partU[s] = a.part[s];
             g.partS[s] = a.part[s] + static_cast<size_t>(g.nbU[s]) * count;
-            most += g.nbU[s] + g.nbS[s];
+            rows += g.nbU[s];
+            all += g.nbU[s] + g.nbS[s];
         }
+        const int most = all <= 160 ? all : rows;
         g.gf = ws + L.gf;
         g.slot = ws + L.slot;
         g.sync = a.sync;

@@ -384,8 +384,8 @@ def test_calls_are_reproducible_and_reuse_a_workspace(torch_cuda):
 
 
 # More workgroups in flight than the device holds, some of which start as their run ends (rank-one updates end after a sweep)
-@pytest.mark.parametrize("shapes", [[(1500, 1100, 16, 16), (900, 2100, 4, 9), (700, 130, 1, 1)], [(1300, 700, 12, 32), (2500, 300, 3, 17)]],
-                         ids=["r0_16", "r0_32"])
+@pytest.mark.parametrize("shapes", [[(1500, 1100, 16, 16), (900, 2100, 4, 9), (700, 130, 1, 1)], [(1300, 700, 12, 32), (2500, 300, 3, 17)],
+                                    [(4200, 3300, 4, 4), (3392, 3393, 8, 20)]], ids=["r0_16", "r0_32", "fewer_workgroups_than_blocks"])
 def test_runs_in_flight_on_several_streams(torch_cuda, shapes):
     torch = torch_cuda
     cu = lambda d: (torch.from_numpy(d["A_star"]).cuda(), torch.from_numpy(d["B_star"]).cuda())
