@@ -377,7 +377,8 @@ lordba_status lordba_ptq(const void* A_star, const void* B_star, uint32_t* packe
  * nothing else may have written to them in between.  After every piece the outputs describe the run so far (info[0]
  * sweeps, info[1] the end flag, ...), so a caller that is willing to wait can enqueue the typical number of sweeps,
  * look at info[1], and enqueue the rest only if the loop has not ended: the result is bit for bit that of lordba_ptq
- * (which is this function with t_begin = 0, t_end = K), without the launches that would return at once.
+ * (which is this function with t_begin = 0, t_end = K), without the launches behind the loop's end that would return at
+ * once (R > 16 or r0 > 32; a piece at smaller ranks is one launch, and in one call there are none to save).
  * 0 <= t_begin <= t_end <= K, else LORDBA_ERR_DIM; everything else as lordba_ptq. */
 lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_star, uint32_t* packedA, uint32_t* packedB,
                                 double* alpha, double* beta, double* gamma, void* s_in, void* s_rank, void* s_out,

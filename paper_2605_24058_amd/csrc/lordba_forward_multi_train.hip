@@ -1,5 +1,5 @@
 // The multi-envelope adapter forward branch as training runs it (t of every envelope is kept): the training instantiations
-// for 2, 3 and 4 envelopes (one variant family each, see launch_mfma_gm).
+// for 2, 3 and 4 envelopes (8-row tiles in the plain grid mode, see launch_mfma_gm).
 #define LORDBA_FWD_TRAINING 1
 #include "lordba_fwd_impl.h"
 #include "lordba_forward_multi_units.h"

@@ -1179,7 +1179,8 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
     // request, and six on 8 with two to four rank blocks instead of the loop over groups of four, which waits for memory once per group (us,
     // four slots or the loop in brackets; 5120 -> 5120: T = 2048, r = 16 14.6 (15.4), training 14.0 (15.7), r = 32 16.3 (17.2), two
     // envelopes 16.1 (17.3), at r = 32 19.9 (20.6); T = 3000, r = 32 24.2 (28.5), r = 64 39.6 (43.3); T = 8192, 5120 -> 8192, r = 64 114
-    // (121)).  Not below 40 chunks (4608 -> 2048, T = 3900, r = 32 19.5 (19.1)), and several envelopes on 8 waves gain nothing.
+    // (121)).  From 40 chunks on, the width the gain was looked for at: 36 lose (4608 -> 2048, T = 3900, r = 32 19.5 (19.1)), 37 to 39 would
+    // gain too (32 calls at each, 4 % on average; 4864 -> 5120, T = 3000, r = 32 22.7 (26.0)).  Several envelopes on 8 waves gain nothing.
     if constexpr (TMV == 8 && ((NW == 16 && L <= 2) || (NW == 8 && L == 1 && RB >= 2))) {
         const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
         const bool narrow = BM == 0 && (a.d_out + 127) / 128 <= NW;   // (see launch_mfma)
@@ -1357,7 +1358,8 @@ lordba_status forward_impl(const void* x, const uint32_t* packedA, const uint32_
     // Tile and workgroup shape.  16-row tiles halve the per-row cost of building sign operands and are taken once
     // T / 16 tiles still fill the 256 CUs; below that, 8-row tiles keep every CU busy.  16 waves per workgroup hide
     // the most latency but leave 128 registers per lane, which is enough up to r = 32 (8 rows) or r = 16 (16 rows)
-    // with one envelope; several envelopes keep L accumulator sets and run on 8 waves.
+    // with one envelope; several envelopes keep L accumulator sets and run on 8 waves, but for two where registers and sizes allow 16
+    // (see one_per_cu below).
     const int rb = static_cast<int>((r + 15) / 16);
     const bool tall = batched ? false
                               : algo == LORDBA_ALGO_AUTO ? T >= 4096 : (algo == LORDBA_ALGO_MFMA_T16 || algo == 5 || algo == 7);

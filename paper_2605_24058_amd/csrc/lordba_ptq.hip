@@ -1310,8 +1310,10 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
     const size_t lds_scale = lds_fixed > lds_beta ? lds_fixed : lds_beta;   // (its last block may run the beta update)
     const int nb01 = a.nb[0] + a.nb[1];
 
-    // One launch for all sweeps where a row's ranks fit the 16 lanes of a row and the Gram pair's tiles the LDS (us per call, launches per
-    // sweep in brackets: 4096^2, R = r0 = 16 1444 (1990), 400 x 500, R = 4 665 (1565), R = 16, r0 = 32 2780 (3260), 16384^2 2590 (4250)).
+    // One launch for all sweeps where a row's ranks fit the 16 lanes of a row and the Gram pair's tiles the LDS, at any number of rows: 1.3 to
+    // 2.8 times as fast as launches per sweep on 42 shapes, also where its at most 64 blocks per step leave compute units without one (ms
+    // per call, launches per sweep in brackets, R = r0 = 16: 512^2 0.80 (1.95), 4096^2 1.20 (2.19), 16384^2 2.3 (4.4), 262144^2 88 (175),
+    // 1048576 x 4096 172 (378); R = 16, r0 = 32 4096^2 2.3 (3.5), 8192^2 2.85 (3.82); R = r0 = 4 4096^2 0.84 (1.67)).
     const bool one_launch = iR <= 16 && ir0 <= 32;
     const void* run_fn = ir0 <= 16 ? reinterpret_cast<const void*>(lordba_ptq_run_kernel<1>) : reinterpret_cast<const void*>(lordba_ptq_run_kernel<2>);
     const size_t lds_run = sizeof(double) * run_lds_doubles(ir0 <= 16 ? 1 : 2);

@@ -16,10 +16,11 @@
 // longer (beta, penalty, consensus gaps) is kept twice, by the parity of the sweep.
 //
 // Blocks: 64 rows of a Tikhonov step (16 waves, four rows each; a lane group per row as in row_ldlt_solve), 128 rows of a
-// scale step (8 of the waves, 16 rows each: 256 rows per block kept 64-bit MFMAs of four waves waiting for each other, 64 gave
-// readers too many shares: a call 1377, 1364, 1505 us), more per block beyond 4096 or 8192 rows, so that a step has at most 64 blocks whose
-// shares every reader adds up.  Gram pairs and the products with them are 64-bit MFMAs whose operands are the registers the
-// rows are in: S = sum over rows of (c u)(c u)^T with lane (rank, row) as both operands.
+// scale step (8 of the waves, 16 rows each), more per block beyond 4096 or 8192 rows, so that a step has at most 64 blocks whose
+// shares every reader adds up.  Fewer rows per scale block give readers more shares, more put the 64-bit MFMAs of four waves behind each
+// other (ms per call, R = r0 = 16, 64, 128 and 256 rows from one build: 512^2 0.78, 0.80, 0.86; 2048^2 0.90, 0.92, 0.97; 4096^2
+// 1.30, 1.20, 1.21; 8192^2 1.68, 1.64, 1.54).  Gram pairs and the products with them are 64-bit MFMAs whose operands are the registers
+// the rows are in: S = sum over rows of (c u)(c u)^T with lane (rank, row) as both operands.
 #pragma once
 
 constexpr int kRunThreads = 1024, kRunWaves = kRunThreads / 64;
@@ -139,6 +140,8 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
     };
     // Lane-derived values and arguments are taken anew in every block, from numbers that the compiler cannot follow: kept over the whole
     // kernel, with the lane masks of every phase that follow from them, they take more registers than there are, scalar ones above all.
+    // (What is left: 29 vector registers in scratch memory, 112 bytes per lane, at factor ranks up to 16, 110 and 324 bytes beyond, and
+    // 160 to 190 scalar ones in lanes of vector registers.)
     int tid = threadIdx.x;
     auto wait_for = [&](int p, int t) {   // true: the run is over
         uint32_t* stop = &sh_stop[waits++ & 1];
