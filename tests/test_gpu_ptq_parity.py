@@ -430,8 +430,9 @@ def test_a_run_enqueued_in_pieces_is_the_same_run(torch_cuda):
     assert int(whole["info"][0].item()) == ref["sweeps"]
 
 
-# Every sweep a piece of its own, on sides of more blocks than one pass makes and of few, and pieces behind the end of the run
-@pytest.mark.parametrize("N,M,R,r0,K", [(9000, 70, 4, 5, 12), (260, 5000, 5, 17, 12), (100, 80, 16, 32, 20)])
+# Every sweep a piece of its own, on sides of more blocks than one pass makes and of few, with fewer workgroups than blocks, and pieces
+# behind the end of the run
+@pytest.mark.parametrize("N,M,R,r0,K", [(9000, 70, 4, 5, 12), (260, 5000, 5, 17, 12), (100, 80, 16, 32, 20), (4096, 3500, 3, 4, 9)])
 def test_many_pieces_of_one_sweep(torch_cuda, N, M, R, r0, K):
     say("  case %dx%d R %d r0 %d" % (N, M, R, r0))
     torch = torch_cuda
