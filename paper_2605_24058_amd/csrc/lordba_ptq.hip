@@ -42,6 +42,7 @@ constexpr int kRowThreads = 512;  // eight waves: the kernels of a sweep
 static_assert(LORDBA_PTQ_MAX_RANK == 32, "the Tikhonov kernel is instantiated for ranks up to 16 and up to 32");
 constexpr int kSyncStride = 32;               // counters of the run kernel lie 128 bytes apart
 constexpr int kSyncWords = 6 * kSyncStride;   // next block, workgroups that have left, arrivals of the four kinds of step
+constexpr int kSyncKeeper = kSyncStride + kSyncStride / 2;   // sweeps whose beta is there (in the line of the second)
 constexpr int kGroup = 16, kMaxGroups = 16;   // blocks whose shares are added up together, and groups of a side (see add_up_group)
 constexpr double kRankFloor = 1e-12;  // a singular value of the update below this fraction of the largest counts as zero
 constexpr int kInfoHead = 8;   // info[0..7]: sweeps, frozen, rho, ||T||_F^2, degenerate, reserved; then one objective per sweep
@@ -91,6 +92,13 @@ __device__ inline double row_rotate16(double v) {
                             __builtin_amdgcn_update_dpp(0, lo, ctrl, 0xf, 0xf, false));
 }
 
+__device__ inline double row_max16(double v) {   // over each row of 16 lanes
+    v = fmax(v, row_rotate16<8>(v));
+    v = fmax(v, row_rotate16<4>(v));
+    v = fmax(v, row_rotate16<2>(v));
+    return fmax(v, row_rotate16<1>(v));
+}
+
 template <int CTRL>
 __device__ inline double dpp_move(double v) {
     return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false),
@@ -121,6 +129,10 @@ __device__ inline double row_lane(double v) {
 // a += (lane K's a) * f for one, two or four numbers: the 64-bit multiply-add takes its first operand from another lane
 // of the row by itself, where the compiler would move both halves first.  The wait states are those between any vector instruction
 // and one that reads its result across lanes; the compiler sees the block as one instruction and adds none.
+template <int K>
+__device__ inline void fma_row_lane(double& a, double from, double f) {   // a += (lane K's `from`) * f
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf" : "+&v"(a) : "v"(from), "v"(f), "n"(K));
+}
 template <int K>
 __device__ inline void fma_own_row_lane(double& a, double f) {
     asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%c2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(f), "n"(K));
@@ -716,24 +728,28 @@ __device__ inline void factor_products(const RowLds& s, int R, int r0) {
     }
 }
 
-// Solves H x = b for a symmetric positive definite 16 x 16 matrix by the 16 lanes of one row of the wave (a smaller system is
-// passed padded with an identity block; R says how many pivots are its own).  Lane l passes column l of H and entry l of b, and
+// Solves (H + diag) x = b for a symmetric positive definite 16 x 16 matrix by the 16 lanes of one row of the wave (a smaller system is
+// passed padded: zero columns and a positive diag).  Lane l passes column l of H, entry l of the diagonal matrix and entry l of b, and
 // receives entry l of x.  Right-looking L D L^T factorisation with the columns in registers and no LDS: lane k's column reaches
 // the others inside the multiply-add, and entry l of it, which scales lane l's update, is by symmetry lane l's own entry k.  The
 // right-hand side rides along, which makes the forward substitution part of the factorisation.  No square root, one reciprocal per
-// column (hardware estimate and two Newton steps).  Bound: sixteen dependent reciprocals and their first update.  With the columns
+// column (hardware estimate of half the digits or a little less and one step of third order).  Bound: four waves of a SIMD issue their 64-bit
+// instructions in turn, and for one wave alone sixteen dependent reciprocals and their first update.  With the columns
 // published in LDS (up to 17 reads per column, for which eight waves shared the LDS of a compute unit) a Tikhonov step of 4096 rows took
-// 5.5 us more (the sweeps of 4096^2, R = 16 as a graph 1725 against 1482 us).  Returns the smallest of the first R pivots in *min_pivot.
+// 5.5 us more (the sweeps of 4096^2, R = 16 as a graph 1725 against 1482 us).  Returns the lane's own pivot in *pivot.
 template <int K>
-__device__ __forceinline__ void ldlt_step(double (&col)[16], double& b, double& ipl, double& minp, int R, int l) {
+__device__ __forceinline__ void ldlt_step(double (&col)[16], double& b, double diag, double& ipl, double& pl, int l) {
     asm volatile("" : "+v"(l));   // (the comparisons with the lane are made where they are needed: kept, they overflow the scalar registers)
-    const double pk = row_lane<K>(col[K]);
-    minp = fmin(minp, K < R ? pk : INFINITY);
-    double ipk = __builtin_amdgcn_rcp(pk);
-    ipk = fma(fma(-pk, ipk, 1.0), ipk, ipk);
-    ipk = fma(fma(-pk, ipk, 1.0), ipk, ipk);
-    ipl = (l == K) ? ipk : ipl;
-    const double f = (l > K) ? -(col[K] * ipk) : 0.0;   // -L'[l][K] for the lanes below the diagonal
+    const double p = col[K] + diag;   // (lane K's is the pivot, and its reciprocal the one that is used)
+    double r = __builtin_amdgcn_rcp(p);
+    const double e = fma(-p, r, 1.0);
+    r = fma(r, fma(e, e, e), r);
+    ipl = (l == K) ? r : ipl;
+    pl = (l == K) ? p : pl;
+    // -L'[l][K] for the lanes below the diagonal; the others get a number below 1e-307, which changes none of their entries
+    double f = 0.0;
+    fma_row_lane<K>(f, r, -col[K]);
+    f = __hiloint2double(l > K ? __double2hiint(f) : 0, __double2loint(f));
     constexpr int n = 15 - K, i1 = K + 1, i2 = i1 + (n & 1), i4 = i2 + (n & 2);
     if constexpr ((n & 1) != 0) fma_own_row_lane<K>(col[i1], f);
     if constexpr ((n & 2) != 0) fma_own_row_lane<K>(col[i2], col[i2 + 1], f);
@@ -741,21 +757,22 @@ __device__ __forceinline__ void ldlt_step(double (&col)[16], double& b, double& 
     if constexpr (n >= 8) fma_own_row_lane<K>(col[i4 + 4], col[i4 + 5], col[i4 + 6], col[i4 + 7], f);
     if constexpr (n >= 12) fma_own_row_lane<K>(col[i4 + 8], col[i4 + 9], col[i4 + 10], col[i4 + 11], f);
     fma_own_row_lane<K>(b, f);
-    if constexpr (K < 15) ldlt_step<K + 1>(col, b, ipl, minp, R, l);
+    if constexpr (K < 15) ldlt_step<K + 1>(col, b, diag, ipl, pl, l);
 }
 template <int K>
 __device__ __forceinline__ void ldlt_back(const double (&col)[16], double& b, double ipl, int l) {
     asm volatile("" : "+v"(l));
-    const double f = (l < K) ? -(col[K] * ipl) : 0.0;   // -L'[K][l]: lane l's own column, entry K, over its pivot
+    const double v = -(col[K] * ipl);   // -L'[K][l]: lane l's own column, entry K, over its pivot
+    const double f = __hiloint2double(l < K ? __double2hiint(v) : 0, __double2loint(v));
     fma_own_row_lane<K>(b, f);
     if constexpr (K > 1) ldlt_back<K - 1>(col, b, ipl, l);
 }
-__device__ __forceinline__ double row_ldlt_solve(double (&col)[16], double b, int R, int l, double* min_pivot) {
-    double minp = INFINITY, ipl = 0.0;
-    ldlt_step<0>(col, b, ipl, minp, R, l);
+__device__ __forceinline__ double row_ldlt_solve(double (&col)[16], double b, double diag, int l, double* pivot) {
+    double pl = 0.0, ipl = 0.0;
+    ldlt_step<0>(col, b, diag, ipl, pl, l);
     b *= ipl;   // H = L' D L'^T with D the pivots and L' unit lower triangular; b held entry l of L'^{-1} b
     ldlt_back<15>(col, b, ipl, l);
-    *min_pivot = minp;
+    *pivot = pl;
     return b;
 }
 
@@ -856,7 +873,7 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
                 col[i] = (act && i < R) ? own : (i == l ? 1.0 : 0.0);
             }
             double min_pivot;   // positive: the matrix is a Gram matrix plus rho_k I
-            if constexpr (RMAX == 16) b = row_ldlt_solve(col, b, R, l, &min_pivot);
+            if constexpr (RMAX == 16) b = row_ldlt_solve(col, b, 0.0, l, &min_pivot);
             else b = group_ldlt_solve<RMAX>(col, b, H, zrow, R, l, base, &min_pivot);
             if (act) {
                 const double x = b;
@@ -898,8 +915,11 @@ __global__ __launch_bounds__(RMAX <= 16 ? kRowThreads : kRowThreads / 2) void lo
 // diagonal pivoting stops at the numerical rank: with G = L L^T, L of full column rank, pinv(G) = L (L^T L)^{-2} L^T (at
 // full rank the ordinary solve).
 __device__ __forceinline__ void beta_pinv_solve(double* G, int ld, double* hv, double* N2, int* perm, double* bt, int R, int l) {
-    double dmax = (l < R) ? G[l * ld + l] : 0.0;
-    for (int m = 32; m >= 1; m >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, m, 64));
+    const int lr = R <= 16 ? l & 15 : l;   // (up to 16 ranks each row of 16 lanes has them all)
+    double dmax = (lr < R) ? G[lr * ld + lr] : 0.0;
+    if (R > 16)
+        for (int m = 32; m >= 16; m >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, m, 64));
+    dmax = row_max16(dmax);
     const double tol = 64.0 * 2.220446049250313e-16 * dmax;
     // Fast path: G is positive definite whenever both sides' iterates have full column rank, so try the factorisation
     // without pivoting first (columns in registers) and keep its result if every pivot clears the rank
@@ -914,12 +934,12 @@ __device__ __forceinline__ void beta_pinv_solve(double* G, int ld, double* hv, d
         for (int i = 0; i < 16; ++i) {
             const int ic = i < R ? i : 0;
             const double own = G[ic * ld + lc];
-            col[i] = (i < R && lg < R) ? own : (i == lg ? 1.0 : 0.0);
+            col[i] = (i < R && lg < R) ? own : 0.0;
         }
-        double min_pivot;
-        const double xf = row_ldlt_solve(col, lg < R ? hv[lc] : 0.0, R, lg, &min_pivot);
+        double pivot;
+        const double xf = row_ldlt_solve(col, lg < R ? hv[lc] : 0.0, lg < R ? 0.0 : 1.0, lg, &pivot);
         wave_sync();
-        if (min_pivot > tol) { solved = true; x = xf; }
+        if (__builtin_amdgcn_ballot_w64(lg < R && !(pivot > tol)) == 0ull) { solved = true; x = xf; }
     }
     int rank = 0;
     for (int k = 0; k < R && !solved; ++k) {
@@ -1200,7 +1220,7 @@ Layout make_layout(int64_t N, int64_t M, int64_t R, int64_t r0) {
     for (int s = 0; s < 2; ++s) {   // (the run kernel keeps its shares in the same place: those of the Tikhonov blocks, then the scale blocks')
         L.u[s] = run_blocks(n[s], kRunRows);
         L.s[s] = run_blocks(n[s], kRunScaleRows);
-        const size_t rows = static_cast<size_t>(L.nb[s]) * L.pstride, run = static_cast<size_t>(L.u[s].nb + L.s[s].nb) * (R * R + R * r0);
+        const size_t rows = static_cast<size_t>(L.nb[s]) * L.pstride, run = static_cast<size_t>(L.u[s].nb + L.s[s].nb) * run_count(static_cast<int>(R), static_cast<int>(r0));
         L.part[s] = take(rows > run ? rows : run);
     }
     for (int s = 0; s < 2; ++s) L.tot[s] = take(L.pstride);
@@ -1408,7 +1428,7 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
             g.nbS[s] = L.s[s].nb;
             g.passS[s] = L.s[s].pass;
             g.partU[s] = a.part[s];
-            g.partS[s] = a.part[s] + static_cast<size_t>(g.nbU[s]) * count;
+            g.partS[s] = a.part[s] + static_cast<size_t>(g.nbU[s]) * run_count(iR, ir0);
             rows += g.nbU[s];
             all += g.nbU[s] + g.nbS[s];
         }

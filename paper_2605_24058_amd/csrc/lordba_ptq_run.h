@@ -4,16 +4,27 @@
 // pair of all rows of the side before it.  As launches of their own the steps of 4096^2, R = 16 took 57 us per sweep, of which
 // the arithmetic is a fraction, and a run that ends after 22 of its 100 sweeps paid 0.5 ms for the launches behind its end.
 // Here the blocks of all steps of all sweeps are numbered in order, and every workgroup takes the next number that nobody has
-// taken (one counter), waits until the step before is complete (one arrival counter per kind of step), does the block,
-// publishes its share of the Gram pair and goes on.  A block waits for blocks with smaller numbers only, and whoever took a
-// number does it before anything else, so the smallest unfinished one is always being worked on: the launch ends whatever the
-// number of workgroups that run at a time, also beside other work on the device, and none of them has to be there.
-// (No result depends on who does which block; sums run in a fixed order.)
+// taken (one counter), waits until the step before is complete, does the block, publishes its share of the Gram pair and goes on.  A block
+// waits for blocks with smaller numbers only, and whoever holds a number does it before any other that it holds, so the smallest unfinished
+// one is always being worked on: the launch ends whatever the number of workgroups that run at a time, also beside other work on the
+// device, and none of them has to be there.  (No result depends on who does which block; sums run in a fixed order.)
 //
-// What one workgroup writes and another reads goes through agent-scope accesses (see `publish`); an arrival is counted after
-// every wave's stores have completed (see `arrive_last`).  Buffers that a later step overwrites have no reader left by then:
-// a step starts when the step before it is complete, and readers are at most three steps behind their writer; what is read
-// longer (beta, penalty, consensus gaps) is kept twice, by the parity of the sweep.
+// What one workgroup writes and another reads goes through agent-scope accesses (see `publish`).  Two kinds of waiting:
+//   - For the shares of the step before, which is all that the chain of steps hangs on, by the shares themselves: each value carries the
+//     parity of its sweep in its last bit (with_mark), and a reader takes the shares as they come.  That needs no wait for the stores, no
+//     arrival and no second trip to memory behind it: 2 us of a step's 12.  What lay in a share's place before has to be known: the first
+//     sweep of a launch goes by the arrivals, and before a reader looks at the shares of sweep t it has seen an arrival that implies that
+//     those of sweep t - 1 are complete (or it could find those of t - 2, which carry the same mark).
+//   - For rows, scales, gaps and beta by arrival counters, one per kind of step; a workgroup counts itself when every wave's stores have
+//     completed (see `arrive_last`).  These waits come early in a block: what they are for was written a step or more before.
+// Buffers that a later step overwrites have no reader left by then: a step publishes when it has read all shares of the step before, and
+// readers are at most three steps behind their writer; what is read longer (beta, penalty, consensus gaps) is kept twice, by the parity of
+// the sweep.
+//
+// Time of a sweep of 4096^2, R = r0 = 16 (64 and 32 workgroups): 38 us, 48 with arrivals for everything, a number asked for when the block
+// before is done (64 workgroups queue 7 us for it) and the loads of a scale step one behind the other.  U1's step 11.8 (shares on their way
+// 1.2, added up 2, beta 3.9, rows 5, share 0.7), U2's 10.5, alpha 8, gamma 6; bound: the chain, in it 64-bit vector arithmetic of four waves
+// per SIMD (rows) and 64 bytes per clock into a compute unit (shares: 64 of 3136 bytes).
 //
 // Blocks: 64 rows of a Tikhonov step (16 waves, four rows each; a lane group per row as in row_ldlt_solve), 128 rows of a
 // scale step (8 of the waves, 16 rows each), more per block beyond 4096 or 8192 rows, so that a step has at most 64 blocks whose
@@ -50,9 +61,11 @@ inline RunBlocks run_blocks(int64_t n, int rows) {
     b.nb = static_cast<int>((n + static_cast<int64_t>(rows) * b.pass - 1) / (static_cast<int64_t>(rows) * b.pass));
     return b;
 }
+// Values of a share: the lower triangle of S by rows, then K by rows.
+__host__ __device__ constexpr int run_count(int R, int r0) { return R * (R + 1) / 2 + R * r0; }
 // LDS of the run kernel in doubles: the two totals, the operands, beta and its work area, scales, the waves' shares.
 constexpr int run_lds_doubles(int RT) {
-    return 2 * (256 + 256 * RT) + 256 + 256 * RT + 16 + (2 * 16 * 17 + 3 * 16 + 8) + 16 * (16 * RT + 1) + kRunWaves * 16 + 2 * kRunWaves + 8 + kRunWaves * 256 * (1 + RT);
+    return 2 * (RT == 1 ? 512 : 768) + 256 + 256 * RT + 16 + (2 * 16 * 17 + 3 * 16 + 8) + 16 * (16 * RT + 1) + kRunWaves * 16 + 2 * kRunWaves + 8 + kRunWaves * 256 * (1 + RT);
 }
 
 typedef double d2 __attribute__((ext_vector_type(2)));
@@ -85,14 +98,23 @@ __device__ inline T* at32(T* p, uint32_t i) {
     return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + i * static_cast<uint32_t>(sizeof(T)));
 }
 
+// A share's values carry the parity of their sweep in the last bit (rounded to 52 bits of significand, which leaves zeros, small whole
+// numbers and what is not finite as they are): a reader that knows what lay in their place before sees by itself whether they are there.
+__device__ inline uint32_t mark_of(double v) { return static_cast<uint32_t>(__double2loint(v)) & 1u; }
+__device__ inline double without_mark(double v) { return __hiloint2double(__double2hiint(v), __double2loint(v) & ~1); }
+__device__ inline double with_mark(double v, uint32_t mark) {
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+    return __longlong_as_double(static_cast<long long>(((u + (u >> 1 & 1u)) & ~1ull) | mark));
+}
+
 template <int RT>   // factor rank at most 16 RT
 __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs) {
     constexpr int NT = 1 + RT;              // 16 x 16 tiles of a Gram pair
-    constexpr int NV = 256 * NT;            // values of a padded pair
+    constexpr int NV = RT == 1 ? 512 : 768; // threads that have a value each: at least run_count(16, 16 RT)
     constexpr int H = NV <= 512 ? 2 : 1;    // threads that share the sum of one value
     typedef const __attribute__((address_space(4))) PtqRunArgs KernelArgs;   // (constant memory: read into scalar registers)
     KernelArgs* arg = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    const int R = arg->a.R, r0 = arg->a.r0, RR = R * R, count = RR + R * r0;
+    const int R = arg->a.R, r0 = arg->a.r0, RP = R * (R + 1) / 2, count = run_count(R, r0);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double* T1 = lds;                  // totals of side 0 and of side 1, as they are stored (for beta)
     double* T2 = T1 + NV;
@@ -105,21 +127,29 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
     double* gfs = cs + kRunWaves * 16;            // [waves][2]
     double* ctl = gfs + 2 * kRunWaves;            // rho, factor of Y, done
     double* red = ctl + 8;                        // [waves][NV]
-    __shared__ uint32_t sh_number, sh_numbers, sh_stop[2], place[NV];
+    __shared__ uint32_t sh_number[2], sh_numbers, sh_stop[2], place[NV];
+    __shared__ uint32_t sh_over;
     int waits = 0;   // (two flags in turn: the next wait's must not be set before every wave has read this one's)
 
-    // Value o of a Gram pair as it is stored: whether there is one (bit 0) and it belongs to S (1), its row and column up to 16 (2..5, 6..9), its
-    // place in G and Kt (10..19) and in a wave's share (20..29).
+    // Value o of a Gram pair as it is stored: whether there is one (bit 0) and it belongs to S (1), its row and column (2..5, 6..10), its
+    // place in G and Kt (11..20; S again at the mirrored place) and in a wave's share (21..30).
     for (int o = threadIdx.x; o < NV; o += kRunThreads) {
-        const bool is_s = o < RR;
-        const int vi = is_s ? o / R : (o - RR) / r0, vj = is_s ? o - vi * R : (o - RR) - vi * r0;
-        const int at = is_s ? (vi >> 1) * 32 + vj * 2 + (vi & 1) : 256 + (vj >> 1) * 32 + vi * 2 + (vj & 1);
-        const int rpos = is_s ? vi * 16 + vj : (1 + (vj >> 4)) * 256 + vi * 16 + (vj & 15);
-        place[o] = o < count ? 1u | (is_s ? 2u : 0u) | vi << 2 | (vj & 15) << 6 | at << 10 | static_cast<uint32_t>(rpos) << 20 : 0u;
-        G[o] = 0.0;   // (Kt follows G)
+        const bool is_s = o < RP;
+        int i = 0, j = o;
+        if (is_s) {
+            while (j > i) j -= ++i;
+        } else {
+            i = (o - RP) / r0;
+            j = (o - RP) - i * r0;
+        }
+        const int at = is_s ? (i >> 1) * 32 + j * 2 + (i & 1) : 256 + (j >> 1) * 32 + i * 2 + (j & 1);
+        const int rpos = is_s ? i * 16 + j : (1 + (j >> 4)) * 256 + i * 16 + (j & 15);
+        place[o] = o < count ? 1u | (is_s ? 2u : 0u) | i << 2 | j << 6 | at << 11 | static_cast<uint32_t>(rpos) << 21 : 0u;
     }
+    for (int o = threadIdx.x; o < 256 * NT; o += kRunThreads) G[o] = 0.0;   // (Kt follows G)
     if (threadIdx.x < 16) bs[threadIdx.x] = 0.0;
     auto arrivals = [&](int p) { return arg->g.sync + (2 + p) * kSyncStride; };
+    uint32_t* const kept = arg->g.sync + kSyncKeeper;   // sweeps whose beta and penalty the keeper has published
     const bool init = arg->g.t_begin == 0;
     auto per = [&](int p) { return p == 0 ? arg->g.nbU[0] + 1 : p == 1 ? arg->g.nbU[1] : arg->g.nbS[p & 1]; };   // (the first step has a keeper: beta and the penalty)
     const uint32_t per_sweep = static_cast<uint32_t>(per(0) + per(1) + per(2) + per(3));
@@ -132,6 +162,8 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         const uint32_t sweeps = static_cast<uint32_t>(arg->g.t_end - arg->g.t_begin);
         if (published(arg->a.ctrl + kDone) != 0.0) sh_numbers = init ? n_init - static_cast<uint32_t>(per(2) + per(3)) : 0u;
         else sh_numbers = n_init + (sweeps == 0u ? 0u : sweeps * per_sweep + 1u);
+        sh_over = 0u;
+        sh_number[0] = __hip_atomic_fetch_add(arg->g.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     auto need = [&](int p, int t) {   // arrivals of step p through sweep t
@@ -140,9 +172,17 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
     };
     // Lane-derived values and arguments are taken anew in every block, from numbers that the compiler cannot follow: kept over the whole
     // kernel, with the lane masks of every phase that follow from them, they take more registers than there are, scalar ones above all.
-    // (What is left: 29 vector registers in scratch memory, 112 bytes per lane, at factor ranks up to 16, 110 and 324 bytes beyond, and
-    // 160 to 190 scalar ones in lanes of vector registers.)
+    // (What is left: 41 vector registers in scratch memory, 92 bytes per lane, at factor ranks up to 16, 92 and 176 bytes beyond, and
+    // 130 to 140 scalar ones in lanes of vector registers.)
     int tid = threadIdx.x;
+    int turn = 0;
+    uint32_t next = 0u;   // the first thread's next number: asked for while it works on the one before
+    // The next number, asked for once the step before the present block's is seen to be complete: workgroups that end a step together queue
+    // for it, 64 of them for 7 us.  Not before: what a workgroup holds while it still waits, nobody else can do meanwhile.  (Whoever holds a
+    // number behind the one it works on does that one first, so the smallest unfinished number is still always being worked on.)
+    auto ask = [&]() {
+        if (tid == 0) next = __hip_atomic_fetch_add(arg->g.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     auto wait_for = [&](int p, int t) {   // true: the run is over
         uint32_t* stop = &sh_stop[waits++ & 1];
         if (tid == 0) {
@@ -154,24 +194,51 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         __syncthreads();
         return __builtin_amdgcn_readfirstlane(*stop) != 0u;
     };
-    auto arrive = [&](int p) {
+    auto arrive = [&](int p, bool keeper = false) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        ++turn;
+        if (tid == 0) sh_number[turn & 1] = next;   // (the other one may not have been read by every wave yet)
         __syncthreads();
-        if (tid == 0) __hip_atomic_fetch_add(arrivals(p), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) {
+            __hip_atomic_fetch_add(arrivals(p), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (keeper) __hip_atomic_fetch_add(kept, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     };
-    auto gather = [&](const double* part, int nb) {   // this thread's share of the sum over the blocks
+    // This thread's share of the sum over the blocks.  With mark < 2 the shares may still be on their way and are taken as they come, by
+    // the sweep's mark that they carry: first one of them alone, until it is there (or the run is over: sh_over), then all.  want_kept:
+    // how many sweeps' beta must have been published too.
+    auto gather = [&](const double* part, int nb, uint32_t mark, int blk, uint32_t want_kept) {
         const int o = H == 2 ? tid & (NV - 1) : tid, h = H == 2 ? wave / (NV / 64) : 0;
-        const int lo = h == 1 ? nb >> 1 : 0, hi = H == 2 && h == 0 ? nb >> 1 : nb;
-        if (o >= count) return 0.0;
+        const int lo = h == 1 ? (nb + 1) >> 1 : 0, hi = H == 2 && h == 0 ? (nb + 1) >> 1 : nb;   // (the first wave always has a block)
+        if ((H == 2 ? (wave * 64) & (NV - 1) : wave * 64) >= count || lo == hi) return 0.0;   // (scalar)
+        const uint32_t oc = static_cast<uint32_t>(o < count ? o : count - 1);
+        if (mark < 2u) {
+            const double* one = part + (lo + blk % (hi - lo)) * count;
+            for (;;) {   // (one wave alone reads the keeper's word for the workgroup: all of them together crowd its memory channel)
+                uint32_t k = want_kept;
+                if (wave == 0) k = __hip_atomic_load(kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool other = mark_of(published(at32(one, oc))) != mark;
+                if (wave == 0 && (k & kStop)) { sh_over = 1u; return 0.0; }
+                if (__builtin_amdgcn_ballot_w64(other || k < want_kept) == 0ull) break;
+                if (__hip_atomic_load(&sh_over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u) return 0.0;
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
         double acc = 0.0;
         for (int b0 = lo; b0 < hi; b0 += 16) {
             double v[16];
+            uint32_t other;
+            do {   // (shares of one step arrive close together: this seldom takes more than two turns)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) v[j] = published(at32(part + (b0 + j < hi ? b0 + j : hi - 1) * count, static_cast<uint32_t>(o)));
+                for (int j = 0; j < 16; ++j) v[j] = published(at32(part + (b0 + j < hi ? b0 + j : hi - 1) * count, oc));
+                other = 0u;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc += b0 + j < hi ? v[j] : 0.0;
+                for (int j = 0; j < 16; ++j) other |= mark_of(v[j]) ^ mark;
+            } while (mark < 2u && __builtin_amdgcn_ballot_w64(other != 0u) != 0ull);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc += b0 + j < hi ? without_mark(v[j]) : 0.0;
         }
-        return acc;
+        return o < count ? acc : 0.0;
     };
     auto combine = [&](double acc) {   // the whole sum, in the threads below NV (contains a barrier)
         if constexpr (H == 2) {
@@ -181,22 +248,22 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         }
         return acc;
     };
-    // the waves' shares added up and published (contains a barrier)
-    auto share = [&](const d4 (&s)[NT], double* part) {
+    // the waves' shares added up and published with the sweep's mark (contains a barrier)
+    auto share = [&](const d4 (&s)[NT], double* part, uint32_t mark) {
 #pragma unroll
         for (int e = 0; e < NT; ++e) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[wave * NV + e * 256 + r * 64 + (tid & 63)] = s[e][r];
+            for (int r = 0; r < 4; ++r) red[(wave * NT + e) * 256 + r * 64 + (tid & 63)] = s[e][r];
         }
         __syncthreads();
         if (tid < count) {
-            const double* at = red + (place[tid] >> 20);
+            const double* at = red + (place[tid] >> 21);
             double v[kRunWaves], acc = 0.0;
 #pragma unroll
-            for (int w = 0; w < kRunWaves; ++w) v[w] = at[w * NV];
+            for (int w = 0; w < kRunWaves; ++w) v[w] = at[w * NT * 256];
 #pragma unroll
             for (int w = 0; w < kRunWaves; ++w) acc += v[w];
-            publish(part + tid, acc);
+            publish(part + tid, with_mark(acc, mark));
         }
     };
 
@@ -204,9 +271,7 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         asm volatile("" : "+v"(tid));
         asm volatile("" : "+s"(arg));
         const int lane = tid & 63, li = lane & 15, q = lane >> 4;
-        if (tid == 0) sh_number = __hip_atomic_fetch_add(arg->g.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        uint32_t rest = __builtin_amdgcn_readfirstlane(sh_number);
+        uint32_t rest = __builtin_amdgcn_readfirstlane(sh_number[turn & 1]);
         if (rest >= __builtin_amdgcn_readfirstlane(sh_numbers)) break;
         int t = -1, p = 0;
         if (rest >= n_init) {
@@ -249,12 +314,25 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
 #pragma unroll
                 for (int e = 0; e < RT; ++e) s[1 + e] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, factor(row, e * 16 + li), s[1 + e], 0, 0, 0);
             }
-            if (side == 1) share(s, arg->g.partU[1] + static_cast<int64_t>(blk) * count);   // (all that alpha needs)
+            ask();
+            if (side == 1) share(s, arg->g.partU[1] + static_cast<int64_t>(blk) * count, t & 1);   // (all that alpha needs)
             arrive(p);
             continue;
         }
         if (p < 2) {   // ---- Tikhonov step of a side, signs and duals; before U1's, beta and the penalty of the sweep before
             const bool update = p == 0 && t > arg->g.t_begin;
+            const bool marked = t > arg->g.t_begin + (p == 0 ? 1 : 0);   // (the shares it waits for are not the first in their place)
+            double acc1 = 0.0;
+            if (update) {
+                // U2's step of the sweep before: its consensus gaps, which are published behind its shares.  (The shares of alpha's step that lie in
+                // their place are then those of one sweep earlier, whose mark is the other one, not of two.)
+                if (wait_for(1, t - 1)) break;
+                if (marked) {
+                    acc1 = combine(gather(arg->g.partS[0], arg->g.nbS[0], static_cast<uint32_t>(t - 1) & 1u, blk, 0u));
+                    if (H == 1) __syncthreads();
+                    if (__builtin_amdgcn_readfirstlane(sh_over) != 0u) break;
+                }
+            }
             if (wait_for(p + 2, t - 1)) break;
             // what the rows need is there already: requested ahead of the wait for the totals
             const int passes = keeper ? 0 : arg->g.passU[side];
@@ -271,9 +349,8 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                 c = in ? c : 0.0;
             };
             request(0);
-            double acc1 = 0.0;
             if (update) {
-                acc1 = combine(gather(arg->g.partS[0], arg->g.nbS[0]));
+                if (!marked) acc1 = combine(gather(arg->g.partS[0], arg->g.nbS[0], 2u, 0, 0u));
                 if (tid < count) T1[tid] = acc1;
                 if (wave == 1) {   // consensus gaps and sign changes of both sides
                     double gap = 0.0, f0 = 0.0, f1 = 0.0;
@@ -299,8 +376,11 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                     }
                 }
             }
-            if (p == 0 ? wait_for(3, t - 1) : wait_for(0, t)) break;
-            double total = gather(p == 0 ? arg->g.partS[1] : arg->g.partU[0], p == 0 ? arg->g.nbS[1] : arg->g.nbU[0]);
+            if (!marked) {
+                if (p == 0 ? wait_for(3, t - 1) : wait_for(0, t)) break;
+            }
+            double total = gather(p == 0 ? arg->g.partS[1] : arg->g.partU[0], p == 0 ? arg->g.nbS[1] : arg->g.nbU[0],
+                                  marked ? static_cast<uint32_t>(p == 0 ? t - 1 : t) & 1u : 2u, blk, p == 0 ? 0u : static_cast<uint32_t>(t - arg->g.t_begin + 1));
             if (!update && tid < 18) {   // beta, rho, factor of Y
                 double v;
                 if (p == 0) v = tid < 16 ? (tid < R ? arg->a.beta[tid] : 0.0) : arg->a.ctrl[tid == 16 ? kRho : kYfac];
@@ -308,8 +388,10 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                 if (tid < 16) bs[tid] = v;
                 else ctl[tid - 16] = v;
             }
+            ask();
             total = combine(total);
             if (H == 1) __syncthreads();
+            if (marked && __builtin_amdgcn_readfirstlane(sh_over) != 0u) break;
             if (update) {
                 double* Gb = bw;
                 double* N2 = Gb + 16 * 17;
@@ -320,9 +402,10 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                 // Eq. (beta-gram), Eq. (beta-pinv): beta = pinv(S1 o S2) h, h_k = K1[k, :] . K2[k, :]
                 if (tid < count) {
                     const uint32_t w = place[tid];
-                    const int i = w >> 2 & 15u;
+                    const int i = w >> 2 & 15u, j = w >> 6 & 31u;
                     T2[tid] = total;
-                    *(w & 2u ? Gb + i * ld + (w >> 6 & 15u) : hp + i * (16 * RT + 1) + (tid - RR - i * r0)) = acc1 * total;
+                    *(w & 2u ? Gb + i * ld + j : hp + i * (16 * RT + 1) + j) = acc1 * total;
+                    if (w & 2u) Gb[j * ld + i] = acc1 * total;
                 }
                 __syncthreads();
                 if (wave == 0) {
@@ -334,8 +417,8 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                         const double v = hp[k * (16 * RT + 1) + at];
                         h += at < r0 ? v : 0.0;
                     }
-                    h += __shfl_xor(h, 1, 64);
-                    h += __shfl_xor(h, 2, 64);
+                    h += dpp_move<0xb1>(h);   // (among the four lanes)
+                    h += dpp_move<0x4e>(h);
                     if (k < R && (lane & 3) == 0) hv[k] = h;
                     if (lane < R) perm[lane] = lane;
                     wave_sync();
@@ -346,7 +429,10 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
             }
             if (tid < count) {
                 const uint32_t w = place[tid];
-                G[w >> 10 & 0x3ffu] = total * (bs[w >> 2 & 15u] * (w & 2u ? bs[w >> 6 & 15u] : 1.0));
+                const int i = w >> 2 & 15u, j = w >> 6 & 31u;
+                const double v = total * (bs[i] * (w & 2u ? bs[j] : 1.0));
+                G[w >> 11 & 0x3ffu] = v;
+                if (w & 2u) G[(j >> 1) * 32 + i * 2 + (j & 1)] = v;
             }
             if (keeper) {
                 const bool done = update && ctl[2] != 0.0, last = done || t == arg->g.t_end;
@@ -355,9 +441,12 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                     double lin = 0.0, quad = 0.0;
                     if (lane < R) {
                         const double bl = bs[lane];
-                        for (int e = 0; e < r0; ++e) lin += T1[RR + lane * r0 + e] * T2[RR + lane * r0 + e];
+                        for (int e = 0; e < r0; ++e) lin += T1[RP + lane * r0 + e] * T2[RP + lane * r0 + e];
                         lin *= bl;
-                        for (int i = 0; i < R; ++i) quad += bl * bs[i] * (T1[lane * R + i] * T2[lane * R + i]);
+                        for (int i = 0; i < R; ++i) {
+                            const int hi = i > lane ? i : lane, at = hi * (hi + 1) / 2 + (i > lane ? lane : i);
+                            quad += bl * bs[i] * (T1[at] * T2[at]);
+                        }
                     }
                     lin = group_sum(lin, 64);
                     quad = group_sum(quad, 64);
@@ -373,11 +462,11 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                     }
                 }
                 if (last) {   // nobody arrives at this step any more; where the run is over, the others may be waiting
-                    if (done && tid < 4) __hip_atomic_fetch_or(arrivals(tid), kStop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (done && tid < 5) __hip_atomic_fetch_or(tid < 4 ? arrivals(tid) : kept, kStop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (before this workgroup counts as gone: whoever leaves last sets the bits back)
                     break;
                 }
-                arrive(0);
+                arrive(0, true);
                 continue;
             }
             if (update && ctl[2] != 0.0) break;
@@ -396,22 +485,21 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                 for (int e = 0; e < RT; ++e) row_products(Kt + e * 256, f[e], li, kb);
                 const double y = yfac * y_old, mo = m_old, cc = c;
                 double b = act ? cc * ((kb[0] + kb[1]) + (kb[2] + kb[3])) + rho_k * (mo - y) : 0.0;
-                const double c2 = cc * cc, diag = act ? rho_k : 1.0;
+                const double c2 = cc * cc;
                 double col[16];
-                int l = li;
+                const double* Gl = G + li * 2;
 #pragma unroll
                 for (int i = 0; i < 16; i += 2) {
-                    asm volatile("" : "+v"(l));   // (see row_ldlt_solve)
-                    const d2 gg = *reinterpret_cast<const d2*>(G + (i >> 1) * 32 + l * 2);
-                    col[i] = fma(c2, gg[0], l == i ? diag : 0.0);
-                    col[i + 1] = fma(c2, gg[1], l == i + 1 ? diag : 0.0);
+                    const d2 gg = *reinterpret_cast<const d2*>(Gl + i * 16);
+                    col[i] = c2 * gg[0];
+                    col[i + 1] = c2 * gg[1];
                 }
                 double fr[RT];
 #pragma unroll
                 for (int e = 0; e < RT; ++e) fr[e] = f[e];
                 if (pass + 1 < passes) request(pass + 1);
-                double min_pivot;   // positive: the matrix is a Gram matrix plus rho_k I
-                const double x = row_ldlt_solve(col, b, R, li, &min_pivot);
+                double pivot;   // positive: the matrix is a Gram matrix plus rho_k I
+                const double x = row_ldlt_solve(col, b, rho_k, li, &pivot);
                 const double mn = (x + y) < 0.0 ? -1.0 : 1.0;
                 const bool live = in && act;
                 if (live) {
@@ -426,10 +514,11 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
 #pragma unroll
                 for (int e = 0; e < RT; ++e) s[1 + e] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, fr[e], s[1 + e], 0, 0, 0);
             }
+            share(s, arg->g.partU[side] + static_cast<int64_t>(blk) * count, t & 1);
             gap = group_sum(gap, 64);
             flips = group_sum(flips, 64);
             if (lane == 0) { gfs[2 * wave] = gap; gfs[2 * wave + 1] = flips; }
-            share(s, arg->g.partU[side] + static_cast<int64_t>(blk) * count);
+            __syncthreads();
             if (tid >= kRunThreads - 64 && lane < 2) {   // (a wave without a value to add up where there are 512)
                 double sum = 0.0;
 #pragma unroll
@@ -442,49 +531,60 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         // ---- Eq. (alpha-update), Eq. (gamma-update): per row, with v = u o beta, (v . (K f)) / (v^T S v), 0 where the denominator is 0
         if (p == 2 ? wait_for(0, t) : wait_for(1, t)) break;
         const int passes = arg->g.passS[side];
-        double xr[4], xk[4], fr[RT][4], fk[RT][4];   // the wave's 16 rows by lane (row, ranks 4 s + q) and by lane (rank, rows 4 s + q)
-        auto request = [&](int pass) {
+        double xr[4], xk[4];   // the wave's 16 rows by lane (row, ranks 4 s + q) and by lane (rank, rows 4 s + q)
+        __half fr[RT][4], fk[RT][4];
+        auto request = [&](int pass) {   // (what is not there is read from the first row and dropped where it is used)
             const int64_t row0 = (static_cast<int64_t>(blk) * passes + pass) * kRunScaleRows + wave * 16;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const int64_t r1 = row0 + li, r2 = row0 + 4 * s + q;
                 const int k = 4 * s + q;
-                const bool in1 = r1 < n && k < R, in2 = r2 < n && li < R;
-                xr[s] = published(arg->a.X[side] + (in1 ? r1 * R + k : 0));
-                xk[s] = published(arg->a.X[side] + (in2 ? r2 * R + li : 0));
-                xr[s] = in1 ? xr[s] : 0.0;
-                xk[s] = in2 ? xk[s] : 0.0;
+                xr[s] = published(arg->a.X[side] + (r1 < n && k < R ? r1 * R + k : 0));
+                xk[s] = published(arg->a.X[side] + (r2 < n && li < R ? r2 * R + li : 0));
 #pragma unroll
                 for (int e = 0; e < RT; ++e) {
-                    fr[e][s] = factor(r1, e * 16 + k);
-                    fk[e][s] = factor(r2, e * 16 + li);
+                    fr[e][s] = F[r1 < n && e * 16 + k < r0 ? r1 * r0 + e * 16 + k : 0];
+                    fk[e][s] = F[r2 < n && e * 16 + li < r0 ? r2 * r0 + e * 16 + li : 0];
                 }
             }
         };
         const bool rows_here = wave < kRunScaleRows / 16;   // (the other waves only add shares up)
+        double beta_k = 0.0;
+        if (tid < 16) beta_k = t < 0 ? (tid < R ? arg->a.beta[tid] : 0.0) : published(arg->g.slot + (t & 1) * kSlot + tid);
         if (rows_here) request(0);
-        if (tid < 16) bs[tid] = t < 0 ? (tid < R ? arg->a.beta[tid] : 0.0) : published(arg->g.slot + (t & 1) * kSlot + tid);
-        if (wait_for(p - 1, t)) break;
+        if (tid < 16) bs[tid] = beta_k;
+        const bool marked = t > arg->g.t_begin;
+        if (!marked && wait_for(p - 1, t)) break;
         {
-            const double total = combine(gather(p == 2 ? arg->g.partU[1] : arg->g.partS[0], p == 2 ? arg->g.nbU[1] : arg->g.nbS[0]));
-            if (tid < count) G[place[tid] >> 10 & 0x3ffu] = total;
+            const double mine = gather(p == 2 ? arg->g.partU[1] : arg->g.partS[0], p == 2 ? arg->g.nbU[1] : arg->g.nbS[0], marked ? t & 1 : 2u, blk, 0u);
+            ask();
+            const double total = combine(mine);
+            if (tid < count) {
+                const uint32_t w = place[tid];
+                const int i = w >> 2 & 15u, j = w >> 6 & 31u;
+                G[w >> 11 & 0x3ffu] = total;
+                if (w & 2u) G[(j >> 1) * 32 + i * 2 + (j & 1)] = total;
+            }
         }
         __syncthreads();
+        if (marked && __builtin_amdgcn_readfirstlane(sh_over) != 0u) break;
         d4 s[NT];
 #pragma unroll
         for (int e = 0; e < NT; ++e) s[e] = d4{0.0, 0.0, 0.0, 0.0};
         for (int pass = 0; pass < passes && rows_here; ++pass) {
             const int64_t row = (static_cast<int64_t>(blk) * passes + pass) * kRunScaleRows + wave * 16 + li;
+            const bool in = row < n;
             d4 sv = {0.0, 0.0, 0.0, 0.0}, kf = {0.0, 0.0, 0.0, 0.0};
             double v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {   // ranks 4 e + q: operand (rank, q) of S, which is symmetric, and of K
                 const int k = 4 * e + q;
-                v[e] = xr[e] * bs[k];
+                v[e] = in && k < R ? xr[e] * bs[k] : 0.0;
                 sv = __builtin_amdgcn_mfma_f64_16x16x4f64(G[(k >> 1) * 32 + li * 2 + (k & 1)], v[e], sv, 0, 0, 0);
 #pragma unroll
                 for (int w = 0; w < RT; ++w)
-                    kf = __builtin_amdgcn_mfma_f64_16x16x4f64(Kt[w * 256 + (k >> 1) * 32 + li * 2 + (k & 1)], fr[w][e], kf, 0, 0, 0);
+                    kf = __builtin_amdgcn_mfma_f64_16x16x4f64(Kt[w * 256 + (k >> 1) * 32 + li * 2 + (k & 1)],
+                                                              in && w * 16 + k < r0 ? static_cast<double>(__half2float(fr[w][e])) : 0.0, kf, 0, 0, 0);
             }
             double num = 0.0, den = 0.0;
 #pragma unroll
@@ -497,7 +597,6 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
             num += __shfl_xor(num, 32, 64);
             den += __shfl_xor(den, 32, 64);
             const double c = den > 0.0 ? num / den : 0.0;
-            const bool in = row < n;
             wave_sync();
             if (q == 0) {
                 cs[wave * 16 + li] = in ? c : 0.0;
@@ -507,9 +606,10 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
             double u[4], fv[RT][4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                u[e] = cs[wave * 16 + 4 * e + q] * xk[e];
+                const bool ink = row - li + 4 * e + q < n;
+                u[e] = ink && li < R ? cs[wave * 16 + 4 * e + q] * xk[e] : 0.0;
 #pragma unroll
-                for (int w = 0; w < RT; ++w) fv[w][e] = fk[w][e];
+                for (int w = 0; w < RT; ++w) fv[w][e] = ink && w * 16 + li < r0 ? static_cast<double>(__half2float(fk[w][e])) : 0.0;
             }
             if (pass + 1 < passes) request(pass + 1);
 #pragma unroll
@@ -519,14 +619,16 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                 for (int w = 0; w < RT; ++w) s[1 + w] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[e], fv[w][e], s[1 + w], 0, 0, 0);
             }
         }
-        share(s, arg->g.partS[side] + static_cast<int64_t>(blk) * count);
+        share(s, arg->g.partS[side] + static_cast<int64_t>(blk) * count, t & 1);
         arrive(p);
     }
-    // The last workgroup to leave sets the counters back for the next launch: by then nobody reads them, and nothing written to them is
-    // still under way.
+    // The last workgroup to leave sets the counters back for the next launch: by then nobody reads them, and nothing written to them (the
+    // numbers asked for ahead too) is still under way.
     if (tid == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (__hip_atomic_fetch_add(arg->g.sync + kSyncStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x) {
             for (int e = 0; e < 6; ++e) __hip_atomic_store(arg->g.sync + e * kSyncStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(kept, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }

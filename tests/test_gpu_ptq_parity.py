@@ -408,6 +408,25 @@ def test_runs_in_flight_on_several_streams(torch_cuda, shapes):
                 assert torch.equal(out[k], alone[i][k]), (rep, i, k)
 
 
+# What lies in a workspace (shares of another run with their marks, all bits set or none, at one, few and 64 blocks per step) changes no bit
+@pytest.mark.parametrize("N,M,R,r0", [(40, 33, 3, 4), (700, 1025, 16, 16), (5000, 300, 7, 20)])
+def test_what_a_workspace_held_before_does_not_matter(torch_cuda, N, M, R, r0):
+    torch = torch_cuda
+    say("ptq stale workspace %dx%d R %d r0 %d" % (N, M, R, r0))
+    runs = [[torch.from_numpy(inputs.make_ptq_inputs(seed, N, M, r0)[k]).cuda() for k in ("A_star", "B_star")] for seed in (64, 65)]
+    ws = torch.zeros(binding.lordba_ptq_workspace_bytes(N, M, R, r0) // 8, dtype=torch.float64, device="cuda")
+    want = binding.lordba_ptq(*runs[0], R, K=9, workspace=ws)
+    want = {k: v.clone() for k, v in want.items()}
+    for K in (1, 2, 3, 4, 0):
+        if K:
+            binding.lordba_ptq(*runs[1], R, K=K, workspace=ws)
+        else:
+            ws.view(torch.int64).fill_(-1)
+        got = binding.lordba_ptq(*runs[0], R, K=9, workspace=ws)
+        for k in ("packedA", "packedB", "alpha", "beta", "gamma", "info", "U1", "U2t"):
+            assert torch.equal(got[k], want[k]), (K, k)
+
+
 def test_a_run_enqueued_in_pieces_is_the_same_run(torch_cuda):
     # lordba_ptq_sweeps: [0, 5) + [5, 6) + [6, 40) against one call of 40 sweeps, bit for bit; the outputs after the first
     # piece are those of the run stopped there (same penalty schedule: K stays 40)
