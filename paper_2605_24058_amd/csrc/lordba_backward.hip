@@ -22,8 +22,8 @@
 //           with row-contiguous 16-byte loads and transposes its 8 x 8 block in registers (v_perm_b32); MFMA e of a step
 //           takes column 8 m + e from lane group m.  dt = beta du (or u = beta t) enters as fp16 hi + lo (+ rest) after a
 //           power-of-two scaling per rank that follows the largest entry seen so far.  Token ranges are split over waves
-//           and workgroups; partial sums are reduced in a fixed order.  One extra workgroup column does d_beta.
-//   finish  sums the partials, applies the carrier signs, the scales and the smooth-sign factor.
+//           and workgroups; partial sums are reduced in a fixed order.
+//   finish  sums the partials, applies the carrier signs, the scales and the smooth-sign factor; and d_beta.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -56,7 +56,7 @@ struct BwdPlan {
     int splits;      // workgroups along the token axis of the wgrad kernel
     int waves;       // waves per workgroup of the wgrad kernel: 4, or 8 on short batches with one rank block (see make_plan)
     // workspace layout, in 4-byte words
-    size_t off_t, off_du, off_dbeta, off_part, words;
+    size_t off_t, off_du, off_part, words;
 };
 
 // ell_fused: envelopes whose partial sums the wgrad kernel holds at once (1: one envelope per wgrad / finish pass).
@@ -86,9 +86,7 @@ BwdPlan make_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, int64_t ell
     // t and du: one [r, t_pad] block per envelope, room for the largest envelope count
     p.off_t = 0;
     p.off_du = p.off_t + static_cast<size_t>(LORDBA_MAX_ENVELOPES) * p.rp * p.t_pad;
-    p.off_dbeta = p.off_du + static_cast<size_t>(LORDBA_MAX_ENVELOPES) * p.rp * p.t_pad;
-    p.off_part = p.off_dbeta + static_cast<size_t>(p.splits) * p.rp * ell_fused;
-    p.off_part = (p.off_part + 3) & ~static_cast<size_t>(3);
+    p.off_part = p.off_du + static_cast<size_t>(LORDBA_MAX_ENVELOPES) * p.rp * p.t_pad;
     p.words = p.off_part + static_cast<size_t>(p.splits) * p.rp * ell_fused * p.dcols;
     return p;
 }
@@ -111,7 +109,6 @@ struct BwdArgs {
     float* d_latB;
     const float* tT;       // t,  rank-major: tT[k * t_stride + token], defined for k < r, token < T
     const float* duT;      // du, rank-major: duT[k * du_stride + token]
-    float* dbeta_part;     // [splits, ell, rp]
     float* part;           // [splits, ell, rp, dcols]
     int T, d_in, d_out, r;
     int rp, t_pad, t_stride, du_stride, nbx, nbg, dcols, tw, splits, waves;
@@ -123,6 +120,34 @@ struct BwdArgs {
     int any;               // widths that are no multiples of 32, or tensors aligned to their elements only
 };
 
+// The scaling of a rank's entries (see the wgrad kernel): cur_e follows the largest entry seen so far, of the eight that each of the four lane
+// groups brings.  Returns the factor (a power of two) by which what has been accumulated has to be rescaled.
+__device__ __forceinline__ float follow_largest(const float (&v)[8], int& cur_e) {
+    float m = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fabsf(v[2]));
+    m = fmaxf(fmaxf(m, fabsf(v[3])), fabsf(v[4]));
+    m = fmaxf(fmaxf(m, fabsf(v[5])), fabsf(v[6]));
+    m = max_of_lane_groups(fmaxf(m, fabsf(v[7])));
+    int e = static_cast<int>((__float_as_uint(m) >> 23) & 0xffu);
+    e = e > 254 ? 254 : e;
+    const int sh = cur_e - e;
+    cur_e = e > cur_e ? e : cur_e;
+    return sh >= 0 ? 1.f : (sh < -126 ? 0.f : __uint_as_float(static_cast<uint32_t>(127 + sh) << 23));
+}
+// v mul as fp16 hi + lo, one rounding each (mixed-precision multiply-adds, two instructions per entry)
+__device__ __forceinline__ void split_scaled(const float (&v)[8], float mul, u4& hi, u4& lo) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        h2 h, l;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            h[j] = static_cast<_Float16>(__builtin_fmaf(v[2 * w + j], mul, 0.f));
+            l[j] = static_cast<_Float16>(__builtin_fmaf(v[2 * w + j], mul, -static_cast<float>(h[j])));
+        }
+        hi[w] = __builtin_bit_cast(uint32_t, h);
+        lo[w] = __builtin_bit_cast(uint32_t, l);
+    }
+}
+
 __global__ void bwd_zero_kernel(float* p, int64_t n) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0.f;
@@ -130,7 +155,7 @@ __global__ void bwd_zero_kernel(float* p, int64_t n) {
 
 // ----------------------------------------------------------------------------------------- wgrad kernel ----
 // Workgroup (cb, s): column block cb of x (cb < nbx: Q, with dt) or of g (P, with u), token rows [s * W tw, (s+1) * W tw),
-// one range of tw rows per wave; the workgroups with cb == 0 also take the share of d_beta of those token rows.  One step = 32 token rows x 128 columns.
+// one range of tw rows per wave.  One step = 32 token rows x 128 columns.
 // G steps are in flight per wave: the loads of a group are issued without any condition (past the end of the wave's range
 // they re-read valid addresses and are not used), so that every wait counts exactly the loads issued after the one it
 // needs; the last group is consumed without issuing anything.
@@ -228,6 +253,28 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         }
     };
     auto convert = [&](int tk0) {  // scale of the group, then its hi / lo (/ rest) operands
+        if constexpr (!ANY) {
+            static_assert(G == 1, "one step at a time");
+            if (tk0 + 32 > a.T) {   // scalar: the last rows (entries past T are undefined)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) sb[0][rb][e >> 2][e & 3] = tk0 + 8 * q + e < a.T ? sb[0][rb][e >> 2][e & 3] : 0u;
+                }
+            }
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(sb[0][rb][e >> 2][e & 3]);
+                if (const float f = follow_largest(v, cur_e[rb]); __builtin_amdgcn_ballot_w64(f != 1.f) != 0ull) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[rb][e] *= f;
+                }
+                split_scaled(v, __uint_as_float(static_cast<uint32_t>(267 - cur_e[rb]) << 23), hl[0][rb][0], hl[0][rb][1]);
+            }
+            return;
+        }
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             float v[G][8];
@@ -368,7 +415,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     for (int rb = 0; rb < RB; ++rb) {
         if (Z > 1 && rb0 + rb >= blocks) break;   // (uniform)
         if (rb > 0) __syncthreads();
-        const float inv = __uint_as_float(static_cast<uint32_t>(cur_e[rb] - 13) << 23);
+        const float inv = __uint_as_float(static_cast<uint32_t>(cur_e[rb] - 13) << 23) * (ANY ? 1.f : beta[rb]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) *reinterpret_cast<f4*>(&red[wave][e][lane][0]) = acc[rb][e] * inv;
         __syncthreads();
@@ -384,47 +431,187 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         *reinterpret_cast<f4*>(dst) = f4{sum[0], sum[1], sum[2], sum[3]};
         if constexpr (NE == 8) *reinterpret_cast<f4*>(dst + 4) = f4{sum[4], sum[5], sum[6], sum[7]};
     }
-    if (cb != 0) return;
-    // The workgroups of the first column block also take the share of d_beta_k = sum_t du[t,k] t[t,k] of their token rows
-    // (a column of workgroups of its own would push the grid past one workgroup per compute unit, i.e. into a second
-    // round): lane (li, q) takes rank li of each block and the tokens 8 q .. 8 q + 7 of every step; fixed order (lane, then
-    // lane groups, then waves).
-    __syncthreads();  // the sums below reuse the reduction area
-    {
-        float* sums = &red[0][0][0][0];
+}
+
+// The same contraction with the tokens streamed through LDS (plain variants only).  A workgroup takes one column block and one range of
+// tokens, TG tiles of 32 tokens per turn; the waves of a tile share it, each for one rank block and 128 / CW of the columns, so that x (or g)
+// passes through a compute unit once whatever the number of rank blocks is and a rank block's operands are converted by CW waves.  The
+// tiles come by direct loads into LDS, S turns of them (the one in work among them): the depth costs no registers.  The sums of the TG waves
+// of a rank block and column part are added through LDS at the end.
+// LDS of a tile: 32 rows of 256 bytes, the 16 pieces of row t moved on by kRot (t / 8) places where a wave has a part of the columns (a
+// lane group reads rows 8 q + e: rows eight apart would share their banks); then per rank block its 16 x 32 entries of du (or t), pieces of four
+// tokens by rank.
+// Waits: a wave's own loads of a turn are complete when at most the loads of the turns behind it are left (they complete in order),
+// everybody's behind the barrier; the place of the turn before, which everybody has read by then, takes the next one.
+// Bound: a wave's chain per tile (LDS, largest entry, conversion, 32 permutes, 16 MFMAs: about 0.5 us with two waves per SIMD) more than the
+// loads (8 KB of x and 2 KB per rank block), and 8 us for launch, first tile, sums and stores.  2048 x 5120 x 5120, four blocks: 15 us, the
+// register kernel 21; with CW = 2 (operands converted twice, twice the barriers per tile and wave) 20, one turn more in flight 15.5.
+template <int B, int CW, int TG, int S>
+__global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kernel(BwdArgs a, int range) {
+    constexpr int W = B * CW * TG, NC = 8 / CW;         // waves; columns per lane index of a wave
+    constexpr int NX = 8 * TG / W, NSM = 2 * B * TG > W ? 2 * B * TG / W : 1, PER = NX + NSM;   // 1024-byte loads of a wave per turn: x, small
+    constexpr int kTileBytes = 8192 + B * 2048, kSlotBytes = TG * kTileBytes, kRot = NC == 4 ? 8 : NC == 2 ? 4 : 0;
+    static_assert(W <= 16 && NX * W == 8 * TG && S >= 2 && (S - 2) * PER < 64, "whole loads per wave, counted by vmcnt");
+    static_assert((TG - 1) * B * CW * NC * 1024 <= S * kSlotBytes, "the sums of the other token groups");
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, q = lane >> 4;
+    const int rbe = a.rp >> 4, blocks = a.ell * rbe;
+    const int cb = blockIdx.x, rbw = wave % B, cw = wave / B % CW, tg = wave / (B * CW);
+    const bool is_x = cb < a.nbx;
+    const int d = is_x ? a.d_in : a.d_out, col0 = (is_x ? cb : cb - a.nbx) * 128;
+    const _Float16* src = is_x ? a.x : a.g;
+    const float* small = is_x ? a.duT : a.tT;   // dt = beta du meets x, u = beta t meets g
+    const int sstride = is_x ? a.du_stride : a.t_stride;
+    const int64_t tk_first = static_cast<int64_t>(blockIdx.y) * range, tk_last = (static_cast<int64_t>(a.T) + 31) & ~31ll;
+    const int tk_begin = static_cast<int>(tk_first < tk_last ? tk_first : tk_last);
+    const int tk_end = static_cast<int>(tk_first + range < tk_last ? tk_first + range : tk_last);
+    const int tiles = tk_begin < tk_end ? (tk_end - tk_begin) >> 5 : 0;
+
+    // the lane's row of the small arrays in its loads (rank block, rank) and its own rank
+    auto row_of = [&](int b, int rank) {   // (past the last block or rank: one that exists, its sums are never used)
+        b = b < blocks ? b : blocks - 1;
+        const int en = b / rbe, rk = (b - en * rbe) * 16 + rank;
+        return en * a.r + (rk < a.r ? rk : a.r - 1);
+    };
+    const int my_block = rbw < blocks ? rbw : blocks - 1, my_rank = (my_block % rbe) * 16 + li;
+    const float beta = my_rank < a.r ? static_cast<float>(a.s_rank[row_of(rbw, li)]) : 0.f;
+    const float* srow[NSM];
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int b = rb0 + rb < blocks ? rb0 + rb : blocks - 1, en = b / rbe, rk = (b - en * rbe) * 16 + li;
-            float s = 0.f;
-            const int row = en * a.r + (rk < a.r ? rk : a.r - 1);  // a rank that exists; the result of a padded rank is dropped below
-            const float* dup = a.duT + static_cast<size_t>(row) * a.du_stride;
-            const float* tp = a.tT + static_cast<size_t>(row) * a.t_stride;
-            for (int tk = tk_begin; tk < tk_end; tk += 32) {  // 32 bytes of each array per lane and step, inside t_pad entries (ANY: inside T)
-                const int tok = tk + 8 * q;
-                auto ld = [&](const float* p, int at) {
-                    if constexpr (!ANY) return load16(p + at);
-                    else return drop_words(load16_word(p + row_piece(at, a.T, row)), at - row_piece(at, a.T, row));
-                };
-                const u4 d0 = ld(dup, tok), d1 = ld(dup, tok + 4), t0 = ld(tp, tok), t1 = ld(tp, tok + 4);
+    for (int k = 0; k < NSM; ++k) {   // load j (two per rank block of a tile): pieces 4 (j % 2) .. of the 16 ranks of block j / 2 % B
+        const int j = (wave + k * W) % (2 * B * TG);
+        srow[k] = small + static_cast<size_t>(row_of((j >> 1) % B, li)) * sstride + ((j & 1) * 4 + q) * 4;
+    }
+    auto first_token = [&](int i, int tile) {   // of tile `tile` of turn i (behind the last tile: it again, not used)
+        const int at = i * TG + tile;
+        return tk_begin + 32 * (at < tiles ? at : tiles - 1);
+    };
+    auto issue = [&](int i) {
+        const uint32_t slot = static_cast<uint32_t>(i % S) * kSlotBytes;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float dv = __uint_as_float(e < 4 ? d0[e & 3] : d1[e & 3]), tv = __uint_as_float(e < 4 ? t0[e & 3] : t1[e & 3]);
-                    s += (tk + 8 * q + e < a.T) ? dv * tv : 0.f;   // select: entries past T are undefined
-                }
-            }
-            if (rk >= a.r) s = 0.f;
-            s += __shfl_xor(s, 16, 64);
-            s += __shfl_xor(s, 32, 64);
-            if (q == 0) sums[(rb * 16 + li) * W + wave] = s;
+        for (int k = 0; k < NX; ++k) {   // four rows of a tile
+            const int j = wave + k * W, r = 4 * (j & 7) + q;
+            const int piece = (li - kRot * (r >> 3)) & 15;
+            int row = first_token(i, j >> 3) + r, col = col0 + piece * 8;
+            row = row < a.T ? row : a.T - 1;   // rows past T meet dt = u = 0
+            col = col < d ? col : d - 8;       // past the end: a valid piece is re-read, its sums are never used
+            const _Float16* p = src + static_cast<size_t>(row) * d + col;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" :: "s"(slot + (j >> 3) * kTileBytes + (j & 7) * 1024u), "v"(p) : "memory");
         }
-        __syncthreads();
-        if (tid < RB * 16 && (rb0 + (tid >> 4)) < blocks) {
-            float tot = 0.f;
 #pragma unroll
-            for (int w = 0; w < W; ++w) tot += sums[tid * W + w];
-            a.dbeta_part[(static_cast<size_t>(blockIdx.y) * blocks + rb0) * 16 + tid] = tot;
+        for (int k = 0; k < NSM; ++k) {
+            const int j = (wave + k * W) % (2 * B * TG), tile = j / (2 * B);
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :: "s"(slot + tile * kTileBytes + 8192u + (j % (2 * B)) * 1024u), "v"(srow[k] + first_token(i, tile)) : "memory");
+        }
+    };
+    // at most n tiles' loads left (n < S - 1), and every read of LDS done
+    auto wait_tiles = [&](int n) {
+#define LORDBA_WAIT(N) if (n == N) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((N < S - 1 ? N : 0) * PER) : "memory"); else
+        LORDBA_WAIT(1) LORDBA_WAIT(2) LORDBA_WAIT(3) LORDBA_WAIT(4) LORDBA_WAIT(5) LORDBA_WAIT(6) LORDBA_WAIT(7) LORDBA_WAIT(8) LORDBA_WAIT(9) LORDBA_WAIT(10)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#undef LORDBA_WAIT
+    };
+    static_assert(S - 2 <= 10, "wait_tiles");
+
+    // (the products with the lo operands have sums of their own: one rounding per tile at the size of the result instead of two.  Error of the
+    // latent gradients against 64 bits, T = 2048, 4096^2, r = 64: 2.15e-7, in one sum 2.4e-7, in the kernel above 2.2e-7)
+    f4 acc[NC], acc_lo[NC];
+#pragma unroll
+    for (int e = 0; e < NC; ++e) acc[e] = acc_lo[e] = f4{0.f, 0.f, 0.f, 0.f};
+    int cur_e = 14;   // (the power-of-two scaling per rank of the kernel above; beta comes in at the end)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (beta: from here on the loads are counted)
+    const int turns = (tiles + TG - 1) / TG;
+#pragma unroll 1
+    for (int i = 0; i < S - 1 && i < turns; ++i) issue(i);
+#pragma unroll 1
+    for (int i = 0; i < turns; ++i) {
+        const int behind = turns - 1 - i;
+        wait_tiles(behind < S - 2 ? behind : S - 2);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (i + S - 1 < turns) issue(i + S - 1);
+        if (i * TG + tg >= tiles) continue;   // (scalar)
+        const unsigned char* slot = smem + (i % S) * kSlotBytes + tg * kTileBytes;
+        float v[8];
+        {
+            const unsigned char* sp = slot + 8192 + rbw * 2048 + (2 * q * 16 + li) * 16;
+            const u4 s0 = load16(sp), s1 = load16(sp + 256);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(e < 4 ? s0[e & 3] : s1[e & 3]);
+        }
+        const int tk = first_token(i, tg) + 8 * q;
+        if (first_token(i, tg) + 32 > a.T) {   // scalar: the last rows (entries past T are undefined)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = tk + e < a.T ? v[e] : 0.f;
+        }
+        if (const float f = follow_largest(v, cur_e); __builtin_amdgcn_ballot_w64(f != 1.f) != 0ull) {
+#pragma unroll
+            for (int e = 0; e < NC; ++e) {
+                acc[e] *= f;
+                acc_lo[e] *= f;
+            }
+        }
+        u4 hi, lo;
+        split_scaled(v, __uint_as_float(static_cast<uint32_t>(267 - cur_e) << 23), hi, lo);
+        uint32_t xr[8][NC / 2];   // token rows 8 q + e of the lane's NC columns
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int at = cw * (16 * NC) * 2 + li * (NC * 2);   // byte in the row
+            const unsigned char* p = slot + (8 * q + e) * 256 + ((at + kRot * 16 * q) & 255);
+            if constexpr (NC == 8) {
+                const u4 w = load16(p);
+                xr[e][0] = w[0]; xr[e][1] = w[1]; xr[e][2] = w[2]; xr[e][3] = w[3];
+            } else if constexpr (NC == 4) {
+                const uint2 w = *reinterpret_cast<const uint2*>(p);
+                xr[e][0] = w.x; xr[e][1] = w.y;
+            } else {
+                xr[e][0] = *reinterpret_cast<const uint32_t*>(p);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+            u4 col8;
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) col8[pr] = __builtin_amdgcn_perm(xr[2 * pr + 1][e >> 1], xr[2 * pr][e >> 1], sel);
+            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(col8), as_h8(hi), acc[e], 0, 0, 0);
+            acc_lo[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(col8), as_h8(lo), acc_lo[e], 0, 0, 0);
         }
     }
+    // Accumulator e, register i of lane (li, q): rank li, column NC (4 q + i) + e of the wave's: 4 NC consecutive columns per lane
+    const float back = __uint_as_float(static_cast<uint32_t>(cur_e - 13) << 23) * beta;
+    float out[4 * NC];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int e = 0; e < NC; ++e) out[i * NC + e] = (acc[e][i] + acc_lo[e][i]) * back;
+    }
+    if constexpr (TG > 1) {   // the token groups' sums, in their order
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        f4* red = reinterpret_cast<f4*>(smem);
+        const int w = wave % (B * CW);
+        if (tg > 0) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) red[((((tg - 1) * B * CW) + w) * NC + i) * 64 + lane] = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
+        }
+        __syncthreads();
+        if (tg > 0) return;
+#pragma unroll
+        for (int t = 1; t < TG; ++t) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                const f4 o = red[((((t - 1) * B * CW) + w) * NC + i) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[4 * i + e] += o[e];
+            }
+        }
+    }
+    if (rbw >= blocks) return;   // (a rank block too many)
+    float* dst = a.part + ((static_cast<size_t>(blockIdx.y) * blocks + rbw) * 16 + li) * a.dcols + static_cast<size_t>(cb) * 128 + (cw * 16 + 4 * q) * NC;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) *reinterpret_cast<f4*>(dst + 4 * i) = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
 }
 
 // ---------------------------------------------------------------------------------------- finish kernel ----
@@ -435,33 +622,186 @@ __device__ __forceinline__ float smooth_sign_factor(float latent, float kappa) {
     return 4.f * kappa * e / (s * s);
 }
 
-// One workgroup per group of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out, d_latentB), plus one for
+// d_beta_k = sum_t du[t, k] t[t, k] of one rank of one envelope (row k of all envelopes' ranks) by a workgroup of NT threads.  (By the wgrad
+// kernel's workgroups of one column block it was up to 5 us behind their other work.)  The order of the sum is fixed: thread, wave, waves.
+template <int NT>
+__device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int k, float* red) {
+    const float* du = a.duT + static_cast<size_t>(k) * a.du_stride;
+    const float* t = a.tT + static_cast<size_t>(k) * a.t_stride;
+    constexpr int U = 4;   // pieces of four tokens in flight
+    auto piece = [&](const float* p, int tok) { return drop_words(load16_word(p + row_piece(tok, a.T, k)), tok - row_piece(tok, a.T, k)); };
+    float acc[U][4];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j][e] = 0.f;
+    }
+    for (int64_t i = 4 * threadIdx.x; i < a.T; i += 4 * U * NT) {
+        u4 dv[U], tv[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int tok = static_cast<int>(i + 4 * j * NT < a.T ? i + 4 * j * NT : i);
+            dv[j] = piece(du, tok);
+            tv[j] = piece(t, tok);
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)   // select: entries past T are undefined
+                acc[j][e] += i + 4 * j * NT + e < a.T ? __uint_as_float(dv[j][e]) * __uint_as_float(tv[j][e]) : 0.f;
+        }
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < U; ++j) s += (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1) s += __shfl_xor(s, step, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float tot = 0.f;
+        for (int w = 0; w < NT / 64; ++w) tot += red[w];
+        a.d_s_rank[k] = tot;
+    }
+}
+
+// Widths that are multiples of 32.  A workgroup takes NG groups of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out,
+// d_latentB); a thread takes four columns and one rank (RK >= r of them), with all envelopes' shares, so that everything it needs is requested at
+// once in 16-byte pieces.  The workgroups in front of these take d_s_rank.  Bound: one trip to memory behind the launch.  2048 x 5120 x 5120, two
+// envelopes at r = 32 4.9 us, with one column per thread, shares eight at a time per envelope and latentB through LDS first 8.2; 4096^2, r = 16
+// 4.3 (4.45).
+template <int RK, int L>
+__global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kernel(BwdArgs a) {
+    constexpr int NT = RK < 32 ? 256 : 8 * RK, NG = NT / (8 * RK);
+    constexpr int SP = L == 1 ? 8 : 4;   // token ranges' shares in flight
+    __shared__ __align__(16) float sh[NG][L][RK][32];
+    __shared__ float lat[NG][32 * RK];
+    const int tid = threadIdx.x, r = a.r, rows = L * a.rp;
+    if (static_cast<int>(blockIdx.x) < L * r) {
+        rank_scale_gradient<NT>(a, blockIdx.x, &lat[0][0]);
+        return;
+    }
+    const int gx = a.d_in >> 5, gg = a.d_out >> 5;
+    const int ng = tid / (8 * RK), k = (tid >> 3) & (RK - 1), c = (tid & 7) * 4;   // group, rank, first of the four columns
+    const int g0 = (static_cast<int>(blockIdx.x) - L * r) * NG + ng;
+    const bool live = g0 < gx + gg && k < r;
+    const int gc = g0 < gx + gg ? g0 : gx + gg - 1, kc = k < r ? k : r - 1;   // (a group and a rank that exist)
+    const bool is_x = gc < gx;
+    const int grp = is_x ? gc : gc - gx, d = is_x ? a.d_in : a.d_out, col = grp * 32 + c;
+    const bool with_lat = a.d_latA != nullptr;   // (null: the carriers are frozen, only the scale gradients are wanted)
+    const float* plane = a.part + static_cast<size_t>(kc) * a.dcols + (is_x ? col : a.nbx * 128 + col);
+    const size_t plane_stride = static_cast<size_t>(rows) * a.dcols, env_stride = static_cast<size_t>(a.rp) * a.dcols;
+    f4 sum[L];
+    u4 v[L][SP];
+    auto request = [&](int sp0) {
+#pragma unroll
+        for (int en = 0; en < L; ++en) {
+#pragma unroll
+            for (int j = 0; j < SP; ++j) {
+                const int sp = sp0 + j < a.splits ? sp0 + j : a.splits - 1;
+                v[en][j] = load16(plane + sp * plane_stride + en * env_stride);
+            }
+        }
+    };
+    request(0);
+    const uint32_t word = (is_x ? a.pA : a.pBt)[kc * (d >> 5) + grp] >> c;
+    uint2 scale[L];
+#pragma unroll
+    for (int en = 0; en < L; ++en)
+        scale[en] = *reinterpret_cast<const uint2*>((is_x ? a.s_in : a.s_out) + static_cast<size_t>(en) * d + col);
+    float latent[4] = {0.f, 0.f, 0.f, 0.f};
+    if (with_lat) {
+        if (is_x) {   // (the same in all lanes of a wave: a group has at least one of its own)
+            const u4 w = *reinterpret_cast<const u4_word*>(a.latA + static_cast<size_t>(kc) * d + col);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) latent[e] = __uint_as_float(w[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) latent[e] = a.latB[static_cast<size_t>(col + e) * r + kc];
+        }
+    }
+#pragma unroll
+    for (int en = 0; en < L; ++en) sum[en] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int sp0 = 0;; sp0 += SP) {
+#pragma unroll
+        for (int en = 0; en < L; ++en) {
+#pragma unroll
+            for (int j = 0; j < SP; ++j) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[en][e] += sp0 + j < a.splits ? __uint_as_float(v[en][j][e]) : 0.f;
+            }
+        }
+        if (sp0 + SP >= a.splits) break;
+        request(sp0 + SP);
+    }
+    float weighted[4] = {0.f, 0.f, 0.f, 0.f};   // sum over the envelopes of scale_e * (Q_e or P_e)[k, col]: dL/dS[k, col]
+#pragma unroll
+    for (int en = 0; en < L; ++en) {
+        f4 ds;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float sc = static_cast<float>(as_h2(e < 2 ? scale[en].x : scale[en].y)[e & 1]);
+            ds[e] = live ? flip(sum[en][e], (word >> e) & 1u) : 0.f;
+            weighted[e] = L == 1 ? sc * sum[en][e] : fmaf(sc, sum[en][e], weighted[e]);
+        }
+        *reinterpret_cast<f4*>(&sh[ng][en][k][c]) = ds;
+    }
+    if (with_lat && live) {
+        float val[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) val[e] = weighted[e] * smooth_sign_factor(latent[e], a.kappa);
+        if (is_x) {
+            u4_word* dst = reinterpret_cast<u4_word*>(a.d_latA + static_cast<size_t>(k) * d + col);
+            u4 w;
+            if (a.accumulate) w = *dst;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(a.accumulate ? __uint_as_float(w[e]) + val[e] : val[e]);
+            *dst = w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) lat[ng][(c + e) * r + k] = val[e];   // (the group's 32 r entries of d_latentB, in their order)
+        }
+    }
+    __syncthreads();
+    const int gt = tid & (8 * RK - 1);   // thread of the group
+    if (g0 >= gx + gg) return;
+    if (with_lat && !is_x) {
+        float* dst = a.d_latB + static_cast<size_t>(grp) * 32 * r;
+        for (int e = gt; e < 32 * r; e += 8 * RK) dst[e] = a.accumulate ? dst[e] + lat[ng][e] : lat[ng][e];
+    }
+    for (int o = gt; o < 32 * L; o += 8 * RK) {   // the sums over the ranks, in their order
+        const int en = o >> 5, cc = o & 31;
+        float tot[4] = {0.f, 0.f, 0.f, 0.f};   // (four sums of a quarter of the ranks each: a chain over 64 would round more often)
+#pragma unroll 4
+        for (int j = 0; j < RK; j += 4) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) tot[m] += sh[ng][en][j + m][cc];
+        }
+        (is_x ? a.d_s_in : a.d_s_out)[static_cast<size_t>(en) * d + grp * 32 + cc] = (tot[0] + tot[1]) + (tot[2] + tot[3]);
+    }
+}
+
+// Any widths: one workgroup per group of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out, d_latentB), behind those for
 // d_s_rank.  Thread (c, kq) takes column c of the group and ranks kq, kq + KQ, ...; every sum has a fixed order.  KQ is the
-// padded rank up to 32: a thread then has one or two dependent rounds of requests instead of r / 8 (the whole backward call at
-// T = 512, 4096 -> 4096, r = 16 18.7 -> 16.5 us; T = 2048, r = 64 54.1 -> 47.7; long batches gain too, KQ = 8 in brackets: T = 4096,
-// 4096^2, r = 16 37.4 (38.3), r = 32 47.6 (49.6); T = 8192, 5120^2 83.7 (84.5), r = 64 136 (140), 13824 -> 5120 165.0 (165.7)).
-template <int KQ, bool ANY>
-__global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
+// padded rank up to 32: a thread then has one or two dependent rounds of requests instead of r / 8.
+template <int KQ>
+__global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_any_kernel(BwdArgs a) {
     constexpr int NT = 32 * KQ;
     __shared__ float sh[LORDBA_MAX_ENVELOPES][NT];
     __shared__ float lat[32 * LORDBA_MAX_RANK];
-    const int gx = (a.d_in + 31) >> 5, gg = (a.d_out + 31) >> 5;
+    const int gx = (a.d_in + 31) >> 5;
     const int tid = threadIdx.x;
     const int r = a.r, ell = a.ell, rows = ell * a.rp;   // rows of one token range's plane of partial sums: all envelopes' rank blocks
-    if (static_cast<int>(blockIdx.x) == gx + gg) {
-        for (int o = tid; o < ell * r; o += NT) {  // d_beta of every envelope: the shares of the token ranges, in their order
-            const int en = o / r, k = o - en * r;
-            float tot = 0.f;
-            for (int sp = 0; sp < a.splits; ++sp) tot += a.dbeta_part[static_cast<size_t>(sp) * rows + en * a.rp + k];
-            a.d_s_rank[en * r + k] = tot;
-        }
+    if (static_cast<int>(blockIdx.x) < ell * r) {
+        rank_scale_gradient<NT>(a, blockIdx.x, sh[0]);
         return;
     }
-    const bool is_x = static_cast<int>(blockIdx.x) < gx;
-    const int grp = is_x ? blockIdx.x : blockIdx.x - gx;
+    const int wg = static_cast<int>(blockIdx.x) - ell * r;
+    const bool is_x = wg < gx;
+    const int grp = is_x ? wg : wg - gx;
     const int d = is_x ? a.d_in : a.d_out;
     const int c = tid & 31, kq = tid >> 5;
-    const bool live = !ANY || grp * 32 + c < d;   // (ANY: the last group may have fewer than 32 columns)
+    const bool live = grp * 32 + c < d;   // (the last group may have fewer than 32 columns)
     const int col = live ? grp * 32 + c : d - 1;
     const float* plane = a.part + (is_x ? col : a.nbx * 128 + col);
     const uint32_t* pk = is_x ? a.pA : a.pBt;   // both [r, d]: the group's 32 bits of rank k are one word
@@ -472,7 +812,7 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
         scale[en] = static_cast<float>(is_x ? a.s_in[static_cast<size_t>(ec) * d + col] : a.s_out[static_cast<size_t>(ec) * d + col]);
         dscale[en] = 0.f;
     }
-    const int lat_n = (ANY && d - grp * 32 < 32 ? d - grp * 32 : 32) * r;
+    const int lat_n = (d - grp * 32 < 32 ? d - grp * 32 : 32) * r;
     if (!is_x && a.d_latB != nullptr) {  // latentB [d_out, r]: the group's 32 rows are 32 r contiguous floats; through LDS for coalesced accesses
         for (int e = tid; e < lat_n; e += NT) lat[e] = a.latB[static_cast<size_t>(grp) * 32 * r + e];
         __syncthreads();
@@ -484,10 +824,10 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_kernel(BwdArgs a) {
         // time, from a clamped index), the carrier word, the latent and, when accumulating, the gradient so far.  The
         // last two come from a harmless address when they are not wanted, so that no request hides behind a branch.
         const size_t n = static_cast<size_t>(k) * d + col;
-        const uint32_t word = ANY ? pk[n >> 5] : pk[k * (d >> 5) + grp];
+        const uint32_t word = pk[n >> 5];
         const float latent = *(lat_x ? a.latA + n : plane);
         const float so_far = *(add_x ? a.d_latA + n : plane);
-        const uint32_t bit = (word >> (ANY ? static_cast<int>(n & 31) : c)) & 1u;
+        const uint32_t bit = (word >> static_cast<int>(n & 31)) & 1u;
         float weighted = 0.f;   // sum over the envelopes of scale_e * (Q_e or P_e)[k, col]: dL/dS[k, col]
 #pragma unroll
         for (int en = 0; en < LORDBA_MAX_ENVELOPES; ++en) {
@@ -600,48 +940,107 @@ lordba_status launch_general(const BwdArgs& a, hipStream_t st) {
 bool aligned_to(const void* p, size_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
 
 template <int KQ>
+void launch_finish_any(const BwdArgs& a, hipStream_t st) {
+    const dim3 groups(a.ell * a.r + (a.d_in + 31) / 32 + (a.d_out + 31) / 32);
+    hipLaunchKernelGGL((lordba_bwd_finish_any_kernel<KQ>), groups, dim3(32 * KQ), 0, st, a);
+}
+template <int RK, int L>
 void launch_finish(const BwdArgs& a, hipStream_t st) {
-    const dim3 groups((a.d_in + 31) / 32 + (a.d_out + 31) / 32 + 1);
-    if (a.any) hipLaunchKernelGGL((lordba_bwd_finish_kernel<KQ, true>), groups, dim3(32 * KQ), 0, st, a);
-    else hipLaunchKernelGGL((lordba_bwd_finish_kernel<KQ, false>), groups, dim3(32 * KQ), 0, st, a);
+    constexpr int NT = RK < 32 ? 256 : 8 * RK, NG = NT / (8 * RK);
+    const unsigned groups = static_cast<unsigned>(a.d_in / 32 + a.d_out / 32);
+    hipLaunchKernelGGL((lordba_bwd_finish_kernel<RK, L>), dim3(L * a.r + (groups + NG - 1) / NG), dim3(NT), 0, st, a);
+}
+template <int L>
+void launch_finish_rank(const BwdArgs& a, hipStream_t st) {
+    // (four rank blocks at most in all: two envelopes have ranks up to 32, three and four up to 16)
+    if (a.r <= 8) return launch_finish<8, L>(a, st);
+    if constexpr (L <= 2)
+        if (a.r > 32 && L == 1) return launch_finish<64, 1>(a, st);
+    if constexpr (L <= 2)
+        if (a.r > 16) return launch_finish<32, L>(a, st);
+    launch_finish<16, L>(a, st);
 }
 
-template <int RB, int W, int Z>
-void launch_wgrad(const BwdArgs& a, hipStream_t st) {
+template <int RB, int W, int Z, bool ANY>
+lordba_status launch_wgrad(const BwdArgs& a, hipStream_t st) {
     const int nb = a.nbx + a.nbg;
     const dim3 grid(Z > 1 ? (nb + 7) / 8 * 8 * Z : nb, a.splits);
-    if (a.any) hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z, true>), grid, dim3(W * 64), 0, st, a);
-    else hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z, false>), grid, dim3(W * 64), 0, st, a);
+    hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z, ANY>), grid, dim3(W * 64), 0, st, a);
+    return LORDBA_OK;
+}
+template <int B, int CW, int TG, int S>
+lordba_status launch_stream(const BwdArgs& a, int64_t range, hipStream_t st) {
+    constexpr size_t lds = S * TG * (8192 + B * 2048);
+    auto kern = lordba_bwd_wgrad_stream_kernel<B, CW, TG, S>;
+    {   // more than 64 KiB of LDS per workgroup, asked for once per device
+        static std::mutex mu;
+        static bool granted[64] = {false};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return LORDBA_ERR_NO_DEVICE;
+        std::lock_guard<std::mutex> g(mu);
+        if (!granted[dev]) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess) {
+                (void)hipGetLastError();
+                return LORDBA_ERR_LAUNCH;
+            }
+            granted[dev] = true;
+        }
+    }
+    hipLaunchKernelGGL(kern, dim3(a.nbx + a.nbg, a.splits), dim3(B * CW * TG * 64), lds, st, a, static_cast<int>(range));
+    return LORDBA_OK;
 }
 
-lordba_status launch_all(const BwdArgs& a, hipStream_t st) {
-    // Rank blocks of all envelopes together over workgroups (Z) and inside one (RB).  A workgroup that held three or four blocks
-    // left one wave per SIMD (462 registers) with nothing to overlap its conversions, products and requests with; two
-    // workgroups with two blocks each read x and g twice, the second time out of the L2 they share (us of the whole backward call,
-    // one workgroup for all blocks in brackets: 2048 x 5120 x 5120, two envelopes at r = 32 49.4 (60.4); 4096 -> 4096, r = 64, T = 2048
-    // 43.5 (53.7), T = 64 22.3 (34.2); T = 8192, 5120^2 135 (152)).  Short batches gain from single blocks too (T = 2048, r = 32 29.9
-    // (31.5), r = 48 38.5 (41.3 with two)), but not four of them (r = 64 46.0), and long ones, which the streams bind, lose (T = 8192, r = 32
-    // 111 (97)).
+lordba_status launch_all(const BwdArgs& args, hipStream_t st) {
+    BwdArgs a = args;
     const bool short_batch = a.T < kShortBatch;
-    switch (a.ell * (a.rp / 16)) {
-        case 1:
-            if (a.waves == 2 * kWgradWaves) launch_wgrad<1, 2 * kWgradWaves, 1>(a, st);
-            else launch_wgrad<1, kWgradWaves, 1>(a, st);
-            break;
-        case 2:
-            if (short_batch) launch_wgrad<1, kWgradWaves, 2>(a, st);
-            else launch_wgrad<2, kWgradWaves, 1>(a, st);
-            break;
-        case 3:
-            if (short_batch) launch_wgrad<1, kWgradWaves, 3>(a, st);
-            else launch_wgrad<2, kWgradWaves, 2>(a, st);
-            break;
-        default: launch_wgrad<2, kWgradWaves, 2>(a, st); break;
+    const int blocks = a.ell * (a.rp / 16);   // rank blocks of all envelopes together
+    // From two rank blocks on the kernel that streams the tokens through LDS, where there is enough to stream: it starts later (tiles have to be in
+    // LDS, its sums go through it at the end) and gains with every tile, of which a compute unit gets T (column blocks) / 8192.  Below, the kernel
+    // that holds the tokens in registers, with a workgroup per block (or two) on short batches (Z), which read x (or g) again out of
+    // the L2 they share.  us of the whole backward call, that kernel in brackets: 4096 -> 4096, T = 2000, r = 32 28.6 (30.0); 5120 -> 11008, r = 32,
+    // T = 600 31.3 (31.0), 1100 39.8 (40.8), 3500 69.8 (80.9); r = 48 36.7 (37.6), 45.2 (48.0), 86.1 (101.9); r = 64 41.8 (41.4), 51.0 (52.4), 97.2 (106);
+    // 1536 -> 1536, T = 1100, r = 48 23.1 (22.2), T = 2000 24.3 (25.0); T = 8192, 5120^2, r = 64 120 (139), two envelopes at r = 16 97.0 (99.5).
+    // One block gains nothing (2048 x 4096^2, r = 16 25.6 (24.3), T = 8192, 13824 -> 5120 174 (169)): nothing is shared.
+    const int64_t tiles = static_cast<int64_t>(a.T) * (a.nbx + a.nbg);
+    const bool stream = !a.any && ((blocks == 2 && (!short_batch || tiles >= 72 * 1024)) || (blocks >= 3 && tiles >= 48 * 1024));
+    int64_t range = static_cast<int64_t>(a.tw) * a.waves;   // token rows of a workgroup
+    if (stream) {
+        // One workgroup fits a compute unit: as few token ranges as leave the last round of 256 workgroups nearly full (at least 0.9 of the
+        // best that the plan, which has the room for the sums, allows), in pieces of 64 rows.  5614 x 10496 -> 6016, three envelopes at
+        // r = 4, 129 column blocks: one range 170 us, three 153.
+        auto filled = [&](int splits) {
+            const int64_t n = static_cast<int64_t>(a.nbx + a.nbg) * splits;
+            return static_cast<double>(n) / static_cast<double>((n + 255) / 256 * 256);
+        };
+        double best = 0.0;
+        for (int k = 1; k <= a.splits; ++k) best = filled(k) > best ? filled(k) : best;
+        int splits = 1;
+        while (splits < a.splits && filled(splits) < 0.9 * best) ++splits;
+        range = ((a.T + splits - 1) / splits + 63) / 64 * 64;
+        a.splits = static_cast<int>((a.T + range - 1) / range);
     }
+    lordba_status s;
+    if (stream) s = blocks == 2 ? launch_stream<2, 1, 4, 3>(a, range, st) : launch_stream<4, 1, 2, 3>(a, range, st);
+    else if (blocks == 1 && a.waves == 2 * kWgradWaves) s = a.any ? launch_wgrad<1, 2 * kWgradWaves, 1, true>(a, st) : launch_wgrad<1, 2 * kWgradWaves, 1, false>(a, st);
+    else if (blocks == 1) s = a.any ? launch_wgrad<1, kWgradWaves, 1, true>(a, st) : launch_wgrad<1, kWgradWaves, 1, false>(a, st);
+    else if (!a.any) s = blocks == 2 ? launch_wgrad<1, kWgradWaves, 2, false>(a, st) : blocks == 3 && short_batch ? launch_wgrad<1, kWgradWaves, 3, false>(a, st) : launch_wgrad<2, kWgradWaves, 2, false>(a, st);
+    // (A workgroup that held three or four blocks left one wave per SIMD, 462 registers, with nothing to overlap its conversions, products
+    // and requests with; short batches gain from single blocks too, but not from four of them: r = 64, T = 2048 46.0 against 43.5 us.)
+    else if (blocks == 2) s = short_batch ? launch_wgrad<1, kWgradWaves, 2, true>(a, st) : launch_wgrad<2, kWgradWaves, 1, true>(a, st);
+    else if (blocks == 3 && short_batch) s = launch_wgrad<1, kWgradWaves, 3, true>(a, st);
+    else s = launch_wgrad<2, kWgradWaves, 2, true>(a, st);
+    if (s != LORDBA_OK) return s;
     if (hipGetLastError() != hipSuccess) return LORDBA_ERR_LAUNCH;
-    if (a.r <= 8) launch_finish<8>(a, st);
-    else if (a.r <= 16) launch_finish<16>(a, st);
-    else launch_finish<32>(a, st);
+    if (a.any) {
+        if (a.r <= 8) launch_finish_any<8>(a, st);
+        else if (a.r <= 16) launch_finish_any<16>(a, st);
+        else launch_finish_any<32>(a, st);
+    } else {
+        if (a.ell == 1) launch_finish_rank<1>(a, st);
+        else if (a.ell == 2) launch_finish_rank<2>(a, st);
+        else if (a.ell == 3) launch_finish_rank<3>(a, st);
+        else launch_finish_rank<4>(a, st);
+    }
     return hipGetLastError() == hipSuccess ? LORDBA_OK : LORDBA_ERR_LAUNCH;
 }
 
@@ -801,7 +1200,6 @@ lordba_status backward_impl(const void* x, const void* g,
         a.d_latB = d_latentB;
         a.tT = tT;
         a.duT = duT + e * r * p.t_pad;
-        a.dbeta_part = ws + p.off_dbeta;
         a.part = ws + p.off_part;
         a.T = static_cast<int>(T);
         a.d_in = static_cast<int>(d_in);

@@ -65,6 +65,13 @@ __device__ __forceinline__ float row_max16(float v) {
     v = fmaxf(v, row_rotate<2>(v));
     return fmaxf(v, row_rotate<1>(v));
 }
+// Maximum over the four lane groups of 16 (lanes li, li + 16, li + 32, li + 48), in every lane.
+__device__ __forceinline__ float max_of_lane_groups(float v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 __device__ __forceinline__ float flip(float v, uint32_t bit) { return __uint_as_float(__float_as_uint(v) ^ (bit << 31)); }
 
 // Row of the MFMA token operand -> token row of the tile.  With 16 token rows it is the identity.  With 8, MFMA

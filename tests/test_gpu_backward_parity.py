@@ -183,6 +183,19 @@ def test_rank_blocks_over_workgroups(torch_cuda, shape):
     check(torch_cuda, inputs.make_backward_inputs(26, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
 
 
+# The tokens streamed through LDS: tiles of 32 rows (a last one with one row, with all but one), turns of two and four tiles, fewer of them than
+# are in flight, token ranges of which the last is short; the line from which two (72 K row times column blocks, or 4096 rows), three and four
+# blocks (48 K) take that kernel, on either side; column blocks of 32 columns and with a tail; ranks at the edges of the finish
+# kernel's (8, 16, 32, 64), whose workgroups hold 4, 2 or 1 groups of columns
+@pytest.mark.parametrize("shape", [(4096, 160, 96, 32), (4097, 96, 32, 17), (4127, 32, 32, 32), (72 * 32, 2080, 2016, 32), (72 * 32 - 1, 2080, 2016, 18),
+                                   (48 * 32, 2080, 2016, 48), (48 * 32 - 1, 2080, 2016, 33), (64, 49184, 49120, 64), (65, 49184, 49120, 49), (33, 190560, 64, 64),
+                                   (31, 203008, 96, 50), (5000, 640, 800, 64), (12289, 224, 288, 40), (40, 4128, 64, 1), (40, 64, 1056, 8), (50, 96, 32, 9)],
+                         ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_tokens_streamed_through_lds(torch_cuda, shape):
+    T, d_in, d_out, r = shape
+    check(torch_cuda, inputs.make_backward_inputs(41, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
+
+
 # Widths around the edges of groups (8), words (32) and column blocks (128) on the element-aligned kernels, every rank-block count,
 # short and long batches
 @pytest.mark.parametrize("shape", [(70, 25, 41, 5), (33, 129, 127, 64), (300, 1000, 3001, 12), (45, 1055, 257, 33), (4100, 135, 250, 17),
