@@ -199,8 +199,22 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     const int c_first = wave * c_each + (wave < c_more ? wave : c_more);   // first chunk of the wave's run
     const int my_n = CA ? c_each + (wave < c_more ? 1 : 0) : (wave < nchunks ? (nchunks - wave + NW - 1) / NW : 0);
     // (the variants with element-aligned accesses keep the round-robin deal too: their rows of carrier bits start at any bit)
-    // (16-byte loads need whole chunks and rows that start on 16-byte boundaries)
+    // (whole chunks and rows that start on 16-byte boundaries)
     const bool wide_a = CA && (d_in & 127) == 0 && (reinterpret_cast<uintptr_t>(a.pA) & 15) == 0;
+    // x slots requested before the first one is consumed; every later one behind the consumption of the one AHEAD places before it.  The memory
+    // pipeline takes requests at the rate at which it returns data, so a wave that requests all of its slots first starts stage 1 when nearly all
+    // of its data is there (11008 -> 4096, r = 64, T = 8: 5.8 us of 17, and stage 1, bound by the vector ALU, another 9.5).  Where few
+    // workgroups run alone a third of the slots is enough, on grids that fill the chip half of them (us, all slots first, with the barrier
+    // below, in brackets; T = 8: 11008 -> 4096, r = 16 6.95 (8.9), r = 64 14.3 (17.0), 5120 -> 5120, r = 64 9.7 (11.1), 4096 -> 4096, r = 64 8.0 (8.4); T = 2048,
+    // r = 64 4096 -> 4096 16.6 (17.3), 5120 -> 5120 20.8 (22.4)).  Not below 8 rows with four slots, which are soon requested (T = 1,
+    // 4096 -> 4096, r = 48 6.57, with two ahead 6.74), nor on the 16-row tiles of one rank block (T = 4096, 5120 -> 5120, r = 16 23.1, with two 23.8).
+    constexpr bool FEW = SPLIT || GM == 5, TALL1 = TMV == 16 && RB == 1 && L == 1;
+    constexpr int AHEAD = !OS || ANY || D1 < 4 || (GM == 3 && D1 == 4) || GM == 4 || TALL1 ? D1 : FEW ? (D1 + 2) / 3 : D1 / 2;
+    // Carrier bits of ragged widths: in dwords per slot where all slots are requested first (T = 2048, 160 -> 4096, r = 16 7.9 us, with the loads of
+    // any alignment below 8.1), and with those loads where slots are requested behind consumed ones: a branch around dwords there makes every
+    // wait conservative (T = 300, 12480 -> 1024, r = 64 22.3 us, with the loads 17.8, the loop 19.5), and the dwords are a gather each
+    // (9760 -> 4096, r = 64, dwords and all slots first in brackets, T = 8 14.2 (21.6), T = 300 16.1 (26.1)).
+    constexpr bool AHEAD_A = CA && AHEAD < D1;
     u4 xbuf[D1][NI];
     uint32_t sinbuf[D1][L];
     uint32_t abits[D1][RB];
@@ -264,7 +278,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
                 abits[slot][rb] = pw[0];
                 abits_hi[slot][rb] = pw[1];
             }
-        } else if (!wide_a) {
+        } else if (!CA || (!AHEAD_A && !wide_a)) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 int rk = rb * 16 + li;
@@ -277,23 +291,45 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     };
     constexpr int AG = CA ? (D1 + 3) / 4 : 1;  // groups of four chunk slots
     u4 awide[AG][CA ? RB : 1];
-    if constexpr (CA) {
-        if (wide_a) {  // needed first, so requested first
+    // first of the four words of rank block rb for this lane's chunk of group g
+    auto first_word = [&](int g, int rb) {
+        int c = c_first + g * 4 + q, rk = rb * 16 + li;
+        c = c < nchunks ? c : nchunks - 1;
+        rk = rk < r ? rk : r - 1;
+        return rk * words_per_row + c * 4;
+    };
+    const int all_words = r * words_per_row;
+    if constexpr (CA) {  // needed first, so requested first
+        // (Rows of any number of words: a last chunk with fewer than four goes on into the next row, where s_in = 0 meets it, and in the last
+        // row the load ends with the tensor and is moved into place below: see AHEAD_A.)
+        if (wide_a) {
 #pragma unroll
             for (int g = 0; g < AG; ++g) {
-                int c = c_first + g * 4 + q;
-                c = c < nchunks ? c : nchunks - 1;
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) awide[g][rb] = load16(at(a.pA, static_cast<uint32_t>(first_word(g, rb)) * 4u));
+            }
+        } else if (AHEAD_A && all_words >= 4) {
+#pragma unroll
+            for (int g = 0; g < AG; ++g) {
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    int rk = rb * 16 + li;
-                    rk = rk < r ? rk : r - 1;
-                    awide[g][rb] = load16(at(a.pA, static_cast<uint32_t>(rk * words_per_row + c * 4) * 4u));
+                    const int w = first_word(g, rb);
+                    awide[g][rb] = load16_word(at(a.pA, static_cast<uint32_t>(w < all_words - 4 ? w : all_words - 4) * 4u));
+                }
+            }
+        } else if (AHEAD_A) {
+#pragma unroll
+            for (int g = 0; g < AG; ++g) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const int w = first_word(g, rb);
+                    awide[g][rb] = u4{a.pA[w], a.pA[w + 1 < all_words ? w + 1 : w], a.pA[w + 2 < all_words ? w + 2 : w], 0u};
                 }
             }
         }
     }
 #pragma unroll
-    for (int slot = 0; slot < D1; ++slot)
+    for (int slot = 0; slot < AHEAD; ++slot)
         if (!ANY || slot < my_n) issue_x(slot, slot);
     __builtin_amdgcn_sched_barrier(0);  // keep the issue order: nothing below may be hoisted above these requests
     float sr[RB][L];
@@ -395,10 +431,20 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     for (int e = tid; e < 256; e += NW * 64) lutp[e] = pm_one_from_bits(static_cast<uint32_t>(e) * 0x10001u);
 
     // ---------------------------------------------------------------- stage 1: sign(A) reduction ---
-    // Every wave works on wave-private LDS as soon as its own data has arrived.  The barrier waits for no data: it only
-    // keeps the fast waves from requesting y_base before the slow ones (held back by the bounded request queue) have
-    // requested their x.
-    __builtin_amdgcn_s_barrier();
+    // Every wave works on wave-private LDS as soon as its own data has arrived.  Where the x pipeline is a loop, on the 16-row tiles of one
+    // rank block and in batches of many tiles, a barrier that waits for no data keeps the fast waves from requesting y_base before the slow
+    // ones (held back by the bounded request queue) have requested their x (us, without it in brackets; 11008 -> 4096, T = 4096, r = 16
+    // 27.5 (28.3), T = 2048 17.4 (17.7); 8192 rows of 5120 -> 5120, 16 adapters 56.9 (57.9)).  Elsewhere it only delays the first wave's stage 1 until
+    // the last one's requests are out (us, with it in brackets; T = 8, r = 16 4096 -> 4096 4.47 (4.76), 5632 -> 2048 5.0 (5.7), 64 rows with their
+    // adapters 6.3 (6.8); T = 1500, 4096 -> 4096, r = 16 8.5 (8.9); T = 2048, 5120 -> 5120, two envelopes at r = 32 16.2 (18.0); T = 3000, r = 16 15.4
+    // (16.0)).  One envelope on 16 waves keeps it where the whole chip starts together on two chunks per wave (T = 2048, 4096 -> 4096, r = 16
+    // 9.68, without it 9.75; 3072 -> 6144, where not every wave has two, 14.8 and 14.4).
+    if constexpr (!FEW && (!OS || GM == 4 || TALL1)) __builtin_amdgcn_s_barrier();
+    else if constexpr (!OS && !POOL && !ANY) {   // (the loop on few tiles: T = 64, 8480 -> 1024, r = 48 11.3 (11.6), T = 300 13.3 (13.0))
+        if (gridDim.x > 16) __builtin_amdgcn_s_barrier();
+    } else if constexpr (!FEW && L == 1 && NW == 16 && D1 == 2) {
+        if (gridDim.x >= 240 && nchunks == D1 * NW) __builtin_amdgcn_s_barrier();   // (uniform)
+    }
     __builtin_amdgcn_sched_barrier(0);
     f4 acc[RB][L];
 #pragma unroll
@@ -449,7 +495,18 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     };
 
     if constexpr (CA) {
-        if (wide_a) {  // lane group q now gets word q of every slot's chunk
+        if (AHEAD_A && !wide_a && all_words >= 4) {  // (uniform)
+#pragma unroll
+            for (int g = 0; g < AG; ++g) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const int over = first_word(g, rb) - (all_words - 4);  // at most 3
+                    u4& v = awide[g][rb];
+                    if (over > 0) v = over == 1 ? u4{v[1], v[2], v[3], v[3]} : over == 2 ? u4{v[2], v[3], v[3], v[3]} : u4{v[3], v[3], v[3], v[3]};
+                }
+            }
+        }
+        if (AHEAD_A || wide_a) {  // lane group q now gets word q of every slot's chunk
 #pragma unroll
             for (int g = 0; g < AG; ++g) {
 #pragma unroll
@@ -464,8 +521,10 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     }
     if (OS) {
 #pragma unroll
-        for (int slot = 0; slot < D1; ++slot)
+        for (int slot = 0; slot < D1; ++slot) {
             if (slot < my_n) consume_x(slot, slot);
+            if (slot + AHEAD < D1) issue_x(slot + AHEAD, slot + AHEAD);
+        }
     } else {
         const int ngroups = (my_n + D1 - 1) / D1;
         for (int g = 0; g + 1 < ngroups; ++g) {
@@ -1194,11 +1253,11 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
     }
     if (per_wave <= 4) return launch_mfma<RB, TMV, NW, 4, true, BM, L>(a, stream);
     if (kDeep && per_wave <= 8 && a.ids == nullptr) return launch_mfma<RB, TMV, NW, (kDeep ? 8 : 4), true, BM, L>(a, stream);  // (the batch mode has 128 registers)
-    // Wide inputs at decode sizes: all chunks of a wave in flight at once here too (up to 12288 columns; the registers are there since
-    // a wave has one output block at most): the loop over groups of four exposed the memory latency once per group.  11008 -> 4096,
-    // T = 8: r = 16 9.4 -> 9.0 us, r = 32 14.1 -> 11.7, r = 64 18.5 -> 17.2 (5.3 of it the vector ALU's: 11008 x 64 signs per workgroup);
-    // T = 300, r = 16 12.9 -> 10.0.  (Wider inputs, such as 13824 columns, stay with the loop: variants with more slots were not built.)
-    constexpr int kOneShot = NW == 16 ? 6 : 12;
+    // Wide inputs at decode sizes: straight-line code for all chunks of a wave here too (up to 14336 columns), as many requested ahead as
+    // stage 1 needs (see AHEAD): the loop over groups of four exposed the memory latency once per group.  us, the loop in brackets, T = 8: 11008 ->
+    // 4096, r = 16 7.0 (9.4), r = 32 9.2 (14.1), r = 64 14.3 (18.5); 13824 -> 5120, r = 16 7.6 (9.4), r = 32 10.4 (13.8), r = 48 13.7 (16.6), r = 64
+    // 17.1 (21.4).  (8 waves from 98 chunks on: with 97, the last one of 32 columns, T = 1, r = 48 14.3 (13.5).)
+    constexpr int kOneShot = NW == 16 ? 6 : 12, kOneShotWide = NW == 16 ? 7 : 14;
     if constexpr (TMV == 8 && L == 1 && !kTraining && (NW == 16 || (NW == 8 && RB >= 3))) {  // (one and two rank blocks run on 16 waves)
         const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
         if (a.ids != nullptr) {
@@ -1208,7 +1267,11 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
                 const int per_wg = pool_split_blocks(a);
                 if (per_wave <= kOneShot && tiles <= kFewPoolTiles && per_wg <= NW && per_wg < (a.d_out + 127) / 128)
                     return launch_mfma_gm<RB, TMV, NW, kOneShot, true, BM, 5, L>(a, stream);
+                if (per_wave > kOneShot && per_wave <= kOneShotWide && tiles <= kFewPoolTiles && per_wg <= NW && per_wg < (a.d_out + 127) / 128)
+                    return launch_mfma_gm<RB, TMV, NW, kOneShotWide, true, BM, 5, L>(a, stream);
             }
+        } else if (per_wave > kOneShot && per_wave <= kOneShotWide && (NW == 16 || nchunks >= 98) && tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
+            return launch_mfma_gm<RB, TMV, NW, kOneShotWide, true, BM, 2, L>(a, stream);
         } else if (per_wave <= kOneShot && tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
             // Slots that a wave has no chunk for repeat a request, so the loop keeps the counts of which few waves have a chunk beyond
             // whole groups of four (us, one-shot against the loop; d_out 1024: 33 chunks, T = 64, r = 48 9.2 : 8.6, 36 9.3 : 9.5, 40 10.1 :

@@ -40,6 +40,11 @@ PLANS = [
     # twelve x slots per wave on 8 waves (three and four rank blocks, whole and ragged carrier words), and the loop beside them
     (9, 11008, 640, 48, 1), (8, 11008, 4096, 64, 1), (11, 9760, 512, 50, 1), (10, 9760, 384, 41, 1), (300, 12288, 1024, 64, 1),
     (9, 8480, 512, 64, 1), (9, 8320, 256, 64, 1), (9, 8480, 256, 48, 1),
+    # fourteen slots on 8 waves and seven on 16 (97 to 112 chunks, the last one whole or ragged), and the loop from 113 chunks on
+    (9, 12320, 640, 48, 1), (8, 13824, 5120, 64, 1), (1, 14336, 136, 41, 1), (300, 14336, 520, 64, 1), (9, 14368, 512, 64, 1),
+    (9, 12320, 640, 16, 1), (8, 13824, 5120, 32, 1), (1, 14336, 136, 12, 1), (300, 14304, 520, 24, 1), (9, 14368, 512, 16, 1),
+    # every wave with two chunks on 16 waves, with and without a chip full of workgroups, and one wave short of it
+    (2040, 4096, 264, 16, 1), (1601, 4096, 264, 8, 1), (2040, 3968, 264, 16, 1), (2040, 4064, 264, 30, 1),
     # eight slots, and the loop
     (9, 4640, 640, 48, 1), (8, 5120, 4096, 64, 1), (13, 8192, 136, 57, 1), (1000, 4608, 512, 33, 1), (9, 4480, 256, 48, 1), (9, 4256, 512, 64, 1),
     # six slots on 16 waves, and the loop
@@ -92,6 +97,7 @@ def test_plan(torch_cuda, plan):
 POOLS = [
     (61, 11008, 640, 16, 3, "decode"), (61, 11008, 640, 16, 3, "mixed"), (61, 11008, 512, 16, 3, "decode"), (9, 9760, 1024, 8, 2, "mixed"),
     (250, 12288, 1152, 16, 4, "segments"),
+    (61, 13824, 640, 16, 3, "decode"), (9, 12320, 1024, 8, 2, "mixed"), (61, 14336, 512, 32, 3, "mixed"), (9, 14368, 512, 16, 2, "decode"),
     (289, 353, 140, 2, 16, "decode"), (1021, 99, 77, 17, 5, "decode"), (300, 130, 205, 40, 3, "mixed"), (1030, 99, 77, 17, 5, "decode"),
     (1033, 353, 140, 8, 4, "segments"),
 ]
