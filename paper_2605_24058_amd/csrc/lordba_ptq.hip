@@ -1332,8 +1332,9 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
 
     // One launch for all sweeps where a row's ranks fit the 16 lanes of a row and the Gram pair's tiles the LDS, at any number of rows: 1.3 to
     // 2.8 times as fast as launches per sweep on 42 shapes, also where its at most 64 blocks per step leave compute units without one (ms
-    // per call, launches per sweep in brackets, R = r0 = 16: 512^2 0.80 (1.95), 4096^2 1.20 (2.19), 16384^2 2.3 (4.4), 262144^2 88 (175),
-    // 1048576 x 4096 172 (378); R = 16, r0 = 32 4096^2 2.3 (3.5), 8192^2 2.85 (3.82); R = r0 = 4 4096^2 0.84 (1.67)).
+    // per call, launches per sweep in brackets, R = r0 = 16: 512^2 0.74 (1.95), 4096^2 0.93 (2.19); R = 16, r0 = 32
+    // 4096^2 1.91 (3.5); before the shares carried a mark also 16384^2 2.3 (4.4), 262144^2 88 (175), 1048576 x 4096 172 (378); 65536^2 25.1,
+    // with the mark 21.9).
     const bool one_launch = iR <= 16 && ir0 <= 32;
     const void* run_fn = ir0 <= 16 ? reinterpret_cast<const void*>(lordba_ptq_run_kernel<1>) : reinterpret_cast<const void*>(lordba_ptq_run_kernel<2>);
     const size_t lds_run = sizeof(double) * run_lds_doubles(ir0 <= 16 ? 1 : 2);
@@ -1417,10 +1418,10 @@ extern "C" lordba_status lordba_ptq_sweeps(const void* A_star, const void* B_sta
         PtqRun& g = args.g;
         // A workgroup for every block of a sweep (each waits, its rows requested, when its step begins) up to 160 of them, beyond that one for
         // every block of a Tikhonov step, at most 129: two runs on two streams then share the chip, where more workgroups of one keep the
-        // other's out while they wait.  ms per run, with all blocks in brackets: 8192^2, R = 16, alone 1.69 (1.73), two streams 0.92 (1.68),
-        // 16 0.95 (1.55; launches per sweep 1.42); 4096^2 1.25 (1.28), 0.67 (0.80), 0.66 (0.77); 3400^2, 163 blocks, 1.21 (1.23), 0.63 (0.64),
-        // 0.60 (0.64).  Smaller ones fit twice as they are, and alone the fewer workgroups lose: 2560^2, 121 blocks, 1.07 (1.02), 512^2
-        // 0.81 (0.80).
+        // other's out while they wait.  ms per run, with all blocks in brackets: 8192^2, R = 16, alone 1.35 (1.51), two streams 0.75 (1.47),
+        // 16 0.79 (1.36; launches per sweep 1.42); 4096^2 0.98 (1.05), 0.57 (0.69), 0.55 (0.65); 3400^2, 163 blocks, 0.99 (1.01), 0.52 (0.57),
+        // 0.48 (0.56).  Smaller ones fit twice as they are, and it makes no difference there: 2560^2, 121 blocks, 0.93 (0.93), 0.48 (0.48), 0.48
+        // (0.49).
         int rows = 1, all = 1;
         for (int s = 0; s < 2; ++s) {
             g.nbU[s] = L.u[s].nb;
