@@ -329,8 +329,10 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
         }
     }
 #pragma unroll
-    for (int slot = 0; slot < AHEAD; ++slot)
+    for (int slot = 0; slot < AHEAD; ++slot) {
         if (!ANY || slot < my_n) issue_x(slot, slot);
+        if constexpr (AHEAD_A) __builtin_amdgcn_sched_barrier(0);
+    }
     __builtin_amdgcn_sched_barrier(0);  // keep the issue order: nothing below may be hoisted above these requests
     float sr[RB][L];
 #pragma unroll
@@ -438,12 +440,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // the last one's requests are out (us, with it in brackets; T = 8, r = 16 4096 -> 4096 4.47 (4.76), 5632 -> 2048 5.0 (5.7), 64 rows with their
     // adapters 6.3 (6.8); T = 1500, 4096 -> 4096, r = 16 8.5 (8.9); T = 2048, 5120 -> 5120, two envelopes at r = 32 16.2 (18.0); T = 3000, r = 16 15.4
     // (16.0)).  One envelope on 16 waves keeps it where the whole chip starts together on two chunks per wave (T = 2048, 4096 -> 4096, r = 16
-    // 9.68, without it 9.75; 3072 -> 6144, where not every wave has two, 14.8 and 14.4).
+    // 9.68, without it 9.75; 3072 -> 6144, where not every wave has two, 14.8 and 14.4), and at widths that are no multiple of 128 (3104 -> 3072 8.6,
+    // without it 9.2).
     if constexpr (!FEW && (!OS || GM == 4 || TALL1)) __builtin_amdgcn_s_barrier();
     else if constexpr (!OS && !POOL && !ANY) {   // (the loop on few tiles: T = 64, 8480 -> 1024, r = 48 11.3 (11.6), T = 300 13.3 (13.0))
         if (gridDim.x > 16) __builtin_amdgcn_s_barrier();
     } else if constexpr (!FEW && L == 1 && NW == 16 && D1 == 2) {
-        if (gridDim.x >= 240 && nchunks == D1 * NW) __builtin_amdgcn_s_barrier();   // (uniform)
+        if (gridDim.x >= 240 && (nchunks == D1 * NW || !wide_a)) __builtin_amdgcn_s_barrier();   // (uniform)
     }
     __builtin_amdgcn_sched_barrier(0);
     f4 acc[RB][L];
@@ -523,7 +526,11 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
 #pragma unroll
         for (int slot = 0; slot < D1; ++slot) {
             if (slot < my_n) consume_x(slot, slot);
-            if (slot + AHEAD < D1) issue_x(slot + AHEAD, slot + AHEAD);
+            if (slot + AHEAD < D1) {
+                __builtin_amdgcn_sched_barrier(0);  // (neither hoisted into the consumption nor mixed with the next one)
+                issue_x(slot + AHEAD, slot + AHEAD);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     } else {
         const int ngroups = (my_n + D1 - 1) / D1;
