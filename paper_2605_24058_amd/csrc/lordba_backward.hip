@@ -496,13 +496,12 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
             row = row < a.T ? row : a.T - 1;   // rows past T meet dt = u = 0
             col = col < d ? col : d - 8;       // past the end: a valid piece is re-read, its sums are never used
             const _Float16* p = src + static_cast<size_t>(row) * d + col;
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" :: "s"(slot + (j >> 3) * kTileBytes + (j & 7) * 1024u), "v"(p) : "memory");
+            load16_to_lds<true>(slot + (j >> 3) * kTileBytes + (j & 7) * 1024u, p);
         }
 #pragma unroll
         for (int k = 0; k < NSM; ++k) {
             const int j = (wave + k * W) % (2 * B * TG), tile = j / (2 * B);
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                         :: "s"(slot + tile * kTileBytes + 8192u + (j % (2 * B)) * 1024u), "v"(srow[k] + first_token(i, tile)) : "memory");
+            load16_to_lds<false>(slot + tile * kTileBytes + 8192u + (j % (2 * B)) * 1024u, srow[k] + first_token(i, tile));
         }
     };
     // at most n tiles' loads left (n < S - 1), and every read of LDS done

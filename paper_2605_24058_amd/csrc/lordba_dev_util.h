@@ -49,6 +49,15 @@ __device__ __forceinline__ h8 clamp_finite(h8 v) {
     const us8 neg = __builtin_elementwise_min(__builtin_bit_cast(us8, v), static_cast<us8>(static_cast<uint16_t>(0xFBFF)));
     return __builtin_bit_cast(h8, __builtin_elementwise_min(__builtin_bit_cast(s8, neg), static_cast<s8>(static_cast<int16_t>(0x7BFF))));
 }
+// 16 bytes per lane straight into LDS: lane l's go to byte lds + 16 l (lds: uniform).  It counts as one vector memory operation of the wave,
+// and the caller waits for it by that count: the compiler, which would wait for every such load in flight before the next read of LDS,
+// does not see it.  It writes M0 for the block, though, where the offset goes; the load has to stand one wait state or more behind that, and
+// inside an asm block the compiler adds none.
+template <bool STREAM>
+__device__ __forceinline__ void load16_to_lds(uint32_t lds, const void* p) {
+    if constexpr (STREAM) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" :: "v"(p), "{m0}"(lds) : "memory");
+    else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(p), "{m0}"(lds) : "memory");
+}
 // Address = uniform base (kept in scalar registers) + unsigned 32-bit byte offset per lane: one add-free addressing
 // mode, no 64-bit vector arithmetic.
 __device__ __forceinline__ const void* at(const void* base, uint32_t byte_off) { return static_cast<const char*>(base) + byte_off; }
