@@ -195,8 +195,11 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     for (int rb = 0; rb < RB; ++rb) {   // block b: envelope b / (rp / 16), ranks 16 (b % (rp / 16)) ..  (past the last block: it again)
         const int b = rb0 + rb < blocks ? rb0 + rb : blocks - 1, en = b / rbe, rk = (b - en * rbe) * 16 + li;
         row_of[rb] = en * a.r + (rk < a.r ? rk : a.r - 1);
-        beta[rb] = rk < a.r ? static_cast<float>(a.s_rank[row_of[rb]]) : 0.f;
+        beta[rb] = rk < a.r ? static_cast<float>(a.s_rank[row_of[rb]]) : ANY ? 0.f : 1.f;   // (a padded rank's sums are never used)
     }
+    bool silent = false;   // a rank without scale among this wave's: it adds nothing, whatever its entries are (!ANY)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) silent |= __builtin_amdgcn_ballot_w64(beta[rb] == 0.f) != 0ull;
     int col = cc * 128 + li * 8;
     const int back = ANY && col > d - 8 ? col - (d - 8) : 0;   // columns that a ragged group was moved back by
     col = ANY ? col - back : (col < d ? col : d - 8);  // past the end: a valid column group is re-read, its sums are never used
@@ -255,11 +258,11 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     auto convert = [&](int tk0) {  // scale of the group, then its hi / lo (/ rest) operands
         if constexpr (!ANY) {
             static_assert(G == 1, "one step at a time");
-            if (tk0 + 32 > a.T) {   // scalar: the last rows (entries past T are undefined)
+            if (silent || tk0 + 32 > a.T) {   // scalar: the last rows (entries past T are undefined)
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) sb[0][rb][e >> 2][e & 3] = tk0 + 8 * q + e < a.T ? sb[0][rb][e >> 2][e & 3] : 0u;
+                    for (int e = 0; e < 8; ++e) sb[0][rb][e >> 2][e & 3] = beta[rb] != 0.f && tk0 + 8 * q + e < a.T ? sb[0][rb][e >> 2][e & 3] : 0u;
                 }
             }
 #pragma unroll
@@ -415,9 +418,9 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     for (int rb = 0; rb < RB; ++rb) {
         if (Z > 1 && rb0 + rb >= blocks) break;   // (uniform)
         if (rb > 0) __syncthreads();
-        const float inv = __uint_as_float(static_cast<uint32_t>(cur_e[rb] - 13) << 23) * (ANY ? 1.f : beta[rb]);
+        const float inv = __uint_as_float(static_cast<uint32_t>(cur_e[rb] - 13) << 23);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) *reinterpret_cast<f4*>(&red[wave][e][lane][0]) = acc[rb][e] * inv;
+        for (int e = 0; e < 8; ++e) *reinterpret_cast<f4*>(&red[wave][e][lane][0]) = acc[rb][e] * inv * (ANY ? 1.f : beta[rb]);   // (one after the other: their product may vanish)
         __syncthreads();
         float sum[NE];
 #pragma unroll
@@ -475,7 +478,7 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
         return en * a.r + (rk < a.r ? rk : a.r - 1);
     };
     const int my_block = rbw < blocks ? rbw : blocks - 1, my_rank = (my_block % rbe) * 16 + li;
-    const float beta = my_rank < a.r ? static_cast<float>(a.s_rank[row_of(rbw, li)]) : 0.f;
+    const float beta = my_rank < a.r ? static_cast<float>(a.s_rank[row_of(rbw, li)]) : 1.f;   // (a padded rank's sums are never used)
     const float* srow[NSM];
 #pragma unroll
     for (int k = 0; k < NSM; ++k) {   // load j (two per rank block of a tile): pieces 4 (j % 2) .. of the 16 ranks of block j / 2 % B
@@ -519,6 +522,7 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
 #pragma unroll
     for (int e = 0; e < NC; ++e) acc[e] = acc_lo[e] = f4{0.f, 0.f, 0.f, 0.f};
     int cur_e = 14;   // (the power-of-two scaling per rank of the kernel above; beta comes in at the end)
+    const bool silent = __builtin_amdgcn_ballot_w64(beta == 0.f) != 0ull;   // a rank without scale: it adds nothing, whatever its entries are
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (beta: from here on the loads are counted)
     const int turns = (tiles + TG - 1) / TG;
 #pragma unroll 1
@@ -540,9 +544,9 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
             for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(e < 4 ? s0[e & 3] : s1[e & 3]);
         }
         const int tk = first_token(i, tg) + 8 * q;
-        if (first_token(i, tg) + 32 > a.T) {   // scalar: the last rows (entries past T are undefined)
+        if (silent || first_token(i, tg) + 32 > a.T) {   // scalar: the last rows (entries past T are undefined)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = tk + e < a.T ? v[e] : 0.f;
+            for (int e = 0; e < 8; ++e) v[e] = beta != 0.f && tk + e < a.T ? v[e] : 0.f;
         }
         if (const float f = follow_largest(v, cur_e); __builtin_amdgcn_ballot_w64(f != 1.f) != 0ull) {
 #pragma unroll
@@ -579,12 +583,12 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
         }
     }
     // Accumulator e, register i of lane (li, q): rank li, column NC (4 q + i) + e of the wave's: 4 NC consecutive columns per lane
-    const float back = __uint_as_float(static_cast<uint32_t>(cur_e - 13) << 23) * beta;
+    const float back = __uint_as_float(static_cast<uint32_t>(cur_e - 13) << 23);
     float out[4 * NC];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
-        for (int e = 0; e < NC; ++e) out[i * NC + e] = (acc[e][i] + acc_lo[e][i]) * back;
+        for (int e = 0; e < NC; ++e) out[i * NC + e] = (acc[e][i] + acc_lo[e][i]) * back * beta;   // (one after the other: their product may vanish)
     }
     if constexpr (TG > 1) {   // the token groups' sums, in their order
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");

@@ -196,6 +196,30 @@ def test_tokens_streamed_through_lds(torch_cuda, shape):
     check(torch_cuda, inputs.make_backward_inputs(41, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
 
 
+# A rank whose scale is zero (how a further envelope starts) adds nothing, whatever t and du hold: every entry of its latent gradients is
+# zero except in the columns where x or g itself is not finite.  Eight and four waves, a workgroup per rank block (two and three), two
+# workgroups for four, and the tokens streamed through LDS (two, three and four blocks)
+@pytest.mark.parametrize("shape", [(40, 96, 64, 16), (4100, 96, 64, 12), (37, 96, 64, 32), (100, 96, 96, 48), (100, 96, 96, 64), (4100, 96, 64, 32),
+                                   (12289, 224, 288, 40), (12289, 224, 288, 64)], ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_a_rank_without_scale_adds_nothing_to_what_is_not_finite(torch_cuda, shape):
+    T, d_in, d_out, r = shape
+    say("  case T%d_%dx%d_r%d" % shape)
+    d = inputs.make_backward_inputs(42, T, d_in, d_out, r)
+    silent = [0, r // 2, r - 1]
+    for all_silent in (False, True):
+        d["s_rank"][silent] = 0.0
+        if all_silent:
+            d["s_rank"][:] = 0.0
+        for k in ("x", "g"):
+            d[k] = d[k].copy()
+            d[k][T // 2, 5], d[k][T - 1, 9] = np.inf, np.nan
+        got = gpu_backward(torch_cuda, d)
+        rest = {k: np.setdiff1d(np.arange(n), (5, 9)) for k, n in (("x", d_in), ("g", d_out))}
+        assert not got["d_latentA"][silent][:, rest["x"]].any() and not got["d_latentB"][rest["g"]][:, silent].any()
+        if all_silent:
+            assert not got["d_s_in"][rest["x"]].any() and not got["d_s_out"][rest["g"]].any()
+
+
 # Widths around the edges of groups (8), words (32) and column blocks (128) on the element-aligned kernels, every rank-block count,
 # short and long batches
 @pytest.mark.parametrize("shape", [(70, 25, 41, 5), (33, 129, 127, 64), (300, 1000, 3001, 12), (45, 1055, 257, 33), (4100, 135, 250, 17),
