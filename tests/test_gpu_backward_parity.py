@@ -387,12 +387,16 @@ def test_unaligned_tensors_and_any_kept_t(torch_cuda):
 
 
 @pytest.mark.parametrize("case", [(2, 203, 1056, 2080, 16), (4, 45, 512, 640, 8), (3, 70, 1024, 768, 16), (2, 4100, 256, 384, 32),
-                                  (4, 37, 512, 512, 16), (4, 4133, 512, 256, 16), (3, 70, 1024, 768, 32)],
+                                  (4, 37, 512, 512, 16), (4, 4133, 512, 256, 16), (3, 70, 1024, 768, 32),
+                                  # above the lines from which the tokens are streamed through LDS: two blocks, three in the kernel of four, four,
+                                  # ranks that fill their blocks and ranks that do not, a last tile and a last column block in part
+                                  (2, 4127, 416, 224, 16), (2, 2305, 2080, 2016, 9), (3, 1537, 2080, 2016, 13), (3, 1500, 2208, 2016, 16),
+                                  (2, 1537, 2080, 2016, 32), (2, 1555, 2016, 2080, 21), (4, 1537, 2080, 2016, 11)],
                          ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
 def test_several_envelopes_in_one_pass(torch_cuda, case):
     """lordba_backward_multi with the workspace of lordba_backward_multi_workspace_bytes: one wgrad and one finish pass hold
-    the partial sums of all envelopes (up to four rank blocks in all; the last case has six and goes envelope by envelope
-    whatever the workspace).  Every output against the oracle, and against the envelope-by-envelope result of the same
+    the partial sums of all envelopes (up to four rank blocks in all; three envelopes at r = 32 have six and go envelope by
+    envelope whatever the workspace).  Every output against the oracle, and against the envelope-by-envelope result of the same
     library (same sums in another order: 1e-5), with recomputed and with kept t."""
     torch = torch_cuda
     ell, T, d_in, d_out, r = case
