@@ -87,7 +87,9 @@ BwdPlan make_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, int64_t ell
     p.off_t = 0;
     p.off_du = p.off_t + static_cast<size_t>(LORDBA_MAX_ENVELOPES) * p.rp * p.t_pad;
     p.off_part = p.off_du + static_cast<size_t>(LORDBA_MAX_ENVELOPES) * p.rp * p.t_pad;
-    p.words = p.off_part + static_cast<size_t>(p.splits) * p.rp * ell_fused * p.dcols;
+    // (one word per sum more than the kernels use: the size that programs keep a workspace of, and the shapes that fit the array of
+    // lordba_backward_noalloc, are the ones they were when the shares of d_s_rank were here)
+    p.words = p.off_part + static_cast<size_t>(p.splits) * p.rp * ell_fused * (p.dcols + 1);
     return p;
 }
 

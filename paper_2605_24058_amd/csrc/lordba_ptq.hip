@@ -1220,7 +1220,7 @@ Layout make_layout(int64_t N, int64_t M, int64_t R, int64_t r0) {
     for (int s = 0; s < 2; ++s) {   // (the run kernel keeps its shares in the same place: those of the Tikhonov blocks, then the scale blocks')
         L.u[s] = run_blocks(n[s], kRunRows);
         L.s[s] = run_blocks(n[s], kRunScaleRows);
-        const size_t rows = static_cast<size_t>(L.nb[s]) * L.pstride, run = static_cast<size_t>(L.u[s].nb + L.s[s].nb) * run_count(static_cast<int>(R), static_cast<int>(r0));
+        const size_t rows = static_cast<size_t>(L.nb[s]) * L.pstride, run = static_cast<size_t>(L.u[s].nb + L.s[s].nb) * (R * R + R * r0);   // (room for whole pairs: the size that programs keep a workspace of)
         L.part[s] = take(rows > run ? rows : run);
     }
     for (int s = 0; s < 2; ++s) L.tot[s] = take(L.pstride);
