@@ -33,6 +33,7 @@
 
 #include "lordba.h"
 #include "lordba_host_util.h"
+#include "lordba_share_mark.h"
 
 namespace {
 

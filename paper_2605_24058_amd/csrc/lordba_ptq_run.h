@@ -11,7 +11,7 @@
 //
 // What one workgroup writes and another reads goes through agent-scope accesses (see `publish`).  Two kinds of waiting:
 //   - For the shares of the step before, which is all that the chain of steps hangs on, by the shares themselves: each value carries the
-//     parity of its sweep in its last bit (with_mark), and a reader takes the shares as they come.  That needs no wait for the stores, no
+//     parity of its sweep in a bit of its exponent (with_mark), and a reader takes the shares as they come.  That needs no wait for the stores, no
 //     arrival and no second trip to memory behind it: 2 us of a step's 12.  What lay in a share's place before has to be known: the first
 //     sweep of a launch goes by the arrivals, and before a reader looks at the shares of sweep t it has seen an arrival that implies that
 //     those of sweep t - 1 are complete (or it could find those of t - 2, which carry the same mark).
@@ -35,7 +35,7 @@
 #pragma once
 
 constexpr int kRunThreads = 1024, kRunWaves = kRunThreads / 64;
-constexpr int kRunRows = 64, kRunScaleRows = 128, kRunMaxBlocks = 64;
+constexpr int kRunRows = 64, kRunScaleRows = 128, kRunMaxBlocks = kMaxShares;
 constexpr int kSlot = 32;            // doubles per parity: beta [16], rho, pending factor of Y
 constexpr uint32_t kStop = 0x80000000u;
 
@@ -96,15 +96,6 @@ template <class T>
 __device__ inline T* at32(T* p, uint32_t i) {
     typedef typename std::conditional<std::is_const<T>::value, const char, char>::type Byte;
     return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + i * static_cast<uint32_t>(sizeof(T)));
-}
-
-// A share's values carry the parity of their sweep in the last bit (rounded to 52 bits of significand, which leaves zeros, small whole
-// numbers and what is not finite as they are): a reader that knows what lay in their place before sees by itself whether they are there.
-__device__ inline uint32_t mark_of(double v) { return static_cast<uint32_t>(__double2loint(v)) & 1u; }
-__device__ inline double without_mark(double v) { return __hiloint2double(__double2hiint(v), __double2loint(v) & ~1); }
-__device__ inline double with_mark(double v, uint32_t mark) {
-    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
-    return __longlong_as_double(static_cast<long long>(((u + (u >> 1 & 1u)) & ~1ull) | mark));
 }
 
 template <int RT>   // factor rank at most 16 RT
@@ -236,9 +227,9 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
                 for (int j = 0; j < 16; ++j) other |= mark_of(v[j]) ^ mark;
             } while (mark < 2u && __builtin_amdgcn_ballot_w64(other != 0u) != 0ull);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc += b0 + j < hi ? without_mark(v[j]) : 0.0;
+            for (int j = 0; j < 16; ++j) acc = fma(b0 + j < hi ? without_mark(v[j]) : 0.0, kShareUnit, acc);
         }
-        return o < count ? acc : 0.0;
+        return o < count ? share_sum(acc) : 0.0;
     };
     auto combine = [&](double acc) {   // the whole sum, in the threads below NV (contains a barrier)
         if constexpr (H == 2) {
