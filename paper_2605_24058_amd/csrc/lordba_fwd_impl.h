@@ -208,7 +208,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // below, in brackets; T = 8: 11008 -> 4096, r = 16 6.95 (8.9), r = 64 14.3 (17.0), 5120 -> 5120, r = 64 9.7 (11.1), 4096 -> 4096, r = 64 8.0 (8.4); T = 2048,
     // r = 64 4096 -> 4096 16.6 (17.3), 5120 -> 5120 20.8 (22.4)).  Not below 8 rows with four slots, which are soon requested (T = 1,
     // 4096 -> 4096, r = 48 6.57, with two ahead 6.74), nor on the 16-row tiles of one rank block (T = 4096, 5120 -> 5120, r = 16 23.1, with two 23.8).
-    constexpr bool FEW = SPLIT || GM == 5, TALL1 = TMV == 16 && RB == 1 && L == 1;
+    constexpr bool FEW = SPLIT || GM == 5, TALL1 = TMV == 16 && RB == 1 && L == 1, TALL4 = TMV == 16 && RB == 4 && L == 1 && D1 == 4;
     constexpr int AHEAD = !OS || ANY || D1 < 4 || (GM == 3 && D1 == 4) || GM == 4 || TALL1 ? D1 : FEW ? (D1 + 2) / 3 : D1 / 2;
     // Carrier bits of ragged widths: in dwords per slot where all slots are requested first (T = 2048, 160 -> 4096, r = 16 7.9 us, with the loads of
     // any alignment below 8.1), and with those loads where slots are requested behind consumed ones: a branch around dwords there makes every
@@ -442,7 +442,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // (16.0)).  One envelope on 16 waves keeps it where the whole chip starts together on two chunks per wave (T = 2048, 4096 -> 4096, r = 16
     // 9.68, without it 9.75; 3072 -> 6144, where not every wave has two, 14.8 and 14.4), and at widths that are no multiple of 128 (3104 -> 3072 8.6,
     // without it 9.2).
-    if constexpr (!FEW && (!OS || GM == 4 || TALL1)) __builtin_amdgcn_s_barrier();
+    // 16-row tiles of four rank blocks keep it too, with four slots per wave: without it they are faster on some devices and slower on others, with it
+    // faster than with all slots first on all four that were tried (4096 -> 11008, r = 64, without it and, with it, all slots first in brackets: T =
+    // 4096 47.4 (46.8, 48.8), 47.5 (47.6, 48.9), 48.2 (49.6, 49.5), 48.4 (49.2, 49.6), T = 8192 89.3 (88.6, 91.2), 90.2 (90.7, 91.6); 4096 -> 4096 with t
+    // kept, T = 8192 40.9 (41.9, 45.6), 42.4 (44.3, 46.9)).  With two slots it costs there as well (7000 x 2048 -> 5632, r = 64 42.4 (41.5)), and so it
+    // does with two and three rank blocks (T = 8192, 4096 -> 4096, r = 48 39.9 (39.2, 42.0), with t kept 39.6 (38.6, 43.6); 4096 -> 11008, r = 32
+    // 45.0 (45.1, 45.9)).
+    if constexpr (!FEW && (!OS || GM == 4 || TALL1 || TALL4)) __builtin_amdgcn_s_barrier();
     else if constexpr (!OS && !POOL && !ANY) {   // (the loop on few tiles: T = 64, 8480 -> 1024, r = 48 11.3 (11.6), T = 300 13.3 (13.0))
         if (gridDim.x > 16) __builtin_amdgcn_s_barrier();
     } else if constexpr (!FEW && L == 1 && NW == 16 && D1 == 2) {
