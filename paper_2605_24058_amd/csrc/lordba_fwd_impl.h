@@ -439,20 +439,22 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, unsigned char* smem, 
     // 27.5 (28.3), T = 2048 17.4 (17.7); 8192 rows of 5120 -> 5120, 16 adapters 56.9 (57.9)).  Elsewhere it only delays the first wave's stage 1 until
     // the last one's requests are out (us, with it in brackets; T = 8, r = 16 4096 -> 4096 4.47 (4.76), 5632 -> 2048 5.0 (5.7), 64 rows with their
     // adapters 6.3 (6.8); T = 1500, 4096 -> 4096, r = 16 8.5 (8.9); T = 2048, 5120 -> 5120, two envelopes at r = 32 16.2 (18.0); T = 3000, r = 16 15.4
-    // (16.0)).  One envelope on 16 waves keeps it where the whole chip starts together on two chunks per wave (T = 2048, 4096 -> 4096, r = 16
-    // 9.68, without it 9.75; 3072 -> 6144, where not every wave has two, 14.8 and 14.4), and at widths that are no multiple of 128 (3104 -> 3072 8.6,
-    // without it 9.2).
+    // (16.0); T = 2048, 3104 -> 3072, r = 16 8.5 (8.8), 2720 -> 3072 8.4 (8.7)).
     // 16-row tiles of four rank blocks keep it too, with four slots per wave: without it they are faster on some devices and slower on others, with it
     // faster than with all slots first on all four that were tried (4096 -> 11008, r = 64, without it and, with it, all slots first in brackets: T =
     // 4096 47.4 (46.8, 48.8), 47.5 (47.6, 48.9), 48.2 (49.6, 49.5), 48.4 (49.2, 49.6), T = 8192 89.3 (88.6, 91.2), 90.2 (90.7, 91.6); 4096 -> 4096 with t
     // kept, T = 8192 40.9 (41.9, 45.6), 42.4 (44.3, 46.9)).  With two slots it costs there as well (7000 x 2048 -> 5632, r = 64 42.4 (41.5)), and so it
     // does with two and three rank blocks (T = 8192, 4096 -> 4096, r = 48 39.9 (39.2, 42.0), with t kept 39.6 (38.6, 43.6); 4096 -> 11008, r = 32
     // 45.0 (45.1, 45.9)).
+    // Last, one envelope on 16 waves with two chunks and two blocks in flight each, where every wave has both chunks and each compute unit a tile:
+    // there it gains up to 3 % on some devices and up to 1 % the other way on others (T = 2048, 4096 -> 4096, r = 16 9.61 (9.73), 9.64 (9.68), 9.66 (9.68), with t kept 10.0
+    // (10.2), 9.8 (9.7), r = 32 11.2 (11.5), 11.7 (11.7), -> 8192 19.5 (20.3)).  Not where a wave has one block, whose request holds up little (4096 -> 2048,
+    // r = 16 8.0 (7.7), r = 32 9.7 (9.4)), nor at ranks of parts of a block up to two blocks each (-> 4096, r = 24 12.2 (11.5), but -> 8192 19.9 (20.9)).
     if constexpr (!FEW && (!OS || GM == 4 || TALL1 || TALL4)) __builtin_amdgcn_s_barrier();
     else if constexpr (!OS && !POOL && !ANY) {   // (the loop on few tiles: T = 64, 8480 -> 1024, r = 48 11.3 (11.6), T = 300 13.3 (13.0))
         if (gridDim.x > 16) __builtin_amdgcn_s_barrier();
     } else if constexpr (!FEW && L == 1 && NW == 16 && D1 == 2) {
-        if (gridDim.x >= 240 && (nchunks == D1 * NW || !wide_a)) __builtin_amdgcn_s_barrier();   // (uniform)
+        if (gridDim.x >= 240 && nchunks == D1 * NW && nblk > (BM == 0 ? NW * D2 : NW)) __builtin_amdgcn_s_barrier();   // (uniform)
     }
     __builtin_amdgcn_sched_barrier(0);
     f4 acc[RB][L];
