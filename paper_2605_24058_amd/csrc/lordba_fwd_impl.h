@@ -1271,7 +1271,8 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
     // Wide inputs at decode sizes: straight-line code for all chunks of a wave here too (up to 14336 columns), as many requested ahead as
     // stage 1 needs (see AHEAD): the loop over groups of four exposed the memory latency once per group.  us, the loop in brackets, T = 8: 11008 ->
     // 4096, r = 16 7.0 (9.4), r = 32 9.2 (14.1), r = 64 14.3 (18.5); 13824 -> 5120, r = 16 7.6 (9.4), r = 32 10.4 (13.8), r = 48 13.7 (16.6), r = 64
-    // 17.1 (21.4).  (8 waves from 98 chunks on: with 97, the last one of 32 columns, T = 1, r = 48 14.3 (13.5).)
+    // 17.1 (21.4).  (On 8 waves 97 chunks only where the last one is whole: 12416 -> 4096, T = 8, r = 48 13.5 (14.3), r = 64 16.1 (17.1), but 12320 -> 4096
+    // 14.9 (14.0), 18.1 (17.5), T = 1 14.6 (13.0): there one wave has a thirteenth chunk, of 32 columns.)
     constexpr int kOneShot = NW == 16 ? 6 : 12, kOneShotWide = NW == 16 ? 7 : 14;
     if constexpr (TMV == 8 && L == 1 && !kTraining && (NW == 16 || (NW == 8 && RB >= 3))) {  // (one and two rank blocks run on 16 waves)
         const int64_t tiles = (static_cast<int64_t>(a.T) + TMV - 1) / TMV;
@@ -1285,7 +1286,7 @@ lordba_status launch_mfma_depth(const FwdArgs& a, hipStream_t stream) {
                 if (per_wave > kOneShot && per_wave <= kOneShotWide && tiles <= kFewPoolTiles && per_wg <= NW && per_wg < (a.d_out + 127) / 128)
                     return launch_mfma_gm<RB, TMV, NW, kOneShotWide, true, BM, 5, L>(a, stream);
             }
-        } else if (per_wave > kOneShot && per_wave <= kOneShotWide && (NW == 16 || nchunks >= 98) && tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
+        } else if (per_wave > kOneShot && per_wave <= kOneShotWide && (NW == 16 || nchunks >= 98 || a.d_in % 128 == 0) && tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
             return launch_mfma_gm<RB, TMV, NW, kOneShotWide, true, BM, 2, L>(a, stream);
         } else if (per_wave <= kOneShot && tiles <= kFewTiles && split_blocks<TMV, NW, false>(a) <= NW) {
             // Slots that a wave has no chunk for repeat a request, so the loop keeps the counts of which few waves have a chunk beyond

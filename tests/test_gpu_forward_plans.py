@@ -40,7 +40,9 @@ PLANS = [
     # twelve x slots per wave on 8 waves (three and four rank blocks, whole and ragged carrier words), and the loop beside them
     (9, 11008, 640, 48, 1), (8, 11008, 4096, 64, 1), (11, 9760, 512, 50, 1), (10, 9760, 384, 41, 1), (300, 12288, 1024, 64, 1),
     (9, 8480, 512, 64, 1), (9, 8320, 256, 64, 1), (9, 8480, 256, 48, 1),
-    # fourteen slots on 8 waves and seven on 16 (97 to 112 chunks, the last one whole or ragged), and the loop from 113 chunks on
+    # fourteen slots on 8 waves and seven on 16 (97 to 112 chunks, the last one whole or ragged; on 8 waves 97 only where it is whole), and the
+    # loop from 113 chunks on
+    (9, 12416, 640, 48, 1), (1, 12416, 512, 64, 1), (8, 12384, 520, 41, 1),
     (9, 12320, 640, 48, 1), (8, 13824, 5120, 64, 1), (1, 14336, 136, 41, 1), (300, 14336, 520, 64, 1), (9, 14368, 512, 64, 1),
     (9, 12320, 640, 16, 1), (8, 13824, 5120, 32, 1), (1, 14336, 136, 12, 1), (300, 14304, 520, 24, 1), (9, 14368, 512, 16, 1),
     # every wave with two chunks on 16 waves, with and without a chip full of workgroups, and one wave short of it
