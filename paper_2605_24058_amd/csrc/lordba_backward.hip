@@ -20,9 +20,10 @@
 //           all envelopes at once; wgrad and finish then run once per envelope.
 //   wgrad   Q and P: MFMA with the token rows as contraction index.  A lane reads 8 token rows x 8 columns of x (or g)
 //           with row-contiguous 16-byte loads and transposes its 8 x 8 block in registers (v_perm_b32); MFMA e of a step
-//           takes column 8 m + e from lane group m.  dt = beta du (or u = beta t) enters as fp16 hi + lo (+ rest) after a
-//           power-of-two scaling per rank that follows the largest entry seen so far.  Token ranges are split over waves
-//           and workgroups; partial sums are reduced in a fixed order.
+//           takes column 8 m + e from lane group m.  du (or t) enters as fp16 hi + lo after a power-of-two scaling per rank that
+//           follows the largest entry seen so far, and beta behind the sums (element-aligned tensors: beta du and beta t enter, as
+//           hi + lo + rest).  Token ranges are split over waves and workgroups; partial sums are reduced in a fixed order.  From
+//           two rank blocks on and with enough to stream, a second kernel takes the tokens through LDS (see there).
 //   finish  sums the partials, applies the carrier signs, the scales and the smooth-sign factor; and d_beta.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -156,7 +157,7 @@ __global__ void bwd_zero_kernel(float* p, int64_t n) {
 }
 
 // ----------------------------------------------------------------------------------------- wgrad kernel ----
-// Workgroup (cb, s): column block cb of x (cb < nbx: Q, with dt) or of g (P, with u), token rows [s * W tw, (s+1) * W tw),
+// Workgroup (cb, s): column block cb of x (cb < nbx: Q, with du) or of g (P, with t), token rows [s * W tw, (s+1) * W tw),
 // one range of tw rows per wave.  One step = 32 token rows x 128 columns.
 // G steps are in flight per wave: the loads of a group are issued without any condition (past the end of the wave's range
 // they re-read valid addresses and are not used), so that every wait counts exactly the loads issued after the one it
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     const int cc = is_x ? cb : cb - a.nbx;
     const int d = is_x ? a.d_in : a.d_out;
     const _Float16* src = is_x ? a.x : a.g;
-    const float* small = is_x ? a.duT : a.tT;   // dt = beta du meets x, u = beta t meets g
+    const float* small = is_x ? a.duT : a.tT;   // du meets x, t meets g (ANY: times beta; otherwise beta comes in at the end)
     const int sstride = is_x ? a.du_stride : a.t_stride;
 
     float beta[RB];
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             int row = tk + 8 * q + e;
-            row = row < a.T ? row : a.T - 1;  // rows past T meet dt = u = 0
+            row = row < a.T ? row : a.T - 1;  // rows past T meet du = t = 0
             const _Float16* p = src + static_cast<size_t>(row) * d + col;
             xb[i][e] = ANY ? load16_any_stream(p) : load16_stream(p);
         }
@@ -278,15 +279,13 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
                 }
                 split_scaled(v, __uint_as_float(static_cast<uint32_t>(267 - cur_e[rb]) << 23), hl[0][rb][0], hl[0][rb][1]);
             }
-            return;
-        }
+        } else {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            float v[G][8];
-            float m = 0.f;
+            for (int rb = 0; rb < RB; ++rb) {
+                float v[G][8];
+                float m = 0.f;
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                if constexpr (ANY) {
+                for (int i = 0; i < G; ++i) {
                     if (tk0 + 32 * i + 32 > a.T) {   // scalar: the row's last entries may have been read from its end
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
@@ -294,41 +293,41 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
                             sb[i][rb][h] = drop_words(sb[i][rb][h], tok - row_piece(tok, a.T, row_of[rb]));
                         }
                     }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float raw = __uint_as_float(sb[i][rb][e >> 2][e & 3]);
+                        // select, not multiply: the padding rows hold undefined values
+                        v[i][e] = tk0 + 32 * i + 8 * q + e < a.T ? raw * beta[rb] : 0.f;
+                        m = fmaxf(m, fabsf(v[i][e]));
+                    }
                 }
+                m = fmaxf(m, __shfl_xor(m, 16, 64));
+                m = fmaxf(m, __shfl_xor(m, 32, 64));
+                int e_new = static_cast<int>((__float_as_uint(m) >> 23) & 0xffu);
+                e_new = e_new > 254 ? 254 : e_new;
+                if (__builtin_amdgcn_ballot_w64(e_new > cur_e[rb]) != 0ull) {   // scalar branch: rare after the first group
+                    const int sh = cur_e[rb] - e_new;                           // < 0 where this lane's rank grows
+                    const float f = sh >= 0 ? 1.f : (sh < -126 ? 0.f : __uint_as_float(static_cast<uint32_t>(127 + sh) << 23));
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float raw = __uint_as_float(sb[i][rb][e >> 2][e & 3]);
-                    // select, not multiply: the padding rows hold undefined values
-                    v[i][e] = (tk0 + 32 * i + 8 * q + e < a.T && (ANY || beta[rb] != 0.f)) ? raw * beta[rb] : 0.f;
-                    m = fmaxf(m, fabsf(v[i][e]));
+                    for (int e = 0; e < 8; ++e) acc[rb][e] *= f;
+                    cur_e[rb] = e_new > cur_e[rb] ? e_new : cur_e[rb];
                 }
-            }
-            m = fmaxf(m, __shfl_xor(m, 16, 64));
-            m = fmaxf(m, __shfl_xor(m, 32, 64));
-            int e_new = static_cast<int>((__float_as_uint(m) >> 23) & 0xffu);
-            e_new = e_new > 254 ? 254 : e_new;
-            if (__builtin_amdgcn_ballot_w64(e_new > cur_e[rb]) != 0ull) {   // scalar branch: rare after the first group
-                const int sh = cur_e[rb] - e_new;                           // < 0 where this lane's rank grows
-                const float f = sh >= 0 ? 1.f : (sh < -126 ? 0.f : __uint_as_float(static_cast<uint32_t>(127 + sh) << 23));
+                const float mul = __uint_as_float(static_cast<uint32_t>(267 - cur_e[rb]) << 23);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[rb][e] *= f;
-                cur_e[rb] = e_new > cur_e[rb] ? e_new : cur_e[rb];
-            }
-            const float mul = __uint_as_float(static_cast<uint32_t>(267 - cur_e[rb]) << 23);
+                for (int i = 0; i < G; ++i) {
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
+                    for (int w = 0; w < 4; ++w) {
+                        float v0 = v[i][2 * w] * mul, v1 = v[i][2 * w + 1] * mul;
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    float v0 = v[i][2 * w] * mul, v1 = v[i][2 * w + 1] * mul;
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        h2 h;
-                        h[0] = static_cast<_Float16>(v0);
-                        h[1] = static_cast<_Float16>(v1);
-                        hl[i][rb][s][w] = __builtin_bit_cast(uint32_t, h);
-                        const bool stop = ANY && s == 0;   // (ANY: nothing is left of an infinity, no inf - inf)
-                        v0 = stop && !(fabsf(v0) < INFINITY) ? 0.f : v0 - static_cast<float>(h[0]);
-                        v1 = stop && !(fabsf(v1) < INFINITY) ? 0.f : v1 - static_cast<float>(h[1]);
+                        for (int s = 0; s < NS; ++s) {
+                            h2 h;
+                            h[0] = static_cast<_Float16>(v0);
+                            h[1] = static_cast<_Float16>(v1);
+                            hl[i][rb][s][w] = __builtin_bit_cast(uint32_t, h);
+                            const bool stop = s == 0;   // (nothing is left of an infinity, no inf - inf)
+                            v0 = stop && !(fabsf(v0) < INFINITY) ? 0.f : v0 - static_cast<float>(h[0]);
+                            v1 = stop && !(fabsf(v1) < INFINITY) ? 0.f : v1 - static_cast<float>(h[1]);
+                        }
                     }
                 }
             }
@@ -439,34 +438,33 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
 }
 
 // The same contraction with the tokens streamed through LDS (plain variants only).  A workgroup takes one column block and one range of
-// tokens, TG tiles of 32 tokens per turn; the waves of a tile share it, each for one rank block and 128 / CW of the columns, so that x (or g)
-// passes through a compute unit once whatever the number of rank blocks is and a rank block's operands are converted by CW waves.  The
-// tiles come by direct loads into LDS, S turns of them (the one in work among them): the depth costs no registers.  The sums of the TG waves
-// of a rank block and column part are added through LDS at the end.
-// LDS of a tile: 32 rows of 256 bytes, the 16 pieces of row t moved on by kRot (t / 8) places where a wave has a part of the columns (a
-// lane group reads rows 8 q + e: rows eight apart would share their banks); then per rank block its 16 x 32 entries of du (or t), pieces of four
-// tokens by rank.
-// Waits: a wave's own loads of a turn are complete when at most the loads of the turns behind it are left (they complete in order),
-// everybody's behind the barrier; the place of the turn before, which everybody has read by then, takes the next one.
+// tokens, TG tiles of 32 tokens per turn; the waves of a tile share it, each for one of the B rank blocks, so that x (or g) passes through a
+// compute unit once whatever the number of rank blocks is.  The tiles come by direct loads into LDS, kTurns turns of them (the one in work among
+// them): the depth costs no registers.  The sums of the TG waves of a rank block are added through LDS at the end.
+// LDS of a tile: 32 rows of 256 bytes; then per rank block its 16 x 32 entries of du (or t), pieces of four tokens by rank.
+// Waits: a wave's own loads of a turn are complete when at most those of the turn behind it are left (they complete in order), everybody's
+// behind the barrier; the place of the turn before, which everybody has read by then, takes the next one.
 // Bound: a wave's chain per tile (LDS, largest entry, conversion, 32 permutes, 16 MFMAs: about 0.5 us with two waves per SIMD) more than the
-// loads (8 KB of x and 2 KB per rank block), and 8 us for launch, first tile, sums and stores.  2048 x 5120 x 5120, four blocks: 15 us, the
-// register kernel 21; with CW = 2 (operands converted twice, twice the barriers per tile and wave) 20, one turn more in flight 15.5.
-template <int B, int CW, int TG, int S>
-__global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kernel(BwdArgs a, int range) {
-    constexpr int W = B * CW * TG, NC = 8 / CW;         // waves; columns per lane index of a wave
-    constexpr int NX = 8 * TG / W, NSM = 2 * B * TG > W ? 2 * B * TG / W : 1, PER = NX + NSM;   // 1024-byte loads of a wave per turn: x, small
-    constexpr int kTileBytes = 8192 + B * 2048, kSlotBytes = TG * kTileBytes, kRot = NC == 4 ? 8 : NC == 2 ? 4 : 0;
-    static_assert(W <= 16 && NX * W == 8 * TG && S >= 2 && (S - 2) * PER < 64, "whole loads per wave, counted by vmcnt");
-    static_assert((TG - 1) * B * CW * NC * 1024 <= S * kSlotBytes, "the sums of the other token groups");
+// loads (8 KB of x and 2 KB per rank block), and launch, first tile, sums and stores.  2048 x 5120 x 5120, two envelopes at r = 32: 20.2 us in a
+// kernel trace, the register kernel 23.2; the whole backward call, with the finish kernel below, 44.0 (50.4), at T = 8192, r = 64 114 (136).  With two
+// waves per rank block, which convert its operands twice for half of the columns each, it was a third slower, with one turn more in
+// flight no faster.
+constexpr int kTurns = 3;
+template <int B, int TG>
+__global__ __launch_bounds__(B * TG * 64) void lordba_bwd_wgrad_stream_kernel(BwdArgs a, int range) {
+    constexpr int W = B * TG, NX = 8 / B, NSM = 2, PER = NX + NSM;   // waves; 1024-byte loads of a wave per turn: x, small
+    constexpr int kTileBytes = 8192 + B * 2048, kSlotBytes = TG * kTileBytes;
+    static_assert(W <= 16 && NX * B == 8 && PER < 64, "whole loads per wave, counted by vmcnt");
+    static_assert((TG - 1) * B * 8192 <= kTurns * kSlotBytes, "the sums of the other token groups");
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, q = lane >> 4;
     const int rbe = a.rp >> 4, blocks = a.ell * rbe;
-    const int cb = blockIdx.x, rbw = wave % B, cw = wave / B % CW, tg = wave / (B * CW);
+    const int cb = blockIdx.x, rbw = wave % B, tg = wave / B;
     const bool is_x = cb < a.nbx;
     const int d = is_x ? a.d_in : a.d_out, col0 = (is_x ? cb : cb - a.nbx) * 128;
     const _Float16* src = is_x ? a.x : a.g;
-    const float* small = is_x ? a.duT : a.tT;   // dt = beta du meets x, u = beta t meets g
+    const float* small = is_x ? a.duT : a.tT;   // du meets x, t meets g
     const int sstride = is_x ? a.du_stride : a.t_stride;
     const int64_t tk_first = static_cast<int64_t>(blockIdx.y) * range, tk_last = (static_cast<int64_t>(a.T) + 31) & ~31ll;
     const int tk_begin = static_cast<int>(tk_first < tk_last ? tk_first : tk_last);
@@ -492,13 +490,12 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
         return tk_begin + 32 * (at < tiles ? at : tiles - 1);
     };
     auto issue = [&](int i) {
-        const uint32_t slot = static_cast<uint32_t>(i % S) * kSlotBytes;
+        const uint32_t slot = static_cast<uint32_t>(i % kTurns) * kSlotBytes;
 #pragma unroll
         for (int k = 0; k < NX; ++k) {   // four rows of a tile
             const int j = wave + k * W, r = 4 * (j & 7) + q;
-            const int piece = (li - kRot * (r >> 3)) & 15;
-            int row = first_token(i, j >> 3) + r, col = col0 + piece * 8;
-            row = row < a.T ? row : a.T - 1;   // rows past T meet dt = u = 0
+            int row = first_token(i, j >> 3) + r, col = col0 + li * 8;
+            row = row < a.T ? row : a.T - 1;   // rows past T meet du = t = 0
             col = col < d ? col : d - 8;       // past the end: a valid piece is re-read, its sums are never used
             const _Float16* p = src + static_cast<size_t>(row) * d + col;
             load16_to_lds<true>(slot + (j >> 3) * kTileBytes + (j & 7) * 1024u, p);
@@ -509,35 +506,26 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
             load16_to_lds<false>(slot + tile * kTileBytes + 8192u + (j % (2 * B)) * 1024u, srow[k] + first_token(i, tile));
         }
     };
-    // at most n tiles' loads left (n < S - 1), and every read of LDS done
-    auto wait_tiles = [&](int n) {
-#define LORDBA_WAIT(N) if (n == N) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((N < S - 1 ? N : 0) * PER) : "memory"); else
-        LORDBA_WAIT(1) LORDBA_WAIT(2) LORDBA_WAIT(3) LORDBA_WAIT(4) LORDBA_WAIT(5) LORDBA_WAIT(6) LORDBA_WAIT(7) LORDBA_WAIT(8) LORDBA_WAIT(9) LORDBA_WAIT(10)
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-#undef LORDBA_WAIT
-    };
-    static_assert(S - 2 <= 10, "wait_tiles");
-
     // (the products with the lo operands have sums of their own: one rounding per tile at the size of the result instead of two.  Error of the
     // latent gradients against 64 bits, T = 2048, 4096^2, r = 64: 2.15e-7, in one sum 2.4e-7, in the kernel above 2.2e-7)
-    f4 acc[NC], acc_lo[NC];
+    f4 acc[8], acc_lo[8];
 #pragma unroll
-    for (int e = 0; e < NC; ++e) acc[e] = acc_lo[e] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < 8; ++e) acc[e] = acc_lo[e] = f4{0.f, 0.f, 0.f, 0.f};
     int cur_e = 14;   // (the power-of-two scaling per rank of the kernel above; beta comes in at the end)
     const bool silent = __builtin_amdgcn_ballot_w64(beta == 0.f) != 0ull;   // a rank without scale: it adds nothing, whatever its entries are
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (beta: from here on the loads are counted)
     const int turns = (tiles + TG - 1) / TG;
 #pragma unroll 1
-    for (int i = 0; i < S - 1 && i < turns; ++i) issue(i);
+    for (int i = 0; i < kTurns - 1 && i < turns; ++i) issue(i);
 #pragma unroll 1
     for (int i = 0; i < turns; ++i) {
-        const int behind = turns - 1 - i;
-        wait_tiles(behind < S - 2 ? behind : S - 2);
+        if (i + 1 < turns) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(PER) : "memory");   // (one turn is behind this one: the next is issued below)
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (i + S - 1 < turns) issue(i + S - 1);
+        if (i + kTurns - 1 < turns) issue(i + kTurns - 1);
         if (i * TG + tg >= tiles) continue;   // (scalar)
-        const unsigned char* slot = smem + (i % S) * kSlotBytes + tg * kTileBytes;
+        const unsigned char* slot = smem + (i % kTurns) * kSlotBytes + tg * kTileBytes;
         float v[8];
         {
             const unsigned char* sp = slot + 8192 + rbw * 2048 + (2 * q * 16 + li) * 16;
@@ -552,30 +540,18 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
         }
         if (const float f = follow_largest(v, cur_e); __builtin_amdgcn_ballot_w64(f != 1.f) != 0ull) {
 #pragma unroll
-            for (int e = 0; e < NC; ++e) {
+            for (int e = 0; e < 8; ++e) {
                 acc[e] *= f;
                 acc_lo[e] *= f;
             }
         }
         u4 hi, lo;
         split_scaled(v, __uint_as_float(static_cast<uint32_t>(267 - cur_e) << 23), hi, lo);
-        uint32_t xr[8][NC / 2];   // token rows 8 q + e of the lane's NC columns
+        u4 xr[8];   // token rows 8 q + e of the lane's 8 columns
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xr[e] = load16(slot + (8 * q + e) * 256 + li * 16);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int at = cw * (16 * NC) * 2 + li * (NC * 2);   // byte in the row
-            const unsigned char* p = slot + (8 * q + e) * 256 + ((at + kRot * 16 * q) & 255);
-            if constexpr (NC == 8) {
-                const u4 w = load16(p);
-                xr[e][0] = w[0]; xr[e][1] = w[1]; xr[e][2] = w[2]; xr[e][3] = w[3];
-            } else if constexpr (NC == 4) {
-                const uint2 w = *reinterpret_cast<const uint2*>(p);
-                xr[e][0] = w.x; xr[e][1] = w.y;
-            } else {
-                xr[e][0] = *reinterpret_cast<const uint32_t*>(p);
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < NC; ++e) {
             const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
             u4 col8;
 #pragma unroll
@@ -584,39 +560,38 @@ __global__ __launch_bounds__(B * CW * TG * 64) void lordba_bwd_wgrad_stream_kern
             acc_lo[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(col8), as_h8(lo), acc_lo[e], 0, 0, 0);
         }
     }
-    // Accumulator e, register i of lane (li, q): rank li, column NC (4 q + i) + e of the wave's: 4 NC consecutive columns per lane
+    // Accumulator e, register i of lane (li, q): rank li, column 8 (4 q + i) + e: 32 consecutive columns per lane
     const float back = __uint_as_float(static_cast<uint32_t>(cur_e - 13) << 23);
-    float out[4 * NC];
+    float out[32];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
-        for (int e = 0; e < NC; ++e) out[i * NC + e] = (acc[e][i] + acc_lo[e][i]) * back * beta;   // (one after the other: their product may vanish)
+        for (int e = 0; e < 8; ++e) out[i * 8 + e] = (acc[e][i] + acc_lo[e][i]) * back * beta;   // (one after the other: their product may vanish)
     }
     if constexpr (TG > 1) {   // the token groups' sums, in their order
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
         f4* red = reinterpret_cast<f4*>(smem);
-        const int w = wave % (B * CW);
         if (tg > 0) {
 #pragma unroll
-            for (int i = 0; i < NC; ++i) red[((((tg - 1) * B * CW) + w) * NC + i) * 64 + lane] = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
+            for (int i = 0; i < 8; ++i) red[(((tg - 1) * B + rbw) * 8 + i) * 64 + lane] = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
         }
         __syncthreads();
         if (tg > 0) return;
 #pragma unroll
         for (int t = 1; t < TG; ++t) {
 #pragma unroll
-            for (int i = 0; i < NC; ++i) {
-                const f4 o = red[((((t - 1) * B * CW) + w) * NC + i) * 64 + lane];
+            for (int i = 0; i < 8; ++i) {
+                const f4 o = red[(((t - 1) * B + rbw) * 8 + i) * 64 + lane];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) out[4 * i + e] += o[e];
             }
         }
     }
     if (rbw >= blocks) return;   // (a rank block too many)
-    float* dst = a.part + ((static_cast<size_t>(blockIdx.y) * blocks + rbw) * 16 + li) * a.dcols + static_cast<size_t>(cb) * 128 + (cw * 16 + 4 * q) * NC;
+    float* dst = a.part + ((static_cast<size_t>(blockIdx.y) * blocks + rbw) * 16 + li) * a.dcols + static_cast<size_t>(cb) * 128 + 32 * q;
 #pragma unroll
-    for (int i = 0; i < NC; ++i) *reinterpret_cast<f4*>(dst + 4 * i) = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<f4*>(dst + 4 * i) = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
 }
 
 // ---------------------------------------------------------------------------------------- finish kernel ----
@@ -672,9 +647,10 @@ __device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int k, flo
 
 // Widths that are multiples of 32.  A workgroup takes NG groups of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out,
 // d_latentB); a thread takes four columns and one rank (RK >= r of them), with all envelopes' shares, so that everything it needs is requested at
-// once in 16-byte pieces.  The workgroups in front of these take d_s_rank.  Bound: one trip to memory behind the launch.  2048 x 5120 x 5120, two
-// envelopes at r = 32 4.9 us, with one column per thread, shares eight at a time per envelope and latentB through LDS first 8.2; 4096^2, r = 16
-// 4.3 (4.45).
+// once in 16-byte pieces (up to eight token ranges with one envelope, four with more).  The workgroups in front of these take d_s_rank.  Bound: one
+// trip to memory behind the launch.  2048 x 5120 x 5120, two envelopes at r = 32 5.2 us in a kernel trace, with one column per thread, shares eight
+// at a time per envelope and latentB through LDS first 8.5; 4096^2, r = 16 4.5 (4.5).  With eight ranges for two and three envelopes the calls of
+// five ranges and more gain 1 % and the others lose 1 to 3 (64 x 4096^2, two envelopes 14.1 us for 13.7).
 template <int RK, int L>
 __global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kernel(BwdArgs a) {
     constexpr int NT = RK < 32 ? 256 : 8 * RK, NG = NT / (8 * RK);
@@ -973,10 +949,10 @@ lordba_status launch_wgrad(const BwdArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((lordba_bwd_wgrad_kernel<RB, kWgradGroup, W, Z, ANY>), grid, dim3(W * 64), 0, st, a);
     return LORDBA_OK;
 }
-template <int B, int CW, int TG, int S>
+template <int B, int TG>
 lordba_status launch_stream(const BwdArgs& a, int64_t range, hipStream_t st) {
-    constexpr size_t lds = S * TG * (8192 + B * 2048);
-    auto kern = lordba_bwd_wgrad_stream_kernel<B, CW, TG, S>;
+    constexpr size_t lds = kTurns * TG * (8192 + B * 2048);
+    auto kern = lordba_bwd_wgrad_stream_kernel<B, TG>;
     {   // more than 64 KiB of LDS per workgroup, asked for once per device
         static std::mutex mu;
         static bool granted[64] = {false};
@@ -991,7 +967,7 @@ lordba_status launch_stream(const BwdArgs& a, int64_t range, hipStream_t st) {
             granted[dev] = true;
         }
     }
-    hipLaunchKernelGGL(kern, dim3(a.nbx + a.nbg, a.splits), dim3(B * CW * TG * 64), lds, st, a, static_cast<int>(range));
+    hipLaunchKernelGGL(kern, dim3(a.nbx + a.nbg, a.splits), dim3(B * TG * 64), lds, st, a, static_cast<int>(range));
     return LORDBA_OK;
 }
 
@@ -1004,7 +980,7 @@ lordba_status launch_all(const BwdArgs& args, hipStream_t st) {
     // that holds the tokens in registers, with a workgroup per block (or two) on short batches (Z), which read x (or g) again out of
     // the L2 they share.  us of the whole backward call, that kernel in brackets: 4096 -> 4096, T = 2000, r = 32 28.6 (30.0); 5120 -> 11008, r = 32,
     // T = 600 31.3 (31.0), 1100 39.8 (40.8), 3500 69.8 (80.9); r = 48 36.7 (37.6), 45.2 (48.0), 86.1 (101.9); r = 64 41.8 (41.4), 51.0 (52.4), 97.2 (106);
-    // 1536 -> 1536, T = 1100, r = 48 23.1 (22.2), T = 2000 24.3 (25.0); T = 8192, 5120^2, r = 64 120 (139), two envelopes at r = 16 97.0 (99.5).
+    // 1536 -> 1536, T = 1100, r = 48 23.1 (22.2), T = 2000 24.3 (25.0); T = 8192, 5120^2, r = 64 114 (136), two envelopes at r = 16 97.0 (99.5).
     // One block gains nothing (2048 x 4096^2, r = 16 25.6 (24.3), T = 8192, 13824 -> 5120 174 (169)): nothing is shared.
     const int64_t tiles = static_cast<int64_t>(a.T) * (a.nbx + a.nbg);
     const bool stream = !a.any && ((blocks == 2 && (!short_batch || tiles >= 72 * 1024)) || (blocks >= 3 && tiles >= 48 * 1024));
@@ -1025,7 +1001,7 @@ lordba_status launch_all(const BwdArgs& args, hipStream_t st) {
         a.splits = static_cast<int>((a.T + range - 1) / range);
     }
     lordba_status s;
-    if (stream) s = blocks == 2 ? launch_stream<2, 1, 4, 3>(a, range, st) : launch_stream<4, 1, 2, 3>(a, range, st);
+    if (stream) s = blocks == 2 ? launch_stream<2, 4>(a, range, st) : launch_stream<4, 2>(a, range, st);
     else if (blocks == 1 && a.waves == 2 * kWgradWaves) s = a.any ? launch_wgrad<1, 2 * kWgradWaves, 1, true>(a, st) : launch_wgrad<1, 2 * kWgradWaves, 1, false>(a, st);
     else if (blocks == 1) s = a.any ? launch_wgrad<1, kWgradWaves, 1, true>(a, st) : launch_wgrad<1, kWgradWaves, 1, false>(a, st);
     else if (!a.any) s = blocks == 2 ? launch_wgrad<1, kWgradWaves, 2, false>(a, st) : blocks == 3 && short_batch ? launch_wgrad<1, kWgradWaves, 3, false>(a, st) : launch_wgrad<2, kWgradWaves, 2, false>(a, st);

@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
     };
     // Lane-derived values and arguments are taken anew in every block, from numbers that the compiler cannot follow: kept over the whole
     // kernel, with the lane masks of every phase that follow from them, they take more registers than there are, scalar ones above all.
-    // (What is left: 41 vector registers in scratch memory, 92 bytes per lane, at factor ranks up to 16, 92 and 176 bytes beyond, and
+    // (What is left: 39 vector registers in scratch memory, 92 bytes per lane, at factor ranks up to 16, 92 and 176 bytes beyond, and
     // 130 to 140 scalar ones in lanes of vector registers.)
     int tid = threadIdx.x;
     int turn = 0;
