@@ -747,7 +747,7 @@ __device__ __forceinline__ void ldlt_step(double (&col)[16], double& b, double d
     r = fma(r, fma(e, e, e), r);
     ipl = (l == K) ? r : ipl;
     pl = (l == K) ? p : pl;
-    // -L'[l][K] for the lanes below the diagonal; the others get a number below 1e-307, which changes none of their entries
+    // -L'[l][K] for the lanes below the diagonal; the others get a number below 1e-313, which changes no entry of theirs but a zero (unused, or as small)
     double f = 0.0;
     fma_row_lane<K>(f, r, -col[K]);
     f = __hiloint2double(l > K ? __double2hiint(f) : 0, __double2loint(f));
