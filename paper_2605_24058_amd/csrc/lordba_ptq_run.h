@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
     };
     // Lane-derived values and arguments are taken anew in every block, from numbers that the compiler cannot follow: kept over the whole
     // kernel, with the lane masks of every phase that follow from them, they take more registers than there are, scalar ones above all.
-    // (What is left: 39 vector registers in scratch memory, 92 bytes per lane, at factor ranks up to 16, 92 and 176 bytes beyond, and
+    // (What is left: 36 vector registers in scratch memory, 84 bytes per lane, at factor ranks up to 16, 92 and 176 bytes beyond, and
     // 130 to 140 scalar ones in lanes of vector registers.)
     int tid = threadIdx.x;
     int turn = 0;
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
             for (;;) {   // (one wave alone reads the keeper's word for the workgroup: all of them together crowd its memory channel)
                 uint32_t k = want_kept;
                 if (wave == 0) k = __hip_atomic_load(kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const bool other = mark_of(published(at32(one, oc))) != mark;
+                const bool other = other_mark(mark_word(published(at32(one, oc)), mark));
                 if (wave == 0 && (k & kStop)) { sh_over = 1u; return 0.0; }
                 if (__builtin_amdgcn_ballot_w64(other || k < want_kept) == 0ull) break;
                 if (__hip_atomic_load(&sh_over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u) return 0.0;
@@ -218,14 +218,14 @@ __global__ __launch_bounds__(kRunThreads) void lordba_ptq_run_kernel(PtqRunArgs)
         double acc = 0.0;
         for (int b0 = lo; b0 < hi; b0 += 16) {
             double v[16];
-            uint32_t other;
+            uint32_t word;
             do {   // (shares of one step arrive close together: this seldom takes more than two turns)
 #pragma unroll
                 for (int j = 0; j < 16; ++j) v[j] = published(at32(part + (b0 + j < hi ? b0 + j : hi - 1) * count, oc));
-                other = 0u;
+                word = 0u;
 #pragma unroll
-                for (int j = 0; j < 16; ++j) other |= mark_of(v[j]) ^ mark;
-            } while (mark < 2u && __builtin_amdgcn_ballot_w64(other != 0u) != 0ull);
+                for (int j = 0; j < 16; ++j) word |= mark_word(v[j], mark);
+            } while (mark < 2u && __builtin_amdgcn_ballot_w64(other_mark(word)) != 0ull);
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc = fma(b0 + j < hi ? without_mark(v[j]) : 0.0, kShareUnit, acc);
         }

@@ -11,7 +11,9 @@ constexpr double kShareUnit = 0x1p512, kShareLimit = 0x1p-8, kNoNumber = 0x1.fff
 constexpr int kMaxShares = 64;
 
 constexpr uint64_t share_bits(double v) { return __builtin_bit_cast(uint64_t, v); }
-constexpr uint32_t mark_of(double stored) { return static_cast<uint32_t>(share_bits(stored) >> 62) & 1u; }
+// Whether a stored value (or one of several whose words are or-ed) carries the other mark: other_mark(mark_word(stored, mark)).
+constexpr uint32_t mark_word(double stored, uint32_t mark) { return static_cast<uint32_t>(share_bits(stored) >> 32) ^ mark << 30; }
+constexpr bool other_mark(uint32_t word) { return (word & 0x40000000u) != 0u; }
 constexpr double with_mark(double v, uint32_t mark) {
     const double scaled = v * (1.0 / kShareUnit);
     return __builtin_bit_cast(double, share_bits(scaled < kShareLimit && scaled > -kShareLimit ? scaled : kNoNumber) | static_cast<uint64_t>(mark) << 62);

@@ -25,7 +25,7 @@ int main() {
         if (n % 101 == 0) v = n % 2 ? 0.0 : -0.0;
         const uint32_t mark = rng() & 1;
         const double stored = with_mark(v, mark);
-        if (mark_of(stored) != mark) return bad("mark", v);
+        if (other_mark(mark_word(stored, mark)) || !other_mark(mark_word(stored, 1 - mark))) return bad("mark", v);
         const double back = without_mark(stored);
         if (bits(back * kShareUnit) != bits(v)) return bad("value", v);
         if (n % kMaxShares == 0) sum = marked = 0.0;
@@ -37,7 +37,7 @@ int main() {
     for (double v : none)
         for (uint32_t mark = 0; mark < 2; ++mark) {
             const double stored = with_mark(v, mark);
-            if (mark_of(stored) != mark) return bad("mark", v);
+            if (other_mark(mark_word(stored, mark)) || !other_mark(mark_word(stored, 1 - mark))) return bad("mark", v);
             const double largest = 0x1.fffffffffffffp503;   // of either sign, before it and behind it
             for (int at = 0; at < kMaxShares; ++at)
                 for (double other : {0.0, largest, -largest}) {
@@ -54,7 +54,7 @@ int main() {
     if (bits(share_sum(most)) != bits(0x1.fffffffffffffp509) || bits(share_sum(least)) != bits(-0x1.fffffffffffffp509)) return bad("the largest sum", most);
     for (double v : {0x1p-511, 0x1.fffffffffffffp-511, 0x1p-562, -0x1.8p-540, 0x1p-600, 5e-324}) {   // the smallest lose what lies below 2^-562
         const double stored = with_mark(v, 1);
-        if (mark_of(stored) != 1 || !(std::fabs(without_mark(stored) * kShareUnit - v) <= 0x1p-563)) return bad("small", v);
+        if (other_mark(mark_word(stored, 1)) || !(std::fabs(without_mark(stored) * kShareUnit - v) <= 0x1p-563)) return bad("small", v);
     }
     return 0;
 }
