@@ -57,7 +57,7 @@ struct BwdPlan {
     int splits;      // workgroups along the token axis of the wgrad kernel
     int waves;       // waves per workgroup of the wgrad kernel: 4, or 8 on short batches with one rank block (see make_plan)
     // workspace layout, in 4-byte words
-    size_t off_t, off_du, off_part, words;
+    size_t off_t, off_du, off_part, off_rank, words;
 };
 
 // ell_fused: envelopes whose partial sums the wgrad kernel holds at once (1: one envelope per wgrad / finish pass).
@@ -88,9 +88,9 @@ BwdPlan make_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, int64_t ell
     p.off_t = 0;
     p.off_du = p.off_t + static_cast<size_t>(LORDBA_MAX_ENVELOPES) * p.rp * p.t_pad;
     p.off_part = p.off_du + static_cast<size_t>(LORDBA_MAX_ENVELOPES) * p.rp * p.t_pad;
-    // (one word per sum more than the kernels use: the size that programs keep a workspace of, and the shapes that fit the array of
-    // lordba_backward_noalloc, are the ones they were when the shares of d_s_rank were here)
-    p.words = p.off_part + static_cast<size_t>(p.splits) * p.rp * ell_fused * (p.dcols + 1);
+    // one word per rank and token range for d_s_rank: arrivals and, one part fewer than there are token ranges, the sums of its parts
+    p.off_rank = p.off_part + static_cast<size_t>(p.splits) * p.rp * ell_fused * p.dcols;
+    p.words = p.off_rank + static_cast<size_t>(p.splits) * p.rp * ell_fused;
     return p;
 }
 
@@ -115,6 +115,8 @@ struct BwdArgs {
     float* part;           // [splits, ell, rp, dcols]
     int T, d_in, d_out, r;
     int rp, t_pad, t_stride, du_stride, nbx, nbg, dcols, tw, splits, waves;
+    float* rank_sums;      // [1 + rank_parts, ell, rp]: arrivals (as whole numbers), then the parts' sums of d_s_rank (rank_parts > 1)
+    int rank_parts;        // workgroups per rank of d_s_rank
     int accumulate;        // latent gradients are added to what the arrays hold (second and later envelopes, one pass each)
     // Envelopes held at once (Eq. (lordba): the carriers are shared, so Q and P of all envelopes contract the same x and g
     // with different small operands).  s_in, s_rank, s_out and the scale gradients then have ell rows, tT and duT one
@@ -154,6 +156,11 @@ __device__ __forceinline__ void split_scaled(const float (&v)[8], float mul, u4&
 __global__ void bwd_zero_kernel(float* p, int64_t n) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0.f;
+}
+
+// No rank has been added up yet: by one wave of the kernel before.
+__device__ __forceinline__ void clear_rank_arrivals(const BwdArgs& a, int lane) {
+    if (a.rank_parts > 1 && blockIdx.x == 0 && blockIdx.y == 0 && lane < a.ell * a.rp) reinterpret_cast<uint32_t*>(a.rank_sums)[lane] = 0u;
 }
 
 // ----------------------------------------------------------------------------------------- wgrad kernel ----
@@ -435,6 +442,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         *reinterpret_cast<f4*>(dst) = f4{sum[0], sum[1], sum[2], sum[3]};
         if constexpr (NE == 8) *reinterpret_cast<f4*>(dst + 4) = f4{sum[4], sum[5], sum[6], sum[7]};
     }
+    if (wave == 0) clear_rank_arrivals(a, lane);
 }
 
 // The same contraction with the tokens streamed through LDS (plain variants only).  A workgroup takes one column block and one range of
@@ -592,6 +600,7 @@ __global__ __launch_bounds__(B * TG * 64) void lordba_bwd_wgrad_stream_kernel(Bw
     float* dst = a.part + ((static_cast<size_t>(blockIdx.y) * blocks + rbw) * 16 + li) * a.dcols + static_cast<size_t>(cb) * 128 + 32 * q;
 #pragma unroll
     for (int i = 0; i < 8; ++i) *reinterpret_cast<f4*>(dst + 4 * i) = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
+    if (wave == 0) clear_rank_arrivals(a, lane);
 }
 
 // ---------------------------------------------------------------------------------------- finish kernel ----
@@ -602,13 +611,11 @@ __device__ __forceinline__ float smooth_sign_factor(float latent, float kappa) {
     return 4.f * kappa * e / (s * s);
 }
 
-// d_beta_k = sum_t du[t, k] t[t, k] of one rank of one envelope (row k of all envelopes' ranks) by a workgroup of NT threads.  (By the wgrad
-// kernel's workgroups of one column block it was up to 5 us behind their other work.)  The order of the sum is fixed: thread, wave, waves.
-template <int NT>
-__device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int k, float* red) {
+// sum_t du[t] t[t] over tokens begin .. end - 1 of row k by the threads of a workgroup: this thread's share, U pieces of four tokens in flight.
+template <int NT, int U>
+__device__ __forceinline__ float token_sum(const BwdArgs& a, int k, int64_t begin, int64_t end) {
     const float* du = a.duT + static_cast<size_t>(k) * a.du_stride;
     const float* t = a.tT + static_cast<size_t>(k) * a.t_stride;
-    constexpr int U = 4;   // pieces of four tokens in flight
     auto piece = [&](const float* p, int tok) { return drop_words(load16_word(p + row_piece(tok, a.T, k)), tok - row_piece(tok, a.T, k)); };
     float acc[U][4];
 #pragma unroll
@@ -616,11 +623,11 @@ __device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int k, flo
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[j][e] = 0.f;
     }
-    for (int64_t i = 4 * threadIdx.x; i < a.T; i += 4 * U * NT) {
+    for (int64_t i = begin + 4 * threadIdx.x; i < end; i += 4 * U * NT) {
         u4 dv[U], tv[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const int tok = static_cast<int>(i + 4 * j * NT < a.T ? i + 4 * j * NT : i);
+            const int tok = static_cast<int>(i + 4 * j * NT < end ? i + 4 * j * NT : i);
             dv[j] = piece(du, tok);
             tv[j] = piece(t, tok);
         }
@@ -628,23 +635,53 @@ __device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int k, flo
         for (int j = 0; j < U; ++j) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)   // select: entries past T are undefined
-                acc[j][e] += i + 4 * j * NT + e < a.T ? __uint_as_float(dv[j][e]) * __uint_as_float(tv[j][e]) : 0.f;
+                acc[j][e] += i + 4 * j * NT + e < end ? __uint_as_float(dv[j][e]) * __uint_as_float(tv[j][e]) : 0.f;
         }
     }
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < U; ++j) s += (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
+    return s;
+}
+// Sum over the threads of a workgroup, in the first one (fixed order: wave, waves).
+template <int NT>
+__device__ __forceinline__ float workgroup_sum(float s, float* red) {
 #pragma unroll
     for (int step = 32; step >= 1; step >>= 1) s += __shfl_xor(s, step, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float tot = 0.f;
+    float tot = 0.f;
+    if (threadIdx.x == 0)
         for (int w = 0; w < NT / 64; ++w) tot += red[w];
-        a.d_s_rank[k] = tot;
-    }
+    return tot;
 }
 
+// d_beta_k = sum_t du[t, k] t[t, k], workgroup wg of rank_parts for each of the ranks of all envelopes.  (By the wgrad kernel's workgroups of one
+// column block it was up to 5 us behind their other work, up to 20 on narrow batches.)  The last one of a rank to arrive adds the parts up, in
+// their order, so the order of the sum is fixed: thread, wave, waves, parts.  One workgroup per rank, whatever T is, keeps the launch waiting on
+// long batches: see rank_parts.
+template <int NT>
+__device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int wg, float* red) {
+    constexpr int U = kRankRound / (4 * NT);
+    const int parts = a.rank_parts, k = wg / parts, part = wg - k * parts;
+    const int64_t span = rank_span(a.T, parts), begin = part * span, end = begin + span < a.T ? begin + span : a.T;
+    float tot = workgroup_sum<NT>(end - begin > kRankRound / 2 ? token_sum<NT, U>(a, k, begin, end) : token_sum<NT, U / 2>(a, k, begin, end), red);
+    if (parts > 1) {
+        uint32_t* last = reinterpret_cast<uint32_t*>(red) + NT / 64;
+        float* sums = a.rank_sums + a.ell * a.rp + k;   // (the arrivals are in front of them)
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(sums + part * a.ell * a.rp, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            *last = __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(a.rank_sums) + k, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == static_cast<uint32_t>(parts);
+        }
+        __syncthreads();
+        if (*last == 0u) return;
+        const int mine = static_cast<int>(threadIdx.x) < parts ? threadIdx.x : 0;
+        const float v = __hip_atomic_load(sums + mine * a.ell * a.rp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        tot = workgroup_sum<NT>(static_cast<int>(threadIdx.x) < parts ? v : 0.f, red);
+    }
+    if (threadIdx.x == 0) a.d_s_rank[k] = tot;
+}
 // Widths that are multiples of 32.  A workgroup takes NG groups of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out,
 // d_latentB); a thread takes four columns and one rank (RK >= r of them), with all envelopes' shares, so that everything it needs is requested at
 // once in 16-byte pieces (up to eight token ranges with one envelope, four with more).  The workgroups in front of these take d_s_rank.  Bound: one
@@ -657,14 +694,14 @@ __global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kern
     constexpr int SP = L == 1 ? 8 : 4;   // token ranges' shares in flight
     __shared__ __align__(16) float sh[NG][L][RK][32];
     __shared__ float lat[NG][32 * RK];
-    const int tid = threadIdx.x, r = a.r, rows = L * a.rp;
-    if (static_cast<int>(blockIdx.x) < L * r) {
+    const int tid = threadIdx.x, r = a.r, rows = L * a.rp, in_front = L * r * a.rank_parts;
+    if (static_cast<int>(blockIdx.x) < in_front) {
         rank_scale_gradient<NT>(a, blockIdx.x, &lat[0][0]);
         return;
     }
     const int gx = a.d_in >> 5, gg = a.d_out >> 5;
     const int ng = tid / (8 * RK), k = (tid >> 3) & (RK - 1), c = (tid & 7) * 4;   // group, rank, first of the four columns
-    const int g0 = (static_cast<int>(blockIdx.x) - L * r) * NG + ng;
+    const int g0 = (static_cast<int>(blockIdx.x) - in_front) * NG + ng;
     const bool live = g0 < gx + gg && k < r;
     const int gc = g0 < gx + gg ? g0 : gx + gg - 1, kc = k < r ? k : r - 1;   // (a group and a rank that exist)
     const bool is_x = gc < gx;
@@ -773,11 +810,12 @@ __global__ __launch_bounds__(32 * KQ) void lordba_bwd_finish_any_kernel(BwdArgs 
     const int gx = (a.d_in + 31) >> 5;
     const int tid = threadIdx.x;
     const int r = a.r, ell = a.ell, rows = ell * a.rp;   // rows of one token range's plane of partial sums: all envelopes' rank blocks
-    if (static_cast<int>(blockIdx.x) < ell * r) {
+    const int in_front = ell * r * a.rank_parts;
+    if (static_cast<int>(blockIdx.x) < in_front) {
         rank_scale_gradient<NT>(a, blockIdx.x, sh[0]);
         return;
     }
-    const int wg = static_cast<int>(blockIdx.x) - ell * r;
+    const int wg = static_cast<int>(blockIdx.x) - in_front;
     const bool is_x = wg < gx;
     const int grp = is_x ? wg : wg - gx;
     const int d = is_x ? a.d_in : a.d_out;
@@ -922,14 +960,14 @@ bool aligned_to(const void* p, size_t n) { return (reinterpret_cast<uintptr_t>(p
 
 template <int KQ>
 void launch_finish_any(const BwdArgs& a, hipStream_t st) {
-    const dim3 groups(a.ell * a.r + (a.d_in + 31) / 32 + (a.d_out + 31) / 32);
+    const dim3 groups(a.ell * a.r * a.rank_parts + (a.d_in + 31) / 32 + (a.d_out + 31) / 32);
     hipLaunchKernelGGL((lordba_bwd_finish_any_kernel<KQ>), groups, dim3(32 * KQ), 0, st, a);
 }
 template <int RK, int L>
 void launch_finish(const BwdArgs& a, hipStream_t st) {
     constexpr int NT = RK < 32 ? 256 : 8 * RK, NG = NT / (8 * RK);
     const unsigned groups = static_cast<unsigned>(a.d_in / 32 + a.d_out / 32);
-    hipLaunchKernelGGL((lordba_bwd_finish_kernel<RK, L>), dim3(L * a.r + (groups + NG - 1) / NG), dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((lordba_bwd_finish_kernel<RK, L>), dim3(L * a.r * a.rank_parts + (groups + NG - 1) / NG), dim3(NT), 0, st, a);
 }
 template <int L>
 void launch_finish_rank(const BwdArgs& a, hipStream_t st) {
@@ -1182,6 +1220,8 @@ lordba_status backward_impl(const void* x, const void* g,
         a.tT = tT;
         a.duT = duT + e * r * p.t_pad;
         a.part = ws + p.off_part;
+        a.rank_sums = ws + p.off_rank;
+        a.rank_parts = rank_parts(T, p.splits - 1);
         a.T = static_cast<int>(T);
         a.d_in = static_cast<int>(d_in);
         a.d_out = static_cast<int>(d_out);

@@ -220,6 +220,15 @@ def test_a_rank_without_scale_adds_nothing_to_what_is_not_finite(torch_cuda, sha
             assert not got["d_s_in"][rest["x"]].any() and not got["d_s_out"][rest["g"]].any()
 
 
+# d_s_rank by one workgroup per rank (two rounds of tokens), by three (the line is at 16384 rows) and five, with workgroups of 256 and 512 threads
+# and on the element-aligned kernels
+@pytest.mark.parametrize("shape", [(16384, 32, 64, 5), (16385, 64, 32, 16), (40001, 32, 32, 64), (40001, 33, 65, 3), (33001, 35, 64, 17), (33001, 33, 40, 33)],
+                         ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_long_batches_sum_rank_scales_in_parts(torch_cuda, shape):
+    T, d_in, d_out, r = shape
+    check(torch_cuda, inputs.make_backward_inputs(43, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
+
+
 # Widths around the edges of groups (8), words (32) and column blocks (128) on the element-aligned kernels, every rank-block count,
 # short and long batches
 @pytest.mark.parametrize("shape", [(70, 25, 41, 5), (33, 129, 127, 64), (300, 1000, 3001, 12), (45, 1055, 257, 33), (4100, 135, 250, 17),
@@ -391,7 +400,8 @@ def test_unaligned_tensors_and_any_kept_t(torch_cuda):
                                   # above the lines from which the tokens are streamed through LDS: two blocks, three in the kernel of four, four,
                                   # ranks that fill their blocks and ranks that do not, a last tile and a last column block in part
                                   (2, 4127, 416, 224, 16), (2, 2305, 2080, 2016, 9), (3, 1537, 2080, 2016, 13), (3, 1500, 2208, 2016, 16),
-                                  (2, 1537, 2080, 2016, 32), (2, 1555, 2016, 2080, 21), (4, 1537, 2080, 2016, 11)],
+                                  (2, 1537, 2080, 2016, 32), (2, 1555, 2016, 2080, 21), (4, 1537, 2080, 2016, 11),
+                                  (3, 20000, 64, 32, 7)],   # d_s_rank of all envelopes in parts
                          ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
 def test_several_envelopes_in_one_pass(torch_cuda, case):
     """lordba_backward_multi with the workspace of lordba_backward_multi_workspace_bytes: one wgrad and one finish pass hold
@@ -526,11 +536,12 @@ def test_several_envelopes(torch_cuda, case):
         assert np.array_equal(v.cpu().numpy(), got[k]), k
 
 
-def test_hip_graph_replays_match_eager(torch_cuda):
+@pytest.mark.parametrize("shape", [(300, 1024, 768, 16), (16385, 64, 32, 16)], ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_hip_graph_replays_match_eager(torch_cuda, shape):
     """bench.py replays a captured graph of backward calls: several replays, with eager work and synchronisations in
     between, against the eager result (the call records kernel nodes only: no memset, no allocation)."""
     torch = torch_cuda
-    T, d_in, d_out, r = 300, 1024, 768, 16
+    T, d_in, d_out, r = shape
     d = inputs.make_backward_inputs(33, T, d_in, d_out, r)
     cu = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
     pA, _ = binding.lordba_pack_signs(d["signsA"], d["signsB"])
