@@ -682,25 +682,34 @@ __device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int wg, fl
     }
     if (threadIdx.x == 0) a.d_s_rank[k] = tot;
 }
+template <int RK>
+constexpr int kFinishThreads = RK < 32 ? 256 : 8 * RK;
+template <int L>
+constexpr int kFinishShares = L == 1 ? 8 : 4;   // token ranges' shares that a thread has in flight
 // Widths that are multiples of 32.  A workgroup takes NG groups of 32 columns of d_in (Q, d_s_in, d_latentA) or of d_out (P, d_s_out,
 // d_latentB); a thread takes four columns and one rank (RK >= r of them), with all envelopes' shares, so that everything it needs is requested at
 // once in 16-byte pieces (up to eight token ranges with one envelope, four with more).  The workgroups in front of these take d_s_rank.  Bound: one
 // trip to memory behind the launch.  2048 x 5120 x 5120, two envelopes at r = 32 5.2 us in a kernel trace, with one column per thread, shares eight
-// at a time per envelope and latentB through LDS first 8.5; 4096^2, r = 16 4.5 (4.5).  With eight ranges for two and three envelopes the calls of
-// five ranges and more gain 1 % and the others lose 1 to 3 (64 x 4096^2, two envelopes 14.1 us for 13.7).
-template <int RK, int L>
-__global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kernel(BwdArgs a) {
-    constexpr int NT = RK < 32 ? 256 : 8 * RK, NG = NT / (8 * RK);
-    constexpr int SP = L == 1 ? 8 : 4;   // token ranges' shares in flight
+// at a time per envelope and latentB through LDS first 8.5; 4096^2, r = 16 4.5 (4.5).
+// Where there are more token ranges than that a workgroup takes one group instead, KS threads per entry with every KS-th range each: more
+// ranges mean fewer column blocks (512 workgroups in all), few workgroups of several groups, and a trip per eight (or four) ranges.  us, several
+// groups in brackets: this kernel at 8192 x 1024 x 1024, r = 4, 32 ranges 3.8 (5.3), 1048576 x 64 x 64, r = 1, 256 ranges 6.8 (20.1); the backward call there
+// 30.1 (32.8), 880 (890), at 4096 x 256 x 256, r = 16 18.8 (21.8), two envelopes at r = 16 8192 x 256 x 256 33.2 (35.8), 1000 x 2048 x 2048 21.8 (22.7).
+template <int RK, int L, int KS>
+__global__ __launch_bounds__(kFinishThreads<RK>) void lordba_bwd_finish_kernel(BwdArgs a) {
+    constexpr int NT = kFinishThreads<RK>, NG = NT / (8 * RK * KS), SP = kFinishShares<L>;
     __shared__ __align__(16) float sh[NG][L][RK][32];
     __shared__ float lat[NG][32 * RK];
+    __shared__ __align__(16) float others[KS > 1 ? KS - 1 : 1][L][RK][32];
+    static_assert(NG * KS * 8 * RK == NT && NG * 32 * RK > NT / 64, "whole groups; room for a workgroup's sums of d_s_rank");
     const int tid = threadIdx.x, r = a.r, rows = L * a.rp, in_front = L * r * a.rank_parts;
     if (static_cast<int>(blockIdx.x) < in_front) {
         rank_scale_gradient<NT>(a, blockIdx.x, &lat[0][0]);
         return;
     }
     const int gx = a.d_in >> 5, gg = a.d_out >> 5;
-    const int ng = tid / (8 * RK), k = (tid >> 3) & (RK - 1), c = (tid & 7) * 4;   // group, rank, first of the four columns
+    const int part = __builtin_amdgcn_readfirstlane(tid / (8 * RK)), ng = KS > 1 ? 0 : part, ks = KS > 1 ? part : 0;   // group, or part of its shares
+    const int k = (tid >> 3) & (RK - 1), c = (tid & 7) * 4;   // rank, first of the four columns
     const int g0 = (static_cast<int>(blockIdx.x) - in_front) * NG + ng;
     const bool live = g0 < gx + gg && k < r;
     const int gc = g0 < gx + gg ? g0 : gx + gg - 1, kc = k < r ? k : r - 1;   // (a group and a rank that exist)
@@ -716,7 +725,7 @@ __global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kern
         for (int en = 0; en < L; ++en) {
 #pragma unroll
             for (int j = 0; j < SP; ++j) {
-                const int sp = sp0 + j < a.splits ? sp0 + j : a.splits - 1;
+                const int at = (sp0 + j) * KS + ks, sp = at < a.splits ? at : a.splits - 1;
                 v[en][j] = load16(plane + sp * plane_stride + en * env_stride);
             }
         }
@@ -728,7 +737,7 @@ __global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kern
     for (int en = 0; en < L; ++en)
         scale[en] = *reinterpret_cast<const uint2*>((is_x ? a.s_in : a.s_out) + static_cast<size_t>(en) * d + col);
     float latent[4] = {0.f, 0.f, 0.f, 0.f};
-    if (with_lat) {
+    if (with_lat && ks == 0) {
         if (is_x) {   // (the same in all lanes of a wave: a group has at least one of its own)
             const u4 w = *reinterpret_cast<const u4_word*>(a.latA + static_cast<size_t>(kc) * d + col);
 #pragma unroll
@@ -746,11 +755,25 @@ __global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kern
 #pragma unroll
             for (int j = 0; j < SP; ++j) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum[en][e] += sp0 + j < a.splits ? __uint_as_float(v[en][j][e]) : 0.f;
+                for (int e = 0; e < 4; ++e) sum[en][e] += (sp0 + j) * KS + ks < a.splits ? __uint_as_float(v[en][j][e]) : 0.f;
             }
         }
-        if (sp0 + SP >= a.splits) break;
+        if ((sp0 + SP) * KS >= a.splits) break;
         request(sp0 + SP);
+    }
+    if constexpr (KS > 1) {   // the parts' sums, in their order
+        if (ks > 0) {
+#pragma unroll
+            for (int en = 0; en < L; ++en) *reinterpret_cast<f4*>(&others[ks - 1][en][k][c]) = sum[en];
+        }
+        __syncthreads();
+        if (ks == 0) {
+#pragma unroll
+            for (int o = 0; o < KS - 1; ++o) {
+#pragma unroll
+                for (int en = 0; en < L; ++en) sum[en] += *reinterpret_cast<const f4*>(&others[o][en][k][c]);
+            }
+        }
     }
     float weighted[4] = {0.f, 0.f, 0.f, 0.f};   // sum over the envelopes of scale_e * (Q_e or P_e)[k, col]: dL/dS[k, col]
 #pragma unroll
@@ -762,9 +785,9 @@ __global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kern
             ds[e] = live ? flip(sum[en][e], (word >> e) & 1u) : 0.f;
             weighted[e] = L == 1 ? sc * sum[en][e] : fmaf(sc, sum[en][e], weighted[e]);
         }
-        *reinterpret_cast<f4*>(&sh[ng][en][k][c]) = ds;
+        if (ks == 0) *reinterpret_cast<f4*>(&sh[ng][en][k][c]) = ds;
     }
-    if (with_lat && live) {
+    if (with_lat && live && ks == 0) {
         float val[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) val[e] = weighted[e] * smooth_sign_factor(latent[e], a.kappa);
@@ -781,13 +804,14 @@ __global__ __launch_bounds__(RK < 32 ? 256 : 8 * RK) void lordba_bwd_finish_kern
         }
     }
     __syncthreads();
-    const int gt = tid & (8 * RK - 1);   // thread of the group
+    constexpr int GT = 8 * RK * KS;
+    const int gt = tid & (GT - 1);   // thread of the group
     if (g0 >= gx + gg) return;
     if (with_lat && !is_x) {
         float* dst = a.d_latB + static_cast<size_t>(grp) * 32 * r;
-        for (int e = gt; e < 32 * r; e += 8 * RK) dst[e] = a.accumulate ? dst[e] + lat[ng][e] : lat[ng][e];
+        for (int e = gt; e < 32 * r; e += GT) dst[e] = a.accumulate ? dst[e] + lat[ng][e] : lat[ng][e];
     }
-    for (int o = gt; o < 32 * L; o += 8 * RK) {   // the sums over the ranks, in their order
+    for (int o = gt; o < 32 * L; o += GT) {   // the sums over the ranks, in their order
         const int en = o >> 5, cc = o & 31;
         float tot[4] = {0.f, 0.f, 0.f, 0.f};   // (four sums of a quarter of the ranks each: a chain over 64 would round more often)
 #pragma unroll 4
@@ -963,11 +987,18 @@ void launch_finish_any(const BwdArgs& a, hipStream_t st) {
     const dim3 groups(a.ell * a.r * a.rank_parts + (a.d_in + 31) / 32 + (a.d_out + 31) / 32);
     hipLaunchKernelGGL((lordba_bwd_finish_any_kernel<KQ>), groups, dim3(32 * KQ), 0, st, a);
 }
+template <int RK, int L, int KS>
+void launch_finish_parts(const BwdArgs& a, hipStream_t st) {
+    constexpr int NT = kFinishThreads<RK>, NG = NT / (8 * RK * KS);
+    const unsigned groups = static_cast<unsigned>(a.d_in / 32 + a.d_out / 32);
+    hipLaunchKernelGGL((lordba_bwd_finish_kernel<RK, L, KS>), dim3(L * a.r * a.rank_parts + (groups + NG - 1) / NG), dim3(NT), 0, st, a);
+}
 template <int RK, int L>
 void launch_finish(const BwdArgs& a, hipStream_t st) {
-    constexpr int NT = RK < 32 ? 256 : 8 * RK, NG = NT / (8 * RK);
-    const unsigned groups = static_cast<unsigned>(a.d_in / 32 + a.d_out / 32);
-    hipLaunchKernelGGL((lordba_bwd_finish_kernel<RK, L>), dim3(L * a.r * a.rank_parts + (groups + NG - 1) / NG), dim3(NT), 0, st, a);
+    constexpr int KS = kFinishThreads<RK> / (8 * RK);
+    if constexpr (KS > 1)
+        if (a.splits > kFinishShares<L>) return launch_finish_parts<RK, L, KS>(a, st);
+    launch_finish_parts<RK, L, 1>(a, st);
 }
 template <int L>
 void launch_finish_rank(const BwdArgs& a, hipStream_t st) {

@@ -220,6 +220,14 @@ def test_a_rank_without_scale_adds_nothing_to_what_is_not_finite(torch_cuda, sha
             assert not got["d_s_in"][rest["x"]].any() and not got["d_s_out"][rest["g"]].any()
 
 
+# Eight token ranges, whose shares a thread of the finish kernel takes at once, nine, ten and many, dealt to four threads (r <= 8) or two
+@pytest.mark.parametrize("shape", [(2048, 96, 64, 8), (2304, 96, 64, 8), (2304, 32, 96, 16), (2500, 64, 64, 2), (4100, 96, 32, 7), (4100, 64, 96, 13), (9000, 64, 32, 16)],
+                         ids=lambda s: "T%d_%dx%d_r%d" % s)
+def test_token_ranges_dealt_to_several_threads(torch_cuda, shape):
+    T, d_in, d_out, r = shape
+    check(torch_cuda, inputs.make_backward_inputs(44, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
+
+
 # d_s_rank by one workgroup per rank (two rounds of tokens), by three (the line is at 16384 rows) and five, with workgroups of 256 and 512 threads
 # and on the element-aligned kernels
 @pytest.mark.parametrize("shape", [(16384, 32, 64, 5), (16385, 64, 32, 16), (40001, 32, 32, 64), (40001, 33, 65, 3), (33001, 35, 64, 17), (33001, 33, 40, 33)],
@@ -401,7 +409,9 @@ def test_unaligned_tensors_and_any_kept_t(torch_cuda):
                                   # ranks that fill their blocks and ranks that do not, a last tile and a last column block in part
                                   (2, 4127, 416, 224, 16), (2, 2305, 2080, 2016, 9), (3, 1537, 2080, 2016, 13), (3, 1500, 2208, 2016, 16),
                                   (2, 1537, 2080, 2016, 32), (2, 1555, 2016, 2080, 21), (4, 1537, 2080, 2016, 11),
-                                  (3, 20000, 64, 32, 7)],   # d_s_rank of all envelopes in parts
+                                  (3, 20000, 64, 32, 7),   # d_s_rank of all envelopes in parts
+                                  # four token ranges, whose shares a thread of the finish kernel takes at once, five, and many over several threads
+                                  (2, 512, 96, 64, 16), (2, 640, 96, 64, 16), (3, 700, 64, 96, 16), (4, 900, 96, 32, 8), (4, 4099, 32, 64, 3)],
                          ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
 def test_several_envelopes_in_one_pass(torch_cuda, case):
     """lordba_backward_multi with the workspace of lordba_backward_multi_workspace_bytes: one wgrad and one finish pass hold
