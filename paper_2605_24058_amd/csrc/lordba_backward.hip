@@ -158,7 +158,8 @@ __global__ void bwd_zero_kernel(float* p, int64_t n) {
     if (i < n) p[i] = 0.f;
 }
 
-// No rank has been added up yet: by one wave of the kernel before.
+// No rank has been added up yet: by one wave of the kernel before, at its start (behind everything else the look at the arguments is a trip to
+// memory that every wave 0 ends with: 0.1 us of a call of 29.7 at 2048 x 4096 x 4096, r = 16).
 __device__ __forceinline__ void clear_rank_arrivals(const BwdArgs& a, int lane) {
     if (a.rank_parts > 1 && blockIdx.x == 0 && blockIdx.y == 0 && lane < a.ell * a.rp) reinterpret_cast<uint32_t*>(a.rank_sums)[lane] = 0u;
 }
@@ -180,6 +181,7 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
     // MFMA instructions ignore the EXEC mask, so they must never sit under a vector-predicated branch.
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, q = lane >> 4;
+    if (wave == 0) clear_rank_arrivals(a, lane);
     const int rbe = a.rp >> 4, blocks = a.ell * rbe;  // rank blocks per envelope, and in all
     int cb = blockIdx.x, rb0 = 0;   // column block, first rank block
     if constexpr (Z > 1) {
@@ -442,7 +444,6 @@ __global__ __launch_bounds__(W * 64) void lordba_bwd_wgrad_kernel(BwdArgs a) {
         *reinterpret_cast<f4*>(dst) = f4{sum[0], sum[1], sum[2], sum[3]};
         if constexpr (NE == 8) *reinterpret_cast<f4*>(dst + 4) = f4{sum[4], sum[5], sum[6], sum[7]};
     }
-    if (wave == 0) clear_rank_arrivals(a, lane);
 }
 
 // The same contraction with the tokens streamed through LDS (plain variants only).  A workgroup takes one column block and one range of
@@ -467,6 +468,7 @@ __global__ __launch_bounds__(B * TG * 64) void lordba_bwd_wgrad_stream_kernel(Bw
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, q = lane >> 4;
+    if (wave == 0) clear_rank_arrivals(a, lane);
     const int rbe = a.rp >> 4, blocks = a.ell * rbe;
     const int cb = blockIdx.x, rbw = wave % B, tg = wave / B;
     const bool is_x = cb < a.nbx;
@@ -600,7 +602,6 @@ __global__ __launch_bounds__(B * TG * 64) void lordba_bwd_wgrad_stream_kernel(Bw
     float* dst = a.part + ((static_cast<size_t>(blockIdx.y) * blocks + rbw) * 16 + li) * a.dcols + static_cast<size_t>(cb) * 128 + 32 * q;
 #pragma unroll
     for (int i = 0; i < 8; ++i) *reinterpret_cast<f4*>(dst + 4 * i) = f4{out[4 * i], out[4 * i + 1], out[4 * i + 2], out[4 * i + 3]};
-    if (wave == 0) clear_rank_arrivals(a, lane);
 }
 
 // ---------------------------------------------------------------------------------------- finish kernel ----
@@ -611,11 +612,12 @@ __device__ __forceinline__ float smooth_sign_factor(float latent, float kappa) {
     return 4.f * kappa * e / (s * s);
 }
 
-// sum_t du[t] t[t] over tokens begin .. end - 1 of row k by the threads of a workgroup: this thread's share, U pieces of four tokens in flight.
-template <int NT, int U>
+// sum_t du[t] t[t] over tokens begin .. end - 1 of row k by the threads of a workgroup: this thread's share.
+template <int NT>
 __device__ __forceinline__ float token_sum(const BwdArgs& a, int k, int64_t begin, int64_t end) {
     const float* du = a.duT + static_cast<size_t>(k) * a.du_stride;
     const float* t = a.tT + static_cast<size_t>(k) * a.t_stride;
+    constexpr int U = 4;   // pieces of four tokens in flight
     auto piece = [&](const float* p, int tok) { return drop_words(load16_word(p + row_piece(tok, a.T, k)), tok - row_piece(tok, a.T, k)); };
     float acc[U][4];
 #pragma unroll
@@ -662,10 +664,9 @@ __device__ __forceinline__ float workgroup_sum(float s, float* red) {
 // long batches: see rank_parts.
 template <int NT>
 __device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int wg, float* red) {
-    constexpr int U = kRankRound / (4 * NT);
-    const int parts = a.rank_parts, k = wg / parts, part = wg - k * parts;
+    const int parts = a.rank_parts, k = parts == 1 ? wg : wg / parts, part = wg - k * parts;
     const int64_t span = rank_span(a.T, parts), begin = part * span, end = begin + span < a.T ? begin + span : a.T;
-    float tot = workgroup_sum<NT>(end - begin > kRankRound / 2 ? token_sum<NT, U>(a, k, begin, end) : token_sum<NT, U / 2>(a, k, begin, end), red);
+    float tot = workgroup_sum<NT>(token_sum<NT>(a, k, begin, end), red);
     if (parts > 1) {
         uint32_t* last = reinterpret_cast<uint32_t*>(red) + NT / 64;
         float* sums = a.rank_sums + a.ell * a.rp + k;   // (the arrivals are in front of them)

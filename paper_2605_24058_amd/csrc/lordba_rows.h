@@ -11,13 +11,13 @@ constexpr int row_piece(int tok, int T, int row) {
     return tok < last ? tok : last;
 }
 
-// d_s_rank of a rank is a sum over T tokens.  A workgroup requests kRankRound of them at once; longer batches are dealt to several (`room`: at most
-// as many as there is workspace for), which costs two more trips to memory: the parts' sums and arrivals, then all sums.  Two rounds of one workgroup
-// take no longer than that (T = 16384, 2048 -> 2048, r = 4 82.5 us for the backward call, in two parts 82.9), four do (T = 65536 278 us in eight parts,
-// 280 in four), and one workgroup for everything took 148 us of a call of 1023 at T = 1048576, 64 -> 64, r = 1 (now 7 of 880).
-constexpr int kRankRound = 8192, kMaxRankParts = 256;   // (a thread for every part in the smallest workgroup)
+// d_s_rank of a rank is a sum over T tokens.  A workgroup of 256 threads requests 4096 of them at a time; longer batches are dealt to several, one per
+// kRankTokens (`room`: at most as many as there is workspace for), which costs two more trips to memory: the parts' sums and arrivals, then all
+// sums.  Four rounds of one workgroup take no longer than that (T = 16384, 2048 -> 2048, r = 4 80.7 us for the backward call, in two parts 81.7); with
+// 16384 each T = 65536 takes 280 (278), and one workgroup for everything took 148 us of a call of 1023 at T = 1048576, 64 -> 64, r = 1 (now 7 of 880).
+constexpr int kRankTokens = 8192, kMaxRankParts = 256;   // (a thread for every part in the smallest workgroup)
 constexpr int rank_parts(long long T, long long room) {
-    const long long wanted = T <= 2 * kRankRound ? 1 : (T + kRankRound - 1) / kRankRound, most = room < kMaxRankParts ? room : kMaxRankParts;
+    const long long wanted = T <= 2 * kRankTokens ? 1 : (T + kRankTokens - 1) / kRankTokens, most = room < kMaxRankParts ? room : kMaxRankParts;
     return wanted <= 1 || most <= 1 ? 1 : static_cast<int>(wanted < most ? wanted : most);
 }
 // Tokens of each part but the last (whole pieces of four).

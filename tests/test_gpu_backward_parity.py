@@ -228,7 +228,7 @@ def test_token_ranges_dealt_to_several_threads(torch_cuda, shape):
     check(torch_cuda, inputs.make_backward_inputs(44, T, d_in, d_out, r), "T%d_%dx%d_r%d" % shape)
 
 
-# d_s_rank by one workgroup per rank (two rounds of tokens), by three (the line is at 16384 rows) and five, with workgroups of 256 and 512 threads
+# d_s_rank by one workgroup per rank (four rounds of tokens), by three (the line is at 16384 rows) and five, with workgroups of 256 and 512 threads
 # and on the element-aligned kernels
 @pytest.mark.parametrize("shape", [(16384, 32, 64, 5), (16385, 64, 32, 16), (40001, 32, 32, 64), (40001, 33, 65, 3), (33001, 35, 64, 17), (33001, 33, 40, 33)],
                          ids=lambda s: "T%d_%dx%d_r%d" % s)

@@ -12,8 +12,8 @@ static int look(long long T, int splits) {
     const long long span = rank_span(T, parts);
     const bool fits = parts >= 1 && parts <= kMaxRankParts && (parts == 1 || 1 + parts <= splits);   // one plane of arrivals, one per part
     const bool covered = span % 4 == 0 && (parts - 1) * span < T && parts * span >= T;              // whole pieces, no part empty
-    const long long needed = (T + kRankRound - 1) / kRankRound;
-    const bool share = T <= 2 * kRankRound || needed > room || needed > kMaxRankParts || span <= kRankRound;
+    const long long needed = (T + kRankTokens - 1) / kRankTokens;
+    const bool share = T <= 2 * kRankTokens || needed > room || needed > kMaxRankParts || span <= kRankTokens;
     if (fits && covered && share) return 0;
     std::printf("T %lld, splits %d: parts %d of %lld\n", T, splits, parts, span);
     return 1;
