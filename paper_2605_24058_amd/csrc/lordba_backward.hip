@@ -116,7 +116,7 @@ struct BwdArgs {
     int T, d_in, d_out, r;
     int rp, t_pad, t_stride, du_stride, nbx, nbg, dcols, tw, splits, waves;
     float* rank_sums;      // [1 + rank_parts, ell, rp]: arrivals (as whole numbers), then the parts' sums of d_s_rank (rank_parts > 1)
-    int rank_parts;        // workgroups per rank of d_s_rank
+    int rank_parts, rank_tokens;   // workgroups per rank of d_s_rank, tokens of each (but the last)
     int accumulate;        // latent gradients are added to what the arrays hold (second and later envelopes, one pass each)
     // Envelopes held at once (Eq. (lordba): the carriers are shared, so Q and P of all envelopes contract the same x and g
     // with different small operands).  s_in, s_rank, s_out and the scale gradients then have ell rows, tT and duT one
@@ -665,7 +665,7 @@ __device__ __forceinline__ float workgroup_sum(float s, float* red) {
 template <int NT>
 __device__ __forceinline__ void rank_scale_gradient(const BwdArgs& a, int wg, float* red) {
     const int parts = a.rank_parts, k = parts == 1 ? wg : wg / parts, part = wg - k * parts;
-    const int64_t span = rank_span(a.T, parts), begin = part * span, end = begin + span < a.T ? begin + span : a.T;
+    const int64_t begin = static_cast<int64_t>(part) * a.rank_tokens, end = begin + a.rank_tokens < a.T ? begin + a.rank_tokens : a.T;
     float tot = workgroup_sum<NT>(token_sum<NT>(a, k, begin, end), red);
     if (parts > 1) {
         uint32_t* last = reinterpret_cast<uint32_t*>(red) + NT / 64;
@@ -1254,6 +1254,7 @@ lordba_status backward_impl(const void* x, const void* g,
         a.part = ws + p.off_part;
         a.rank_sums = ws + p.off_rank;
         a.rank_parts = rank_parts(T, p.splits - 1);
+        a.rank_tokens = static_cast<int>(rank_span(T, a.rank_parts));   // (whole pieces of four: T + 3 at most)
         a.T = static_cast<int>(T);
         a.d_in = static_cast<int>(d_in);
         a.d_out = static_cast<int>(d_out);
