@@ -1053,18 +1053,22 @@ lordba_status launch_all(const BwdArgs& args, hipStream_t st) {
     // 1536 -> 1536, T = 1100, r = 48 23.1 (22.2), T = 2000 24.3 (25.0); T = 8192, 5120^2, r = 64 114 (136), two envelopes at r = 16 97.0 (99.5).
     // One block gains nothing (2048 x 4096^2, r = 16 25.6 (24.3), T = 8192, 13824 -> 5120 174 (169)): nothing is shared.
     const int64_t tiles = static_cast<int64_t>(a.T) * (a.nbx + a.nbg);
-    const bool stream = !a.any && ((blocks == 2 && (!short_batch || tiles >= 72 * 1024)) || (blocks >= 3 && tiles >= 48 * 1024));
+    const bool enough = !a.any && ((blocks == 2 && (!short_batch || tiles >= 72 * 1024)) || (blocks >= 3 && tiles >= 48 * 1024));
+    // One workgroup fits a compute unit: as few token ranges as leave the last round of 256 workgroups nearly full (at least 0.9 of the
+    // best that the plan, which has the room for the sums, allows), in pieces of 64 rows.  5614 x 10496 -> 6016, three envelopes at
+    // r = 4, 129 column blocks: one range 170 us, three 153.
+    auto filled = [&](int splits) {
+        const int64_t n = static_cast<int64_t>(a.nbx + a.nbg) * splits;
+        return static_cast<double>(n) / static_cast<double>((n + 255) / 256 * 256);
+    };
+    double best = 0.0;
+    for (int k = 1; k <= a.splits; ++k) best = filled(k) > best ? filled(k) : best;
+    // Not three rank blocks where that is little more than half of the chip (129 to 161 column blocks below 4096 rows, one range): a quarter of the
+    // waves has nothing to do as it is, and single blocks over workgroups fill it (three envelopes at r = 4, the streamed kernel in brackets: 129
+    // column blocks, T = 400 35.4 (38.5), T = 1200 62.2 (65.8), 136, T = 2000 79.6 (83.0), 154, T = 800 52.4 (53.3), but 170 59.3 (56.5)).
+    const bool stream = enough && !(blocks == 3 && best < 0.63);
     int64_t range = static_cast<int64_t>(a.tw) * a.waves;   // token rows of a workgroup
     if (stream) {
-        // One workgroup fits a compute unit: as few token ranges as leave the last round of 256 workgroups nearly full (at least 0.9 of the
-        // best that the plan, which has the room for the sums, allows), in pieces of 64 rows.  5614 x 10496 -> 6016, three envelopes at
-        // r = 4, 129 column blocks: one range 170 us, three 153.
-        auto filled = [&](int splits) {
-            const int64_t n = static_cast<int64_t>(a.nbx + a.nbg) * splits;
-            return static_cast<double>(n) / static_cast<double>((n + 255) / 256 * 256);
-        };
-        double best = 0.0;
-        for (int k = 1; k <= a.splits; ++k) best = filled(k) > best ? filled(k) : best;
         int splits = 1;
         while (splits < a.splits && filled(splits) < 0.9 * best) ++splits;
         range = ((a.T + splits - 1) / splits + 63) / 64 * 64;

@@ -410,6 +410,8 @@ def test_unaligned_tensors_and_any_kept_t(torch_cuda):
                                   (2, 4127, 416, 224, 16), (2, 2305, 2080, 2016, 9), (3, 1537, 2080, 2016, 13), (3, 1500, 2208, 2016, 16),
                                   (2, 1537, 2080, 2016, 32), (2, 1555, 2016, 2080, 21), (4, 1537, 2080, 2016, 11),
                                   (3, 20000, 64, 32, 7),   # d_s_rank of all envelopes in parts
+                                  # three blocks, 129 column blocks in one token range: half of the chip; 162, from which the tokens are streamed
+                                  (3, 400, 8416, 8064, 5), (3, 320, 10368, 10336, 3),
                                   # four token ranges, whose shares a thread of the finish kernel takes at once, five, and many over several threads
                                   (2, 512, 96, 64, 16), (2, 640, 96, 64, 16), (3, 700, 64, 96, 16), (4, 900, 96, 32, 8), (4, 4099, 32, 64, 3)],
                          ids=lambda c: "ell%d_T%d_%dx%d_r%d" % c)
